@@ -198,17 +198,21 @@ typedef struct coda_epi_op {
  * multiple of 16 when A is stored [K x M] (trans = 1), else it is free.  Mixed operand dtypes are CODA_ERR_DTYPE,
  * sizes that break these rules CODA_ERR_SHAPE.
  *
- * workspace / workspace_bytes (device memory, 16-byte aligned; may be NULL): scratch for sharing output tiles
- * among workgroups (split-K / stream-K).  A shape with fewer than 256 output tiles (256 x 256, counted with a ragged
- * edge) leaves compute units idle, and a shape with more ends with a partly filled round of tiles.  When those
- * tiles (the "tail") number at most 128 and the contraction is long enough (K >= 2048, and every workgroup must be
- * spared at least 64 K-steps of 32 elements), coda_gemm_workspace_bytes returns a non-zero size, and a call that brings
- * that much workspace cuts the K-steps of the tail, laid end to end, into up to 256 equal contiguous ranges, one or two
- * workgroups each (a range may end in one tile and begin in the next): partial tiles go to the workspace in fp32, and
- * the workgroup that reaches a tile last adds its parts up in a fixed order (the result does not depend on arrival
- * order) and runs the epilogue program on the sum.  Without a workspace (NULL) the same shape runs unsplit.  A non-NULL
- * workspace smaller than coda_gemm_workspace_bytes(...) is CODA_ERR_WORKSPACE.  The workspace needs no initialisation
- * and holds nothing between calls; two calls that share one must not overlap in time.
+ * workspace / workspace_bytes (device memory, 16-byte aligned; may be NULL): scratch for dividing the contraction among
+ * workgroups.  A shape with fewer than 256 output tiles (256 x 256, counted with a ragged edge) leaves compute units
+ * idle, and a shape with more ends with a partly filled round of tiles.  When those tiles (the "tail") number at most 128
+ * and the contraction is long enough (K >= 2048, and every workgroup must be spared at least 64 K-steps of 32 elements),
+ * coda_gemm_workspace_bytes returns a non-zero size, and a call that brings that much workspace divides the tail in one of
+ * two ways, chosen from the sizes, operand type and layouts alone:
+ *   - few tiles or few rows: tiles of 32, 64 or 128 rows x 128 columns, each cut along K into equal ranges, one workgroup
+ *     each; the fp32 partials go to the workspace and a second kernel adds them up in range order and runs the program;
+ *   - otherwise the K-steps of the tail, laid end to end, are cut into up to 256 equal contiguous ranges, one or two
+ *     workgroups each (a range may end in one tile and begin in the next): partial tiles go to the workspace in fp32, and
+ *     the workgroup that reaches a tile last adds its parts up in a fixed order (the result does not depend on arrival
+ *     order) and runs the epilogue program on the sum.
+ * Without a workspace (NULL) the same shape runs undivided.  A non-NULL workspace smaller than
+ * coda_gemm_workspace_bytes(...) is CODA_ERR_WORKSPACE.  The workspace needs no initialisation and holds nothing between
+ * calls; two calls that share one must not overlap in time.
  */
 CODA_API coda_status coda_gemm(void *stream, int64_t M, int64_t N, int64_t K, const coda_mat *A,
                       const coda_mat *B, const coda_epi_op *prog /* host */, int32_t n_ops,

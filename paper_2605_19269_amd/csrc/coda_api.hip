@@ -5,6 +5,7 @@
 
 #include "aux_kernels.hpp"
 #include "gemm_launch.hpp"
+#include "small_launch.hpp"
 #include "splitk_plan.hpp"
 
 #include <mutex>
@@ -314,6 +315,9 @@ coda_status gemm_impl(void *stream, int64_t M, int64_t N, int64_t K, const coda_
         const size_t need = coda::splitk_bytes(pl);
         if (!aligned16(workspace)) return CODA_ERR_ALIGN;
         if (workspace_bytes < need) return CODA_ERR_WORKSPACE;
+        const coda::SmallPlan sp = coda::plan_small(M, N, K, f8, ak);
+        if (sp.nsplit > 0)
+            return launch_status(coda::launch_gemm_small(sp, ps.mode, f8, ak, bkc, p, static_cast<float *>(workspace), s));
         if (pl.chunks > 0) {
             p.split_from = pl.first;
             p.tail_tiles = pl.tail;

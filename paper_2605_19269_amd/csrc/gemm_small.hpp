@@ -1,0 +1,282 @@
+// gemm_small.hpp -- the contraction with small output tiles, for shapes that the 256 x 256 tiles leave mostly idle.
+//
+// A 256 x 256 tile is the right size when there are hundreds of them.  A decoding batch has one row of tiles (24 of them
+// for a 6144-wide projection), every workgroup then multiplies 224 or more rows of padding, and one workgroup's load of a
+// CU's share of the weights is all that is in flight on its CU.  Here a tile is BM x 128 with BM = 32, 64 or 128, the
+// contraction of every tile is cut into `nsplit` ranges, and two workgroups fit a CU, so that the whole chip streams the
+// operands however few tiles there are.
+//
+// The workgroups leave their fp32 partial tiles in the workspace, row-major [range][M][N], and end.  The epilogue program
+// then runs in a second kernel (epi_rows.hpp) that adds the ranges up in order: parallel over rows and columns instead of
+// one workgroup per tile, and ordered by the stream instead of by tickets, so that the partials travel as ordinary cached
+// stores and loads.
+//
+// Mainloop: a ring of S stages in LDS filled by direct-to-LDS loads; a stage is 128 bytes of the contraction per row of a
+// K-contiguous operand, or the same number of k-rows of an MN-contiguous one.  One barrier per stage, and the fragments of
+// the next MFMA step are read while the current ones are multiplied.  Up to 64 rows the kernel is bound by HBM (28672 x
+// 4096 bf16 weights against one row: 45 us with the epilogue, 5.2 TB/s, the rate of a large copy), at 128 rows by LDS: 64 KB or
+// more of fragments and 32 KB of fill per stage against 512 cycles of MFMA.
+#pragma once
+#include "gemm_kernel.hpp"
+
+namespace coda {
+
+struct SmallParams {
+    const unsigned char *A, *B;
+    int64_t lda, ldb;        // row pitches in bytes
+    int M, N, K;
+    int tiles_m, tiles_n, nsplit;
+    float *part;             // [nsplit][M][N]
+};
+
+template <int BM_, int WGM_, int WGN_, int S_, bool F8_>
+struct SmallCfg {
+    static constexpr int BM = BM_, BN = 128, WGM = WGM_, WGN = WGN_, BKB = 128, S = S_, NW = WGM * WGN, NT = NW * 64;
+    static constexpr bool F8 = F8_;
+    static constexpr int ESZ = F8 ? 1 : 2, BK = BKB / ESZ;        // contraction elements per stage
+    static constexpr int WTM = BM / WGM, WTN = BN / WGN;
+    static constexpr int A_BYTES = BM * BKB, B_BYTES = BN * BKB, STAGE = A_BYTES + B_BYTES, LDS = S * STAGE;
+    static constexpr int LA = A_BYTES / 1024 / NW, LB = B_BYTES / 1024 / NW;   // wave-loads of 1 KB per wave and stage
+    static_assert(A_BYTES % (1024 * NW) == 0 && B_BYTES % (1024 * NW) == 0, "every wave issues the same number of loads");
+    static_assert(WTM % 16 == 0 && WTN % 16 == 0 && S >= 2 && LDS <= 160 * 1024, "LDS");
+};
+
+// Byte offset, from the tile's first element, of the 16-byte chunk that lane `lane` of wave-load j fetches, and in `ck` the
+// chunk's first contraction index within the stage.  The LDS position is the lane's (direct-to-LDS); the swizzle that
+// keeps the fragment reads free of bank conflicts is applied here, on the global side.  `valid`: rows (columns) of the
+// operand tile that exist; positions past it fetch the last existing row (chunk) again and are masked where results are stored.
+template <class C, bool KCONT>
+__device__ __forceinline__ uint32_t small_goffset(int j, int lane, int64_t ldb, int valid, int &ck)
+{
+    if constexpr (KCONT) {                           // [rows][128 B]: chunk c of row r at c ^ (r & 7)
+        const int r = j * 8 + (lane >> 3), c = (lane & 7) ^ (r & 7);
+        ck = c * (16 / C::ESZ);
+        return (uint32_t)((int64_t)(r < valid ? r : valid - 1) * ldb + c * 16);
+    } else if constexpr (!C::F8) {                   // [BK][128 columns], 16 chunks a k-row: the granule swizzle of lds_mn
+        const int idx = j * 64 + lane, k = idx >> 4, pc = idx & 15;
+        const int col = ((((pc >> 1) ^ mn_swz(k)) * 2) + (pc & 1)) * 8;
+        ck = k;
+        return (uint32_t)((int64_t)k * ldb + (col < valid ? col : valid - 8) * 2);
+    } else {                                         // [128][128 B]: chunk c of k-row k at c ^ (k & 7)
+        const int k = j * 8 + (lane >> 3), c = (lane & 7) ^ (k & 7);
+        ck = k;
+        return (uint32_t)((int64_t)k * ldb + (c * 16 < valid ? c * 16 : valid - 16));
+    }
+}
+
+typedef __attribute__((ext_vector_type(4))) int i32x4;
+template <class C>
+using SmallFrag = typename std::conditional<C::F8, i32x8, bf16x8>::type;
+
+// Fragment of 16 rows (columns) from row0 on: bf16: lane -> row lane % 16, k = 32 h + 8 (lane / 16) .. + 7;
+// 8-bit: k = 32 (lane / 16) .. + 31 (one MFMA covers the stage's 128).
+template <class C, bool KCONT>
+__device__ __forceinline__ SmallFrag<C> small_frag(const unsigned char *tile, int row0, int lane, int h)
+{
+    if constexpr (C::F8 && KCONT) {
+        const int r = row0 + (lane & 15), c = 2 * (lane >> 4), sw = r & 7;
+        const i32x4 lo = *reinterpret_cast<const i32x4 *>(tile + r * 128 + ((c ^ sw) << 4));
+        const i32x4 hi = *reinterpret_cast<const i32x4 *>(tile + r * 128 + (((c + 1) ^ sw) << 4));
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    } else if constexpr (C::F8) {
+        // transposing reads as in dl_frag_mn_f8, eight k-rows each: the lane's four reads are its 32 consecutive k
+        typedef int v2i __attribute__((ext_vector_type(2)));
+        typedef __attribute__((address_space(3))) v2i lds_v2i;
+        const int i = lane & 15, k0 = 32 * (lane >> 4) + (i >> 1);      // k0 & 7 is the same in all four reads
+        const unsigned char *a = tile + k0 * 128 + (((row0 >> 4) ^ (k0 & 7)) << 4) + ((i & 1) << 3);
+        const v2i r0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i *)(a));
+        const v2i r1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i *)(a + 8 * 128));
+        const v2i r2 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i *)(a + 16 * 128));
+        const v2i r3 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i *)(a + 24 * 128));
+        return i32x8{r0[0], r0[1], r1[0], r1[1], r2[0], r2[1], r3[0], r3[1]};
+    } else if constexpr (KCONT) {
+        return dl_frag16_pair(tile, row0, lane, h);
+    } else {
+        return dl_frag16<128, false>(tile + h * 32 * 256, row0, lane);
+    }
+}
+
+// Workgroup -> (range, tile): every XCD gets a contiguous run of ids, ranges outermost, tiles in groups of eight tile rows
+// walked column by column (tile_coords), so that the workgroups of an XCD share operand panels in its L2.
+__device__ __host__ __forceinline__ void small_coords(int bid, int tiles_m, int tiles_n, int nsplit, int &tm, int &tn, int &split)
+{
+    const int tiles = tiles_m * tiles_n, nb = tiles * nsplit;
+    const int x = bid & 7, q = bid >> 3, base = nb >> 3, rem = nb & 7;
+    const int id = x * base + (x < rem ? x : rem) + q;
+    split = id / tiles;
+    const int t = id - split * tiles, grp = t / (8 * tiles_n), first = grp * 8;
+    const int gm = tiles_m - first < 8 ? tiles_m - first : 8, in = t - grp * 8 * tiles_n;
+    tm = first + in % gm;
+    tn = in / gm;
+}
+
+template <int N>
+__device__ __forceinline__ void wait_loads()
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// loads of `ahead` stages (at most MAX) may be in flight
+template <int MAX, int L>
+__device__ __forceinline__ void wait_stages(int ahead)
+{
+    if constexpr (MAX <= 0) wait_loads<0>();
+    else if (ahead == MAX) wait_loads<MAX * L>();
+    else wait_stages<MAX - 1, L>(ahead);
+}
+
+// The contraction of one tile over the stages [kbeg, kbeg + KT) (elements from kbeg * BK on, zeros past K), KT >= 1.
+// On return no wave reads or fills the ring any more.
+template <class C, bool AK, bool BKC>
+__device__ __forceinline__ void small_contract(f32x4 (&acc)[C::WTM / 16][C::WTN / 16], const SmallParams &p, int m0, int n0, int kbeg, int rot0,
+                                               int KT, unsigned char *smem)
+{
+    static_assert(AK || C::BM == 128, "an A whose rows are not contiguous in K is staged as 128-wide k-rows");
+    constexpr int NB = C::WTM / 16, NU = C::WTN / 16, S = C::S, L = C::LA + C::LB;
+    constexpr int KS = C::F8 ? 1 : 2;                // MFMA steps per stage
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave % C::WGM, wn = wave / C::WGM;
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int u = 0; u < NU; ++u) acc[i][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    uint32_t offa[C::LA], offb[C::LB];
+    int cka[C::LA], ckb[C::LB];
+    const int valid_m = p.M - m0 < C::BM ? p.M - m0 : C::BM, valid_n = p.N - n0 < C::BN ? p.N - n0 : C::BN;
+#pragma unroll
+    for (int i = 0; i < C::LA; ++i) offa[i] = small_goffset<C, AK>(wave * C::LA + i, lane, p.lda, valid_m, cka[i]);
+#pragma unroll
+    for (int i = 0; i < C::LB; ++i) offb[i] = small_goffset<C, BKC>(wave * C::LB + i, lane, p.ldb, valid_n, ckb[i]);
+    const int64_t stepa = AK ? (int64_t)C::BKB : C::BK * p.lda, stepb = BKC ? (int64_t)C::BKB : C::BK * p.ldb;
+    const unsigned char *ga = p.A + (AK ? (int64_t)m0 * p.lda : (int64_t)m0 * C::ESZ) + kbeg * stepa;
+    const unsigned char *gb = p.B + (BKC ? (int64_t)n0 * p.ldb : (int64_t)n0 * C::ESZ) + kbeg * stepb;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
+    // The stage that reaches past K (the last one of the last range, if K is not a whole number of stages): a lane whose
+    // chunk lies past K stores zeros at its LDS position instead of fetching.  Fewer loads than L may then be counted, so
+    // from the issue of that stage on the waits are for everything.
+    const bool ragged = (kbeg + KT) * C::BK > p.K;
+    // B rows contiguous in K: the rows of a stage lie a whole row pitch apart, which for the usual widths is a multiple of
+    // the memory channels' interleave, so workgroups that walk K in step would all pull on the same few channels.  Every
+    // column of tiles starts its range at another stage and wraps around.
+    const int rot = BKC && !ragged ? rot0 % KT : 0;
+    auto issue = [&](int t) {
+        unsigned char *slot = smem + (t % S) * C::STAGE;
+        const uint32_t la = lds0 + (uint32_t)((t % S) * C::STAGE), lb = la + C::A_BYTES;
+        const int ts = t + rot < KT ? t + rot : t + rot - KT;
+        const unsigned char *sa = ga + (int64_t)ts * stepa, *sb = gb + (int64_t)ts * stepb;
+        if (ragged && t == KT - 1) {
+            const int left = p.K - (kbeg + t) * C::BK;
+#pragma unroll
+            for (int i = 0; i < C::LA; ++i) {
+                const int at = (wave * C::LA + i) * 1024;
+                if (cka[i] < left) dl_load16(offa[i], sa, la + (uint32_t)at);
+                else *reinterpret_cast<u32x4 *>(slot + at + lane * 16) = u32x4{0u, 0u, 0u, 0u};
+            }
+#pragma unroll
+            for (int i = 0; i < C::LB; ++i) {
+                const int at = (wave * C::LB + i) * 1024;
+                if (ckb[i] < left) dl_load16(offb[i], sb, lb + (uint32_t)at);
+                else *reinterpret_cast<u32x4 *>(slot + C::A_BYTES + at + lane * 16) = u32x4{0u, 0u, 0u, 0u};
+            }
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < C::LA; ++i) dl_load16(offa[i], sa, la + (uint32_t)((wave * C::LA + i) * 1024));
+#pragma unroll
+        for (int i = 0; i < C::LB; ++i) dl_load16(offb[i], sb, lb + (uint32_t)((wave * C::LB + i) * 1024));
+    };
+    SmallFrag<C> fa0[NB], fb0[NU], fa1[NB], fb1[NU];
+    auto read = [&](SmallFrag<C>(&fa)[NB], SmallFrag<C>(&fb)[NU], int t, int h) {
+        const unsigned char *sa = smem + (t % S) * C::STAGE, *sb = sa + C::A_BYTES;
+#pragma unroll
+        for (int u = 0; u < NU; ++u) fb[u] = small_frag<C, BKC>(sb, wn * C::WTN + u * 16, lane, h);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) fa[i] = small_frag<C, AK>(sa, wm * C::WTM + i * 16, lane, h);
+    };
+    // Stage w has landed for this wave (later stages may be in flight), its own LDS reads so far have returned and its zero
+    // stores are done; behind the barrier that holds for all waves: stage w may be read, the slot of stage w - 1 refilled.
+    auto arrive = [&](int w) {
+        const int ahead = KT - 1 - w;
+        if (ragged && ahead <= S - 1) wait_loads<0>();
+        else if (ahead >= S - 2) wait_loads<(S - 2) * L>();
+        else wait_stages<S - 3, L>(ahead);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // MFMA step h of stage t on the fragments f*, while those of the next step, g*, are read.  The last step of a stage takes
+    // its next fragments from the next stage: that is where the stage's one barrier and the refill of its slot are.
+    auto step = [&](int t, int h, SmallFrag<C>(&fa)[NB], SmallFrag<C>(&fb)[NU], SmallFrag<C>(&ga_)[NB], SmallFrag<C>(&gb_)[NU]) {
+        if (h + 1 < KS) {
+            read(ga_, gb_, t, h + 1);
+        } else if (t + 1 < KT) {
+            arrive(t + 1);
+            if (t + S < KT) issue(t + S);
+            read(ga_, gb_, t + 1, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                if constexpr (C::F8)
+                    acc[i][u] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fb[u], fa[i], acc[i][u], 0, 0, 0, 0, 0, 0);
+                else
+                    acc[i][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[u], fa[i], acc[i][u], 0, 0, 0);
+            }
+    };
+#pragma unroll
+    for (int t = 0; t < S; ++t)
+        if (t < KT) issue(t);
+    if (KT >= S && !(ragged && KT == S)) {
+        wait_loads<(S - 1) * L>();
+    } else {
+        wait_loads<0>();
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    read(fa0, fb0, 0, 0);
+    if constexpr (KS == 2) {
+        for (int t = 0; t < KT; ++t) {
+            step(t, 0, fa0, fb0, fa1, fb1);
+            step(t, 1, fa1, fb1, fa0, fb0);
+        }
+    } else {
+        int t = 0;
+        for (; t + 1 < KT; t += 2) {
+            step(t, 0, fa0, fb0, fa1, fb1);
+            step(t + 1, 0, fa1, fb1, fa0, fb0);
+        }
+        if (t < KT) step(t, 0, fa0, fb0, fa1, fb1);
+    }
+    __syncthreads();
+}
+
+template <class C, bool AK, bool BKC>
+__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_small_partial(const SmallParams p)
+{
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[C::LDS];
+    constexpr int NB = C::WTM / 16, NU = C::WTN / 16;
+    int tm, tn, split;
+    small_coords((int)blockIdx.x, p.tiles_m, p.tiles_n, p.nsplit, tm, tn, split);
+    const int stages = (p.K + C::BK - 1) / C::BK;
+    const int k0 = (int)((int64_t)split * stages / p.nsplit), k1 = (int)((int64_t)(split + 1) * stages / p.nsplit);   // k1 > k0: nsplit <= stages
+    f32x4 acc[NB][NU];
+    const int m0 = tm * C::BM, n0 = tn * C::BN;
+    small_contract<C, AK, BKC>(acc, p, m0, n0, k0, tn, k1 - k0, smem);
+
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int m = m0 + (wave % C::WGM) * C::WTM + (lane & 15), n = n0 + (wave / C::WGM) * C::WTN + (lane >> 4) * 4;
+    float *out = p.part + (int64_t)split * p.M * p.N;
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+            if (m + i * 16 < p.M && n + u * 16 < p.N)
+                *reinterpret_cast<f32x4 *>(out + (int64_t)(m + i * 16) * p.N + n + u * 16) = acc[i][u];
+}
+
+}  // namespace coda

@@ -1,0 +1,64 @@
+// The split contraction with small output tiles (gemm_small.hpp) and the epilogue over its partials (epi_rows.hpp):
+// instantiations and host launchers.
+#include "gemm_small.hpp"
+#include "epi_rows.hpp"
+#include "small_launch.hpp"
+
+namespace coda {
+
+template <class C, bool AK, bool BKC>
+static hipError_t launch_partial(const SmallParams &p, hipStream_t s)
+{
+    hipLaunchKernelGGL((gemm_small_partial<C, AK, BKC>), dim3((unsigned)(p.tiles_m * p.tiles_n * p.nsplit)), dim3(C::NT), 0, s, p);
+    return hipGetLastError();
+}
+// Rings (measured at N x K = 28672 x 4096 bf16, 235 MB of weights): 32 rows, stages of 20 KB: two 58 us, three 45, four 48,
+// seven 50 -- past the ~40 KB in flight that the latency of memory asks for, more only queue up; 64 rows, stages of 24 KB:
+// two 62, three 50, six 50.  128 rows, one workgroup of eight waves per CU, stages of 32 KB: two 81, four 58; or two
+// workgroups of four waves with two stages each where there are tiles for both (768 x 4096 x 14336: 112 us against 150).
+template <bool BKC, bool F8>
+static hipError_t launch_bm(const SmallPlan &pl, bool ak, const SmallParams &p, hipStream_t s)
+{
+    if (pl.bm == 32) return launch_partial<SmallCfg<32, 1, 4, 3, F8>, true, BKC>(p, s);
+    if (pl.bm == 64) return launch_partial<SmallCfg<64, 1, 4, 3, F8>, true, BKC>(p, s);
+    if (pl.dense) return ak ? launch_partial<SmallCfg<128, 2, 2, 2, F8>, true, BKC>(p, s) : launch_partial<SmallCfg<128, 2, 2, 2, F8>, false, BKC>(p, s);
+    return ak ? launch_partial<SmallCfg<128, 2, 4, 4, F8>, true, BKC>(p, s) : launch_partial<SmallCfg<128, 2, 4, 4, F8>, false, BKC>(p, s);
+}
+
+template <int EPI>
+static hipError_t launch_rows(const GemmParams &p, const float *part, int nsplit, hipStream_t s)
+{
+    if constexpr (EPI == EPI_RMSNORM_BWD)
+        hipLaunchKernelGGL((epi_cols_kernel<EPI>), dim3((unsigned)((p.N + 63) / 64), (unsigned)((p.M + 255) / 256)), dim3(1024), 0, s, p, part, nsplit);
+    else
+        hipLaunchKernelGGL((epi_rows_kernel<EPI>), dim3((unsigned)((p.N + 255) / 256), (unsigned)((p.M + EPI_ROWS - 1) / EPI_ROWS)), dim3(256), 0, s, p,
+                           part, nsplit);
+    return hipGetLastError();
+}
+
+hipError_t launch_gemm_small(const SmallPlan &pl, int mode, bool f8, bool ak, bool bkc, const GemmParams &p, float *part, hipStream_t s)
+{
+    const int64_t esz = f8 ? 1 : 2;
+    SmallParams q{};
+    q.A = reinterpret_cast<const unsigned char *>(p.A);
+    q.B = reinterpret_cast<const unsigned char *>(p.B);
+    q.lda = p.lda * esz;
+    q.ldb = p.ldb * esz;
+    q.M = p.M; q.N = p.N; q.K = p.K;
+    q.tiles_m = (p.M + pl.bm - 1) / pl.bm;
+    q.tiles_n = (p.N + 127) / 128;
+    q.nsplit = pl.nsplit;
+    q.part = part;
+    const hipError_t e = f8 ? (bkc ? launch_bm<true, true>(pl, ak, q, s) : launch_bm<false, true>(pl, ak, q, s))
+                            : (bkc ? launch_bm<true, false>(pl, ak, q, s) : launch_bm<false, false>(pl, ak, q, s));
+    if (e != hipSuccess) return e;
+    switch (mode) {
+    case EPI_LINEAR: return launch_rows<EPI_LINEAR>(p, part, pl.nsplit, s);
+    case EPI_SWIGLU_FWD: return launch_rows<EPI_SWIGLU_FWD>(p, part, pl.nsplit, s);
+    case EPI_SWIGLU_BWD: return launch_rows<EPI_SWIGLU_BWD>(p, part, pl.nsplit, s);
+    case EPI_RMSNORM_BWD: return launch_rows<EPI_RMSNORM_BWD>(p, part, pl.nsplit, s);
+    default: return launch_rows<EPI_ACCUM>(p, part, pl.nsplit, s);
+    }
+}
+
+}  // namespace coda

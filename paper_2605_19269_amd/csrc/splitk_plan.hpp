@@ -70,4 +70,55 @@ inline size_t splitk_bytes(const SplitPlan &pl)
     return SPLITK_CNT_BYTES + (size_t)pl.tail * (size_t)pl.stride * PLAN_TILE_M * PLAN_TILE_N * sizeof(float);
 }
 
+
+// Plan of the contractions with small output tiles (gemm_small.hpp): bm x 128 tiles, each cut along K into `nsplit` ranges
+// whose fp32 partials [nsplit][M][N] lie in the workspace.  It takes the place of the shared 256 x 256 tiles where every
+// tile of the shape would be shared (plan.first == 0), within the workspace that plan asks for, so that the sizes callers
+// see do not depend on which of the two runs.
+//
+// Up to 64 rows (one tile row) the operands stream from memory once and the small tiles always win: 1 / 32 / 64 rows,
+// N x K = 6144 x 4096: 14 / 15 / 17 us against 47; 28672 x 4096: 45 / 46 / 50 against 104; 4096 x 14336: 26 / 28 / 30
+// against 75.  One workgroup per CU is the best count there (at 6144 x 4096: 96, 240, 480, 768 workgroups: 18.9, 14.1,
+// 15.2, 16.3 us): twice as many pay more exchange and fill for bytes in flight that memory does not need.
+//
+// Above that, both kernels are modelled in microseconds from their measured parts:
+//   one stage (128 bytes of K) of a 128 x 128 tile, one workgroup per CU:        0.66, two per CU: 2.34e-3 per workgroup
+//   partials: written once and read once at 5 TB/s; launches and epilogue: 6
+//   one K-step (64 bytes of K) of a 256 x 256 tile: 0.83; exchange of its parts: 10 + 5 per part of a tile
+// e.g. 384 x 6144 x 4096: model 39, measured 40 (256 x 256: 58); 1024 x 2048 x 8192: 57, 52 (80); 1024 x 4096 x 14336: 137, 145,
+// where the large tiles run 118 and keep the shape.  The small tiles must win by a tenth.
+struct SmallPlan {
+    int bm;        // tile rows: 32, 64 or 128 (tiles are 128 columns wide)
+    int nsplit;    // ranges of the contraction; 0: the shape runs on the large tiles
+    int dense;     // 128 rows: two workgroups of four waves per CU instead of one of eight
+};
+constexpr int64_t SMALL_MAX_SPLIT = 16, SMALL_MIN_STAGES = 4;   // beyond that the exchange costs what the ranges save
+inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_contiguous)
+{
+    const SmallPlan none = {0, 0, 0};
+    const SplitPlan big = plan_splitk(M, N, K, f8);
+    if (big.chunks == 0 || big.first != 0) return none;
+    const int64_t esz = f8 ? 1 : 2, stages = (K * esz + 127) / 128;
+    const int64_t budget = (int64_t)splitk_bytes(big) / (M * N * 4);              // ranges whose partials fit
+    const int bm = !a_k_contiguous || M > 64 ? 128 : (M > 32 ? 64 : 32);
+    const int64_t tiles = ((M + bm - 1) / bm) * ((N + 127) / 128);
+    auto ranges = [&](int64_t workgroups) {
+        int64_t ns = workgroups / tiles;
+        if (ns > SMALL_MAX_SPLIT) ns = SMALL_MAX_SPLIT;
+        if (ns > stages / SMALL_MIN_STAGES) ns = stages / SMALL_MIN_STAGES;
+        if (ns > budget) ns = budget;
+        return ns;
+    };
+    const int64_t ns1 = ranges(SPLITK_CUS), ns2 = ranges(2 * SPLITK_CUS);
+    if (M <= 64) return SmallPlan{bm, (int)(ns1 > 0 ? ns1 : ns2), 0};             // (none if not even one fits)
+    auto exchange = [&](int64_t ns) { return 6.0 + (double)(ns * M * N) * 8.0 / 5e6; };
+    const double never = 1e30;
+    const double t1 = ns1 > 0 ? 0.66 * (double)((stages + ns1 - 1) / ns1) + exchange(ns1) : never;
+    const double t2 = ns2 > ns1 ? 2.34e-3 * (double)(tiles * ns2 * ((stages + ns2 - 1) / ns2)) + exchange(ns2) : never;
+    const int64_t pairs = (K * esz + 127) / 128, longest = 2 * ((big.tail * pairs + big.chunks - 1) / big.chunks);
+    const double t_big = 0.83 * (double)longest + 10.0 + 5.0 * big.stride;
+    if ((t1 < t2 ? t1 : t2) > 0.9 * t_big) return none;
+    return t1 <= t2 ? SmallPlan{bm, (int)ns1, 0} : SmallPlan{bm, (int)ns2, 1};
+}
+
 }  // namespace coda

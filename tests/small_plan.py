@@ -1,0 +1,24 @@
+"""ctypes access to the host build of the small-tile plan (tests/small_plan_host.hip)."""
+import ctypes
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
+def load(folder):
+    so = str(folder / "small_plan_host.so")
+    subprocess.run([HIPCC, "--offload-host-only", "-O1", "-std=c++17", "-fPIC", "-shared", "-Wno-inline-asm", "-o", so,
+                    os.path.join(ROOT, "tests", "small_plan_host.hip")], check=True, capture_output=True)
+    lib = ctypes.CDLL(so)
+    lib.host_small_plan.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 2 + [ctypes.POINTER(ctypes.c_int)]
+    lib.host_small_map.argtypes = [ctypes.c_int] * 3 + [ctypes.POINTER(ctypes.c_int)]
+    return lib
+
+
+def plan(lib, M, N, K, f8=False, ak=True):
+    """(tile rows, ranges, dense); ranges = 0: the shape runs on the large tiles."""
+    out = (ctypes.c_int * 3)()
+    lib.host_small_plan(M, N, K, int(f8), int(ak), out)
+    return tuple(out)
