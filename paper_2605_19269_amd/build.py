@@ -30,7 +30,13 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function", "-Wno-inline-asm",
          "-fvisibility=hidden", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
+# The small-tile kernels: MFMA accumulators in ordinary registers.  Workgroups of few waves and much LDS leave a wave 512
+# registers, and the compiler then keeps the accumulators in the upper half and copies them around every MFMA.
+FLAGS_SMALL = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
+
 SOURCES = ["coda_api.hip", "aux_kernels.hip", "gemm_small_inst.hip",
+           "gemm_direct_inst_nn.hip", "gemm_direct_inst_nt.hip", "gemm_direct_inst_tn.hip", "gemm_direct_inst_tt.hip",
+           "gemm_direct_inst_f8_nn.hip", "gemm_direct_inst_f8_nt.hip", "gemm_direct_inst_f8_tn.hip", "gemm_direct_inst_f8_tt.hip",
            "gemm_inst_nn.hip", "gemm_inst_nt.hip", "gemm_inst_tn.hip", "gemm_inst_tt.hip",
            "gemm_inst_f8_nn.hip", "gemm_inst_f8_nt.hip", "gemm_inst_f8_tn.hip", "gemm_inst_f8_tt.hip"]
 SOURCES_BENCH = ["baseline_kernels.hip", "calib_kernels.hip"]
@@ -47,7 +53,8 @@ def _compile(src, force):
     newest = max(os.path.getmtime(p) for p in [path] + _headers())
     if not force and os.path.exists(obj) and os.path.getmtime(obj) >= newest:
         return obj, ""
-    r = subprocess.run([HIPCC] + FLAGS + ["-Rpass-analysis=kernel-resource-usage", "-c", path, "-o", obj],
+    flags = FLAGS + (FLAGS_SMALL if src.startswith(("gemm_small", "gemm_direct")) else [])
+    r = subprocess.run([HIPCC] + flags + ["-Rpass-analysis=kernel-resource-usage", "-c", path, "-o", obj],
                        capture_output=True, text=True)
     text = r.stdout + r.stderr
     with open(obj + ".resources", "w") as f:

@@ -29,9 +29,9 @@ struct SmallParams {
     float *part;             // [nsplit][M][N]
 };
 
-template <int BM_, int WGM_, int WGN_, int S_, bool F8_>
+template <int BM_, int BN_, int WGM_, int WGN_, int S_, bool F8_>
 struct SmallCfg {
-    static constexpr int BM = BM_, BN = 128, WGM = WGM_, WGN = WGN_, BKB = 128, S = S_, NW = WGM * WGN, NT = NW * 64;
+    static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, BKB = 128, S = S_, NW = WGM * WGN, NT = NW * 64;
     static constexpr bool F8 = F8_;
     static constexpr int ESZ = F8 ? 1 : 2, BK = BKB / ESZ;        // contraction elements per stage
     static constexpr int WTM = BM / WGM, WTN = BN / WGN;
@@ -41,24 +41,33 @@ struct SmallCfg {
     static_assert(WTM % 16 == 0 && WTN % 16 == 0 && S >= 2 && LDS <= 160 * 1024, "LDS");
 };
 
+// 8-bit k-rows of ROWS bytes: the eight k-rows of a transposing read fall into different bank groups
+template <int ROWS>
+__device__ __forceinline__ int small_swz_f8(int c, int k)
+{
+    return c ^ (ROWS == 64 ? (k >> 1) & 3 : (ROWS == 128 ? (k & 7) : 2 * (k & 7)));
+}
+
 // Byte offset, from the tile's first element, of the 16-byte chunk that lane `lane` of wave-load j fetches, and in `ck` the
 // chunk's first contraction index within the stage.  The LDS position is the lane's (direct-to-LDS); the swizzle that
 // keeps the fragment reads free of bank conflicts is applied here, on the global side.  `valid`: rows (columns) of the
 // operand tile that exist; positions past it fetch the last existing row (chunk) again and are masked where results are stored.
-template <class C, bool KCONT>
+template <class C, bool KCONT, int ROWS>
 __device__ __forceinline__ uint32_t small_goffset(int j, int lane, int64_t ldb, int valid, int &ck)
 {
     if constexpr (KCONT) {                           // [rows][128 B]: chunk c of row r at c ^ (r & 7)
         const int r = j * 8 + (lane >> 3), c = (lane & 7) ^ (r & 7);
         ck = c * (16 / C::ESZ);
         return (uint32_t)((int64_t)(r < valid ? r : valid - 1) * ldb + c * 16);
-    } else if constexpr (!C::F8) {                   // [BK][128 columns], 16 chunks a k-row: the granule swizzle of lds_mn
-        const int idx = j * 64 + lane, k = idx >> 4, pc = idx & 15;
-        const int col = ((((pc >> 1) ^ mn_swz(k)) * 2) + (pc & 1)) * 8;
+    } else if constexpr (!C::F8) {                   // [64][ROWS columns]: the granule swizzle of lds_mn
+        constexpr int CPR = ROWS / 8;
+        const int idx = j * 64 + lane, k = idx / CPR, pc = idx % CPR;
+        const int col = ((((pc >> 1) ^ mn_swz(k)) & (ROWS / 16 - 1)) * 2 + (pc & 1)) * 8;
         ck = k;
         return (uint32_t)((int64_t)k * ldb + (col < valid ? col : valid - 8) * 2);
-    } else {                                         // [128][128 B]: chunk c of k-row k at c ^ (k & 7)
-        const int k = j * 8 + (lane >> 3), c = (lane & 7) ^ (k & 7);
+    } else {                                         // [128][ROWS columns]: chunk c of k-row k at small_swz_f8(c, k)
+        constexpr int CPR = ROWS / 16;
+        const int idx = j * 64 + lane, k = idx / CPR, c = small_swz_f8<ROWS>(idx % CPR, k);
         ck = k;
         return (uint32_t)((int64_t)k * ldb + (c * 16 < valid ? c * 16 : valid - 16));
     }
@@ -70,7 +79,7 @@ using SmallFrag = typename std::conditional<C::F8, i32x8, bf16x8>::type;
 
 // Fragment of 16 rows (columns) from row0 on: bf16: lane -> row lane % 16, k = 32 h + 8 (lane / 16) .. + 7;
 // 8-bit: k = 32 (lane / 16) .. + 31 (one MFMA covers the stage's 128).
-template <class C, bool KCONT>
+template <class C, bool KCONT, int ROWS>
 __device__ __forceinline__ SmallFrag<C> small_frag(const unsigned char *tile, int row0, int lane, int h)
 {
     if constexpr (C::F8 && KCONT) {
@@ -83,16 +92,16 @@ __device__ __forceinline__ SmallFrag<C> small_frag(const unsigned char *tile, in
         typedef int v2i __attribute__((ext_vector_type(2)));
         typedef __attribute__((address_space(3))) v2i lds_v2i;
         const int i = lane & 15, k0 = 32 * (lane >> 4) + (i >> 1);      // k0 & 7 is the same in all four reads
-        const unsigned char *a = tile + k0 * 128 + (((row0 >> 4) ^ (k0 & 7)) << 4) + ((i & 1) << 3);
+        const unsigned char *a = tile + k0 * ROWS + (small_swz_f8<ROWS>(row0 >> 4, k0) << 4) + ((i & 1) << 3);
         const v2i r0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i *)(a));
-        const v2i r1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i *)(a + 8 * 128));
-        const v2i r2 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i *)(a + 16 * 128));
-        const v2i r3 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i *)(a + 24 * 128));
+        const v2i r1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i *)(a + 8 * ROWS));
+        const v2i r2 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i *)(a + 16 * ROWS));
+        const v2i r3 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i *)(a + 24 * ROWS));
         return i32x8{r0[0], r0[1], r1[0], r1[1], r2[0], r2[1], r3[0], r3[1]};
     } else if constexpr (KCONT) {
         return dl_frag16_pair(tile, row0, lane, h);
     } else {
-        return dl_frag16<128, false>(tile + h * 32 * 256, row0, lane);
+        return dl_frag16<ROWS, false>(tile + h * 32 * ROWS * 2, row0, lane);
     }
 }
 
@@ -145,9 +154,9 @@ __device__ __forceinline__ void small_contract(f32x4 (&acc)[C::WTM / 16][C::WTN 
     int cka[C::LA], ckb[C::LB];
     const int valid_m = p.M - m0 < C::BM ? p.M - m0 : C::BM, valid_n = p.N - n0 < C::BN ? p.N - n0 : C::BN;
 #pragma unroll
-    for (int i = 0; i < C::LA; ++i) offa[i] = small_goffset<C, AK>(wave * C::LA + i, lane, p.lda, valid_m, cka[i]);
+    for (int i = 0; i < C::LA; ++i) offa[i] = small_goffset<C, AK, C::BM>(wave * C::LA + i, lane, p.lda, valid_m, cka[i]);
 #pragma unroll
-    for (int i = 0; i < C::LB; ++i) offb[i] = small_goffset<C, BKC>(wave * C::LB + i, lane, p.ldb, valid_n, ckb[i]);
+    for (int i = 0; i < C::LB; ++i) offb[i] = small_goffset<C, BKC, C::BN>(wave * C::LB + i, lane, p.ldb, valid_n, ckb[i]);
     const int64_t stepa = AK ? (int64_t)C::BKB : C::BK * p.lda, stepb = BKC ? (int64_t)C::BKB : C::BK * p.ldb;
     const unsigned char *ga = p.A + (AK ? (int64_t)m0 * p.lda : (int64_t)m0 * C::ESZ) + kbeg * stepa;
     const unsigned char *gb = p.B + (BKC ? (int64_t)n0 * p.ldb : (int64_t)n0 * C::ESZ) + kbeg * stepb;
@@ -158,64 +167,51 @@ __device__ __forceinline__ void small_contract(f32x4 (&acc)[C::WTM / 16][C::WTN 
     const bool ragged = (kbeg + KT) * C::BK > p.K;
     // B rows contiguous in K: the rows of a stage lie a whole row pitch apart, which for the usual widths is a multiple of
     // the memory channels' interleave, so workgroups that walk K in step would all pull on the same few channels.  Every
-    // column of tiles starts its range at another stage and wraps around.
-    const int rot = BKC && !ragged ? rot0 % KT : 0;
-    auto issue = [&](int t) {
-        unsigned char *slot = smem + (t % S) * C::STAGE;
-        const uint32_t la = lds0 + (uint32_t)((t % S) * C::STAGE), lb = la + C::A_BYTES;
-        const int ts = t + rot < KT ? t + rot : t + rot - KT;
-        const unsigned char *sa = ga + (int64_t)ts * stepa, *sb = gb + (int64_t)ts * stepb;
-        if (ragged && t == KT - 1) {
-            const int left = p.K - (kbeg + t) * C::BK;
+    // column of tiles starts its range at another stage and wraps around (28672 x 4096 8-bit, one row: 30 us against 27).
+    const int rot = __builtin_amdgcn_readfirstlane(BKC && !ragged ? rot0 % KT : 0);
+    int next = rot;                                  // the next stage to fetch, and its slot
+    uint32_t slot_in = 0;
+    auto advance = [&]() {
+        ++next;
+        if (BKC) next = next == KT ? 0 : next;
+        slot_in = slot_in + C::STAGE == C::LDS ? 0u : slot_in + C::STAGE;
+    };
+    auto issue = [&]() {
+        const unsigned char *sa = ga + (int64_t)next * stepa, *sb = gb + (int64_t)next * stepb;
+        const uint32_t la = lds0 + slot_in + (uint32_t)(wave * C::LA * 1024), lb = lds0 + slot_in + (uint32_t)(C::A_BYTES + wave * C::LB * 1024);
 #pragma unroll
-            for (int i = 0; i < C::LA; ++i) {
-                const int at = (wave * C::LA + i) * 1024;
-                if (cka[i] < left) dl_load16(offa[i], sa, la + (uint32_t)at);
-                else *reinterpret_cast<u32x4 *>(slot + at + lane * 16) = u32x4{0u, 0u, 0u, 0u};
-            }
+        for (int i = 0; i < C::LA; ++i) dl_load16(offa[i], sa, la + (uint32_t)(i * 1024));
 #pragma unroll
-            for (int i = 0; i < C::LB; ++i) {
-                const int at = (wave * C::LB + i) * 1024;
-                if (ckb[i] < left) dl_load16(offb[i], sb, lb + (uint32_t)at);
-                else *reinterpret_cast<u32x4 *>(slot + C::A_BYTES + at + lane * 16) = u32x4{0u, 0u, 0u, 0u};
-            }
-            return;
+        for (int i = 0; i < C::LB; ++i) dl_load16(offb[i], sb, lb + (uint32_t)(i * 1024));
+        advance();
+    };
+    auto issue_last = [&]() {                        // the stage that reaches past K
+        const int have = p.K - (kbeg + KT - 1) * C::BK;
+        const unsigned char *sa = ga + (int64_t)next * stepa, *sb = gb + (int64_t)next * stepb;
+        unsigned char *slot = smem + slot_in + lane * 16;
+#pragma unroll
+        for (int i = 0; i < C::LA; ++i) {
+            const int at = (wave * C::LA + i) * 1024;
+            if (cka[i] < have) dl_load16(offa[i], sa, lds0 + slot_in + (uint32_t)at);
+            else *reinterpret_cast<u32x4 *>(slot + at) = u32x4{0u, 0u, 0u, 0u};
         }
 #pragma unroll
-        for (int i = 0; i < C::LA; ++i) dl_load16(offa[i], sa, la + (uint32_t)((wave * C::LA + i) * 1024));
-#pragma unroll
-        for (int i = 0; i < C::LB; ++i) dl_load16(offb[i], sb, lb + (uint32_t)((wave * C::LB + i) * 1024));
+        for (int i = 0; i < C::LB; ++i) {
+            const int at = C::A_BYTES + (wave * C::LB + i) * 1024;
+            if (ckb[i] < have) dl_load16(offb[i], sb, lds0 + slot_in + (uint32_t)at);
+            else *reinterpret_cast<u32x4 *>(slot + at) = u32x4{0u, 0u, 0u, 0u};
+        }
     };
     SmallFrag<C> fa0[NB], fb0[NU], fa1[NB], fb1[NU];
-    auto read = [&](SmallFrag<C>(&fa)[NB], SmallFrag<C>(&fb)[NU], int t, int h) {
-        const unsigned char *sa = smem + (t % S) * C::STAGE, *sb = sa + C::A_BYTES;
+    uint32_t slot_out = 0;                           // the slot being read
+    auto read = [&](SmallFrag<C>(&fa)[NB], SmallFrag<C>(&fb)[NU], int h) {
+        const unsigned char *ta = smem + slot_out, *tb = ta + C::A_BYTES;
 #pragma unroll
-        for (int u = 0; u < NU; ++u) fb[u] = small_frag<C, BKC>(sb, wn * C::WTN + u * 16, lane, h);
+        for (int u = 0; u < NU; ++u) fb[u] = small_frag<C, BKC, C::BN>(tb, wn * C::WTN + u * 16, lane, h);
 #pragma unroll
-        for (int i = 0; i < NB; ++i) fa[i] = small_frag<C, AK>(sa, wm * C::WTM + i * 16, lane, h);
+        for (int i = 0; i < NB; ++i) fa[i] = small_frag<C, AK, C::BM>(ta, wm * C::WTM + i * 16, lane, h);
     };
-    // Stage w has landed for this wave (later stages may be in flight), its own LDS reads so far have returned and its zero
-    // stores are done; behind the barrier that holds for all waves: stage w may be read, the slot of stage w - 1 refilled.
-    auto arrive = [&](int w) {
-        const int ahead = KT - 1 - w;
-        if (ragged && ahead <= S - 1) wait_loads<0>();
-        else if (ahead >= S - 2) wait_loads<(S - 2) * L>();
-        else wait_stages<S - 3, L>(ahead);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    // MFMA step h of stage t on the fragments f*, while those of the next step, g*, are read.  The last step of a stage takes
-    // its next fragments from the next stage: that is where the stage's one barrier and the refill of its slot are.
-    auto step = [&](int t, int h, SmallFrag<C>(&fa)[NB], SmallFrag<C>(&fb)[NU], SmallFrag<C>(&ga_)[NB], SmallFrag<C>(&gb_)[NU]) {
-        if (h + 1 < KS) {
-            read(ga_, gb_, t, h + 1);
-        } else if (t + 1 < KT) {
-            arrive(t + 1);
-            if (t + S < KT) issue(t + S);
-            read(ga_, gb_, t + 1, 0);
-        }
+    auto mma = [&](const SmallFrag<C>(&fa)[NB], const SmallFrag<C>(&fb)[NU]) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < NB; ++i)
@@ -226,44 +222,93 @@ __device__ __forceinline__ void small_contract(f32x4 (&acc)[C::WTM / 16][C::WTN 
                 else
                     acc[i][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[u], fa[i], acc[i][u], 0, 0, 0);
             }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // Behind the wait for a stage's loads: this wave's own LDS reads so far have returned and its zero stores are done;
+    // behind the barrier that, and the stage's arrival, hold for all waves: it may be read, the slot before it refilled.
+    auto meet = [&]() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt(0), known to the compiler: its own waits below count from here
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");
+    };
+    auto next_slot = [&]() { slot_out = slot_out + C::STAGE == C::LDS ? 0u : slot_out + C::STAGE; };
+    // Stage t on the fragments f*; the reads of the next MFMA step are in flight under every step.  The last step of a stage
+    // takes its next fragments from the next stage: that is where the stage's one barrier and the refill of its slot are.
+    // `steady`: the refill exists and lies inside K, no stage in flight is the one past K.
+    auto stage = [&](int t, bool steady, SmallFrag<C>(&fa)[NB], SmallFrag<C>(&fb)[NU], SmallFrag<C>(&ha)[NB], SmallFrag<C>(&hb)[NU]) {
+        if constexpr (KS == 2) {
+            read(ha, hb, 1);
+            mma(fa, fb);
+        }
+        if (steady) {
+            wait_loads<(S - 2) * L>();
+            meet();
+            issue();
+            next_slot();
+        } else if (t + 1 < KT) {
+            const int ahead = KT - 2 - t;            // stages behind t + 1
+            if (ragged && ahead <= S - 1) wait_loads<0>();
+            else if (ahead >= S - 2) wait_loads<(S - 2) * L>();
+            else wait_stages<S - 3, L>(ahead);
+            meet();
+            if (t + S < KT) {
+                if (ragged && t + S == KT - 1) issue_last();
+                else issue();
+            }
+            next_slot();
+        }
+        if constexpr (KS == 2) {
+            if (steady || t + 1 < KT) read(fa, fb, 0);
+            mma(ha, hb);
+        } else {
+            if (steady || t + 1 < KT) read(ha, hb, 0);
+            mma(fa, fb);
+        }
     };
 #pragma unroll
     for (int t = 0; t < S; ++t)
-        if (t < KT) issue(t);
+        if (t < KT) {
+            if (ragged && t == KT - 1) issue_last();
+            else issue();
+        }
     if (KT >= S && !(ragged && KT == S)) {
         wait_loads<(S - 1) * L>();
     } else {
         wait_loads<0>();
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-    read(fa0, fb0, 0, 0);
+    meet();
+    read(fa0, fb0, 0);
+    int t = 0;
     if constexpr (KS == 2) {
-        for (int t = 0; t < KT; ++t) {
-            step(t, 0, fa0, fb0, fa1, fb1);
-            step(t, 1, fa1, fb1, fa0, fb0);
-        }
+        for (; t + S + (ragged ? 1 : 0) < KT; ++t) stage(t, true, fa0, fb0, fa1, fb1);
+        for (; t < KT; ++t) stage(t, false, fa0, fb0, fa1, fb1);
     } else {
-        int t = 0;
-        for (; t + 1 < KT; t += 2) {
-            step(t, 0, fa0, fb0, fa1, fb1);
-            step(t + 1, 0, fa1, fb1, fa0, fb0);
+        // two stages per trip: the fragment buffers swap roles
+        for (; t + 1 + S + (ragged ? 1 : 0) < KT; t += 2) {
+            stage(t, true, fa0, fb0, fa1, fb1);
+            stage(t + 1, true, fa1, fb1, fa0, fb0);
         }
-        if (t < KT) step(t, 0, fa0, fb0, fa1, fb1);
+        for (; t < KT; t += 2) {
+            stage(t, false, fa0, fb0, fa1, fb1);
+            if (t + 1 < KT) stage(t + 1, false, fa1, fb1, fa0, fb0);
+        }
     }
     __syncthreads();
 }
 
 template <class C, bool AK, bool BKC>
-__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_small_partial(const SmallParams p)
+__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2), amdgpu_num_vgpr(256))) void gemm_small_partial(const SmallParams p)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[C::LDS];
     constexpr int NB = C::WTM / 16, NU = C::WTN / 16;
     int tm, tn, split;
     small_coords((int)blockIdx.x, p.tiles_m, p.tiles_n, p.nsplit, tm, tn, split);
     const int stages = (p.K + C::BK - 1) / C::BK;
-    const int k0 = (int)((int64_t)split * stages / p.nsplit), k1 = (int)((int64_t)(split + 1) * stages / p.nsplit);   // k1 > k0: nsplit <= stages
+    const int k0 = __builtin_amdgcn_readfirstlane((int)((int64_t)split * stages / p.nsplit));
+    const int k1 = __builtin_amdgcn_readfirstlane((int)((int64_t)(split + 1) * stages / p.nsplit));   // k1 > k0: nsplit <= stages
     f32x4 acc[NB][NU];
     const int m0 = tm * C::BM, n0 = tn * C::BN;
     small_contract<C, AK, BKC>(acc, p, m0, n0, k0, tn, k1 - k0, smem);
@@ -277,6 +322,26 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2))) v
         for (int u = 0; u < NU; ++u)
             if (m + i * 16 < p.M && n + u * 16 < p.N)
                 *reinterpret_cast<f32x4 *>(out + (int64_t)(m + i * 16) * p.N + n + u * 16) = acc[i][u];
+}
+
+// The whole launch in one kernel: the contraction undivided, then the epilogue program of the large kernels on the tile.
+// The callers' row-reduction partials are per 256 columns, so programs with one take the 256-wide tiles.
+template <class C, bool AK, bool BKC, int EPI>
+__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2), amdgpu_num_vgpr(256))) void gemm_small_direct(const GemmParams g, const SmallParams p)
+{
+    constexpr int RED = 2 * C::WGN * C::BM * 4;
+    static_assert(C::LDS + RED <= 160 * 1024 && EPI != EPI_RMSNORM_BWD, "LDS; column partials are per 256 rows");
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[C::LDS + RED];
+    int tm, tn, split;
+    small_coords((int)blockIdx.x, p.tiles_m, p.tiles_n, 1, tm, tn, split);
+    const int m0 = tm * C::BM, n0 = tn * C::BN;
+    Acc16<C> acc;
+    small_contract<C, AK, BKC>(acc.a, p, m0, n0, 0, tn, (p.K + C::BK - 1) / C::BK, smem);
+    float *red = reinterpret_cast<float *>(smem + C::LDS);
+    if (C::BM < 128 || m0 + C::BM > p.M || n0 + C::BN > p.N)
+        run_epilogue<C, Acc16<C>, EPI, true, C::LDS>(acc, g, m0, n0, tn, smem, red, (int)threadIdx.x);
+    else
+        run_epilogue<C, Acc16<C>, EPI, false, C::LDS>(acc, g, m0, n0, tn, smem, red, (int)threadIdx.x);
 }
 
 }  // namespace coda

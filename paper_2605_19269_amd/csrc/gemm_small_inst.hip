@@ -19,10 +19,10 @@ static hipError_t launch_partial(const SmallParams &p, hipStream_t s)
 template <bool BKC, bool F8>
 static hipError_t launch_bm(const SmallPlan &pl, bool ak, const SmallParams &p, hipStream_t s)
 {
-    if (pl.bm == 32) return launch_partial<SmallCfg<32, 1, 4, 3, F8>, true, BKC>(p, s);
-    if (pl.bm == 64) return launch_partial<SmallCfg<64, 1, 4, 3, F8>, true, BKC>(p, s);
-    if (pl.dense) return ak ? launch_partial<SmallCfg<128, 2, 2, 2, F8>, true, BKC>(p, s) : launch_partial<SmallCfg<128, 2, 2, 2, F8>, false, BKC>(p, s);
-    return ak ? launch_partial<SmallCfg<128, 2, 4, 4, F8>, true, BKC>(p, s) : launch_partial<SmallCfg<128, 2, 4, 4, F8>, false, BKC>(p, s);
+    if (pl.bm == 32) return launch_partial<SmallCfg<32, 128, 1, 4, 3, F8>, true, BKC>(p, s);
+    if (pl.bm == 64) return launch_partial<SmallCfg<64, 128, 1, 4, 3, F8>, true, BKC>(p, s);
+    if (pl.dense) return ak ? launch_partial<SmallCfg<128, 128, 2, 2, 2, F8>, true, BKC>(p, s) : launch_partial<SmallCfg<128, 128, 2, 2, 2, F8>, false, BKC>(p, s);
+    return ak ? launch_partial<SmallCfg<128, 128, 2, 4, 4, F8>, true, BKC>(p, s) : launch_partial<SmallCfg<128, 128, 2, 4, 4, F8>, false, BKC>(p, s);
 }
 
 template <int EPI>
@@ -36,7 +36,7 @@ static hipError_t launch_rows(const GemmParams &p, const float *part, int nsplit
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_small(const SmallPlan &pl, int mode, bool f8, bool ak, bool bkc, const GemmParams &p, float *part, hipStream_t s)
+static SmallParams small_params(const GemmParams &p, bool f8)
 {
     const int64_t esz = f8 ? 1 : 2;
     SmallParams q{};
@@ -45,6 +45,12 @@ hipError_t launch_gemm_small(const SmallPlan &pl, int mode, bool f8, bool ak, bo
     q.lda = p.lda * esz;
     q.ldb = p.ldb * esz;
     q.M = p.M; q.N = p.N; q.K = p.K;
+    return q;
+}
+
+hipError_t launch_gemm_small(const SmallPlan &pl, int mode, bool f8, bool ak, bool bkc, const GemmParams &p, float *part, hipStream_t s)
+{
+    SmallParams q = small_params(p, f8);
     q.tiles_m = (p.M + pl.bm - 1) / pl.bm;
     q.tiles_n = (p.N + 127) / 128;
     q.nsplit = pl.nsplit;
@@ -59,6 +65,16 @@ hipError_t launch_gemm_small(const SmallPlan &pl, int mode, bool f8, bool ak, bo
     case EPI_RMSNORM_BWD: return launch_rows<EPI_RMSNORM_BWD>(p, part, pl.nsplit, s);
     default: return launch_rows<EPI_ACCUM>(p, part, pl.nsplit, s);
     }
+}
+
+hipError_t launch_gemm_direct(int tile, int mode, bool f8, bool ak, bool bkc, const GemmParams &p, hipStream_t s)
+{
+    const SmallParams q = small_params(p, f8);
+    if (f8)
+        return ak ? (bkc ? launch_small_direct<true, true, true>(tile, mode, p, q, s) : launch_small_direct<true, true, false>(tile, mode, p, q, s))
+                  : (bkc ? launch_small_direct<true, false, true>(tile, mode, p, q, s) : launch_small_direct<true, false, false>(tile, mode, p, q, s));
+    return ak ? (bkc ? launch_small_direct<false, true, true>(tile, mode, p, q, s) : launch_small_direct<false, true, false>(tile, mode, p, q, s))
+              : (bkc ? launch_small_direct<false, false, true>(tile, mode, p, q, s) : launch_small_direct<false, false, false>(tile, mode, p, q, s));
 }
 
 }  // namespace coda

@@ -91,11 +91,12 @@ struct SmallPlan {
     int bm;        // tile rows: 32, 64 or 128 (tiles are 128 columns wide)
     int nsplit;    // ranges of the contraction; 0: the shape runs on the large tiles
     int dense;     // 128 rows: two workgroups of four waves per CU instead of one of eight
+    double us;     // modelled time
 };
 constexpr int64_t SMALL_MAX_SPLIT = 16, SMALL_MIN_STAGES = 4;   // beyond that the exchange costs what the ranges save
 inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_contiguous)
 {
-    const SmallPlan none = {0, 0, 0};
+    const SmallPlan none = {0, 0, 0, 0.0};
     const SplitPlan big = plan_splitk(M, N, K, f8);
     if (big.chunks == 0 || big.first != 0) return none;
     const int64_t esz = f8 ? 1 : 2, stages = (K * esz + 127) / 128;
@@ -110,15 +111,71 @@ inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_c
         return ns;
     };
     const int64_t ns1 = ranges(SPLITK_CUS), ns2 = ranges(2 * SPLITK_CUS);
-    if (M <= 64) return SmallPlan{bm, (int)(ns1 > 0 ? ns1 : ns2), 0};             // (none if not even one fits)
     auto exchange = [&](int64_t ns) { return 6.0 + (double)(ns * M * N) * 8.0 / 5e6; };
+    if (M <= 64) {
+        const int64_t ns = ns1 > 0 ? ns1 : ns2;
+        if (ns == 0) return none;
+        return SmallPlan{bm, (int)ns, 0, 0.62 * (double)((stages + ns - 1) / ns) + exchange(ns)};
+    }
     const double never = 1e30;
     const double t1 = ns1 > 0 ? 0.66 * (double)((stages + ns1 - 1) / ns1) + exchange(ns1) : never;
     const double t2 = ns2 > ns1 ? 2.34e-3 * (double)(tiles * ns2 * ((stages + ns2 - 1) / ns2)) + exchange(ns2) : never;
     const int64_t pairs = (K * esz + 127) / 128, longest = 2 * ((big.tail * pairs + big.chunks - 1) / big.chunks);
     const double t_big = 0.83 * (double)longest + 10.0 + 5.0 * big.stride;
     if ((t1 < t2 ? t1 : t2) > 0.9 * t_big) return none;
-    return t1 <= t2 ? SmallPlan{bm, (int)ns1, 0} : SmallPlan{bm, (int)ns2, 1};
+    return t1 <= t2 ? SmallPlan{bm, (int)ns1, 0, t1} : SmallPlan{bm, (int)ns2, 1, t2};
+}
+
+// Undivided launches with small tiles, rows x columns of the tile: for what neither plan above divides (a short
+// contraction, no workspace) but 256 x 256 tiles leave mostly idle.  Row reductions are per 256 columns (`wide`), A with
+// rows not contiguous in K takes 128-row tiles, and the column reduction of RMSNORM_BWD stays on 256-row tiles.
+// 128x128_PAIR: two workgroups per CU, so that one's read-modify-write of the gradient runs under the other's contraction.
+//
+// Model in microseconds: launch, fill and epilogue, then per stage (128 bytes of K) and round of 256 workgroups, as
+// measured (bf16, cold weights; before is 256 x 256): 1 x 6144 x 2048: 64x64 12.9, 128x128 19.2, before 44.7; 1 x 2048 x 2000
+// with row sums: 32x256 18.3, 64x256 21.5, before 48.8; 509 x 6144 x 2048: 128x128 22.6, 128x256 31.7, before 46.1; 509 x
+// 16384 x 2048: 128x128 44.4, 128x256 34.8, before 46.8; 1000 x 16384 x 2048: 128x256 66.8, 256 x 256 55.4, which keeps it.
+// A plan_small() with one range per tile gives way to these where the model says so: 96 x 28672 x 4096 8-bit SwiGLU: 128x128
+// 29.2, partials and second kernel 34.2.
+// The gradient programs also read and write 8 bytes per element at 5 TB/s: 2048 x 11264 x 1000: PAIR 78.3, before 83.3.
+enum DirectTile : int { DIRECT_NONE = 0, DIRECT_64x64, DIRECT_32x256, DIRECT_64x256, DIRECT_128x128, DIRECT_128x128_PAIR, DIRECT_128x256 };
+enum DirectProgram : int { DIRECT_PROG_LINEAR, DIRECT_PROG_SWIGLU_FWD, DIRECT_PROG_SWIGLU_BWD, DIRECT_PROG_ACCUM };
+struct DirectPlan {
+    int tile;
+    double us;     // modelled time
+};
+inline DirectPlan plan_direct(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_contiguous, DirectProgram prog, bool wide)
+{
+    DirectPlan best = {DIRECT_NONE, 0.0};
+    if (M <= 0 || N <= 0 || K <= 0) return best;
+    const double stages = (double)((K * (f8 ? 1 : 2) + 127) / 128);
+    const double rmw = prog == DIRECT_PROG_ACCUM ? (double)M * (double)N * 8.0 / 5e6 : 0.0;
+    auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    auto rounds = [&](int64_t t) { return (double)((t + SPLITK_CUS - 1) / SPLITK_CUS); };
+    const int64_t big = tiles(PLAN_TILE_M, PLAN_TILE_N);
+    const double fill = big < SPLITK_CUS ? (double)big / (double)SPLITK_CUS : 1.0;
+    best.us = 0.92 * (6.0 + stages * (1.15 + 0.4 * fill) * rounds(big) + rmw);    // what a small tile has to beat
+    auto offer = [&](int tile, double us) {
+        if (us < best.us) best = DirectPlan{tile, us};
+    };
+    const bool few = a_k_contiguous && (prog == DIRECT_PROG_LINEAR || prog == DIRECT_PROG_SWIGLU_FWD);
+    // weights from HBM: 4.6 TB/s in rows of 64 columns, 5.6 in rows of 128 (28672 x 4096 bf16: 52.9 us, 44.4)
+    auto stream = [&](double us, double rate) {
+        const double hbm = (double)N * (double)K * (f8 ? 1.0 : 2.0) / rate;
+        return us > hbm ? us : hbm;
+    };
+    if (few && !wide) offer(DIRECT_64x64, 4.0 + stream(stages * 0.30 * rounds(tiles(64, 64)), 4.6e6));
+    if (few && prog == DIRECT_PROG_LINEAR) {
+        offer(DIRECT_32x256, 5.3 + stages * 0.45 * rounds(tiles(32, 256)));
+        offer(DIRECT_64x256, 5.5 + stages * 0.52 * rounds(tiles(64, 256)));
+    }
+    if (!wide) offer(DIRECT_128x128, 4.5 + stream(stages * 0.50 * rounds(tiles(128, 128)), 5.6e6) + rmw);
+    if (prog == DIRECT_PROG_ACCUM) {
+        const double pairs = (double)tiles(128, 128) / (2.0 * SPLITK_CUS);
+        offer(DIRECT_128x128_PAIR, 6.0 + stages * (pairs < 0.95 ? 0.95 : pairs) + 0.5 * rmw);
+    }
+    offer(DIRECT_128x256, 6.0 + stages * 0.85 * rounds(tiles(128, 256)) + rmw);
+    return best;
 }
 
 }  // namespace coda

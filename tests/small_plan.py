@@ -13,6 +13,7 @@ def load(folder):
                     os.path.join(ROOT, "tests", "small_plan_host.hip")], check=True, capture_output=True)
     lib = ctypes.CDLL(so)
     lib.host_small_plan.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 2 + [ctypes.POINTER(ctypes.c_int)]
+    lib.host_direct_tile.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 4
     lib.host_small_map.argtypes = [ctypes.c_int] * 3 + [ctypes.POINTER(ctypes.c_int)]
     return lib
 
@@ -22,3 +23,12 @@ def plan(lib, M, N, K, f8=False, ak=True):
     out = (ctypes.c_int * 3)()
     lib.host_small_plan(M, N, K, int(f8), int(ak), out)
     return tuple(out)
+
+
+TILES = ["256x256", "64x64", "32x256", "64x256", "128x128", "128x128_PAIR", "128x256"]     # coda::DirectTile
+PROGRAMS = ["linear", "swiglu_fwd", "swiglu_bwd", "accum"]                                 # coda::DirectProgram
+
+
+def direct_tile(lib, M, N, K, f8=False, ak=True, prog="linear", wide=False):
+    """The tile of an undivided launch; wide: the program reduces over rows."""
+    return TILES[lib.host_direct_tile(M, N, K, int(f8), int(ak), PROGRAMS.index(prog), int(wide))]

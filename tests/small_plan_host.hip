@@ -12,6 +12,12 @@ __attribute__((visibility("default"))) void host_small_plan(int64_t M, int64_t N
     plan[0] = pl.bm; plan[1] = pl.nsplit; plan[2] = pl.dense;
 }
 
+// the undivided small tile of a program (coda::DirectTile; 0: 256 x 256 tiles)
+__attribute__((visibility("default"))) int host_direct_tile(int64_t M, int64_t N, int64_t K, int f8, int ak, int prog, int wide)
+{
+    return coda::plan_direct(M, N, K, f8 != 0, ak != 0, (coda::DirectProgram)prog, wide != 0).tile;
+}
+
 // out[3 * bid ..] = tile row, tile column, range
 __attribute__((visibility("default"))) void host_small_map(int tiles_m, int tiles_n, int nsplit, int *out)
 {

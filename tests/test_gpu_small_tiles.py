@@ -158,3 +158,98 @@ def test_every_program(oracle, plans, M, N, K):
     G.assert_bf16_close(G.host_f64(Oout.t), refO, "O_out")
     G.assert_bf16_close(G.host_f64(Cout.t), refC, "C_out")
     G.assert_f32_signed_close(G.host_f64(dgp).sum(axis=0), refdg, "dgamma")
+
+
+# undivided launches: (M, N, K, f8, A transposed, B transposed, program, row reduction, tile): every tile with a ragged M, N and K, in
+# bf16 and 8 bits, both layouts of B (128-row tiles: all four), and one whole shape of the tiles that skip bounds checks
+DIRECT = [(1, 200, 72, False, False, False, "linear", False, "64x64"), (70, 520, 1000, False, False, True, "linear", False, "64x64"),
+          (33, 336, 1040, True, False, False, "linear", False, "64x64"), (100, 264, 272, True, False, True, "linear", False, "64x64"),
+          (1, 264, 8, False, False, False, "linear", True, "32x256"), (40, 520, 1000, False, False, True, "linear", True, "32x256"),
+          (33, 528, 1040, True, False, False, "linear", True, "32x256"), (20, 264, 272, True, False, True, "linear", True, "32x256"),
+          (2040, 2040, 1000, False, False, False, "linear", True, "64x256"), (2040, 2040, 1000, False, False, True, "linear", True, "64x256"),
+          (2040, 2032, 1040, True, False, False, "linear", True, "64x256"), (2040, 2032, 1040, True, False, True, "linear", True, "64x256"),
+          (8, 200, 72, False, False, False, "swiglu_fwd", False, "64x64"), (300, 1040, 1040, True, False, False, "swiglu_fwd", False, "64x64"),
+          (500, 6160, 1000, False, False, False, "swiglu_fwd", False, "128x128"), (512, 6144, 1024, False, False, True, "swiglu_fwd", False, "128x128"),
+          (500, 6160, 2064, True, False, False, "swiglu_fwd", False, "128x128"), (500, 6160, 2064, True, False, True, "swiglu_fwd", False, "128x128"),
+          (72, 520, 200, False, True, False, "linear", False, "128x128"), (72, 520, 200, False, True, True, "linear", False, "128x128"),
+          (80, 528, 400, True, True, False, "linear", False, "128x128"), (80, 528, 400, True, True, True, "linear", False, "128x128"),
+          (500, 16376, 1000, False, False, False, "swiglu_fwd", False, "128x256"), (512, 16384, 1024, False, False, False, "swiglu_fwd", False, "128x256"),
+          (500, 1032, 1000, False, False, True, "swiglu_bwd", True, "128x256"), (512, 1024, 1024, False, False, True, "swiglu_bwd", True, "128x256"),
+          (80, 528, 400, True, True, False, "linear", True, "128x256"), (80, 528, 400, True, True, True, "linear", True, "128x256"),
+          (504, 1032, 1000, False, True, True, "linear", True, "128x256"), (504, 1032, 1000, False, True, False, "linear", True, "128x256"),
+          (500, 1040, 1040, True, False, False, "swiglu_bwd", True, "128x256"), (500, 1040, 1040, True, False, True, "swiglu_bwd", True, "128x256"),
+          (1000, 2056, 504, False, True, False, "accum", False, "128x128"), (2048, 11264, 512, False, True, False, "accum", False, "128x128_PAIR"),
+          (2040, 4104, 1000, False, True, True, "accum", False, "128x128_PAIR"), (2032, 4112, 1040, True, True, False, "accum", False, "128x128_PAIR")]
+
+
+@pytest.mark.parametrize("M,N,K,f8,ta,tb,prog,red,tile", DIRECT)
+def test_undivided(oracle, plans, M, N, K, f8, ta, tb, prog, red, tile):
+    assert small_plan.direct_tile(plans, M, N, K, f8, not ta, prog, red) == tile
+    g = np.random.Generator(np.random.PCG64(5000 + M + N + K + 2 * ta + tb))
+    dA, dB, A, B = operands(oracle, g, M, N, K, ta, tb, f8, a_std=1e-2 if prog == "swiglu_bwd" else 1.0)
+    rows = None if M <= 300 else np.unique(np.concatenate([np.arange(0, M, 97), np.arange(0, M, 128), [M - 2, M - 1]]))
+    idx = torch.arange(M).cuda() if rows is None else torch.from_numpy(rows).cuda()
+    pick = lambda t: G.host_f64(t[idx])
+    r = synth.uniform_f32(g, (M,), 0.02, 0.06) if f8 else synth.uniform_f32(g, (M,), 0.5, 1.5)
+    dr, r64, nblk = G.dev_f32(r), r.astype(np.float64), coda.coda_row_partial_blocks(N)
+    part = torch.full((nblk, M), G.SENTINEL_F32, dtype=torch.float32, device="cuda")
+    kw = dict(transA=ta, transB=tb)
+    if prog == "linear":
+        C = synth.normal_bf16(g, (M, N), 1.0)
+        dC, Y = G.dev_bf16(C), G.Guarded(M, N, torch.bfloat16)
+        coda.coda_gemm(dA, dB, [coda.row_scale(dr), coda.add_tile(dC)] + ([coda.row_sumsq(part)] if red else []) + [coda.store(Y.t)], **kw)
+        torch.cuda.synchronize()
+        Y.check_guards(); Y.written()
+        ref, refss = oracle.gemm_residual_sumsq(A, B, r=r64, C=C, rows=rows, **kw)[:2]
+        G.assert_bf16_close(pick(Y.t), ref, "row scale + residual")
+        if red:
+            for b in range(nblk):
+                G.assert_sumsq_close(pick(part[b]), (ref[:, 256 * b:256 * b + 256] ** 2).sum(axis=1), "row sum of squares, block %d" % b)
+            y = np.ascontiguousarray(g.integers(0, N, M), dtype=np.int32)
+            dy, L = torch.from_numpy(y).cuda(), G.Guarded(M, N, torch.bfloat16)
+            pmax, psum = (torch.full((nblk, M), G.SENTINEL_F32, device="cuda") for _ in range(2))
+            zt, lse = (torch.full((M,), G.SENTINEL_F32, device="cuda") for _ in range(2))
+            coda.coda_gemm(dA, dB, [coda.row_scale(dr), coda.lse_partial(dy, pmax, psum, zt), coda.store(L.t)], **kw)
+            coda.coda_lse_finalize(pmax, psum, M, nblk, lse_out=lse)
+            torch.cuda.synchronize()
+            refZ, refzt, reflse = oracle.gemm_rowscale_lse(A, B, y, r=r64, rows=rows, **kw)
+            L.check_guards(); L.written()
+            G.assert_bf16_close(pick(L.t), refZ, "logits")
+            G.assert_f32_signed_close(pick(zt), refzt, "target logit")
+            G.assert_f32_signed_close(pick(lse), reflse, "lse")
+        else:
+            hd, T = 24, 50
+            cos, sin = synth.rope_tables(T, hd)
+            pos = np.ascontiguousarray(g.integers(0, T, M), dtype=np.int32)
+            dcos, dsin, dpos, Q = G.dev_f32(cos), G.dev_f32(sin), torch.from_numpy(pos).cuda(), G.Guarded(M, N, torch.bfloat16)
+            coda.coda_gemm(dA, dB, [coda.row_scale(dr), coda.rope(dcos, dsin, dpos, hd, N - 8), coda.store(Q.t)], **kw)
+            torch.cuda.synchronize()
+            Q.check_guards(); Q.written()
+            G.assert_bf16_close(pick(Q.t), oracle.gemm_rowscale_rope(A, B, cos, sin, pos, hd, N - 8, r=r64, rows=rows, **kw), "rope")
+    elif prog == "swiglu_fwd":
+        H, Z = G.Guarded(M, N // 2, torch.bfloat16), G.Guarded(M, N, torch.bfloat16)
+        coda.coda_gemm(dA, dB, [coda.row_scale(dr), coda.swiglu_fwd(Z.t), coda.store(H.t)], **kw)
+        torch.cuda.synchronize()
+        H.check_guards(); H.written(); Z.check_guards(); Z.written()
+        refH, refZ = oracle.gemm_rowscale_swiglu(A, B, r=r64, want_preact=True, rows=rows, **kw)
+        G.assert_bf16_close(pick(H.t), refH, "swiglu forward")
+        G.assert_bf16_close(pick(Z.t), refZ, "pre-activation")
+    elif prog == "swiglu_bwd":
+        Zin = synth.normal_bf16(g, (M, 2 * N), 1.0)
+        dZin, dZ, O = G.dev_bf16(Zin), G.Guarded(M, 2 * N, torch.bfloat16), G.Guarded(M, N, torch.bfloat16)
+        coda.coda_gemm(dA, dB, [coda.swiglu_bwd(dZin, act_out=O.t, stat_out=part), coda.store(dZ.t)], **kw)
+        torch.cuda.synchronize()
+        dZ.check_guards(); dZ.written(); O.check_guards(); O.written()
+        refdZ, refO, refstat = oracle.gemm_swiglu_bwd(A, B, Zin, rows=rows, **kw)
+        G.assert_bf16_close(pick(dZ.t), refdZ, "dZ")
+        G.assert_bf16_close(pick(O.t), refO, "activation")
+        G.assert_f32_signed_close(G.host_f64(part[:, idx]).sum(axis=0), refstat, "row statistic")
+    else:
+        Gin = synth.normal_f32(g, (M, N), 1e-1)
+        buf = G.Guarded(M, N, torch.float32, pad_cols=4)
+        buf.t.copy_(torch.from_numpy(Gin))
+        buf.ref = buf.full.clone()
+        coda.coda_gemm(dA, dB, [coda.accum_f32(buf.t)], **kw)
+        torch.cuda.synchronize()
+        buf.check_guards()
+        G.assert_f32_signed_close(pick(buf.t), oracle.gemm_accumulate(A, B, Gin, rows=rows, **kw), "accumulate")

@@ -42,3 +42,27 @@ def test_map_is_a_bijection(lib, tiles_m, tiles_n, ns):
     m = np.array(out).reshape(n, 3)
     assert (m.min(axis=0) >= 0).all() and (m.max(axis=0) == [tiles_m - 1, tiles_n - 1, ns - 1]).all()
     assert len({tuple(r) for r in m}) == n
+
+
+def test_undivided_tiles_suit_the_program(lib):
+    """Row reductions take 256-wide tiles, A not contiguous in K 128 rows; large launches keep the 256 x 256 tiles."""
+    rng = random.Random(6)
+    seen = set()
+    for _ in range(4000):
+        M, N, K = 8 * int(2 ** rng.uniform(0, 11)), 16 * int(2 ** rng.uniform(0, 10.5)), 16 * int(2 ** rng.uniform(0, 9))
+        for prog in small_plan.PROGRAMS:
+            for f8 in (False, True):
+                for ak in (True, False):
+                    for wide in (False, True) if prog in ("linear", "swiglu_bwd") else (False,):
+                        t = small_plan.direct_tile(lib, M, N, K, f8, ak, prog, wide)
+                        seen.add(t)
+                        if wide:
+                            assert t.endswith("x256")
+                        if not ak or prog in ("swiglu_bwd", "accum"):
+                            assert t.startswith(("128x", "256x"))
+                        if prog == "swiglu_fwd":
+                            assert t not in ("32x256", "64x256")
+                        assert (t != "128x128_PAIR") or prog == "accum"
+    assert seen == set(small_plan.TILES)
+    for M, N, K in ((8192, 16384, 2048), (16384, 6144, 4096), (8192, 32768, 4096), (8192, 8192, 8192)):
+        assert small_plan.direct_tile(lib, M, N, K) == "256x256"
