@@ -148,6 +148,8 @@ inline DirectPlan plan_direct(int64_t M, int64_t N, int64_t K, bool f8, bool a_k
 {
     DirectPlan best = {DIRECT_NONE, 0.0};
     if (M <= 0 || N <= 0 || K <= 0) return best;
+    // where a workspace lets the last round be shared, the tiles of the whole rounds are the same bits with and without one
+    if (plan_splitk(M, N, K, f8).first > 0) return best;
     const double stages = (double)((K * (f8 ? 1 : 2) + 127) / 128);
     const double rmw = prog == DIRECT_PROG_ACCUM ? (double)M * (double)N * 8.0 / 5e6 : 0.0;
     auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
