@@ -14,14 +14,14 @@ static hipError_t launch_partial(const SmallParams &p, hipStream_t s)
 }
 // Rings (measured at N x K = 28672 x 4096 bf16, 235 MB of weights): 32 rows, stages of 20 KB: two 58 us, three 45, four 48,
 // seven 50 -- past the ~40 KB in flight that the latency of memory asks for, more only queue up; 64 rows, stages of 24 KB:
-// two 62, three 50, six 50.  128 rows, one workgroup of eight waves per CU, stages of 32 KB: two 81, four 58; or two
-// workgroups of four waves with two stages each where there are tiles for both (768 x 4096 x 14336: 112 us against 150).
+// two 62, three 50, six 50.  128 rows: eight waves, one workgroup per CU, four stages of 32 KB (two: 81, four: 58) or, for
+// 256 columns, three of 48 KB.
 template <bool BKC, bool F8>
-static hipError_t launch_bm(const SmallPlan &pl, bool ak, const SmallParams &p, hipStream_t s)
+static hipError_t launch_tile(const SmallPlan &pl, bool ak, const SmallParams &p, hipStream_t s)
 {
     if (pl.bm == 32) return launch_partial<SmallCfg<32, 128, 1, 4, 3, F8>, true, BKC>(p, s);
     if (pl.bm == 64) return launch_partial<SmallCfg<64, 128, 1, 4, 3, F8>, true, BKC>(p, s);
-    if (pl.dense) return ak ? launch_partial<SmallCfg<128, 128, 2, 2, 2, F8>, true, BKC>(p, s) : launch_partial<SmallCfg<128, 128, 2, 2, 2, F8>, false, BKC>(p, s);
+    if (pl.bn == 256) return ak ? launch_partial<SmallCfg<128, 256, 2, 4, 3, F8>, true, BKC>(p, s) : launch_partial<SmallCfg<128, 256, 2, 4, 3, F8>, false, BKC>(p, s);
     return ak ? launch_partial<SmallCfg<128, 128, 2, 4, 4, F8>, true, BKC>(p, s) : launch_partial<SmallCfg<128, 128, 2, 4, 4, F8>, false, BKC>(p, s);
 }
 
@@ -52,11 +52,11 @@ hipError_t launch_gemm_small(const SmallPlan &pl, int mode, bool f8, bool ak, bo
 {
     SmallParams q = small_params(p, f8);
     q.tiles_m = (p.M + pl.bm - 1) / pl.bm;
-    q.tiles_n = (p.N + 127) / 128;
+    q.tiles_n = (p.N + pl.bn - 1) / pl.bn;
     q.nsplit = pl.nsplit;
     q.part = part;
-    const hipError_t e = f8 ? (bkc ? launch_bm<true, true>(pl, ak, q, s) : launch_bm<false, true>(pl, ak, q, s))
-                            : (bkc ? launch_bm<true, false>(pl, ak, q, s) : launch_bm<false, false>(pl, ak, q, s));
+    const hipError_t e = f8 ? (bkc ? launch_tile<true, true>(pl, ak, q, s) : launch_tile<false, true>(pl, ak, q, s))
+                            : (bkc ? launch_tile<true, false>(pl, ak, q, s) : launch_tile<false, false>(pl, ak, q, s));
     if (e != hipSuccess) return e;
     switch (mode) {
     case EPI_LINEAR: return launch_rows<EPI_LINEAR>(p, part, pl.nsplit, s);

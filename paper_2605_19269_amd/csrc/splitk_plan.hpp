@@ -71,7 +71,7 @@ inline size_t splitk_bytes(const SplitPlan &pl)
 }
 
 
-// Plan of the contractions with small output tiles (gemm_small.hpp): bm x 128 tiles, each cut along K into `nsplit` ranges
+// Plan of the contractions with small output tiles (gemm_small.hpp): bm x bn tiles, each cut along K into `nsplit` ranges
 // whose fp32 partials [nsplit][M][N] lie in the workspace.  It takes the place of the shared 256 x 256 tiles where every
 // tile of the shape would be shared (plan.first == 0), within the workspace that plan asks for, so that the sizes callers
 // see do not depend on which of the two runs.
@@ -81,49 +81,44 @@ inline size_t splitk_bytes(const SplitPlan &pl)
 // against 75.  One workgroup per CU is the best count there (at 6144 x 4096: 96, 240, 480, 768 workgroups: 18.9, 14.1,
 // 15.2, 16.3 us): twice as many pay more exchange and fill for bytes in flight that memory does not need.
 //
-// Above that, both kernels are modelled in microseconds from their measured parts:
-//   one stage (128 bytes of K) of a 128 x 128 tile, one workgroup per CU:        0.66, two per CU: 2.34e-3 per workgroup
+// Above that, the candidates are modelled in microseconds from their measured parts:
+//   one stage (128 bytes of K) of a 128 x 128 tile 0.57, of a 128 x 256 tile 0.83, one workgroup of either per CU
 //   partials: written once and read once at 5 TB/s; launches and epilogue: 6
-//   one K-step (64 bytes of K) of a 256 x 256 tile: 0.83; exchange of its parts: 10 + 5 per part of a tile
-// e.g. 384 x 6144 x 4096: model 39, measured 40 (256 x 256: 58); 1024 x 2048 x 8192: 57, 52 (80); 1024 x 4096 x 14336: 137, 145,
-// where the large tiles run 118 and keep the shape.  The small tiles must win by a tenth.
+//   one K-step (64 bytes of K) of a 256 x 256 tile 0.83; exchange of its parts 12 and 0.019 per range and slot, 25 more
+//   when ranges straddle tiles
+// e.g. (128 x 128 / 128 x 256 / 256 x 256, measured; the model is within 6 %, 256 x 256 within 20 %) 509 x 2048 x 8192: 32.5
+// / 32.9 / 61.7; 1000 x 2048 x 11264: 64.0 / 58.7 / 90.5; 768 x 4096 x 14336: 137 / 110 / 144; 1024 x 4096 x 14336: 150 / 129 /
+// 124, where the large tiles stay.  The small tiles must win by a tenth.  (Two workgroups of 128 x 128 tiles per CU, four
+// waves and two stages each, lie between: 384 x 6144 x 4096 40.6, 128 x 256 38.0; 768 x 4096 x 14336 113.)
 struct SmallPlan {
-    int bm;        // tile rows: 32, 64 or 128 (tiles are 128 columns wide)
+    int bm, bn;    // the tile: 32, 64 or 128 rows, 128 (or, with 128 rows, 256) columns
     int nsplit;    // ranges of the contraction; 0: the shape runs on the large tiles
-    int dense;     // 128 rows: two workgroups of four waves per CU instead of one of eight
     double us;     // modelled time
 };
 constexpr int64_t SMALL_MAX_SPLIT = 16, SMALL_MIN_STAGES = 4;   // beyond that the exchange costs what the ranges save
 inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_contiguous)
 {
+    if (M <= 0 || N <= 0 || K <= 0) return SmallPlan{0, 0, 0, 0.0};
     const SmallPlan none = {0, 0, 0, 0.0};
     const SplitPlan big = plan_splitk(M, N, K, f8);
     if (big.chunks == 0 || big.first != 0) return none;
     const int64_t esz = f8 ? 1 : 2, stages = (K * esz + 127) / 128;
     const int64_t budget = (int64_t)splitk_bytes(big) / (M * N * 4);              // ranges whose partials fit
-    const int bm = !a_k_contiguous || M > 64 ? 128 : (M > 32 ? 64 : 32);
-    const int64_t tiles = ((M + bm - 1) / bm) * ((N + 127) / 128);
-    auto ranges = [&](int64_t workgroups) {
-        int64_t ns = workgroups / tiles;
+    auto offer = [&](int bm, int bn, double stage_us) {
+        const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+        int64_t ns = SPLITK_CUS / tiles;
         if (ns > SMALL_MAX_SPLIT) ns = SMALL_MAX_SPLIT;
         if (ns > stages / SMALL_MIN_STAGES) ns = stages / SMALL_MIN_STAGES;
         if (ns > budget) ns = budget;
-        return ns;
+        if (ns < 1) return none;
+        return SmallPlan{bm, bn, (int)ns, 6.0 + stage_us * (double)((stages + ns - 1) / ns) + (double)(ns * M * N) * 8.0 / 5e6};
     };
-    const int64_t ns1 = ranges(SPLITK_CUS), ns2 = ranges(2 * SPLITK_CUS);
-    auto exchange = [&](int64_t ns) { return 6.0 + (double)(ns * M * N) * 8.0 / 5e6; };
-    if (M <= 64) {
-        const int64_t ns = ns1 > 0 ? ns1 : ns2;
-        if (ns == 0) return none;
-        return SmallPlan{bm, (int)ns, 0, 0.62 * (double)((stages + ns - 1) / ns) + exchange(ns)};
-    }
-    const double never = 1e30;
-    const double t1 = ns1 > 0 ? 0.66 * (double)((stages + ns1 - 1) / ns1) + exchange(ns1) : never;
-    const double t2 = ns2 > ns1 ? 2.34e-3 * (double)(tiles * ns2 * ((stages + ns2 - 1) / ns2)) + exchange(ns2) : never;
-    const int64_t pairs = (K * esz + 127) / 128, longest = 2 * ((big.tail * pairs + big.chunks - 1) / big.chunks);
-    const double t_big = 0.83 * (double)longest + 10.0 + 5.0 * big.stride;
-    if ((t1 < t2 ? t1 : t2) > 0.9 * t_big) return none;
-    return t1 <= t2 ? SmallPlan{bm, (int)ns1, 0, t1} : SmallPlan{bm, (int)ns2, 1, t2};
+    if (M <= 64 && a_k_contiguous) return M <= 32 ? offer(32, 128, 0.62) : offer(64, 128, 0.62);
+    const SmallPlan narrow = offer(128, 128, 0.57), wide = offer(128, 256, 0.83);
+    const SmallPlan best = wide.nsplit == 0 || (narrow.nsplit != 0 && narrow.us <= wide.us) ? narrow : wide;
+    const int64_t longest = 2 * ((big.tail * stages + big.chunks - 1) / big.chunks);   // K-steps of the longest range
+    const double t_big = 0.83 * (double)longest + 12.0 + 0.019 * big.chunks * big.stride + (big.pieces > 1 ? 25.0 : 0.0);
+    return best.nsplit != 0 && best.us <= 0.9 * t_big ? best : none;
 }
 
 // Undivided launches with small tiles, rows x columns of the tile: for what neither plan above divides (a short
@@ -132,12 +127,16 @@ inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_c
 // 128x128_PAIR: two workgroups per CU, so that one's read-modify-write of the gradient runs under the other's contraction.
 //
 // Model in microseconds: launch, fill and epilogue, then per stage (128 bytes of K) and round of 256 workgroups, as
-// measured (bf16, cold weights; before is 256 x 256): 1 x 6144 x 2048: 64x64 12.9, 128x128 19.2, before 44.7; 1 x 2048 x 2000
-// with row sums: 32x256 18.3, 64x256 21.5, before 48.8; 509 x 6144 x 2048: 128x128 22.6, 128x256 31.7, before 46.1; 509 x
-// 16384 x 2048: 128x128 44.4, 128x256 34.8, before 46.8; 1000 x 16384 x 2048: 128x256 66.8, 256 x 256 55.4, which keeps it.
+// measured with cold weights (bf16; before is 256 x 256): 64 x 6144 x 2048: 64x64 15.5, 128x128 20.6, before 45.1; 64 x 22272 x
+// 4096: 128x128 41.0, 64x64 50.6, before 83.8, with row sums: 32x256 51.5, 64x256 55.4, before 86.8; 300 x 11008 x 3000 with
+// row sums: 64x256 41.1, 128x256 46.0, before 67.8; 509 x 6144 x 2048: 128x128 22.6, 128x256 31.7, before 46.1; 509 x 16384 x
+// 2048: 128x256 34.8, 128x128 44.4, before 46.8; 257 x 22312 x 4096: 64x256 105, 128x256 120, 256 x 256 94, which keeps it, as it
+// does 1000 x 16384 x 2048 (128x256 66.8, 256 x 256 55.4).
 // A plan_small() with one range per tile gives way to these where the model says so: 96 x 28672 x 4096 8-bit SwiGLU: 128x128
 // 29.2, partials and second kernel 34.2.
-// The gradient programs also read and write 8 bytes per element at 5 TB/s: 2048 x 11264 x 1000: PAIR 78.3, before 83.3.
+// The gradient program also reads and writes 8 bytes per element, two thirds of it (PAIR: half) beside the contraction of
+// other workgroups: 2048 x 11264 x 1000: PAIR 78, 256 x 256 85; 5976 x 2968 x 720: 52, 67; 5632 x 2048 x 2552: 72, 69 and 11008 x
+// 4096 x 1000: 129, 126, which stay.
 enum DirectTile : int { DIRECT_NONE = 0, DIRECT_64x64, DIRECT_32x256, DIRECT_64x256, DIRECT_128x128, DIRECT_128x128_PAIR, DIRECT_128x256 };
 enum DirectProgram : int { DIRECT_PROG_LINEAR, DIRECT_PROG_SWIGLU_FWD, DIRECT_PROG_SWIGLU_BWD, DIRECT_PROG_ACCUM };
 struct DirectPlan {
@@ -156,27 +155,28 @@ inline DirectPlan plan_direct(int64_t M, int64_t N, int64_t K, bool f8, bool a_k
     auto rounds = [&](int64_t t) { return (double)((t + SPLITK_CUS - 1) / SPLITK_CUS); };
     const int64_t big = tiles(PLAN_TILE_M, PLAN_TILE_N);
     const double fill = big < SPLITK_CUS ? (double)big / (double)SPLITK_CUS : 1.0;
-    best.us = 0.92 * (6.0 + stages * (1.15 + 0.4 * fill) * rounds(big) + rmw);    // what a small tile has to beat
+    best.us = (prog == DIRECT_PROG_ACCUM ? 0.99 : 0.92) * (6.0 + stages * (1.15 + 0.4 * fill) * rounds(big) + 0.64 * rmw);    // what a small tile has to beat
     auto offer = [&](int tile, double us) {
         if (us < best.us) best = DirectPlan{tile, us};
     };
     const bool few = a_k_contiguous && (prog == DIRECT_PROG_LINEAR || prog == DIRECT_PROG_SWIGLU_FWD);
-    // weights from HBM: 4.6 TB/s in rows of 64 columns, 5.6 in rows of 128 (28672 x 4096 bf16: 52.9 us, 44.4)
+    // weights from HBM: 4.6 TB/s in rows of 64 columns, 5.6 in rows of 128 (28672 x 4096 bf16: 52.9 us, 44.4), 3.9 through one 256-wide
+    // workgroup per CU
     auto stream = [&](double us, double rate) {
         const double hbm = (double)N * (double)K * (f8 ? 1.0 : 2.0) / rate;
         return us > hbm ? us : hbm;
     };
-    if (few && !wide) offer(DIRECT_64x64, 4.0 + stream(stages * 0.30 * rounds(tiles(64, 64)), 4.6e6));
+    if (few && !wide) offer(DIRECT_64x64, 4.0 + stream(stages * 0.34 * rounds(tiles(64, 64)), 4.6e6));
     if (few && prog == DIRECT_PROG_LINEAR) {
-        offer(DIRECT_32x256, 5.3 + stages * 0.45 * rounds(tiles(32, 256)));
-        offer(DIRECT_64x256, 5.5 + stages * 0.52 * rounds(tiles(64, 256)));
+        offer(DIRECT_32x256, 5.3 + stream(stages * 0.55 * rounds(tiles(32, 256)), 3.9e6));
+        offer(DIRECT_64x256, 5.5 + stages * 0.68 * rounds(tiles(64, 256)));
     }
-    if (!wide) offer(DIRECT_128x128, 4.5 + stream(stages * 0.50 * rounds(tiles(128, 128)), 5.6e6) + rmw);
+    if (!wide) offer(DIRECT_128x128, 4.5 + stream(stages * 0.57 * rounds(tiles(128, 128)), 5.6e6) + rmw);
     if (prog == DIRECT_PROG_ACCUM) {
         const double pairs = (double)tiles(128, 128) / (2.0 * SPLITK_CUS);
-        offer(DIRECT_128x128_PAIR, 6.0 + stages * (pairs < 0.95 ? 0.95 : pairs) + 0.5 * rmw);
+        offer(DIRECT_128x128_PAIR, 6.0 + 1.08 * stages * (pairs < 0.9 ? 0.9 : pairs) + 0.55 * rmw);
     }
-    offer(DIRECT_128x256, 6.0 + stages * 0.85 * rounds(tiles(128, 256)) + rmw);
+    offer(DIRECT_128x256, 6.0 + stages * 0.88 * rounds(tiles(128, 256)) + rmw);
     return best;
 }
 

@@ -19,7 +19,7 @@ def load(folder):
 
 
 def plan(lib, M, N, K, f8=False, ak=True):
-    """(tile rows, ranges, dense); ranges = 0: the shape runs on the large tiles."""
+    """(tile rows, tile columns, ranges); ranges = 0: the shape runs on the large tiles."""
     out = (ctypes.c_int * 3)()
     lib.host_small_plan(M, N, K, int(f8), int(ak), out)
     return tuple(out)

@@ -5,11 +5,11 @@
 
 extern "C" {
 
-// plan[0..2] = tile rows, ranges (0: large tiles), dense
+// plan[0..2] = tile rows, tile columns, ranges (0: large tiles)
 __attribute__((visibility("default"))) void host_small_plan(int64_t M, int64_t N, int64_t K, int f8, int ak, int *plan)
 {
     const coda::SmallPlan pl = coda::plan_small(M, N, K, f8 != 0, ak != 0);
-    plan[0] = pl.bm; plan[1] = pl.nsplit; plan[2] = pl.dense;
+    plan[0] = pl.bm; plan[1] = pl.bn; plan[2] = pl.nsplit;
 }
 
 // the undivided small tile of a program (coda::DirectTile; 0: 256 x 256 tiles)

@@ -1,5 +1,4 @@
-"""GPU parity of the small-tile contraction and of the row-wise epilogue behind it: every tile height and both occupancies of
-the 128-row tiles, at the edges of M, N and K, every epilogue program, all layouts, bf16 and 8-bit operands, against the
+"""GPU parity of the small-tile contraction and of the row-wise epilogue behind it: every tile, at the edges of M, N and K, every epilogue program, all layouts, bf16 and 8-bit operands, against the
 oracle with the bounds of gpu_util."""
 import numpy as np
 import pytest
@@ -42,20 +41,20 @@ def operands(oracle, g, M, N, K, ta, tb, f8, a_std=1.0, b_std=0.05):
     return G.dev_bf16(A), G.dev_bf16(B), A, B
 
 
-# (M, N, K, f8, A transposed, B transposed, expected (tile rows, dense)): one row; a full tile row; one row past it; ragged
-# widths; K past a whole stage by 8 (bf16), 16 (8-bit); two tile rows; one and two workgroups per CU; all layouts
-CASES = [(1, 264, 4104, False, False, False, (32, 0)), (32, 1000, 6144, False, False, True, (32, 0)), (33, 520, 4168, False, False, False, (64, 0)),
-         (64, 256, 8192, False, False, True, (64, 0)), (65, 776, 4104, False, False, False, (128, 0)), (200, 1032, 4096, False, False, True, (128, 0)),
-         (72, 520, 4168, False, True, False, (128, 0)), (128, 256, 4096, False, True, True, (128, 0)), (192, 6152, 4104, False, False, False, (128, 1)),
-         (8, 256, 4112, True, False, True, (32, 0)), (31, 528, 4096, True, False, False, (32, 0)), (50, 520, 4112, True, False, True, (64, 0)),
-         (96, 784, 4112, True, False, False, (128, 0)), (112, 272, 4096, True, True, False, (128, 0)), (144, 264, 4112, True, True, True, (128, 0)),
-         (200, 8208, 4112, True, False, True, (128, 1)), (192, 8208, 4112, True, False, False, (128, 1))]
+# (M, N, K, f8, A transposed, B transposed, expected tile): one row; a full tile row; one row past it; ragged
+# widths; K past a whole stage by 8 (bf16), 16 (8-bit); two tile rows; both widths of the 128-row tiles; all layouts
+CASES = [(1, 264, 4104, False, False, False, (32, 128)), (32, 1000, 6144, False, False, True, (32, 128)), (33, 520, 4168, False, False, False, (64, 128)),
+         (64, 256, 8192, False, False, True, (64, 128)), (65, 776, 4104, False, False, False, (128, 128)), (200, 1032, 4096, False, False, True, (128, 128)),
+         (72, 520, 4168, False, True, False, (128, 128)), (128, 256, 4096, False, True, True, (128, 128)), (1000, 2056, 11272, False, False, True, (128, 256)), (1000, 1032, 8200, False, False, False, (128, 256)), (504, 2056, 11272, False, True, False, (128, 256)), (504, 2056, 11272, False, True, True, (128, 256)),
+         (8, 256, 4112, True, False, True, (32, 128)), (31, 528, 4096, True, False, False, (32, 128)), (50, 520, 4112, True, False, True, (64, 128)),
+         (96, 784, 4112, True, False, False, (128, 128)), (112, 272, 4096, True, True, False, (128, 128)), (144, 264, 4112, True, True, True, (128, 128)),
+         (1000, 2056, 11280, True, False, True, (128, 256)), (1000, 2064, 11280, True, False, False, (128, 256)), (1008, 2064, 11280, True, True, False, (128, 256)), (1008, 2064, 11280, True, True, True, (128, 256))]
 
 
 @pytest.mark.parametrize("M,N,K,f8,ta,tb,expect", CASES)
 def test_linear_program(oracle, plans, M, N, K, f8, ta, tb, expect):
-    bm, ns, dense = small_plan.plan(plans, M, N, K, f8, not ta)
-    assert ns > 0 and (bm, dense) == expect
+    bm, bn, ns = small_plan.plan(plans, M, N, K, f8, not ta)
+    assert ns > 0 and (bm, bn) == expect
     g = np.random.Generator(np.random.PCG64(4000 + M + N + K + 2 * ta + tb))
     dA, dB, A, B = operands(oracle, g, M, N, K, ta, tb, f8)
     C, r, gamma = synth.normal_bf16(g, (M, N), 1.0), synth.uniform_f32(g, (M,), 0.02, 0.06), synth.uniform_f32(g, (N,), 0.5, 1.5)
@@ -81,7 +80,7 @@ def test_linear_program(oracle, plans, M, N, K, f8, ta, tb, expect):
 
 @pytest.mark.parametrize("M,N,K", [(1, 264, 4104), (40, 520, 4096), (200, 1032, 4168)])
 def test_every_program(oracle, plans, M, N, K):
-    assert small_plan.plan(plans, M, N, K)[1] > 0
+    assert small_plan.plan(plans, M, N, K)[2] > 0
     g = np.random.Generator(np.random.PCG64(4500 + M))
     dA, dB, A, B = operands(oracle, g, M, N, K, False, False, False)
     r, ws, nblk = synth.uniform_f32(g, (M,), 0.5, 1.5), workspace(M, N, K), coda.coda_row_partial_blocks(N)
