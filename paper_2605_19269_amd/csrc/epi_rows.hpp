@@ -7,25 +7,25 @@
 // few rows spread over the chip.  Bound by reading the partials (from L2 and the memory-side cache, where the first
 // kernel left them).
 //
-// RMSNORM_BWD also reduces over the columns of 256-row blocks: there a workgroup owns 256 rows x 64 columns, 16 lanes a row.
+// RMSNORM_BWD also reduces over the columns of 256-row blocks: there a workgroup owns 256 rows x 32 columns, 8 lanes a row.
 #pragma once
 #include "gemm_kernel.hpp"
 
 namespace coda {
 
+// The ranges' partials of four columns, added up in range order, eight loads in flight: with one row there is nothing else to
+// hide a load's latency under (4096 columns of 8 ranges, one row: 4.0 us with the last three loaded one by one).
 __device__ __forceinline__ f32x4 sum_parts(const float *part, int nsplit, int64_t stride)
 {
-    // four loads in flight, added up in range order
-    f32x4 v = *reinterpret_cast<const f32x4 *>(part);
-    int s = 1;
-    for (; s + 3 < nsplit; s += 4) {
-        f32x4 t[4];
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < nsplit; s += 8) {
+        f32x4 t[8];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) t[q] = *reinterpret_cast<const f32x4 *>(part + (s + q) * stride);
+        for (int q = 0; q < 8; ++q) t[q] = *reinterpret_cast<const f32x4 *>(part + (s + q < nsplit ? s + q : nsplit - 1) * stride);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v += t[q];
+        for (int q = 0; q < 8; ++q)
+            if (s + q < nsplit) v = s + q == 0 ? t[q] : v + t[q];
     }
-    for (; s < nsplit; ++s) v += *reinterpret_cast<const f32x4 *>(part + s * stride);
     return v;
 }
 __device__ __forceinline__ f32x4 unpack4(u32x2 c) { return f32x4{bf16_lo(c[0]), bf16_hi(c[0]), bf16_lo(c[1]), bf16_hi(c[1])}; }
@@ -38,6 +38,7 @@ __device__ __forceinline__ float wave_sum(float v)
 }
 
 constexpr int EPI_ROWS = 4;    // rows (waves) per workgroup
+constexpr int EPI_COLS = 32;   // columns per workgroup of epi_cols_kernel: 256 workgroups at 1000 x 2048 (64 columns: half the CUs idle)
 
 template <int EPI>
 __global__ __launch_bounds__(256) void epi_rows_kernel(const GemmParams p, const float *__restrict__ part, const int nsplit)
@@ -48,6 +49,15 @@ __global__ __launch_bounds__(256) void epi_rows_kernel(const GemmParams p, const
     if (m >= p.M) return;
     const bool ok = n < p.N;
     const int64_t plane = (int64_t)p.M * p.N;
+    // the program's own inputs travel with the partials
+    float rs = 1.0f;
+    u32x2 res = {0u, 0u};
+    u32x4 z = {0u, 0u, 0u, 0u};
+    int pos = 0;
+    if ((EPI == EPI_LINEAR || EPI == EPI_SWIGLU_FWD) && p.row_scale) rs = p.row_scale[m];
+    if (EPI == EPI_LINEAR && p.rope_cos) pos = clampi(p.rope_pos[m], 0, p.rope_T - 1);
+    if (EPI == EPI_LINEAR && p.add && ok) res = *reinterpret_cast<const u32x2 *>(p.add + (int64_t)m * p.ld_add + n);
+    if (EPI == EPI_SWIGLU_BWD && ok) z = *reinterpret_cast<const u32x4 *>(p.Z + (int64_t)m * p.ldz + 2 * n);
     f32x4 v = {0.f, 0.f, 0.f, 0.f};
     if (ok) v = sum_parts(part + (int64_t)m * p.N + n, nsplit, plane);
     float red = 0.0f;
@@ -60,14 +70,13 @@ __global__ __launch_bounds__(256) void epi_rows_kernel(const GemmParams p, const
         return;
     } else if constexpr (EPI == EPI_SWIGLU_FWD) {
         if (!ok) return;
-        v *= p.row_scale ? p.row_scale[m] : 1.0f;
+        v *= rs;
         const float h0 = v[0] * fast_sigmoid(v[0]) * v[1], h1 = v[2] * fast_sigmoid(v[2]) * v[3];
         *reinterpret_cast<uint32_t *>(reinterpret_cast<uint16_t *>(p.out) + (int64_t)m * p.ld_out + (n >> 1)) = pack_bf16x2(h0, h1);
         if (p.out2) *reinterpret_cast<u32x2 *>(p.out2 + (int64_t)m * p.ld_out2 + n) = pack4(v);
         return;
     } else if constexpr (EPI == EPI_SWIGLU_BWD) {
         if (ok) {
-            const u32x4 z = *reinterpret_cast<const u32x4 *>(p.Z + (int64_t)m * p.ldz + 2 * n);
             u32x4 dz;
             f32x4 act;
 #pragma unroll
@@ -83,7 +92,6 @@ __global__ __launch_bounds__(256) void epi_rows_kernel(const GemmParams p, const
             if (p.out2) *reinterpret_cast<u32x2 *>(p.out2 + (int64_t)m * p.ld_out2 + n) = pack4(act);
         }
     } else {
-        const float rs = p.row_scale ? p.row_scale[m] : 1.0f;
         if (p.lse_max) {
             constexpr float NEG_INF = -__builtin_inff(), LOG2E = 1.4426950408889634f;
             const f32x4 s = v * rs;
@@ -107,8 +115,8 @@ __global__ __launch_bounds__(256) void epi_rows_kernel(const GemmParams p, const
         v *= rs;
         if (ok) {
             if (p.rope_cos && n < p.rope_cols)
-                rope_unit(v, p, (int64_t)clampi(p.rope_pos[m], 0, p.rope_T - 1) * p.rope_half, (n >> 1) % p.rope_half);
-            if (p.add) v += unpack4(*reinterpret_cast<const u32x2 *>(p.add + (int64_t)m * p.ld_add + n));
+                rope_unit(v, p, (int64_t)pos * p.rope_half, (n >> 1) % p.rope_half);
+            if (p.add) v += unpack4(res);
             red = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
             if (p.side)
                 *reinterpret_cast<u32x2 *>(p.side + (int64_t)m * p.ld_side + n) = pack4(v * *reinterpret_cast<const f32x4 *>(p.col_scale + n));
@@ -125,13 +133,13 @@ __global__ __launch_bounds__(256) void epi_rows_kernel(const GemmParams p, const
     }
 }
 
-// RMSNORM_BWD: 16 waves; 16 lanes x 4 columns a row, 64 rows per step of the workgroup.
+// RMSNORM_BWD: 256 rows x 32 columns, 16 waves of eight rows a step, 8 lanes x 4 columns a row.
 template <int EPI>
 __global__ __launch_bounds__(1024) void epi_cols_kernel(const GemmParams p, const float *__restrict__ part, const int nsplit)
 {
-    constexpr int ROWS = 256, COLS = 64, STEP = 64;
-    __shared__ f32x4 cs[STEP][COLS / 4];
-    const int rl = threadIdx.x >> 4, cl = threadIdx.x & 15, n = blockIdx.x * COLS + cl * 4;
+    constexpr int ROWS = 256, COLS = EPI_COLS, STEP = 128;
+    __shared__ f32x4 cs[16][COLS / 4];
+    const int rl = threadIdx.x >> 3, cl = threadIdx.x & 7, n = blockIdx.x * COLS + cl * 4;
     const bool nok = n < p.N;
     const int64_t plane = (int64_t)p.M * p.N;
     f32x4 dg = {0.f, 0.f, 0.f, 0.f}, gm = dg;
@@ -140,24 +148,32 @@ __global__ __launch_bounds__(1024) void epi_cols_kernel(const GemmParams p, cons
     for (int st = 0; st < ROWS / STEP; ++st) {
         const int m = blockIdx.y * ROWS + st * STEP + rl;
         if (m >= p.M || !nok) continue;
+        // the row's own inputs travel with the partials
         const float rr = p.rn_r[m], zz = p.rn_z[m] * p.rn_zscale;
+        const u32x2 c = *reinterpret_cast<const u32x2 *>(p.rn_c + (int64_t)m * p.ld_rn_c + n);
+        u32x2 res = {0u, 0u};
+        if (p.add) res = *reinterpret_cast<const u32x2 *>(p.add + (int64_t)m * p.ld_add + n);
         const f32x4 d = sum_parts(part + (int64_t)m * p.N + n, nsplit, plane);
-        const f32x4 cn = unpack4(*reinterpret_cast<const u32x2 *>(p.rn_c + (int64_t)m * p.ld_rn_c + n)) * rr;
+        const f32x4 cn = unpack4(c) * rr;
         f32x4 o = (d * gm - cn * zz) * rr;
-        if (p.add) o += unpack4(*reinterpret_cast<const u32x2 *>(p.add + (int64_t)m * p.ld_add + n));
+        if (p.add) o += unpack4(res);
         dg += d * cn;
         *reinterpret_cast<u32x2 *>(reinterpret_cast<uint16_t *>(p.out) + (int64_t)m * p.ld_out + n) = pack4(o);
         if (p.out2) *reinterpret_cast<u32x2 *>(p.out2 + (int64_t)m * p.ld_out2 + n) = pack4(cn * gm);
     }
     if (p.colred_mode == ROWRED_NONE) return;
-    cs[rl][cl] = dg;
+    // column sums: the eight rows of a wave, then the sixteen waves in order
+#pragma unroll
+    for (int off = 8; off < 64; off <<= 1)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dg[e] += __shfl_xor(dg[e], off, 64);
+    if ((threadIdx.x & 63) < 8) cs[threadIdx.x >> 6][cl] = dg;
     __syncthreads();
-    if (threadIdx.x >= COLS) return;
-    float t = 0.0f;
-#pragma unroll 8
-    for (int r = 0; r < STEP; ++r) t += reinterpret_cast<const float *>(cs[r])[threadIdx.x];
     const int nc = blockIdx.x * COLS + threadIdx.x;
-    if (nc >= p.N) return;
+    if (threadIdx.x >= COLS || nc >= p.N) return;
+    float t = 0.0f;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) t += reinterpret_cast<const float *>(cs[w])[threadIdx.x];
     if (p.colred_mode == ROWRED_PARTIALS) p.colred[(int64_t)blockIdx.y * p.N + nc] = t;
     else atomicAdd(p.colred + nc, t);
 }

@@ -29,7 +29,7 @@ template <int EPI>
 static hipError_t launch_rows(const GemmParams &p, const float *part, int nsplit, hipStream_t s)
 {
     if constexpr (EPI == EPI_RMSNORM_BWD)
-        hipLaunchKernelGGL((epi_cols_kernel<EPI>), dim3((unsigned)((p.N + 63) / 64), (unsigned)((p.M + 255) / 256)), dim3(1024), 0, s, p, part, nsplit);
+        hipLaunchKernelGGL((epi_cols_kernel<EPI>), dim3((unsigned)((p.N + EPI_COLS - 1) / EPI_COLS), (unsigned)((p.M + 255) / 256)), dim3(1024), 0, s, p, part, nsplit);
     else
         hipLaunchKernelGGL((epi_rows_kernel<EPI>), dim3((unsigned)((p.N + 255) / 256), (unsigned)((p.M + EPI_ROWS - 1) / EPI_ROWS)), dim3(256), 0, s, p,
                            part, nsplit);
