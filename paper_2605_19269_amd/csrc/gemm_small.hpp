@@ -176,15 +176,19 @@ __device__ __forceinline__ void small_contract(f32x4 (&acc)[C::WTM / 16][C::WTN 
         if (BKC) next = next == KT ? 0 : next;
         slot_in = slot_in + C::STAGE == C::LDS ? 0u : slot_in + C::STAGE;
     };
-    auto issue = [&]() {
+    // part q of Q of the stage's loads; the last part moves on to the next stage
+    auto issue_part = [&](int q, int Q) {
         const unsigned char *sa = ga + (int64_t)next * stepa, *sb = gb + (int64_t)next * stepb;
         const uint32_t la = lds0 + slot_in + (uint32_t)(wave * C::LA * 1024), lb = lds0 + slot_in + (uint32_t)(C::A_BYTES + wave * C::LB * 1024);
 #pragma unroll
-        for (int i = 0; i < C::LA; ++i) dl_load16(offa[i], sa, la + (uint32_t)(i * 1024));
-#pragma unroll
-        for (int i = 0; i < C::LB; ++i) dl_load16(offb[i], sb, lb + (uint32_t)(i * 1024));
-        advance();
+        for (int i = 0; i < L; ++i) {
+            if (i < q * L / Q || i >= (q + 1) * L / Q) continue;
+            if (i < C::LA) dl_load16(offa[i < C::LA ? i : 0], sa, la + (uint32_t)(i * 1024));
+            else dl_load16(offb[i < C::LA ? 0 : i - C::LA], sb, lb + (uint32_t)((i - C::LA) * 1024));
+        }
+        if (q == Q - 1) advance();
     };
+    auto issue = [&]() { issue_part(0, 1); };
     auto issue_last = [&]() {                        // the stage that reaches past K
         const int have = p.K - (kbeg + KT - 1) * C::BK;
         const unsigned char *sa = ga + (int64_t)next * stepa, *sb = gb + (int64_t)next * stepb;
@@ -204,17 +208,28 @@ __device__ __forceinline__ void small_contract(f32x4 (&acc)[C::WTM / 16][C::WTN 
     };
     SmallFrag<C> fa0[NB], fb0[NU], fa1[NB], fb1[NU];
     uint32_t slot_out = 0;                           // the slot being read
-    auto read = [&](SmallFrag<C>(&fa)[NB], SmallFrag<C>(&fb)[NU], int h) {
+    // part q of Q of a step's fragments
+    auto read_part = [&](SmallFrag<C>(&fa)[NB], SmallFrag<C>(&fb)[NU], int h, int q, int Q) {
         const unsigned char *ta = smem + slot_out, *tb = ta + C::A_BYTES;
 #pragma unroll
-        for (int u = 0; u < NU; ++u) fb[u] = small_frag<C, BKC, C::BN>(tb, wn * C::WTN + u * 16, lane, h);
-#pragma unroll
-        for (int i = 0; i < NB; ++i) fa[i] = small_frag<C, AK, C::BM>(ta, wm * C::WTM + i * 16, lane, h);
-    };
-    auto mma = [&](const SmallFrag<C>(&fa)[NB], const SmallFrag<C>(&fb)[NU]) {
-        __builtin_amdgcn_sched_barrier(0);
+        for (int u = 0; u < NU; ++u)
+            if (u >= q * NU / Q && u < (q + 1) * NU / Q) fb[u] = small_frag<C, BKC, C::BN>(tb, wn * C::WTN + u * 16, lane, h);
 #pragma unroll
         for (int i = 0; i < NB; ++i)
+            if (i >= q * NB / Q && i < (q + 1) * NB / Q) fa[i] = small_frag<C, AK, C::BM>(ta, wm * C::WTM + i * 16, lane, h);
+    };
+    // One MFMA step on f*, a row of blocks at a time.  `beside(i)` issues the loads and fragment reads of the next step: behind
+    // row i where two waves share a SIMD in step, so that the matrix pipe starts at once after a barrier and works while they
+    // are issued in its shadow (128x256: 509 x 16384 x 2048 37.5 -> 34.7 us); ahead of the rows where a wave has its SIMD to
+    // itself or shares it with another workgroup's (1 x 6144 x 2048 at 64x64: 12.8 us against 13.5).
+    auto mma = [&](const SmallFrag<C>(&fa)[NB], const SmallFrag<C>(&fb)[NU], auto beside) {
+        if (C::NW < 8) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) beside(i);
+        }
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            if (C::NW >= 8 || i == 0) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int u = 0; u < NU; ++u) {
                 if constexpr (C::F8)
@@ -222,6 +237,10 @@ __device__ __forceinline__ void small_contract(f32x4 (&acc)[C::WTM / 16][C::WTN 
                 else
                     acc[i][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[u], fa[i], acc[i][u], 0, 0, 0);
             }
+            if (C::NW < 8) continue;
+            __builtin_amdgcn_sched_barrier(0);
+            beside(i);
+        }
         __builtin_amdgcn_sched_barrier(0);
     };
     // Behind the wait for a stage's loads: this wave's own LDS reads so far have returned and its zero stores are done;
@@ -239,34 +258,34 @@ __device__ __forceinline__ void small_contract(f32x4 (&acc)[C::WTM / 16][C::WTN 
     // takes its next fragments from the next stage: that is where the stage's one barrier and the refill of its slot are.
     // `steady`: the refill exists and lies inside K, no stage in flight is the one past K.
     auto stage = [&](int t, bool steady, SmallFrag<C>(&fa)[NB], SmallFrag<C>(&fb)[NU], SmallFrag<C>(&ha)[NB], SmallFrag<C>(&hb)[NU]) {
-        if constexpr (KS == 2) {
-            read(ha, hb, 1);
-            mma(fa, fb);
-        }
+        if constexpr (KS == 2) mma(fa, fb, [&](int i) { read_part(ha, hb, 1, i, NB); });
+        const bool more = steady || t + 1 < KT;      // there is a next stage to read
+        bool fill = steady;                          // and one to fetch, in full
         if (steady) {
             wait_loads<(S - 2) * L>();
             meet();
-            issue();
             next_slot();
-        } else if (t + 1 < KT) {
+        } else if (more) {
             const int ahead = KT - 2 - t;            // stages behind t + 1
             if (ragged && ahead <= S - 1) wait_loads<0>();
             else if (ahead >= S - 2) wait_loads<(S - 2) * L>();
             else wait_stages<S - 3, L>(ahead);
             meet();
-            if (t + S < KT) {
-                if (ragged && t + S == KT - 1) issue_last();
-                else issue();
-            }
             next_slot();
+            fill = t + S < KT;
+            if (ragged && t + S == KT - 1) {
+                issue_last();
+                fill = false;
+            }
         }
-        if constexpr (KS == 2) {
-            if (steady || t + 1 < KT) read(fa, fb, 0);
-            mma(ha, hb);
-        } else {
-            if (steady || t + 1 < KT) read(ha, hb, 0);
-            mma(fa, fb);
-        }
+        auto next_step = [&](SmallFrag<C>(&na)[NB], SmallFrag<C>(&nb)[NU]) {
+            return [&](int i) {
+                if (fill) issue_part(i, NB);
+                if (more) read_part(na, nb, 0, i, NB);
+            };
+        };
+        if constexpr (KS == 2) mma(ha, hb, next_step(fa, fb));
+        else mma(fa, fb, next_step(ha, hb));
     };
 #pragma unroll
     for (int t = 0; t < S; ++t)
@@ -280,7 +299,7 @@ __device__ __forceinline__ void small_contract(f32x4 (&acc)[C::WTM / 16][C::WTN 
         wait_loads<0>();
     }
     meet();
-    read(fa0, fb0, 0);
+    read_part(fa0, fb0, 0, 0, 1);
     int t = 0;
     if constexpr (KS == 2) {
         for (; t + S + (ragged ? 1 : 0) < KT; ++t) stage(t, true, fa0, fb0, fa1, fb1);
