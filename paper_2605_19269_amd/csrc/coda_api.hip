@@ -319,6 +319,7 @@ coda_status gemm_impl(void *stream, int64_t M, int64_t N, int64_t K, const coda_
                                                                            : coda::DIRECT_PROG_ACCUM;
         direct = coda::plan_direct(M, N, K, f8, ak, prog, wide);
     }
+    int chain = INT32_MAX;
     // the contraction is divided only when the caller brought the workspace for it; without one the shape runs undivided
     if (workspace) {
         const coda::SplitPlan pl = coda::plan_splitk(M, N, K, f8);
@@ -326,9 +327,10 @@ coda_status gemm_impl(void *stream, int64_t M, int64_t N, int64_t K, const coda_
         if (!aligned16(workspace)) return CODA_ERR_ALIGN;
         if (workspace_bytes < need) return CODA_ERR_WORKSPACE;
         if (pl.chunks > 0) {
+            chain = coda::splitk_longest_stages(pl, K, f8);
             const coda::SmallPlan sp = coda::plan_small(M, N, K, f8, ak);
-            if (sp.nsplit > 0 && (direct.tile == coda::DIRECT_NONE || sp.us <= direct.us))
-                return launch_status(coda::launch_gemm_small(sp, ps.mode, f8, ak, bkc, p, static_cast<float *>(workspace), s));
+            if (sp.nsplit > 0 && (sp.us <= direct.us || !(f8 ? direct.tile != coda::DIRECT_NONE : coda::direct_has_chains(direct.tile))))
+                return launch_status(coda::launch_gemm_small(sp, ps.mode, f8, ak, bkc, p, chain, static_cast<float *>(workspace), s));
             if (sp.nsplit == 0) {
                 direct.tile = coda::DIRECT_NONE;     // shared 256 x 256 tiles
                 p.split_from = pl.first;
@@ -343,7 +345,7 @@ coda_status gemm_impl(void *stream, int64_t M, int64_t N, int64_t K, const coda_
             }
         }
     }
-    if (direct.tile != coda::DIRECT_NONE) return launch_status(coda::launch_gemm_direct(direct.tile, ps.mode, f8, ak, bkc, p, s));
+    if (direct.tile != coda::DIRECT_NONE) return launch_status(coda::launch_gemm_direct(direct.tile, ps.mode, f8, ak, bkc, p, chain, s));
     if (f8) {
         if (ak && !bkc)
             e = dispatch_mode_f8<true, false>(ps.mode, kind, p, s);

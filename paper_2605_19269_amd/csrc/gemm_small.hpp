@@ -26,6 +26,7 @@ struct SmallParams {
     int64_t lda, ldb;        // row pitches in bytes
     int M, N, K;
     int tiles_m, tiles_n, nsplit;
+    int chain;               // longest chain of fp32 additions, in stages (bf16)
     float *part;             // [nsplit][M][N]
 };
 
@@ -136,7 +137,7 @@ __device__ __forceinline__ void wait_stages(int ahead)
 
 // The contraction of one tile over the stages [kbeg, kbeg + KT) (elements from kbeg * BK on, zeros past K), KT >= 1.
 // On return no wave reads or fills the ring any more.
-template <class C, bool AK, bool BKC>
+template <class C, bool AK, bool BKC, bool CHAINS>
 __device__ __forceinline__ void small_contract(f32x4 (&acc)[C::WTM / 16][C::WTN / 16], const SmallParams &p, int m0, int n0, int kbeg, int rot0,
                                                int KT, unsigned char *smem)
 {
@@ -253,6 +254,31 @@ __device__ __forceinline__ void small_contract(f32x4 (&acc)[C::WTM / 16][C::WTN 
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("" ::: "memory");
     };
+    // Chains: the accumulators are added to `sum` and start again from zero every p.chain stages, so that a range that is longer
+    // than the ones the shape had on shared 256 x 256 tiles is no less accurate (509 x 2048 x 8192 in four ranges against 64 bits:
+    // 2.7e-7 in one chain each, 1.9e-7 in two, as in eight ranges).  8-bit products go without: their own rounding inside the
+    // MFMA, 1.3e-5, covers it; so do the tiles that only take over undivided launches (2 to 3 % at 128x256).
+    f32x4 sum[CHAINS ? NB : 1][CHAINS ? NU : 1];
+    int chain = p.chain;
+    if constexpr (CHAINS) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int u = 0; u < NU; ++u) sum[i][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    auto end_of_stage = [&]() {
+        if constexpr (CHAINS)
+            if (--chain == 0) {
+                chain = p.chain;
+#pragma unroll
+                for (int i = 0; i < NB; ++i)
+#pragma unroll
+                    for (int u = 0; u < NU; ++u) {
+                        sum[i][u] += acc[i][u];
+                        acc[i][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    }
+            }
+    };
     auto next_slot = [&]() { slot_out = slot_out + C::STAGE == C::LDS ? 0u : slot_out + C::STAGE; };
     // Stage t on the fragments f*; the reads of the next MFMA step are in flight under every step.  The last step of a stage
     // takes its next fragments from the next stage: that is where the stage's one barrier and the refill of its slot are.
@@ -286,6 +312,7 @@ __device__ __forceinline__ void small_contract(f32x4 (&acc)[C::WTM / 16][C::WTN 
         };
         if constexpr (KS == 2) mma(ha, hb, next_step(fa, fb));
         else mma(fa, fb, next_step(ha, hb));
+        end_of_stage();
     };
 #pragma unroll
     for (int t = 0; t < S; ++t)
@@ -315,6 +342,12 @@ __device__ __forceinline__ void small_contract(f32x4 (&acc)[C::WTM / 16][C::WTN 
             if (t + 1 < KT) stage(t + 1, false, fa1, fb1, fa0, fb0);
         }
     }
+    if constexpr (CHAINS) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int u = 0; u < NU; ++u) acc[i][u] = sum[i][u] + acc[i][u];
+    }
     __syncthreads();
 }
 
@@ -330,7 +363,7 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2), am
     const int k1 = __builtin_amdgcn_readfirstlane((int)((int64_t)(split + 1) * stages / p.nsplit));   // k1 > k0: nsplit <= stages
     f32x4 acc[NB][NU];
     const int m0 = tm * C::BM, n0 = tn * C::BN;
-    small_contract<C, AK, BKC>(acc, p, m0, n0, k0, tn, k1 - k0, smem);
+    small_contract<C, AK, BKC, !C::F8>(acc, p, m0, n0, k0, tn, k1 - k0, smem);
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int m = m0 + (wave % C::WGM) * C::WTM + (lane & 15), n = n0 + (wave / C::WGM) * C::WTN + (lane >> 4) * 4;
@@ -345,7 +378,7 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2), am
 
 // The whole launch in one kernel: the contraction undivided, then the epilogue program of the large kernels on the tile.
 // The callers' row-reduction partials are per 256 columns, so programs with one take the 256-wide tiles.
-template <class C, bool AK, bool BKC, int EPI>
+template <class C, bool AK, bool BKC, int EPI, bool CHAINS>
 __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2), amdgpu_num_vgpr(256))) void gemm_small_direct(const GemmParams g, const SmallParams p)
 {
     constexpr int RED = 2 * C::WGN * C::BM * 4;
@@ -355,7 +388,7 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2), am
     small_coords((int)blockIdx.x, p.tiles_m, p.tiles_n, 1, tm, tn, split);
     const int m0 = tm * C::BM, n0 = tn * C::BN;
     Acc16<C> acc;
-    small_contract<C, AK, BKC>(acc.a, p, m0, n0, 0, tn, (p.K + C::BK - 1) / C::BK, smem);
+    small_contract<C, AK, BKC, CHAINS>(acc.a, p, m0, n0, 0, tn, (p.K + C::BK - 1) / C::BK, smem);
     float *red = reinterpret_cast<float *>(smem + C::LDS);
     if (C::BM < 128 || m0 + C::BM > p.M || n0 + C::BN > p.N)
         run_epilogue<C, Acc16<C>, EPI, true, C::LDS>(acc, g, m0, n0, tn, smem, red, (int)threadIdx.x);

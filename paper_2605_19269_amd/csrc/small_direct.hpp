@@ -6,13 +6,13 @@
 
 namespace coda {
 
-template <class C, bool AK, bool BKC, int EPI>
+template <class C, bool AK, bool BKC, int EPI, bool CHAINS = false>
 static hipError_t launch_direct(const GemmParams &g, SmallParams p, hipStream_t s)
 {
     p.tiles_m = (p.M + C::BM - 1) / C::BM;
     p.tiles_n = (p.N + C::BN - 1) / C::BN;
     p.nsplit = 1;
-    hipLaunchKernelGGL((gemm_small_direct<C, AK, BKC, EPI>), dim3((unsigned)(p.tiles_m * p.tiles_n)), dim3(C::NT), 0, s, g, p);
+    hipLaunchKernelGGL((gemm_small_direct<C, AK, BKC, EPI, CHAINS>), dim3((unsigned)(p.tiles_m * p.tiles_n)), dim3(C::NT), 0, s, g, p);
     return hipGetLastError();
 }
 
@@ -20,14 +20,14 @@ template <bool F8, bool AK, bool BKC, int EPI>
 static hipError_t direct_tile(int tile, const GemmParams &g, const SmallParams &p, hipStream_t s)
 {
     if constexpr (AK && (EPI == EPI_LINEAR || EPI == EPI_SWIGLU_FWD))
-        if (tile == DIRECT_64x64) return launch_direct<SmallCfg<64, 64, 2, 1, 4, F8>, AK, BKC, EPI>(g, p, s);
+        if (tile == DIRECT_64x64) return launch_direct<SmallCfg<64, 64, 2, 1, 4, F8>, AK, BKC, EPI, !F8>(g, p, s);
     if constexpr (AK && EPI == EPI_LINEAR) {
         if (tile == DIRECT_32x256) return launch_direct<SmallCfg<32, 256, 1, 4, 4, F8>, AK, BKC, EPI>(g, p, s);
         if (tile == DIRECT_64x256) return launch_direct<SmallCfg<64, 256, 2, 4, 3, F8>, AK, BKC, EPI>(g, p, s);
     }
     if constexpr (EPI == EPI_ACCUM)
         if (tile == DIRECT_128x128_PAIR) return launch_direct<SmallCfg<128, 128, 2, 2, 2, F8>, AK, BKC, EPI>(g, p, s);
-    if (tile == DIRECT_128x128) return launch_direct<SmallCfg<128, 128, 4, 2, 4, F8>, AK, BKC, EPI>(g, p, s);
+    if (tile == DIRECT_128x128) return launch_direct<SmallCfg<128, 128, 4, 2, 4, F8>, AK, BKC, EPI, !F8>(g, p, s);
     if (tile == DIRECT_128x256) return launch_direct<SmallCfg<128, 256, 2, 4, 3, F8>, AK, BKC, EPI>(g, p, s);
     return hipErrorInvalidConfiguration;             // a tile that the plan does not give this program
 }

@@ -71,6 +71,13 @@ inline size_t splitk_bytes(const SplitPlan &pl)
 }
 
 
+// Stages (128 bytes of K, a pair of K-steps) of a plan's longest range: its longest chain of additions.
+inline int splitk_longest_stages(const SplitPlan &pl, int64_t K, bool f8)
+{
+    const int64_t stages = (K * (f8 ? 1 : 2) + 127) / 128;
+    return (int)((pl.tail * stages + pl.chunks - 1) / pl.chunks);
+}
+
 // Plan of the contractions with small output tiles (gemm_small.hpp): bm x bn tiles, each cut along K into `nsplit` ranges
 // whose fp32 partials [nsplit][M][N] lie in the workspace.  It takes the place of the shared 256 x 256 tiles where every
 // tile of the shape would be shared (plan.first == 0), within the workspace that plan asks for, so that the sizes callers
@@ -116,8 +123,7 @@ inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_c
     if (M <= 64 && a_k_contiguous) return M <= 32 ? offer(32, 128, 0.62) : offer(64, 128, 0.62);
     const SmallPlan narrow = offer(128, 128, 0.57), wide = offer(128, 256, 0.83);
     const SmallPlan best = wide.nsplit == 0 || (narrow.nsplit != 0 && narrow.us <= wide.us) ? narrow : wide;
-    const int64_t longest = 2 * ((big.tail * stages + big.chunks - 1) / big.chunks);   // K-steps of the longest range
-    const double t_big = 0.83 * (double)longest + 12.0 + 0.019 * big.chunks * big.stride + (big.pieces > 1 ? 25.0 : 0.0);
+    const double t_big = 0.83 * 2.0 * splitk_longest_stages(big, K, f8) + 12.0 + 0.019 * big.chunks * big.stride + (big.pieces > 1 ? 25.0 : 0.0);
     return best.nsplit != 0 && best.us <= 0.9 * t_big ? best : none;
 }
 
@@ -139,6 +145,8 @@ inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_c
 // 4096 x 1000: 129, 126, which stay.
 enum DirectTile : int { DIRECT_NONE = 0, DIRECT_64x64, DIRECT_32x256, DIRECT_64x256, DIRECT_128x128, DIRECT_128x128_PAIR, DIRECT_128x256 };
 enum DirectProgram : int { DIRECT_PROG_LINEAR, DIRECT_PROG_SWIGLU_FWD, DIRECT_PROG_SWIGLU_BWD, DIRECT_PROG_ACCUM };
+// Tiles whose bf16 kernels keep to a longest chain of additions: they may take over shapes that a workspace divides.
+inline bool direct_has_chains(int tile) { return tile == DIRECT_64x64 || tile == DIRECT_128x128; }
 struct DirectPlan {
     int tile;
     double us;     // modelled time
