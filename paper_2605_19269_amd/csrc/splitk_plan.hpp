@@ -181,10 +181,12 @@ inline DirectPlan plan_direct(int64_t M, int64_t N, int64_t K, bool f8, bool a_k
     }
     if (!wide) offer(DIRECT_128x128, 4.5 + stream(stages * 0.57 * rounds(tiles(128, 128)), 5.6e6) + rmw);
     if (prog == DIRECT_PROG_ACCUM) {
-        const double pairs = (double)tiles(128, 128) / (2.0 * SPLITK_CUS);
-        offer(DIRECT_128x128_PAIR, 6.0 + 1.08 * stages * (pairs < 0.9 ? 0.9 : pairs) + 0.55 * rmw);
+        // rounds of two per CU; what is left over runs two or one per CU (1424 x 6304 x 12920: 600 tiles lose 30 % to 256 x 256)
+        const int64_t t = tiles(128, 128), whole = t / (2 * SPLITK_CUS), left = t % (2 * SPLITK_CUS);
+        const double rest = left == 0 ? 0.0 : (left <= SPLITK_CUS ? 0.66 : 1.08);
+        offer(DIRECT_128x128_PAIR, 6.0 + stages * (1.08 * (double)whole + rest) + 0.55 * rmw);
     }
-    offer(DIRECT_128x256, 6.0 + stages * 0.88 * rounds(tiles(128, 256)) + rmw);
+    offer(DIRECT_128x256, (6.0 + stages * 0.88 * rounds(tiles(128, 256)) + rmw) * (prog == DIRECT_PROG_ACCUM ? 1.07 : 1.0));
     return best;
 }
 

@@ -178,7 +178,7 @@ DIRECT = [(1, 200, 72, False, False, False, "linear", False, "64x64"), (70, 520,
           (504, 1032, 1000, False, True, True, "linear", True, "128x256"), (504, 1032, 1000, False, True, False, "linear", True, "128x256"),
           (500, 1040, 1040, True, False, False, "swiglu_bwd", True, "128x256"), (500, 1040, 1040, True, False, True, "swiglu_bwd", True, "128x256"),
           (1000, 2056, 504, False, True, False, "accum", False, "128x128"), (2048, 11264, 512, False, True, False, "accum", False, "128x128_PAIR"),
-          (2040, 4104, 1000, False, True, True, "accum", False, "128x128_PAIR"), (2032, 4112, 1040, True, True, False, "accum", False, "128x128_PAIR")]
+          (2040, 11272, 504, False, True, True, "accum", False, "128x128_PAIR"), (2032, 11280, 1040, True, True, False, "accum", False, "128x128_PAIR")]
 
 
 @pytest.mark.parametrize("M,N,K,f8,ta,tb,prog,red,tile", DIRECT)
