@@ -185,8 +185,8 @@ typedef struct coda_epi_op {
  * multiple of 8; and M a multiple of 8 when A is used transposed.  No other
  * divisibility is required (edge tiles are predicated).
  *
- * Reproducibility: the order of the fp32 additions behind an output element depends only on the shapes, layouts and the
- * element's position, never on timing; with CODA_REDUCE_PARTIALS every output of a call is bitwise identical from call
+ * Reproducibility: the order of the fp32 additions behind an element of D depends only on the shapes, operand type, layouts,
+ * on whether a workspace is given and on the element's position, never on the program or on timing; with CODA_REDUCE_PARTIALS every output of a call is bitwise identical from call
  * to call (CODA_REDUCE_ATOMIC sums may differ in their last bits).
  *
  * 8-bit operands: A and B may both be CODA_F8E4M3 (ld in elements = bytes, a multiple of 16), in any of the four

@@ -309,43 +309,34 @@ coda_status gemm_impl(void *stream, int64_t M, int64_t N, int64_t K, const coda_
     const bool bkc = B->trans;   // B stored [N x K]: contraction index contiguous
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e;
-    // the best undivided launch with small tiles, if one beats 256 x 256 tiles
-    coda::DirectPlan direct = {coda::DIRECT_NONE, 0.0};
-    if (ps.mode != coda::EPI_RMSNORM_BWD) {
-        const bool wide = p.rowred_mode != coda::ROWRED_NONE || p.lse_max;
-        const coda::DirectProgram prog = ps.mode == coda::EPI_LINEAR       ? coda::DIRECT_PROG_LINEAR
-                                         : ps.mode == coda::EPI_SWIGLU_FWD ? coda::DIRECT_PROG_SWIGLU_FWD
-                                         : ps.mode == coda::EPI_SWIGLU_BWD ? coda::DIRECT_PROG_SWIGLU_BWD
-                                                                           : coda::DIRECT_PROG_ACCUM;
-        direct = coda::plan_direct(M, N, K, f8, ak, prog, wide);
-    }
-    int chain = INT32_MAX;
-    // the contraction is divided only when the caller brought the workspace for it; without one the shape runs undivided
     if (workspace) {
-        const coda::SplitPlan pl = coda::plan_splitk(M, N, K, f8);
-        const size_t need = coda::splitk_bytes(pl);
         if (!aligned16(workspace)) return CODA_ERR_ALIGN;
-        if (workspace_bytes < need) return CODA_ERR_WORKSPACE;
-        if (pl.chunks > 0) {
-            chain = coda::splitk_longest_stages(pl, K, f8);
-            const coda::SmallPlan sp = coda::plan_small(M, N, K, f8, ak);
-            if (sp.nsplit > 0 && (sp.us <= direct.us || !(f8 ? direct.tile != coda::DIRECT_NONE : coda::direct_has_chains(direct.tile))))
-                return launch_status(coda::launch_gemm_small(sp, ps.mode, f8, ak, bkc, p, chain, static_cast<float *>(workspace), s));
-            if (sp.nsplit == 0) {
-                direct.tile = coda::DIRECT_NONE;     // shared 256 x 256 tiles
-                p.split_from = pl.first;
-                p.tail_tiles = pl.tail;
-                p.tail_chunks = pl.chunks;
-                p.tail_pieces = pl.pieces;
-                p.ws_stride = pl.stride;
-                p.ws_cnt = static_cast<unsigned *>(workspace);
-                p.ws_part = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + coda::SPLITK_CNT_BYTES);
-                hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(256), 0, s, p.ws_cnt, pl.tail);
-                if ((e = hipGetLastError()) != hipSuccess) return launch_status(e);
-            }
-        }
+        if (workspace_bytes < coda::splitk_bytes(coda::plan_splitk(M, N, K, f8))) return CODA_ERR_WORKSPACE;
     }
-    if (direct.tile != coda::DIRECT_NONE) return launch_status(coda::launch_gemm_direct(direct.tile, ps.mode, f8, ak, bkc, p, chain, s));
+    const coda::DirectProgram program = ps.mode == coda::EPI_LINEAR       ? coda::DIRECT_PROG_LINEAR
+                                        : ps.mode == coda::EPI_SWIGLU_FWD ? coda::DIRECT_PROG_SWIGLU_FWD
+                                        : ps.mode == coda::EPI_SWIGLU_BWD ? coda::DIRECT_PROG_SWIGLU_BWD
+                                        : ps.mode == coda::EPI_ACCUM      ? coda::DIRECT_PROG_ACCUM
+                                                                          : coda::DIRECT_PROG_RMSNORM_BWD;
+    const bool wide = p.rowred_mode != coda::ROWRED_NONE || p.lse_max;
+    const coda::Route route = coda::plan_route(M, N, K, f8, ak, bkc, program, wide, workspace != nullptr);
+    if (route.kind == coda::ROUTE_DIVIDED)
+        return launch_status(coda::launch_gemm_small(route.small, ps.mode, f8, ak, bkc, p, route.chain, static_cast<float *>(workspace), s));
+    if (route.kind == coda::ROUTE_DIRECT)
+        return launch_status(coda::launch_gemm_direct(route.tile, ps.mode, f8, ak, bkc, p, route.chain, route.rot_cols, s));
+    if (route.kind == coda::ROUTE_WHOLE) p.rot_cols = route.rot_cols > 0 ? route.rot_cols : 0;
+    if (route.kind == coda::ROUTE_SHARED) {
+        const coda::SplitPlan &pl = route.shared;
+        p.split_from = pl.first;
+        p.tail_tiles = pl.tail;
+        p.tail_chunks = pl.chunks;
+        p.tail_pieces = pl.pieces;
+        p.ws_stride = pl.stride;
+        p.ws_cnt = static_cast<unsigned *>(workspace);
+        p.ws_part = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + coda::SPLITK_CNT_BYTES);
+        hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(256), 0, s, p.ws_cnt, pl.tail);
+        if ((e = hipGetLastError()) != hipSuccess) return launch_status(e);
+    }
     if (f8) {
         if (ak && !bkc)
             e = dispatch_mode_f8<true, false>(ps.mode, kind, p, s);

@@ -49,6 +49,7 @@ struct GemmParams {
     int64_t lda, ldb;       // element pitches of the matrices as stored
     int M, N, K;
     int tiles_m, tiles_n;
+    int rot_cols;           // B K-contiguous, few rows: tile columns start at K-step pair (n0 / rot_cols) % pairs and wrap around; 0: at 0
     // epilogue operands (null = op absent)
     const float *row_scale;              // f32[M]
     const uint16_t *add; int64_t ld_add; // bf16 [M x N]
@@ -130,6 +131,18 @@ __device__ __host__ __forceinline__ void tile_coords(int bid, int nb, int tiles_
     tm = first_m + in_grp % gm;
     tn = in_grp / gm;
 }
+// The XCD that tile_coords gives a tile to: bid % 8 of the workgroup that owns it.
+__device__ __host__ __forceinline__ int tile_xcd(int tm, int tn, int tiles_m, int tiles_n)
+{
+    constexpr int XCDS = 8, GROUP_M = 8;
+    const int grp = tm / GROUP_M, first_m = grp * GROUP_M;
+    const int gm = (tiles_m - first_m) < GROUP_M ? (tiles_m - first_m) : GROUP_M;
+    const int id = grp * GROUP_M * tiles_n + tn * gm + (tm - first_m);
+    const int nb = tiles_m * tiles_n, base = nb / XCDS, rem = nb % XCDS, full = rem * (base + 1);   // the first rem XCDs own base + 1 tiles
+    return id < full ? id / (base + 1) : rem + (id - full) / base;
+}
+// First K-step of a tile of A B^T on XCD x when all KT (even) K-steps are its own: see `rot` in gemm_item_dl.
+__device__ __host__ __forceinline__ int xcd_rotation(int x, int KT) { return (x * (KT / 8)) & ~1; }
 
 // ---------------------------------------------------------------------------------
 // The kernel
@@ -1342,7 +1355,12 @@ __device__ __forceinline__ void gemm_item_dl(const GemmParams &p, const WorkItem
     // together, so that panel sharing in its L2 is kept.  Measured +3 to +4 % on the SwiGLU backward and +2 % on the RMSNorm
     // backward (their epilogue bursts no longer coincide chip-wide), nothing on a plain store; the other layouts lose 1-2 %
     // with it and walk K from zero.  The order of the fp32 additions of a tile depends on its XCD, not on timing.
-    const int rot = (AK && BKC && !RAGGED && nsplit == 1 && KT == KT_all) ? ((((int)blockIdx.x & 7) * (KT / 8)) & ~1) : 0;
+    // Ragged launches start where the host says (rot_cols; not with a K that is no whole number of pairs).
+    int rot = 0;
+    if (BKC && nsplit == 1 && KT == KT_all) {
+        if (AK && !RAGGED) rot = xcd_rotation((int)blockIdx.x & 7, KT);
+        if (RAGGED && p.rot_cols) rot = n0 / p.rot_cols % (KT / 2) * 2;
+    }
     auto rotated = [&](int t) {   // position along K of the workgroup's t-th K-step (rot and KT are even: pairs stay pairs)
         int tg = t + rot;
         if (tg >= KT) tg -= KT;
@@ -1796,6 +1814,14 @@ __device__ __forceinline__ void gemm_item_dl_f8(const GemmParams &p, const WorkI
     const unsigned char *ga = reinterpret_cast<const unsigned char *>(p.A) + (AK ? (int64_t)m0 * p.lda : (int64_t)m0) + kbeg * stepa;
     const unsigned char *gb = reinterpret_cast<const unsigned char *>(p.B) + (BKC ? (int64_t)n0 * p.ldb : (int64_t)n0) + kbeg * stepb;
     const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
+    // where the tile starts along K, as in the bf16 kernel
+    int rot = 0;
+    if (BKC && RAGGED && nsplit == 1 && KT == KT_all && p.rot_cols) rot = n0 / p.rot_cols % (KT / 2) * 2;
+    auto rotated = [&](int t) {
+        int tg = t + rot;
+        if (tg >= KT) tg -= KT;
+        return tg;
+    };
 
     auto a_slot = [&](int t) { return ((t >> 1) % 3) * (2 * C::A_BYTES); };      // the pair that contains K-step t
     auto b_slot = [&](int t) { return A_REGION + ((t >> 1) & 1) * (2 * C::B_BYTES); };   // the pair that contains K-step t
@@ -1803,7 +1829,7 @@ __device__ __forceinline__ void gemm_item_dl_f8(const GemmParams &p, const WorkI
     // `inside`: the caller knows that the pair lies within K (no test, no zero fill)
     auto issue_a = [&](int t, int part, bool inside = false) {
         const int slot = a_slot(t);
-        const unsigned char *sa = ga + (int64_t)t * stepa;
+        const unsigned char *sa = ga + (int64_t)(BKC && RAGGED ? rotated(t) : t) * stepa;
         const int i0 = part == 1 ? LAP / 2 : 0, i1 = part == 0 ? LAP / 2 : LAP;
         if (RAGGED && !inside && (kbeg + t + 2) * BKB > p.K) {
             // the pair reaches past K: a lane whose chunk lies past K stores zeros at its LDS position instead of fetching
@@ -1824,7 +1850,7 @@ __device__ __forceinline__ void gemm_item_dl_f8(const GemmParams &p, const WorkI
     // loads of B for the pair of K-steps t, t + 1 (t even)
     auto issue_b = [&](int t, bool inside = false) {
         const int slot = b_slot(t);
-        const unsigned char *sb = gb + (int64_t)t * stepb;
+        const unsigned char *sb = gb + (int64_t)(BKC && RAGGED ? rotated(t) : t) * stepb;
         if (RAGGED && !inside && (kbeg + t + 2) * BKB > p.K) {
             const int k_left = p.K - (kbeg + t) * BKB;
 #pragma unroll

@@ -13,11 +13,14 @@
 //
 // Mainloop: a ring of S stages in LDS filled by direct-to-LDS loads; a stage is 128 bytes of the contraction per row of a
 // K-contiguous operand, or the same number of k-rows of an MN-contiguous one.  One barrier per stage, and the fragments of
-// the next MFMA step are read while the current ones are multiplied.  Up to 64 rows the kernel is bound by HBM (28672 x
-// 4096 bf16 weights against one row: 45 us with the epilogue, 5.2 TB/s, the rate of a large copy), at 128 rows by LDS: 64 KB or
-// more of fragments and 32 KB of fill per stage against 512 cycles of MFMA.
+// the next MFMA step are read while the current ones are multiplied.  The MFMA instructions and their order along K are those
+// of the 256 x 256 tiles, so that an undivided launch gives the same sums, bit for bit, on any tile (8-bit: 16x16x128, which rounds
+// otherwise, is within some 10 % of 32x32x64 either way).  Up to 64 rows the kernel is bound by HBM (28672 x 4096 bf16 weights
+// against one row: 45 us with the epilogue, 5.2 TB/s, the rate of a large copy), at 128 rows by LDS: 64 KB or more of fragments
+// and 32 KB of fill per stage against 512 cycles of MFMA.
 #pragma once
 #include "gemm_kernel.hpp"
+#include "splitk_plan.hpp"
 
 namespace coda {
 
@@ -27,6 +30,8 @@ struct SmallParams {
     int M, N, K;
     int tiles_m, tiles_n, nsplit;
     int chain;               // longest chain of fp32 additions, in stages (bf16)
+    int rot_cols;            // B K-contiguous: a tile starts at stage n0 / rot_cols of its range and wraps around; undivided also 0:
+                             // at stage 0, ROT_XCD: where its 256 x 256 tile starts (see gemm_item_dl)
     float *part;             // [nsplit][M][N]
 };
 
@@ -36,17 +41,18 @@ struct SmallCfg {
     static constexpr bool F8 = F8_;
     static constexpr int ESZ = F8 ? 1 : 2, BK = BKB / ESZ;        // contraction elements per stage
     static constexpr int WTM = BM / WGM, WTN = BN / WGN;
+    static constexpr int FR = F8 ? 32 : 16;                       // rows (columns) of an MFMA block
     static constexpr int A_BYTES = BM * BKB, B_BYTES = BN * BKB, STAGE = A_BYTES + B_BYTES, LDS = S * STAGE;
     static constexpr int LA = A_BYTES / 1024 / NW, LB = B_BYTES / 1024 / NW;   // wave-loads of 1 KB per wave and stage
     static_assert(A_BYTES % (1024 * NW) == 0 && B_BYTES % (1024 * NW) == 0, "every wave issues the same number of loads");
-    static_assert(WTM % 16 == 0 && WTN % 16 == 0 && S >= 2 && LDS <= 160 * 1024, "LDS");
+    static_assert(WTM % FR == 0 && WTN % FR == 0 && S >= 2 && LDS <= 160 * 1024, "LDS");
 };
 
-// 8-bit k-rows of ROWS bytes: the eight k-rows of a transposing read fall into different bank groups
+// 8-bit k-rows of ROWS bytes: the eight k-rows of a transposing read of two adjacent chunks fall into different bank groups
 template <int ROWS>
 __device__ __forceinline__ int small_swz_f8(int c, int k)
 {
-    return c ^ (ROWS == 64 ? (k >> 1) & 3 : (ROWS == 128 ? (k & 7) : 2 * (k & 7)));
+    return c ^ (2 * (ROWS == 64 ? (k >> 2) & 1 : (ROWS == 128 ? (k >> 1) & 3 : k & 7)));
 }
 
 // Byte offset, from the tile's first element, of the 16-byte chunk that lane `lane` of wave-load j fetches, and in `ck` the
@@ -56,8 +62,8 @@ __device__ __forceinline__ int small_swz_f8(int c, int k)
 template <class C, bool KCONT, int ROWS>
 __device__ __forceinline__ uint32_t small_goffset(int j, int lane, int64_t ldb, int valid, int &ck)
 {
-    if constexpr (KCONT) {                           // [rows][128 B]: chunk c of row r at c ^ (r & 7)
-        const int r = j * 8 + (lane >> 3), c = (lane & 7) ^ (r & 7);
+    if constexpr (KCONT) {                           // [rows][128 B]: chunk c of row r at c ^ (r & 7), 8-bit c ^ ((r >> 1) & 7)
+        const int r = j * 8 + (lane >> 3), c = (lane & 7) ^ ((C::F8 ? r >> 1 : r) & 7);
         ck = c * (16 / C::ESZ);
         return (uint32_t)((int64_t)(r < valid ? r : valid - 1) * ldb + c * 16);
     } else if constexpr (!C::F8) {                   // [64][ROWS columns]: the granule swizzle of lds_mn
@@ -74,26 +80,24 @@ __device__ __forceinline__ uint32_t small_goffset(int j, int lane, int64_t ldb, 
     }
 }
 
-typedef __attribute__((ext_vector_type(4))) int i32x4;
 template <class C>
 using SmallFrag = typename std::conditional<C::F8, i32x8, bf16x8>::type;
+template <class C>
+using SmallAcc = typename std::conditional<C::F8, Acc32<C>, Acc16<C>>::type;
 
-// Fragment of 16 rows (columns) from row0 on: bf16: lane -> row lane % 16, k = 32 h + 8 (lane / 16) .. + 7;
-// 8-bit: k = 32 (lane / 16) .. + 31 (one MFMA covers the stage's 128).
+// Fragment of C::FR rows (columns) from row0 on, step h (0 / 1) of the stage: bf16: lane -> row lane % 16, k = 32 h + 8 (lane / 16)
+// .. + 7; 8-bit: row lane % 32, k = 64 h + 32 (lane / 32) .. + 31.
 template <class C, bool KCONT, int ROWS>
 __device__ __forceinline__ SmallFrag<C> small_frag(const unsigned char *tile, int row0, int lane, int h)
 {
     if constexpr (C::F8 && KCONT) {
-        const int r = row0 + (lane & 15), c = 2 * (lane >> 4), sw = r & 7;
-        const i32x4 lo = *reinterpret_cast<const i32x4 *>(tile + r * 128 + ((c ^ sw) << 4));
-        const i32x4 hi = *reinterpret_cast<const i32x4 *>(tile + r * 128 + (((c + 1) ^ sw) << 4));
-        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        return dl_frag_pair_f8(tile, row0, lane, h);
     } else if constexpr (C::F8) {
         // transposing reads as in dl_frag_mn_f8, eight k-rows each: the lane's four reads are its 32 consecutive k
         typedef int v2i __attribute__((ext_vector_type(2)));
         typedef __attribute__((address_space(3))) v2i lds_v2i;
-        const int i = lane & 15, k0 = 32 * (lane >> 4) + (i >> 1);      // k0 & 7 is the same in all four reads
-        const unsigned char *a = tile + k0 * ROWS + (small_swz_f8<ROWS>(row0 >> 4, k0) << 4) + ((i & 1) << 3);
+        const int i = lane & 15, g = lane >> 4, k0 = 64 * h + 32 * (g >> 1) + (i >> 1);      // k0 & 7 is the same in all four reads
+        const unsigned char *a = tile + k0 * ROWS + (small_swz_f8<ROWS>((row0 >> 4) + (g & 1), k0) << 4) + ((i & 1) << 3);
         const v2i r0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i *)(a));
         const v2i r1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i *)(a + 8 * ROWS));
         const v2i r2 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i *)(a + 16 * ROWS));
@@ -138,19 +142,15 @@ __device__ __forceinline__ void wait_stages(int ahead)
 // The contraction of one tile over the stages [kbeg, kbeg + KT) (elements from kbeg * BK on, zeros past K), KT >= 1.
 // On return no wave reads or fills the ring any more.
 template <class C, bool AK, bool BKC, bool CHAINS>
-__device__ __forceinline__ void small_contract(f32x4 (&acc)[C::WTM / 16][C::WTN / 16], const SmallParams &p, int m0, int n0, int kbeg, int rot0,
-                                               int KT, unsigned char *smem)
+__device__ __forceinline__ void small_contract(SmallAcc<C> &acc, const SmallParams &p, int m0, int n0, int kbeg, int rot0, int KT,
+                                               unsigned char *smem)
 {
     static_assert(AK || C::BM == 128, "an A whose rows are not contiguous in K is staged as 128-wide k-rows");
-    constexpr int NB = C::WTM / 16, NU = C::WTN / 16, S = C::S, L = C::LA + C::LB;
-    constexpr int KS = C::F8 ? 1 : 2;                // MFMA steps per stage
+    constexpr int NB = C::WTM / C::FR, NU = C::WTN / C::FR, S = C::S, L = C::LA + C::LB;
+    typedef typename std::conditional<C::F8, f32x16, f32x4>::type Block;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave % C::WGM, wn = wave / C::WGM;
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-        for (int u = 0; u < NU; ++u) acc[i][u] = f32x4{0.f, 0.f, 0.f, 0.f};
-
+    acc_zero(acc);
     uint32_t offa[C::LA], offb[C::LB];
     int cka[C::LA], ckb[C::LB];
     const int valid_m = p.M - m0 < C::BM ? p.M - m0 : C::BM, valid_n = p.N - n0 < C::BN ? p.N - n0 : C::BN;
@@ -167,8 +167,9 @@ __device__ __forceinline__ void small_contract(f32x4 (&acc)[C::WTM / 16][C::WTN 
     // from the issue of that stage on the waits are for everything.
     const bool ragged = (kbeg + KT) * C::BK > p.K;
     // B rows contiguous in K: the rows of a stage lie a whole row pitch apart, which for the usual widths is a multiple of
-    // the memory channels' interleave, so workgroups that walk K in step would all pull on the same few channels.  Every
-    // column of tiles starts its range at another stage and wraps around (28672 x 4096 8-bit, one row: 30 us against 27).
+    // the memory channels' interleave, so workgroups that walk K in step would all pull on the same few channels.  Where
+    // p.rot_cols says so, every column of tiles starts its range at another stage and wraps around (28672 x 4096 8-bit, one
+    // row: 30 us against 27; 65536 x 4096 bf16, one row, undivided: 124 against 97).
     const int rot = __builtin_amdgcn_readfirstlane(BKC && !ragged ? rot0 % KT : 0);
     int next = rot;                                  // the next stage to fetch, and its slot
     uint32_t slot_in = 0;
@@ -207,26 +208,26 @@ __device__ __forceinline__ void small_contract(f32x4 (&acc)[C::WTM / 16][C::WTN 
             else *reinterpret_cast<u32x4 *>(slot + at) = u32x4{0u, 0u, 0u, 0u};
         }
     };
-    SmallFrag<C> fa0[NB], fb0[NU], fa1[NB], fb1[NU];
+    SmallFrag<C> fa[NB], fb[NU], ha[NB], hb[NU];     // fragments of a stage's first and second MFMA step
     uint32_t slot_out = 0;                           // the slot being read
     // part q of Q of a step's fragments
     auto read_part = [&](SmallFrag<C>(&fa)[NB], SmallFrag<C>(&fb)[NU], int h, int q, int Q) {
         const unsigned char *ta = smem + slot_out, *tb = ta + C::A_BYTES;
 #pragma unroll
         for (int u = 0; u < NU; ++u)
-            if (u >= q * NU / Q && u < (q + 1) * NU / Q) fb[u] = small_frag<C, BKC, C::BN>(tb, wn * C::WTN + u * 16, lane, h);
+            if (u >= q * NU / Q && u < (q + 1) * NU / Q) fb[u] = small_frag<C, BKC, C::BN>(tb, wn * C::WTN + u * C::FR, lane, h);
 #pragma unroll
         for (int i = 0; i < NB; ++i)
-            if (i >= q * NB / Q && i < (q + 1) * NB / Q) fa[i] = small_frag<C, AK, C::BM>(ta, wm * C::WTM + i * 16, lane, h);
+            if (i >= q * NB / Q && i < (q + 1) * NB / Q) fa[i] = small_frag<C, AK, C::BM>(ta, wm * C::WTM + i * C::FR, lane, h);
     };
-    // One MFMA step on f*, a row of blocks at a time.  `beside(i)` issues the loads and fragment reads of the next step: behind
-    // row i where two waves share a SIMD in step, so that the matrix pipe starts at once after a barrier and works while they
+    // One MFMA step on f*, a row of blocks at a time (8-bit: block by block, those take twice as long).  `beside(i, n)` issues part i
+    // of n of the loads and fragment reads of the next step: behind row i where two waves share a SIMD in step, so that the matrix pipe starts at once after a barrier and works while they
     // are issued in its shadow (128x256: 509 x 16384 x 2048 37.5 -> 34.7 us); ahead of the rows where a wave has its SIMD to
     // itself or shares it with another workgroup's (1 x 6144 x 2048 at 64x64: 12.8 us against 13.5).
     auto mma = [&](const SmallFrag<C>(&fa)[NB], const SmallFrag<C>(&fb)[NU], auto beside) {
         if (C::NW < 8) {
 #pragma unroll
-            for (int i = 0; i < NB; ++i) beside(i);
+            for (int i = 0; i < NB; ++i) beside(i, NB);
         }
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
@@ -234,13 +235,17 @@ __device__ __forceinline__ void small_contract(f32x4 (&acc)[C::WTM / 16][C::WTN 
 #pragma unroll
             for (int u = 0; u < NU; ++u) {
                 if constexpr (C::F8)
-                    acc[i][u] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fb[u], fa[i], acc[i][u], 0, 0, 0, 0, 0, 0);
+                    acc.a[i][u] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[u], fa[i], acc.a[i][u], 0, 0, 0, 0, 0, 0);
                 else
-                    acc[i][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[u], fa[i], acc[i][u], 0, 0, 0);
+                    acc.a[i][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[u], fa[i], acc.a[i][u], 0, 0, 0);
+                if (C::NW < 8 || !C::F8) continue;
+                __builtin_amdgcn_sched_barrier(0);
+                beside(i * NU + u, NB * NU);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            if (C::NW < 8) continue;
+            if (C::NW < 8 || C::F8) continue;
             __builtin_amdgcn_sched_barrier(0);
-            beside(i);
+            beside(i, NB);
         }
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -258,13 +263,13 @@ __device__ __forceinline__ void small_contract(f32x4 (&acc)[C::WTM / 16][C::WTN 
     // than the ones the shape had on shared 256 x 256 tiles is no less accurate (509 x 2048 x 8192 in four ranges against 64 bits:
     // 2.7e-7 in one chain each, 1.9e-7 in two, as in eight ranges).  8-bit products go without: their own rounding inside the
     // MFMA, 1.3e-5, covers it; so do the tiles that only take over undivided launches (2 to 3 % at 128x256).
-    f32x4 sum[CHAINS ? NB : 1][CHAINS ? NU : 1];
+    Block sum[CHAINS ? NB : 1][CHAINS ? NU : 1];
     int chain = p.chain;
     if constexpr (CHAINS) {
 #pragma unroll
         for (int i = 0; i < NB; ++i)
 #pragma unroll
-            for (int u = 0; u < NU; ++u) sum[i][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int u = 0; u < NU; ++u) sum[i][u] = Block{};
     }
     auto end_of_stage = [&]() {
         if constexpr (CHAINS)
@@ -274,17 +279,17 @@ __device__ __forceinline__ void small_contract(f32x4 (&acc)[C::WTM / 16][C::WTN 
                 for (int i = 0; i < NB; ++i)
 #pragma unroll
                     for (int u = 0; u < NU; ++u) {
-                        sum[i][u] += acc[i][u];
-                        acc[i][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        sum[i][u] += acc.a[i][u];
+                        acc.a[i][u] = Block{};
                     }
             }
     };
     auto next_slot = [&]() { slot_out = slot_out + C::STAGE == C::LDS ? 0u : slot_out + C::STAGE; };
-    // Stage t on the fragments f*; the reads of the next MFMA step are in flight under every step.  The last step of a stage
+    // Stage t, f* being read already; the reads of the next MFMA step are in flight under every step.  The last step of a stage
     // takes its next fragments from the next stage: that is where the stage's one barrier and the refill of its slot are.
     // `steady`: the refill exists and lies inside K, no stage in flight is the one past K.
-    auto stage = [&](int t, bool steady, SmallFrag<C>(&fa)[NB], SmallFrag<C>(&fb)[NU], SmallFrag<C>(&ha)[NB], SmallFrag<C>(&hb)[NU]) {
-        if constexpr (KS == 2) mma(fa, fb, [&](int i) { read_part(ha, hb, 1, i, NB); });
+    auto stage = [&](int t, bool steady) {
+        mma(fa, fb, [&](int i, int n) { read_part(ha, hb, 1, i, n); });
         const bool more = steady || t + 1 < KT;      // there is a next stage to read
         bool fill = steady;                          // and one to fetch, in full
         if (steady) {
@@ -304,14 +309,10 @@ __device__ __forceinline__ void small_contract(f32x4 (&acc)[C::WTM / 16][C::WTN 
                 fill = false;
             }
         }
-        auto next_step = [&](SmallFrag<C>(&na)[NB], SmallFrag<C>(&nb)[NU]) {
-            return [&](int i) {
-                if (fill) issue_part(i, NB);
-                if (more) read_part(na, nb, 0, i, NB);
-            };
-        };
-        if constexpr (KS == 2) mma(ha, hb, next_step(fa, fb));
-        else mma(fa, fb, next_step(ha, hb));
+        mma(ha, hb, [&](int i, int n) {
+            if (fill) issue_part(i, n);
+            if (more) read_part(fa, fb, 0, i, n);
+        });
         end_of_stage();
     };
 #pragma unroll
@@ -326,27 +327,15 @@ __device__ __forceinline__ void small_contract(f32x4 (&acc)[C::WTM / 16][C::WTN 
         wait_loads<0>();
     }
     meet();
-    read_part(fa0, fb0, 0, 0, 1);
+    read_part(fa, fb, 0, 0, 1);
     int t = 0;
-    if constexpr (KS == 2) {
-        for (; t + S + (ragged ? 1 : 0) < KT; ++t) stage(t, true, fa0, fb0, fa1, fb1);
-        for (; t < KT; ++t) stage(t, false, fa0, fb0, fa1, fb1);
-    } else {
-        // two stages per trip: the fragment buffers swap roles
-        for (; t + 1 + S + (ragged ? 1 : 0) < KT; t += 2) {
-            stage(t, true, fa0, fb0, fa1, fb1);
-            stage(t + 1, true, fa1, fb1, fa0, fb0);
-        }
-        for (; t < KT; t += 2) {
-            stage(t, false, fa0, fb0, fa1, fb1);
-            if (t + 1 < KT) stage(t + 1, false, fa1, fb1, fa0, fb0);
-        }
-    }
+    for (; t + S + (ragged ? 1 : 0) < KT; ++t) stage(t, true);
+    for (; t < KT; ++t) stage(t, false);
     if constexpr (CHAINS) {
 #pragma unroll
         for (int i = 0; i < NB; ++i)
 #pragma unroll
-            for (int u = 0; u < NU; ++u) acc[i][u] = sum[i][u] + acc[i][u];
+            for (int u = 0; u < NU; ++u) acc.a[i][u] = sum[i][u] + acc.a[i][u];
     }
     __syncthreads();
 }
@@ -355,25 +344,43 @@ template <class C, bool AK, bool BKC>
 __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2), amdgpu_num_vgpr(256))) void gemm_small_partial(const SmallParams p)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[C::LDS];
-    constexpr int NB = C::WTM / 16, NU = C::WTN / 16;
     int tm, tn, split;
     small_coords((int)blockIdx.x, p.tiles_m, p.tiles_n, p.nsplit, tm, tn, split);
     const int stages = (p.K + C::BK - 1) / C::BK;
     const int k0 = __builtin_amdgcn_readfirstlane((int)((int64_t)split * stages / p.nsplit));
     const int k1 = __builtin_amdgcn_readfirstlane((int)((int64_t)(split + 1) * stages / p.nsplit));   // k1 > k0: nsplit <= stages
-    f32x4 acc[NB][NU];
+    SmallAcc<C> acc;
     const int m0 = tm * C::BM, n0 = tn * C::BN;
-    small_contract<C, AK, BKC, !C::F8>(acc, p, m0, n0, k0, tn, k1 - k0, smem);
+    small_contract<C, AK, BKC, !C::F8>(acc, p, m0, n0, k0, n0 / p.rot_cols, k1 - k0, smem);
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m = m0 + (wave % C::WGM) * C::WTM + (lane & 15), n = n0 + (wave / C::WGM) * C::WTN + (lane >> 4) * 4;
+    const int mw = m0 + wave % C::WGM * C::WTM, nw = n0 + wave / C::WGM * C::WTN;
     float *out = p.part + (int64_t)split * p.M * p.N;
+    if constexpr (C::F8) {
+        // a lane's four columns and its partner's are 32 bytes of a row: rows of the wave's tile by way of LDS (eight ranges of 256 x
+        // 1984 x 4336: 17.2 us, stored from registers 18.9)
+        constexpr int RB = C::WTN * 4, UB = 16 * SmallAcc<C>::LQ;
+        unsigned char *reg = smem + wave * 32 * RB;
+        const uint32_t ulane = Stage<RB>::template unit_lane<16, 32>(lane);
 #pragma unroll
-    for (int i = 0; i < NB; ++i)
+        for (int i = 0; i < SmallAcc<C>::NB; ++i) {
 #pragma unroll
-        for (int u = 0; u < NU; ++u)
-            if (m + i * 16 < p.M && n + u * 16 < p.N)
-                *reinterpret_cast<f32x4 *>(out + (int64_t)(m + i * 16) * p.N + n + u * 16) = acc[i][u];
+            for (int u = 0; u < SmallAcc<C>::NU; ++u)
+                *reinterpret_cast<f32x4 *>(reg + Stage<RB>::template unit_addr<32>(ulane, 0, u * UB)) = acc.get(i, u);
+            stage_fence();
+            stage_store<RB, 32, true, false>(reg, reinterpret_cast<unsigned char *>(out + (int64_t)(mw + i * 32) * p.N + nw), (int64_t)p.N * 4,
+                                             p.M - mw - i * 32, (p.N - nw) * 4, lane);
+            stage_fence();
+        }
+    } else {
+        const int m = mw + (lane & 15), n = nw + (lane >> 4) * 4;
+#pragma unroll
+        for (int i = 0; i < SmallAcc<C>::NB; ++i)
+#pragma unroll
+            for (int u = 0; u < SmallAcc<C>::NU; ++u)
+                if (m + i * 16 < p.M && n + u * 16 < p.N)
+                    *reinterpret_cast<f32x4 *>(out + (int64_t)(m + i * 16) * p.N + n + u * 16) = acc.get(i, u);
+    }
 }
 
 // The whole launch in one kernel: the contraction undivided, then the epilogue program of the large kernels on the tile.
@@ -387,13 +394,19 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2), am
     int tm, tn, split;
     small_coords((int)blockIdx.x, p.tiles_m, p.tiles_n, 1, tm, tn, split);
     const int m0 = tm * C::BM, n0 = tn * C::BN;
-    Acc16<C> acc;
-    small_contract<C, AK, BKC, CHAINS>(acc.a, p, m0, n0, 0, tn, (p.K + C::BK - 1) / C::BK, smem);
+    SmallAcc<C> acc;
+    const int stages = (p.K + C::BK - 1) / C::BK;
+    int rot0 = 0;
+    if (BKC && p.rot_cols == ROT_XCD)
+        rot0 = xcd_rotation(tile_xcd(m0 / 256, n0 / 256, (p.M + 255) / 256, (p.N + 255) / 256), 2 * stages) / 2;
+    else if (BKC && p.rot_cols)
+        rot0 = n0 / p.rot_cols;
+    small_contract<C, AK, BKC, CHAINS>(acc, p, m0, n0, 0, rot0, stages, smem);
     float *red = reinterpret_cast<float *>(smem + C::LDS);
     if (C::BM < 128 || m0 + C::BM > p.M || n0 + C::BN > p.N)
-        run_epilogue<C, Acc16<C>, EPI, true, C::LDS>(acc, g, m0, n0, tn, smem, red, (int)threadIdx.x);
+        run_epilogue<C, SmallAcc<C>, EPI, true, C::LDS>(acc, g, m0, n0, tn, smem, red, (int)threadIdx.x);
     else
-        run_epilogue<C, Acc16<C>, EPI, false, C::LDS>(acc, g, m0, n0, tn, smem, red, (int)threadIdx.x);
+        run_epilogue<C, SmallAcc<C>, EPI, false, C::LDS>(acc, g, m0, n0, tn, smem, red, (int)threadIdx.x);
 }
 
 }  // namespace coda

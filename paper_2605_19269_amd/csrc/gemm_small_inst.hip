@@ -36,7 +36,7 @@ static hipError_t launch_rows(const GemmParams &p, const float *part, int nsplit
     return hipGetLastError();
 }
 
-static SmallParams small_params(const GemmParams &p, bool f8, int chain)
+static SmallParams small_params(const GemmParams &p, bool f8, int chain, int rot_cols)
 {
     const int64_t esz = f8 ? 1 : 2;
     SmallParams q{};
@@ -46,12 +46,13 @@ static SmallParams small_params(const GemmParams &p, bool f8, int chain)
     q.ldb = p.ldb * esz;
     q.M = p.M; q.N = p.N; q.K = p.K;
     q.chain = chain;
+    q.rot_cols = rot_cols;
     return q;
 }
 
 hipError_t launch_gemm_small(const SmallPlan &pl, int mode, bool f8, bool ak, bool bkc, const GemmParams &p, int chain, float *part, hipStream_t s)
 {
-    SmallParams q = small_params(p, f8, chain);
+    SmallParams q = small_params(p, f8, chain, (int)PLAN_TILE_N);
     q.tiles_m = (p.M + pl.bm - 1) / pl.bm;
     q.tiles_n = (p.N + pl.bn - 1) / pl.bn;
     q.nsplit = pl.nsplit;
@@ -68,9 +69,9 @@ hipError_t launch_gemm_small(const SmallPlan &pl, int mode, bool f8, bool ak, bo
     }
 }
 
-hipError_t launch_gemm_direct(int tile, int mode, bool f8, bool ak, bool bkc, const GemmParams &p, int chain, hipStream_t s)
+hipError_t launch_gemm_direct(int tile, int mode, bool f8, bool ak, bool bkc, const GemmParams &p, int chain, int rot_cols, hipStream_t s)
 {
-    const SmallParams q = small_params(p, f8, chain);
+    const SmallParams q = small_params(p, f8, chain, rot_cols);
     if (f8)
         return ak ? (bkc ? launch_small_direct<true, true, true>(tile, mode, p, q, s) : launch_small_direct<true, true, false>(tile, mode, p, q, s))
                   : (bkc ? launch_small_direct<true, false, true>(tile, mode, p, q, s) : launch_small_direct<true, false, false>(tile, mode, p, q, s));

@@ -122,7 +122,9 @@ inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_c
     };
     if (M <= 64 && a_k_contiguous) return M <= 32 ? offer(32, 128, 0.62) : offer(64, 128, 0.62);
     const SmallPlan narrow = offer(128, 128, 0.57), wide = offer(128, 256, 0.83);
-    const SmallPlan best = wide.nsplit == 0 || (narrow.nsplit != 0 && narrow.us <= wide.us) ? narrow : wide;
+    // one range: programs without row reductions run undivided and pay no partials (plan_route), and all take the same plan
+    auto cost = [&](const SmallPlan &p) { return p.us - (p.nsplit == 1 ? 0.5 * (double)(M * N) * 8.0 / 5e6 : 0.0); };
+    const SmallPlan best = wide.nsplit == 0 || (narrow.nsplit != 0 && cost(narrow) <= cost(wide)) ? narrow : wide;
     const double t_big = 0.83 * 2.0 * splitk_longest_stages(big, K, f8) + 12.0 + 0.019 * big.chunks * big.stride + (big.pieces > 1 ? 25.0 : 0.0);
     return best.nsplit != 0 && best.us <= 0.9 * t_big ? best : none;
 }
@@ -144,7 +146,7 @@ inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_c
 // other workgroups: 2048 x 11264 x 1000: PAIR 78, 256 x 256 85; 5976 x 2968 x 720: 52, 67; 5632 x 2048 x 2552: 72, 69 and 11008 x
 // 4096 x 1000: 129, 126, which stay.
 enum DirectTile : int { DIRECT_NONE = 0, DIRECT_64x64, DIRECT_32x256, DIRECT_64x256, DIRECT_128x128, DIRECT_128x128_PAIR, DIRECT_128x256 };
-enum DirectProgram : int { DIRECT_PROG_LINEAR, DIRECT_PROG_SWIGLU_FWD, DIRECT_PROG_SWIGLU_BWD, DIRECT_PROG_ACCUM };
+enum DirectProgram : int { DIRECT_PROG_LINEAR, DIRECT_PROG_SWIGLU_FWD, DIRECT_PROG_SWIGLU_BWD, DIRECT_PROG_ACCUM, DIRECT_PROG_RMSNORM_BWD };
 // Tiles whose bf16 kernels keep to a longest chain of additions: they may take over shapes that a workspace divides.
 inline bool direct_has_chains(int tile) { return tile == DIRECT_64x64 || tile == DIRECT_128x128; }
 struct DirectPlan {
@@ -154,7 +156,7 @@ struct DirectPlan {
 inline DirectPlan plan_direct(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_contiguous, DirectProgram prog, bool wide)
 {
     DirectPlan best = {DIRECT_NONE, 0.0};
-    if (M <= 0 || N <= 0 || K <= 0) return best;
+    if (M <= 0 || N <= 0 || K <= 0 || prog == DIRECT_PROG_RMSNORM_BWD) return best;
     // where a workspace lets the last round be shared, the tiles of the whole rounds are the same bits with and without one
     if (plan_splitk(M, N, K, f8).first > 0) return best;
     const double stages = (double)((K * (f8 ? 1 : 2) + 127) / 128);
@@ -188,6 +190,64 @@ inline DirectPlan plan_direct(int64_t M, int64_t N, int64_t K, bool f8, bool a_k
     }
     offer(DIRECT_128x256, (6.0 + stages * 0.88 * rounds(tiles(128, 256)) + rmw) * (prog == DIRECT_PROG_ACCUM ? 1.07 : 1.0));
     return best;
+}
+
+// Route of a call.  The order of the additions behind an element must not depend on the program, so what divides the
+// contraction is decided by the sizes, operand type and layouts alone:
+//   whole or undivided small tiles, chain INT32_MAX: the MFMAs of a tile along K from the place that rot_cols says, the same
+//     sums on every tile size;
+//   shared: the ranges of `shared`;
+//   divided: the ranges of `small`, folded every `chain` stages, started at the stage of rot_cols.
+// The program chooses only between tiles of one order: an undivided tile takes the place of a division into one range, with
+// that range's chain and starting stages (96 x 28672 x 4096 8-bit SwiGLU: 29 us against 34 with partials and a second kernel).
+// It does not take the place of more ranges, where it would be 5 to 20 % ahead for a program without row reductions (809 x
+// 4096 x 4096: 37 us against 44, 512 x 6144 x 4096 A^T B SwiGLU 40, 43) and behind for one with.
+enum RouteKind : int { ROUTE_WHOLE = 0, ROUTE_SHARED, ROUTE_DIVIDED, ROUTE_DIRECT };
+struct Route {
+    RouteKind kind;
+    int tile;          // ROUTE_DIRECT: a DirectTile
+    int chain;         // longest chain of additions in stages; INT32_MAX: one chain (small tiles)
+    int rot_cols;      // see SmallParams; ROUTE_WHOLE: GemmParams::rot_cols if positive
+    SplitPlan shared;  // ROUTE_SHARED
+    SmallPlan small;   // ROUTE_DIVIDED
+};
+// Where an undivided tile starts along K if B is K-contiguous.  256 x 256 tiles of a whole bf16 A B^T start by XCD, and small tiles
+// with them.  Up to 256 rows (a row of 256 x 256 tiles: no panels to share) the tiles start by column, in steps of 256 (1 x 65536 x 4096
+// 97 us, from stage 0 124; 32 x 50256 x 4096 8-bit 40, 54); not where a workspace would leave whole rounds to the 256 x 256 tiles.
+constexpr int ROT_XCD = -1;
+inline int undivided_rotation(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_contiguous, bool b_k_contiguous)
+{
+    if (!b_k_contiguous || K <= 0 || K % (f8 ? 128 : 64)) return 0;
+    if (M % PLAN_TILE_M == 0 && N % PLAN_TILE_N == 0) return a_k_contiguous && !f8 ? ROT_XCD : 0;
+    return M <= PLAN_TILE_M && plan_splitk(M, N, K, f8).first == 0 ? (int)PLAN_TILE_N : 0;
+}
+inline Route plan_route(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_contiguous, bool b_k_contiguous, DirectProgram prog, bool wide,
+                        bool workspace)
+{
+    Route r = {ROUTE_WHOLE, DIRECT_NONE, INT32_MAX, undivided_rotation(M, N, K, f8, a_k_contiguous, b_k_contiguous), {0, 0, 0, 0, 1}, {0, 0, 0, 0.0}};
+    const DirectPlan direct = plan_direct(M, N, K, f8, a_k_contiguous, prog, wide);
+    // the contraction is divided only when the caller brought the workspace for it; without one the shape runs undivided
+    if (workspace) {
+        r.shared = plan_splitk(M, N, K, f8);
+        if (r.shared.chunks > 0) {
+            r.small = plan_small(M, N, K, f8, a_k_contiguous);
+            if (r.small.nsplit == 0) {
+                r.kind = ROUTE_SHARED;
+                return r;
+            }
+            r.chain = splitk_longest_stages(r.shared, K, f8);
+            r.rot_cols = (int)PLAN_TILE_N;      // a column of the widest tile
+            if (r.small.nsplit > 1 || r.small.us <= direct.us || !(f8 ? direct.tile != DIRECT_NONE : direct_has_chains(direct.tile))) {
+                r.kind = ROUTE_DIVIDED;
+                return r;
+            }
+        }
+    }
+    if (direct.tile != DIRECT_NONE) {
+        r.kind = ROUTE_DIRECT;
+        r.tile = direct.tile;
+    }
+    return r;
 }
 
 }  // namespace coda

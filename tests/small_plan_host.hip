@@ -18,6 +18,25 @@ __attribute__((visibility("default"))) int host_direct_tile(int64_t M, int64_t N
     return coda::plan_direct(M, N, K, f8 != 0, ak != 0, (coda::DirectProgram)prog, wide != 0).tile;
 }
 
+// route[0..6] = coda::RouteKind, tile, chain, rot_cols, ranges, tile rows and columns of a divided launch
+__attribute__((visibility("default"))) void host_route(int64_t M, int64_t N, int64_t K, int f8, int ak, int bkc, int prog, int wide, int workspace, int *route)
+{
+    const coda::Route r = coda::plan_route(M, N, K, f8 != 0, ak != 0, bkc != 0, (coda::DirectProgram)prog, wide != 0, workspace != 0);
+    route[0] = r.kind; route[1] = r.tile; route[2] = r.chain; route[3] = r.rot_cols;
+    route[4] = r.small.nsplit; route[5] = r.small.bm; route[6] = r.small.bn;
+}
+
+// whether tile_xcd() inverts tile_coords() on a grid of tiles
+__attribute__((visibility("default"))) int host_tile_xcd_ok(int tiles_m, int tiles_n)
+{
+    for (int bid = 0; bid < tiles_m * tiles_n; ++bid) {
+        int tm, tn;
+        coda::tile_coords(bid, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
+        if (coda::tile_xcd(tm, tn, tiles_m, tiles_n) != bid % 8) return 0;
+    }
+    return 1;
+}
+
 // out[3 * bid ..] = tile row, tile column, range
 __attribute__((visibility("default"))) void host_small_map(int tiles_m, int tiles_n, int nsplit, int *out)
 {

@@ -1,0 +1,38 @@
+"""Host checks of the promise that the order of the additions behind an element of D does not depend on the program: every program of
+a shape gets kernels of one order."""
+import random
+
+import pytest
+
+from tests import small_plan
+
+ALL = [("linear", False), ("linear", True), ("swiglu_fwd", False), ("swiglu_bwd", False), ("swiglu_bwd", True), ("accum", False), ("rmsnorm_bwd", False)]
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    return small_plan.load(tmp_path_factory.mktemp("small_plan"))
+
+
+def test_programs_of_a_shape_share_one_order(lib):
+    rng = random.Random(11)
+    mixed = set()
+    for _ in range(3000):
+        M, N, K = 16 * int(2 ** rng.uniform(0, 9)), 16 * int(2 ** rng.uniform(0, 12)), 16 * int(2 ** rng.uniform(0, 10))
+        if rng.random() < 0.3:
+            M, N, K = -(-M // 256) * 256, -(-N // 256) * 256, -(-K // 128) * 128
+        for f8 in (False, True):
+            for ak in (True, False):
+                for bkc in (True, False):
+                    for ws in (True, False):
+                        routes = [small_plan.Route(lib, M, N, K, f8, ak, bkc, prog, wide, ws) for prog, wide in ALL]
+                        assert len({r.order for r in routes}) == 1, (M, N, K, f8, ak, bkc, ws, [(r.kind, r.tile, r.order) for r in routes])
+                        if len({r.kind for r in routes}) > 1:
+                            mixed.add((ws, tuple(sorted({r.kind for r in routes}))))
+    assert {(False, ("direct", "whole")), (True, ("direct", "divided"))} <= mixed       # the sizes are not of one kernel each
+
+
+@pytest.mark.parametrize("tiles_m", [1, 2, 3, 7, 8, 9, 16, 21])
+def test_small_tiles_know_the_xcd_of_their_large_tile(lib, tiles_m):
+    for tiles_n in (1, 2, 3, 5, 8, 13, 40):
+        assert lib.host_tile_xcd_ok(tiles_m, tiles_n)
