@@ -29,7 +29,7 @@ struct SmallParams {
     int64_t lda, ldb;        // row pitches in bytes
     int M, N, K;
     int tiles_m, tiles_n, nsplit;
-    int chain;               // longest chain of fp32 additions, in stages (bf16)
+    int chain;               // longest chain of fp32 additions, in stages
     int rot_cols;            // B K-contiguous: a tile starts at stage n0 / rot_cols of its range and wraps around; undivided also 0:
                              // at stage 0, ROT_XCD: where its 256 x 256 tile starts (see gemm_item_dl)
     float *part;             // [nsplit][M][N]
@@ -261,8 +261,7 @@ __device__ __forceinline__ void small_contract(SmallAcc<C> &acc, const SmallPara
     };
     // Chains: the accumulators are added to `sum` and start again from zero every p.chain stages, so that a range that is longer
     // than the ones the shape had on shared 256 x 256 tiles is no less accurate (509 x 2048 x 8192 in four ranges against 64 bits:
-    // 2.7e-7 in one chain each, 1.9e-7 in two, as in eight ranges).  8-bit products go without: their own rounding inside the
-    // MFMA, 1.3e-5, covers it; so do the tiles that only take over undivided launches (2 to 3 % at 128x256).
+    // 2.7e-7 in one chain each, 1.9e-7 in two, as in eight ranges).  Not in launches that nothing divides (2 to 3 % at 128x256).
     Block sum[CHAINS ? NB : 1][CHAINS ? NU : 1];
     int chain = p.chain;
     if constexpr (CHAINS) {
@@ -351,7 +350,7 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2), am
     const int k1 = __builtin_amdgcn_readfirstlane((int)((int64_t)(split + 1) * stages / p.nsplit));   // k1 > k0: nsplit <= stages
     SmallAcc<C> acc;
     const int m0 = tm * C::BM, n0 = tn * C::BN;
-    small_contract<C, AK, BKC, !C::F8>(acc, p, m0, n0, k0, n0 / p.rot_cols, k1 - k0, smem);
+    small_contract<C, AK, BKC, true>(acc, p, m0, n0, k0, n0 / p.rot_cols, k1 - k0, smem);
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int mw = m0 + wave % C::WGM * C::WTM, nw = n0 + wave / C::WGM * C::WTN;

@@ -6,7 +6,7 @@
 
 namespace coda {
 
-template <class C, bool AK, bool BKC, int EPI, bool CHAINS = false>
+template <class C, bool AK, bool BKC, int EPI, bool CHAINS>
 static hipError_t launch_direct(const GemmParams &g, SmallParams p, hipStream_t s)
 {
     p.tiles_m = (p.M + C::BM - 1) / C::BM;
@@ -16,19 +16,26 @@ static hipError_t launch_direct(const GemmParams &g, SmallParams p, hipStream_t 
     return hipGetLastError();
 }
 
+// The 256-wide tiles without chains where there is one only (2 to 3 % at 128x256).
+template <class C, bool AK, bool BKC, int EPI>
+static hipError_t launch_wide(const GemmParams &g, const SmallParams &p, hipStream_t s)
+{
+    return p.chain == INT32_MAX ? launch_direct<C, AK, BKC, EPI, false>(g, p, s) : launch_direct<C, AK, BKC, EPI, true>(g, p, s);
+}
+
 template <bool F8, bool AK, bool BKC, int EPI>
 static hipError_t direct_tile(int tile, const GemmParams &g, const SmallParams &p, hipStream_t s)
 {
     if constexpr (AK && (EPI == EPI_LINEAR || EPI == EPI_SWIGLU_FWD))
-        if (tile == DIRECT_64x64) return launch_direct<SmallCfg<64, 64, 2, 1, 4, F8>, AK, BKC, EPI, !F8>(g, p, s);
+        if (tile == DIRECT_64x64) return launch_direct<SmallCfg<64, 64, 2, 1, 4, F8>, AK, BKC, EPI, true>(g, p, s);
     if constexpr (AK && EPI == EPI_LINEAR) {
-        if (tile == DIRECT_32x256) return launch_direct<SmallCfg<32, 256, 1, 4, 4, F8>, AK, BKC, EPI>(g, p, s);
-        if (tile == DIRECT_64x256) return launch_direct<SmallCfg<64, 256, 2, 4, 3, F8>, AK, BKC, EPI>(g, p, s);
+        if (tile == DIRECT_32x256) return launch_wide<SmallCfg<32, 256, 1, 4, 4, F8>, AK, BKC, EPI>(g, p, s);
+        if (tile == DIRECT_64x256) return launch_wide<SmallCfg<64, 256, 2, 4, 3, F8>, AK, BKC, EPI>(g, p, s);
     }
     if constexpr (EPI == EPI_ACCUM)
-        if (tile == DIRECT_128x128_PAIR) return launch_direct<SmallCfg<128, 128, 2, 2, 2, F8>, AK, BKC, EPI>(g, p, s);
-    if (tile == DIRECT_128x128) return launch_direct<SmallCfg<128, 128, 4, 2, 4, F8>, AK, BKC, EPI, !F8>(g, p, s);
-    if (tile == DIRECT_128x256) return launch_direct<SmallCfg<128, 256, 2, 4, 3, F8>, AK, BKC, EPI>(g, p, s);
+        if (tile == DIRECT_128x128_PAIR) return launch_direct<SmallCfg<128, 128, 2, 2, 2, F8>, AK, BKC, EPI, false>(g, p, s);
+    if (tile == DIRECT_128x128) return launch_direct<SmallCfg<128, 128, 4, 2, 4, F8>, AK, BKC, EPI, true>(g, p, s);
+    if (tile == DIRECT_128x256) return launch_wide<SmallCfg<128, 256, 2, 4, 3, F8>, AK, BKC, EPI>(g, p, s);
     return hipErrorInvalidConfiguration;             // a tile that the plan does not give this program
 }
 

@@ -122,7 +122,7 @@ inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_c
     };
     if (M <= 64 && a_k_contiguous) return M <= 32 ? offer(32, 128, 0.62) : offer(64, 128, 0.62);
     const SmallPlan narrow = offer(128, 128, 0.57), wide = offer(128, 256, 0.83);
-    // one range: programs without row reductions run undivided and pay no partials (plan_route), and all take the same plan
+    // one range: most programs run undivided and pay no partials (plan_route), and all take the same plan
     auto cost = [&](const SmallPlan &p) { return p.us - (p.nsplit == 1 ? 0.5 * (double)(M * N) * 8.0 / 5e6 : 0.0); };
     const SmallPlan best = wide.nsplit == 0 || (narrow.nsplit != 0 && cost(narrow) <= cost(wide)) ? narrow : wide;
     const double t_big = 0.83 * 2.0 * splitk_longest_stages(big, K, f8) + 12.0 + 0.019 * big.chunks * big.stride + (big.pieces > 1 ? 25.0 : 0.0);
@@ -140,20 +140,18 @@ inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_c
 // row sums: 64x256 41.1, 128x256 46.0, before 67.8; 509 x 6144 x 2048: 128x128 22.6, 128x256 31.7, before 46.1; 509 x 16384 x
 // 2048: 128x256 34.8, 128x128 44.4, before 46.8; 257 x 22312 x 4096: 64x256 105, 128x256 120, 256 x 256 94, which keeps it, as it
 // does 1000 x 16384 x 2048 (128x256 66.8, 256 x 256 55.4).
-// A plan_small() with one range per tile gives way to these where the model says so: 96 x 28672 x 4096 8-bit SwiGLU: 128x128
+// A plan_small() with one range per tile gives way to these (`chains`: all but PAIR keep to its chain) where the model says so: 96 x 28672 x 4096 8-bit SwiGLU: 128x128
 // 29.2, partials and second kernel 34.2.
 // The gradient program also reads and writes 8 bytes per element, two thirds of it (PAIR: half) beside the contraction of
 // other workgroups: 2048 x 11264 x 1000: PAIR 78, 256 x 256 85; 5976 x 2968 x 720: 52, 67; 5632 x 2048 x 2552: 72, 69 and 11008 x
 // 4096 x 1000: 129, 126, which stay.
 enum DirectTile : int { DIRECT_NONE = 0, DIRECT_64x64, DIRECT_32x256, DIRECT_64x256, DIRECT_128x128, DIRECT_128x128_PAIR, DIRECT_128x256 };
 enum DirectProgram : int { DIRECT_PROG_LINEAR, DIRECT_PROG_SWIGLU_FWD, DIRECT_PROG_SWIGLU_BWD, DIRECT_PROG_ACCUM, DIRECT_PROG_RMSNORM_BWD };
-// Tiles whose bf16 kernels keep to a longest chain of additions: they may take over shapes that a workspace divides.
-inline bool direct_has_chains(int tile) { return tile == DIRECT_64x64 || tile == DIRECT_128x128; }
 struct DirectPlan {
     int tile;
     double us;     // modelled time
 };
-inline DirectPlan plan_direct(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_contiguous, DirectProgram prog, bool wide)
+inline DirectPlan plan_direct(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_contiguous, DirectProgram prog, bool wide, bool chains = false)
 {
     DirectPlan best = {DIRECT_NONE, 0.0};
     if (M <= 0 || N <= 0 || K <= 0 || prog == DIRECT_PROG_RMSNORM_BWD) return best;
@@ -182,7 +180,7 @@ inline DirectPlan plan_direct(int64_t M, int64_t N, int64_t K, bool f8, bool a_k
         offer(DIRECT_64x256, 5.5 + stages * 0.68 * rounds(tiles(64, 256)));
     }
     if (!wide) offer(DIRECT_128x128, 4.5 + stream(stages * 0.57 * rounds(tiles(128, 128)), 5.6e6) + rmw);
-    if (prog == DIRECT_PROG_ACCUM) {
+    if (prog == DIRECT_PROG_ACCUM && !chains) {
         // rounds of two per CU; what is left over runs two or one per CU (1424 x 6304 x 12920: 600 tiles lose 30 % to 256 x 256)
         const int64_t t = tiles(128, 128), whole = t / (2 * SPLITK_CUS), left = t % (2 * SPLITK_CUS);
         const double rest = left == 0 ? 0.0 : (left <= SPLITK_CUS ? 0.66 : 1.08);
@@ -225,7 +223,7 @@ inline Route plan_route(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_conti
                         bool workspace)
 {
     Route r = {ROUTE_WHOLE, DIRECT_NONE, INT32_MAX, undivided_rotation(M, N, K, f8, a_k_contiguous, b_k_contiguous), {0, 0, 0, 0, 1}, {0, 0, 0, 0.0}};
-    const DirectPlan direct = plan_direct(M, N, K, f8, a_k_contiguous, prog, wide);
+    DirectPlan direct = plan_direct(M, N, K, f8, a_k_contiguous, prog, wide);
     // the contraction is divided only when the caller brought the workspace for it; without one the shape runs undivided
     if (workspace) {
         r.shared = plan_splitk(M, N, K, f8);
@@ -237,7 +235,8 @@ inline Route plan_route(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_conti
             }
             r.chain = splitk_longest_stages(r.shared, K, f8);
             r.rot_cols = (int)PLAN_TILE_N;      // a column of the widest tile
-            if (r.small.nsplit > 1 || r.small.us <= direct.us || !(f8 ? direct.tile != DIRECT_NONE : direct_has_chains(direct.tile))) {
+            if (r.small.nsplit == 1) direct = plan_direct(M, N, K, f8, a_k_contiguous, prog, wide, true);
+            if (r.small.nsplit > 1 || direct.tile == DIRECT_NONE || r.small.us <= direct.us) {
                 r.kind = ROUTE_DIVIDED;
                 return r;
             }

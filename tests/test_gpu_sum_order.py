@@ -83,3 +83,43 @@ def test_every_program_has_the_same_d(plans, M, N, K, f8, ta, tb, ws, tiles):
     O, one = b16(M, N), torch.ones(max(M, N), device="cuda")
     gemm(coda.rmsnorm_bwd(b16(M, N), one[:M], f32(M), one[:N]), coda.store(O))
     assert torch.equal(O, Db), "RMSNorm backward"
+
+
+# M, N, K, f8: undivided tiles in place of one range (all that fold, with and without row sums), the divided tiles with one and several
+# ranges; chains that divide a range and that do not
+CHAINED = [(32, 28672, 4096, False), (96, 28672, 4096, True), (40, 20480, 8192, False), (512, 14336, 6144, True), (200, 28672, 4096, False), (200, 28672, 4096, True),
+           (2, 16400, 23040, True), (1000, 4096, 4096, True), (509, 2048, 8192, False), (1000, 2048, 11264, True), (1000, 2048, 11264, False)]
+
+
+@pytest.mark.parametrize("M,N,K,f8", CHAINED)
+def test_long_sums_fold_at_the_length_of_the_shared_ranges(plans, M, N, K, f8):
+    """A large value in the first stage swallows the small products that follow it in its chain, one MFMA step at a time (each is less than
+    half its last place), and none of those in other chains, whose sums are added as a whole."""
+    stage = 128 if f8 else 64
+    stages = K // stage
+    assert K % stage == 0
+    if f8:                                     # 128 x 448^2 < 2^25: last place 2; a step of 64 products adds 2^-1, a stage 1
+        A, B = torch.full((M, K), 2.0 ** -3), torch.full((K, N), 2.0 ** -4)
+        A[:, :stage], B[:stage] = 448.0, 448.0
+        A, B = (t.to(torch.float8_e4m3fn).view(torch.uint8).cuda() for t in (A, B))
+        big, ulp, per_stage = 128 * 448.0 ** 2, 2.0, 1.0
+    else:                                      # 2^30: last place 128; a step of 32 products adds 32, a stage 64
+        A, B = torch.ones(M, K), torch.ones(K, N)
+        A[:, 0], B[0] = 2.0 ** 15, 2.0 ** 15
+        A, B = (t.bfloat16().cuda() for t in (A, B))
+        big, ulp, per_stage = 2.0 ** 30, 128.0, 64.0
+    work = torch.empty(coda.coda_gemm_workspace_bytes(M, N, K, []), dtype=torch.uint8, device="cuda")
+    for wide in (False, True):
+        route = small_plan.Route(plans, M, N, K, f8, True, False, "linear", wide, True)
+        ranges, chain = route.order[:2]
+        assert chain < stages, "a range of its own would not show it"
+        first = min(chain, stages // ranges)                       # stages of the chain with the large value
+        others = (stages - first) * per_stage
+        folds = ranges * -(-stages // ranges // chain) + ranges
+        D = torch.zeros(M, N, dtype=torch.float32, device="cuda")
+        ops = [coda.row_sumsq(torch.zeros(coda.coda_row_partial_blocks(N), M, device="cuda"))] if wide else []
+        coda.coda_gemm(A, B, ops + [coda.store(D, f32=True)], workspace=work)
+        tol = 0.5 * ulp * folds                                    # half a last place for each sum that is added to the large one
+        assert others > 2 * tol
+        err = (D.double() - (big + others)).abs().max().item()
+        assert err <= tol, (route.kind, route.tile, route.order, err, tol)
