@@ -15,6 +15,7 @@ def load(folder):
     lib.host_small_plan.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 2 + [ctypes.POINTER(ctypes.c_int)]
     lib.host_direct_tile.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 4
     lib.host_route.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 6 + [ctypes.POINTER(ctypes.c_int)]
+    lib.host_split_plan.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int, ctypes.POINTER(ctypes.c_int)]
     lib.host_small_map.argtypes = [ctypes.c_int] * 3 + [ctypes.POINTER(ctypes.c_int)]
     return lib
 
@@ -23,6 +24,13 @@ def plan(lib, M, N, K, f8=False, ak=True):
     """(tile rows, tile columns, ranges); ranges = 0: the shape runs on the large tiles."""
     out = (ctypes.c_int * 3)()
     lib.host_small_plan(M, N, K, int(f8), int(ak), out)
+    return tuple(out)
+
+
+def shared(lib, M, N, K, f8=False):
+    """(first shared 256 x 256 tile, shared tiles, ranges, workgroups a range); no ranges: nothing is shared."""
+    out = (ctypes.c_int * 4)()
+    lib.host_split_plan(M, N, K, int(f8), out)
     return tuple(out)
 
 

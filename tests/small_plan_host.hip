@@ -26,6 +26,13 @@ __attribute__((visibility("default"))) void host_route(int64_t M, int64_t N, int
     route[4] = r.small.nsplit; route[5] = r.small.bm; route[6] = r.small.bn;
 }
 
+// plan[0..3] = coda::SplitPlan: first shared tile, shared tiles, ranges, workgroups a range
+__attribute__((visibility("default"))) void host_split_plan(int64_t M, int64_t N, int64_t K, int f8, int *plan)
+{
+    const coda::SplitPlan pl = coda::plan_splitk(M, N, K, f8 != 0);
+    plan[0] = pl.first; plan[1] = pl.tail; plan[2] = pl.chunks; plan[3] = pl.pieces;
+}
+
 // whether tile_xcd() inverts tile_coords() on a grid of tiles
 __attribute__((visibility("default"))) int host_tile_xcd_ok(int tiles_m, int tiles_n)
 {

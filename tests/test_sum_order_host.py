@@ -32,6 +32,28 @@ def test_programs_of_a_shape_share_one_order(lib):
     assert {(False, ("direct", "whole")), (True, ("direct", "divided"))} <= mixed       # the sizes are not of one kernel each
 
 
+def test_chains_are_as_short_as_the_pieces_of_a_shared_tile(lib):
+    """Where small tiles take over a shape that would be shared, their chains are no longer than a shared tile's stages over the ranges
+    that reach into it, straddling or not."""
+    rng = random.Random(12)
+    straddling = 0
+    for _ in range(6000):
+        M, N, K = int(2 ** rng.uniform(0, 12)), 16 * int(2 ** rng.uniform(0, 11)), 16 * int(2 ** rng.uniform(7, 10.5))
+        f8 = rng.random() < 0.5
+        first, tail, chunks, pieces = small_plan.shared(lib, M, N, K, f8)
+        r = small_plan.Route(lib, M, N, K, f8, workspace=True)
+        if not chunks or r.kind == "shared":
+            continue
+        assert first == 0
+        straddling += pieces > 1
+        stages = -(-K * (1 if f8 else 2) // 128)
+        # range c holds the stages (of all tiles, end to end) from c * tail * stages / chunks on
+        starts = [c * tail * stages // chunks for c in range(chunks)]
+        reach = max(sum(1 for c in range(chunks) if starts[c] < (t + 1) * stages and (starts + [tail * stages])[c + 1] > t * stages) for t in range(tail))
+        assert r.order[1] == -(-stages // reach), (M, N, K, f8)
+    assert straddling > 20
+
+
 @pytest.mark.parametrize("tiles_m", [1, 2, 3, 7, 8, 9, 16, 21])
 def test_small_tiles_know_the_xcd_of_their_large_tile(lib, tiles_m):
     for tiles_n in (1, 2, 3, 5, 8, 13, 40):
