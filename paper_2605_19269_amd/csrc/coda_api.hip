@@ -309,10 +309,6 @@ coda_status gemm_impl(void *stream, int64_t M, int64_t N, int64_t K, const coda_
     const bool bkc = B->trans;   // B stored [N x K]: contraction index contiguous
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e;
-    if (workspace) {
-        if (!aligned16(workspace)) return CODA_ERR_ALIGN;
-        if (workspace_bytes < coda::splitk_bytes(coda::plan_splitk(M, N, K, f8))) return CODA_ERR_WORKSPACE;
-    }
     const coda::DirectProgram program = ps.mode == coda::EPI_LINEAR       ? coda::DIRECT_PROG_LINEAR
                                         : ps.mode == coda::EPI_SWIGLU_FWD ? coda::DIRECT_PROG_SWIGLU_FWD
                                         : ps.mode == coda::EPI_SWIGLU_BWD ? coda::DIRECT_PROG_SWIGLU_BWD
@@ -320,6 +316,10 @@ coda_status gemm_impl(void *stream, int64_t M, int64_t N, int64_t K, const coda_
                                                                           : coda::DIRECT_PROG_RMSNORM_BWD;
     const bool wide = p.rowred_mode != coda::ROWRED_NONE || p.lse_max;
     const coda::Route route = coda::plan_route(M, N, K, f8, ak, bkc, program, wide, workspace != nullptr);
+    if (workspace) {
+        if (!aligned16(workspace)) return CODA_ERR_ALIGN;
+        if (workspace_bytes < coda::splitk_bytes(route.shared)) return CODA_ERR_WORKSPACE;
+    }
     if (route.kind == coda::ROUTE_DIVIDED)
         return launch_status(coda::launch_gemm_small(route.small, ps.mode, f8, ak, bkc, p, route.chain, static_cast<float *>(workspace), s));
     if (route.kind == coda::ROUTE_DIRECT)

@@ -35,7 +35,8 @@ struct SplitPlan {
     int stride;   // exchange slots per shared tile: the largest number of ranges that reach into one tile
     int pieces;   // 1: every range lies in one tile; 2: ranges straddle tile boundaries (two workgroups per range)
 };
-inline SplitPlan plan_splitk(int64_t M, int64_t N, int64_t K, bool f8 = false)
+// `slots` false: without `stride`, whose count over the tail takes up to a microsecond.
+inline SplitPlan plan_splitk(int64_t M, int64_t N, int64_t K, bool f8 = false, bool slots = true)
 {
     const SplitPlan none = {0, 0, 0, 0, 1};
     if (M <= 0 || N <= 0 || K <= 0) return none;
@@ -56,7 +57,7 @@ inline SplitPlan plan_splitk(int64_t M, int64_t N, int64_t K, bool f8 = false)
     // ranges per tile: tile a is reached by the ranges that hold its first and its last pair, and those in between
     const int64_t total = tail * pairs;
     int64_t stride = 1;
-    for (int64_t a = 0; a < tail; ++a) {
+    for (int64_t a = 0; slots && a < tail; ++a) {
         const int64_t c_lo = ((a * pairs + 1) * chunks + total - 1) / total - 1;
         const int64_t c_hi = (((a + 1) * pairs) * chunks + total - 1) / total - 1;
         if (c_hi - c_lo + 1 > stride) stride = c_hi - c_lo + 1;
@@ -112,11 +113,9 @@ struct SmallPlan {
     double us;     // modelled time
 };
 constexpr int64_t SMALL_MAX_SPLIT = 16, SMALL_MIN_STAGES = 4;   // beyond that the exchange costs what the ranges save
-inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_contiguous)
+inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_contiguous, const SplitPlan &big)
 {
-    if (M <= 0 || N <= 0 || K <= 0) return SmallPlan{0, 0, 0, 0.0};
     const SmallPlan none = {0, 0, 0, 0.0};
-    const SplitPlan big = plan_splitk(M, N, K, f8);
     if (big.chunks == 0 || big.first != 0) return none;
     const int64_t esz = f8 ? 1 : 2, stages = (K * esz + 127) / 128;
     const int64_t budget = (int64_t)splitk_bytes(big) / (M * N * 4);              // ranges whose partials fit
@@ -160,12 +159,13 @@ struct DirectPlan {
     int tile;
     double us;     // modelled time
 };
-inline DirectPlan plan_direct(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_contiguous, DirectProgram prog, bool wide, bool chains = false)
+inline DirectPlan plan_direct(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_contiguous, DirectProgram prog, bool wide, const SplitPlan &big_plan,
+                              bool chains = false)
 {
     DirectPlan best = {DIRECT_NONE, 0.0};
     if (M <= 0 || N <= 0 || K <= 0 || prog == DIRECT_PROG_RMSNORM_BWD) return best;
     // where a workspace lets the last round be shared, the tiles of the whole rounds are the same bits with and without one
-    if (plan_splitk(M, N, K, f8).first > 0) return best;
+    if (big_plan.first > 0) return best;
     const double stages = (double)((K * (f8 ? 1 : 2) + 127) / 128);
     const double rmw = prog == DIRECT_PROG_ACCUM ? (double)M * (double)N * 8.0 / 5e6 : 0.0;
     auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
@@ -215,40 +215,38 @@ struct Route {
     int tile;          // ROUTE_DIRECT: a DirectTile
     int chain;         // longest chain of additions in stages; INT32_MAX: one chain (small tiles)
     int rot_cols;      // see SmallParams; ROUTE_WHOLE: GemmParams::rot_cols if positive
-    SplitPlan shared;  // ROUTE_SHARED
+    SplitPlan shared;  // ROUTE_SHARED; the workspace that any route asks for
     SmallPlan small;   // ROUTE_DIVIDED
 };
 // Where an undivided tile starts along K if B is K-contiguous.  256 x 256 tiles of a whole bf16 A B^T start by XCD, and small tiles
 // with them.  Up to 256 rows (a row of 256 x 256 tiles: no panels to share) the tiles start by column, in steps of 256 (1 x 65536 x 4096
 // 97 us, from stage 0 124; 32 x 50256 x 4096 8-bit 40, 54); not where a workspace would leave whole rounds to the 256 x 256 tiles.
 constexpr int ROT_XCD = -1;
-inline int undivided_rotation(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_contiguous, bool b_k_contiguous)
+inline int undivided_rotation(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_contiguous, bool b_k_contiguous, const SplitPlan &big)
 {
     if (!b_k_contiguous || K <= 0 || K % (f8 ? 128 : 64)) return 0;
     if (M % PLAN_TILE_M == 0 && N % PLAN_TILE_N == 0) return a_k_contiguous && !f8 ? ROT_XCD : 0;
-    return M <= PLAN_TILE_M && plan_splitk(M, N, K, f8).first == 0 ? (int)PLAN_TILE_N : 0;
+    return M <= PLAN_TILE_M && big.first == 0 ? (int)PLAN_TILE_N : 0;
 }
 inline Route plan_route(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_contiguous, bool b_k_contiguous, DirectProgram prog, bool wide,
                         bool workspace)
 {
-    Route r = {ROUTE_WHOLE, DIRECT_NONE, INT32_MAX, undivided_rotation(M, N, K, f8, a_k_contiguous, b_k_contiguous), {0, 0, 0, 0, 1}, {0, 0, 0, 0.0}};
-    DirectPlan direct = plan_direct(M, N, K, f8, a_k_contiguous, prog, wide);
+    const SplitPlan big = plan_splitk(M, N, K, f8, workspace);      // once a call
+    Route r = {ROUTE_WHOLE, DIRECT_NONE, INT32_MAX, undivided_rotation(M, N, K, f8, a_k_contiguous, b_k_contiguous, big), big, {0, 0, 0, 0.0}};
+    DirectPlan direct = plan_direct(M, N, K, f8, a_k_contiguous, prog, wide, big);
     // the contraction is divided only when the caller brought the workspace for it; without one the shape runs undivided
-    if (workspace) {
-        r.shared = plan_splitk(M, N, K, f8);
-        if (r.shared.chunks > 0) {
-            r.small = plan_small(M, N, K, f8, a_k_contiguous);
-            if (r.small.nsplit == 0) {
-                r.kind = ROUTE_SHARED;
-                return r;
-            }
-            r.chain = splitk_chain(r.shared, K, f8);
-            r.rot_cols = (int)PLAN_TILE_N;      // a column of the widest tile
-            if (r.small.nsplit == 1) direct = plan_direct(M, N, K, f8, a_k_contiguous, prog, wide, true);
-            if (r.small.nsplit > 1 || direct.tile == DIRECT_NONE || r.small.us <= direct.us) {
-                r.kind = ROUTE_DIVIDED;
-                return r;
-            }
+    if (workspace && big.chunks > 0) {
+        r.small = plan_small(M, N, K, f8, a_k_contiguous, big);
+        if (r.small.nsplit == 0) {
+            r.kind = ROUTE_SHARED;
+            return r;
+        }
+        r.chain = splitk_chain(big, K, f8);
+        r.rot_cols = (int)PLAN_TILE_N;      // a column of the widest tile
+        if (r.small.nsplit == 1) direct = plan_direct(M, N, K, f8, a_k_contiguous, prog, wide, big, true);
+        if (r.small.nsplit > 1 || direct.tile == DIRECT_NONE || r.small.us <= direct.us) {
+            r.kind = ROUTE_DIVIDED;
+            return r;
         }
     }
     if (direct.tile != DIRECT_NONE) {

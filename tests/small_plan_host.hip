@@ -8,14 +8,14 @@ extern "C" {
 // plan[0..2] = tile rows, tile columns, ranges (0: large tiles)
 __attribute__((visibility("default"))) void host_small_plan(int64_t M, int64_t N, int64_t K, int f8, int ak, int *plan)
 {
-    const coda::SmallPlan pl = coda::plan_small(M, N, K, f8 != 0, ak != 0);
+    const coda::SmallPlan pl = coda::plan_small(M, N, K, f8 != 0, ak != 0, coda::plan_splitk(M, N, K, f8 != 0));
     plan[0] = pl.bm; plan[1] = pl.bn; plan[2] = pl.nsplit;
 }
 
 // the undivided small tile of a program (coda::DirectTile; 0: 256 x 256 tiles)
 __attribute__((visibility("default"))) int host_direct_tile(int64_t M, int64_t N, int64_t K, int f8, int ak, int prog, int wide)
 {
-    return coda::plan_direct(M, N, K, f8 != 0, ak != 0, (coda::DirectProgram)prog, wide != 0).tile;
+    return coda::plan_direct(M, N, K, f8 != 0, ak != 0, (coda::DirectProgram)prog, wide != 0, coda::plan_splitk(M, N, K, f8 != 0)).tile;
 }
 
 // route[0..6] = coda::RouteKind, tile, chain, rot_cols, ranges, tile rows and columns of a divided launch
