@@ -254,7 +254,8 @@ def coda_gemm(A, B, ops, transA=False, transB=False, stream=None, workspace=None
     a, b = mat(A, transA), mat(B, transB)
     M, K = (a.cols, a.rows) if transA else (a.rows, a.cols)
     N = b.rows if transB else b.cols
-    arr, n = _prog(list(ops))
+    ops = list(ops)      # of a generator too: the ops own the tensors, and stay until the call returns
+    arr, n = _prog(ops)
     _check(_lib.coda_gemm(_stream(stream), M, N, K, ctypes.byref(a), ctypes.byref(b), arr, n,
                           None if workspace is None else workspace.data_ptr(),
                           0 if workspace is None else workspace.numel() * workspace.element_size()))
