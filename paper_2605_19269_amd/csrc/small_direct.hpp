@@ -16,7 +16,7 @@ static hipError_t launch_direct(const GemmParams &g, SmallParams p, hipStream_t 
     return hipGetLastError();
 }
 
-// The 256-wide tiles without chains where there is one only (2 to 3 % at 128x256).
+// 64x256 and 128x256 without chains where there is one only (2 to 3 % at 128x256).
 template <class C, bool AK, bool BKC, int EPI>
 static hipError_t launch_wide(const GemmParams &g, const SmallParams &p, hipStream_t s)
 {
@@ -29,7 +29,7 @@ static hipError_t direct_tile(int tile, const GemmParams &g, const SmallParams &
     if constexpr (AK && (EPI == EPI_LINEAR || EPI == EPI_SWIGLU_FWD))
         if (tile == DIRECT_64x64) return launch_direct<SmallCfg<64, 64, 2, 1, 4, F8>, AK, BKC, EPI, true>(g, p, s);
     if constexpr (AK && EPI == EPI_LINEAR) {
-        if (tile == DIRECT_32x256) return launch_wide<SmallCfg<32, 256, 1, 4, 4, F8>, AK, BKC, EPI>(g, p, s);
+        if (tile == DIRECT_32x256) return launch_direct<SmallCfg<32, 256, 1, 4, 4, F8>, AK, BKC, EPI, false>(g, p, s);
         if (tile == DIRECT_64x256) return launch_wide<SmallCfg<64, 256, 2, 4, 3, F8>, AK, BKC, EPI>(g, p, s);
     }
     if constexpr (EPI == EPI_ACCUM)

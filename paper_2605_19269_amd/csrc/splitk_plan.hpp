@@ -148,7 +148,7 @@ inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_c
 // row sums: 64x256 41.1, 128x256 46.0, before 67.8; 509 x 6144 x 2048: 128x128 22.6, 128x256 31.7, before 46.1; 509 x 16384 x
 // 2048: 128x256 34.8, 128x128 44.4, before 46.8; 257 x 22312 x 4096: 64x256 105, 128x256 120, 256 x 256 94, which keeps it, as it
 // does 1000 x 16384 x 2048 (128x256 66.8, 256 x 256 55.4).
-// A plan_small() with one range per tile gives way to these (`chains`: all but PAIR keep to its chain) where the model says so: 96 x 28672 x 4096 8-bit SwiGLU: 128x128
+// A plan_small() with one range per tile gives way to these (`chains`: all but PAIR and 32x256 keep to its chain) where the model says so: 96 x 28672 x 4096 8-bit SwiGLU: 128x128
 // 29.2, partials and second kernel 34.2.
 // The gradient program also reads and writes 8 bytes per element, two thirds of it (PAIR: half) beside the contraction of
 // other workgroups: 2048 x 11264 x 1000: PAIR 78, 256 x 256 85; 5976 x 2968 x 720: 52, 67; 5632 x 2048 x 2552: 72, 69 and 11008 x
@@ -183,19 +183,27 @@ inline DirectPlan plan_direct(int64_t M, int64_t N, int64_t K, bool f8, bool a_k
         const double hbm = (double)N * (double)K * (f8 ? 1.0 : 2.0) / rate;
         return us > hbm ? us : hbm;
     };
+    // 8-bit, several rounds of 256-wide tiles: past 16 stages 256 x 256 tiles are ahead by 5 to 20 % (384 x 58320 x 15968: 397,
+    // 128x256 486), below that up to as much behind (3598 x 5456 x 352: 45, 37)
+    auto crowded = [&](int64_t bm) { return f8 && tiles(bm, 256) > SPLITK_CUS && stages > 16.0; };
     if (few && !wide) offer(DIRECT_64x64, 4.0 + stream(stages * 0.34 * rounds(tiles(64, 64)), 4.6e6));
     if (few && prog == DIRECT_PROG_LINEAR) {
-        offer(DIRECT_32x256, 5.3 + stream(stages * 0.55 * rounds(tiles(32, 256)), 3.9e6));
-        offer(DIRECT_64x256, 5.5 + stages * 0.68 * rounds(tiles(64, 256)));
+        if (!chains) offer(DIRECT_32x256, 5.3 + stream(stages * 0.55 * rounds(tiles(32, 256)), 3.9e6));
+        if (!crowded(64)) offer(DIRECT_64x256, 5.5 + stages * 0.68 * rounds(tiles(64, 256)));
     }
-    if (!wide) offer(DIRECT_128x128, 4.5 + stream(stages * 0.57 * rounds(tiles(128, 128)), 5.6e6) + rmw);
-    if (prog == DIRECT_PROG_ACCUM && !chains) {
+    // every further round pays its fill and epilogue: 897 x 19712 x 200 SwiGLU, five rounds: 28.3, 256 x 256 26.6; 3426 x 2832 x 160
+    // 8-bit, three: 17.0, 14.8
+    if (!wide) offer(DIRECT_128x128, 2.5 + 2.0 * rounds(tiles(128, 128)) + stream(stages * 0.57 * rounds(tiles(128, 128)), 5.6e6) + rmw);
+    // bf16 contractions of a few stages that 256 x 256 tiles nearly fill one round with have nothing to run the updates under: 4096 x
+    // 4096 x 32 PAIR 29.2, 256 x 256 27.0; 2248 x 5912 x 96 26.8, 25.4
+    const bool bare = !f8 && big <= SPLITK_CUS && fill > 0.8 && stages < 4.0;
+    if (prog == DIRECT_PROG_ACCUM && !chains && !bare) {
         // rounds of two per CU; what is left over runs two or one per CU (1424 x 6304 x 12920: 600 tiles lose 30 % to 256 x 256)
         const int64_t t = tiles(128, 128), whole = t / (2 * SPLITK_CUS), left = t % (2 * SPLITK_CUS);
         const double rest = left == 0 ? 0.0 : (left <= SPLITK_CUS ? 0.66 : 1.08);
         offer(DIRECT_128x128_PAIR, 6.0 + stages * (1.08 * (double)whole + rest) + 0.55 * rmw);
     }
-    offer(DIRECT_128x256, (6.0 + stages * 0.88 * rounds(tiles(128, 256)) + rmw) * (prog == DIRECT_PROG_ACCUM ? 1.07 : 1.0));
+    if (!crowded(128)) offer(DIRECT_128x256, (6.0 + stages * 0.88 * rounds(tiles(128, 256)) + rmw) * (prog == DIRECT_PROG_ACCUM ? 1.07 : 1.0));
     return best;
 }
 

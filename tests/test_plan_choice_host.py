@@ -1,0 +1,37 @@
+"""Host checks of where the plan of the small tiles draws its lines: sizes at which both sides were timed on the GPU, with the faster one
+(microseconds, 256 x 256 tiles first)."""
+import pytest
+
+from tests import small_plan
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    return small_plan.load(tmp_path_factory.mktemp("small_plan"))
+
+
+# M, N, K, 8-bit, A transposed, B transposed, program, row reduction
+LARGE = [(4096, 4096, 32, False, True, False, "accum", False),              # 27.0, 29.2 two 128x128 a CU
+         (4096, 4096, 192, False, True, False, "accum", False),             # 30.0, 31.9
+         (2248, 5912, 96, False, True, False, "accum", False),              # 25.3, 26.8
+         (3426, 2832, 160, True, False, False, "linear", False),            # 14.7, 17.7 three rounds of 128x128
+         (292, 46864, 3920, True, False, True, "linear", True),             # 118.7, 137.7 three rounds of 128x256
+         (1915, 12816, 4752, True, False, False, "swiglu_fwd", False),      # 115.0, 133.5
+         (384, 58320, 15968, True, False, False, "swiglu_fwd", False)]      # 402, 480
+SMALL = [(897, 19712, 200, False, False, False, "swiglu_fwd", False, "128x256"),     # 26.6, 23.6 (128x128 28.2)
+         (32, 55056, 176, True, True, False, "accum", False, "128x128_PAIR"),        # 10.0, 8.3 (128x128 11.9)
+         (768, 8784, 96, False, False, True, "swiglu_fwd", False, "128x256"),        # 10.6, 7.7 (128x128 9.7)
+         (3598, 5456, 352, True, False, True, "linear", True, "128x256"),            # 44.8, 36.9
+         (6144, 4096, 96, False, True, False, "accum", False, "128x128_PAIR"),       # 46.4, 41.2
+         (2048, 8192, 128, True, True, False, "accum", False, "128x128_PAIR")]       # 33.5, 30.5
+
+
+@pytest.mark.parametrize("M,N,K,f8,ta,tb,prog,red", LARGE)
+def test_large_tiles_where_they_are_faster(lib, M, N, K, f8, ta, tb, prog, red):
+    assert small_plan.Route(lib, M, N, K, f8, not ta, tb, prog, red).kind == "whole"
+
+
+@pytest.mark.parametrize("M,N,K,f8,ta,tb,prog,red,tile", SMALL)
+def test_small_tiles_where_they_are_faster(lib, M, N, K, f8, ta, tb, prog, red, tile):
+    r = small_plan.Route(lib, M, N, K, f8, not ta, tb, prog, red)
+    assert (r.kind, r.tile) == ("direct", tile)
