@@ -1,7 +1,7 @@
 """The library only enqueues kernels on the caller's stream (no allocation, no synchronisation, no memset), so a
 sequence of its calls can be captured into a HIP graph.  Captured here: the tiny MLP chain (row statistics, up-projection
 with SwiGLU, down-projection with residual and row sums of squares, SwiGLU backward, fp32 weight-gradient accumulation) and
-a split-K launch whose ticket counters are re-zeroed by a kernel inside the captured sequence.  Every replay is compared
+a launch on divided small tiles (shared 256 x 256 tiles and their ticket counters: test_gpu_routes.py).  Every replay is compared
 bit for bit with the eager run of the same calls, with eager work and synchronisations between the replays."""
 import numpy as np
 import pytest
@@ -22,7 +22,7 @@ def test_captured_chain_replays_match_eager():
     Wdn, R = G.dev_bf16(synth.normal_bf16(g, (F, d), 0.05)), G.dev_bf16(synth.normal_bf16(g, (M, d), 1.0))
     dY = G.dev_bf16(synth.normal_bf16(g, (M, d), 1e-2))
     G0 = G.dev_f32(synth.normal_f32(g, (F, d), 1e-3))
-    # split-K case: 4 output tiles, long contraction
+    # divided contraction: 4 output tiles of 256 x 256, long K
     Ms, Ns, Ks = 512, 512, 4096
     As, Bs = G.dev_bf16(synth.normal_bf16(g, (Ms, Ks), 1.0)), G.dev_bf16(synth.normal_bf16(g, (Ks, Ns), 0.02))
     need = coda.coda_gemm_workspace_bytes(Ms, Ns, Ks, [])

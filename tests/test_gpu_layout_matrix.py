@@ -1,7 +1,8 @@
 """GPU parity, layout x epilogue matrix: every epilogue mode of coda_gemm is instantiated once per operand
 layout (A or A^T, B or B^T).  Each (layout, mode) pair is run on a shape of whole 256 x 256 x 64 tiles, on a shape
 ragged in every dimension (clamped fetches, zero-filled K tail, bounds-checked epilogue) and on a shape ragged
-in M and N only, against the CPU oracle."""
+in M and N only, against the CPU oracle.  At these sizes all but RMSNorm backward run on small tiles; the same matrix on 256 x 256
+tiles is in test_gpu_routes.py."""
 import numpy as np
 import pytest
 import torch

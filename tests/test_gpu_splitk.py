@@ -1,6 +1,9 @@
 """GPU parity of split-K: shapes with few output tiles and a long contraction, run with the workspace that lets
 several workgroups share a tile.  Results must match the oracle to the same bar as the unsplit kernels, must not
-depend on which workgroup finishes last (bitwise equal across repeats), and the workspace rules of the C ABI hold."""
+depend on which workgroup finishes last (bitwise equal across repeats), and the workspace rules of the C ABI hold.
+
+The plan sends shapes this small to divided small tiles, so that of the shared 256 x 256 tiles only test_splitk_last_round_only
+runs here; the sizes, programs and layouts that run on them are in test_gpu_routes.py, which asserts the kind of kernel."""
 import numpy as np
 import pytest
 import torch
@@ -38,7 +41,7 @@ def operands(g, M, N, K, transA, transB, a_std=1.0, b_std=0.05):
     return A, B
 
 
-# (M, N, K) -> parts: 4 tiles, K = 4096 -> 4;  1 tile, K = 8192 -> 8;  2 tiles, K = 3072 -> 3;
+# (M, N, K) -> parts of 256 x 256 tiles, which set the workspace's size: 4 tiles, K = 4096 -> 4;  1 tile, K = 8192 -> 8;  2 tiles, K = 3072 -> 3;
 # 1 tile, K = 6272 (196 K-steps of 32) -> 6 parts of 32 or 34 steps;
 # 2 x 2 tiles with a ragged edge in M and N, K = 4096 -> 4; the same with a ragged K = 4168 (132 K-steps) -> 4 parts of 32 or 34
 SHAPES = [(512, 512, 4096), (256, 256, 8192), (256, 512, 3072), (256, 256, 6272), (504, 264, 4096), (504, 264, 4168)]
@@ -215,10 +218,9 @@ def test_splitk_last_round_only(oracle, transB):
 
 @pytest.mark.parametrize("M,N,K,transA", [(2560, 1024, 8192, False), (2500, 1000, 8200, False), (2560, 1024, 8192, True)])
 def test_balanced_round_with_ranges_that_straddle_tiles(oracle, M, N, K, transA):
-    """40 output tiles with a long contraction: 8 parts each would need 320 workgroups, so the K-steps of all tiles, laid end
-    to end, are cut into 256 equal ranges; most ranges end in one tile and begin in the next (a workgroup then runs two
-    work items), and a tile is finished by whichever of its up to 8 contributors arrives last.  Whole and ragged shapes,
-    both A layouts; sampled rows of every tile row against the oracle, bitwise equal across repeats."""
+    """40 output tiles with a long contraction: 8 parts each would need 320 workgroups, so the workspace is that of 256 equal
+    ranges that straddle tiles.  Within it the plan runs divided 128 x 256 tiles (straddling ranges themselves: test_gpu_routes.py).
+    Whole and ragged shapes, both A layouts; sampled rows of every tile row against the oracle, bitwise equal across repeats."""
     g = np.random.Generator(np.random.PCG64(1200 + M + K + transA))
     A, B = operands(g, M, N, K, transA, False, b_std=0.02)
     C = synth.normal_bf16(g, (M, N), 1.0)

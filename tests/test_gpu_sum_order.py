@@ -27,7 +27,7 @@ def plans(tmp_path_factory):
 
 # M, N, K, f8, A transposed, B transposed, workspace, tiles of the programs.  In turn: tiles of different widths; few rows of A B^T, which
 # start by column, next to a 256 x 256 tile, bf16 and 8-bit; a whole shape of A B^T, which starts by XCD; ragged K; A^T B;
-# 8-bit on all tiles; one range, taken over by an undivided tile
+# 8-bit on all tiles; one range, taken over by an undivided tile; several ranges; ranges that straddle tiles
 CASES = [(300, 11008, 3000, False, False, False, False, {"64x256", "128x256", "256x256"}),
          (40, 2048, 1024, False, False, True, False, {"32x256", "64x64", "128x256", "128x128", "256x256"}),
          (40, 2048, 1024, True, False, True, False, {"32x256", "64x64", "128x256", "128x128", "256x256"}),
@@ -38,7 +38,7 @@ CASES = [(300, 11008, 3000, False, False, False, False, {"64x256", "128x256", "2
          (96, 28672, 4096, True, False, True, True, {"64x256", "128x128"}),
          (32, 28672, 4096, False, False, True, True, {"32x128", "128x128"}),
          (32, 28672, 4096, False, False, False, True, {"32x128", "128x128"}),
-         (809, 4096, 4096, False, False, False, True, {"128x256"})]
+         (809, 4096, 4096, False, False, False, True, {"128x256"}), (1168, 3248, 6160, False, False, True, True, {"256x256"}), (768, 5632, 12288, True, False, False, True, {"256x256"})]
 
 
 @pytest.mark.parametrize("M,N,K,f8,ta,tb,ws,tiles", CASES)
@@ -46,7 +46,7 @@ def test_every_program_has_the_same_d(plans, M, N, K, f8, ta, tb, ws, tiles):
     progs = [("linear", False), ("linear", True), ("swiglu_fwd", False), ("swiglu_bwd", False), ("swiglu_bwd", True), ("accum", False), ("rmsnorm_bwd", False)]
     routes = [small_plan.Route(plans, M, N, K, f8, not ta, tb, prog, wide, ws) for prog, wide in progs]
     assert {r.tile for r in routes} == tiles
-    assert len({r.kind for r in routes}) > 1 or len({r.ranges for r in routes}) == 1 < routes[0].ranges
+    assert len({r.kind for r in routes}) > 1 or routes[0].ranges > 1 or routes[0].kind == "shared"
     g = torch.Generator(device="cuda").manual_seed(M + N + K)
     draw = lambda shape, std: torch.randn(shape, device="cuda", generator=g) * std
     A, B = draw((K, M) if ta else (M, K), 1.0), draw((N, K) if tb else (K, N), 1.0 if f8 else 0.05)

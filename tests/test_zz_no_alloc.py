@@ -1,6 +1,7 @@
 """The entry point that allocates nothing (coda_gemm_static_ws: split-K through the library's static device array) against
 coda_gemm with a caller workspace: same results bit for bit, on two calls in a row, the second with a smaller input, so
-that whatever the first call left in the array (partials, counters) must not leak into the second."""
+that whatever the first call left in the array (partials) must not leak into the second.  These sizes run on divided small tiles;
+shared 256 x 256 tiles and their ticket counters in the array: test_gpu_routes.py."""
 import numpy as np
 import pytest
 import torch
@@ -49,7 +50,7 @@ def _run_pair(coda, oracle, M, N, K, seed, first_call_on_this_gpu=False):
 def test_static_scratch_matches_workspace_on_two_calls_in_a_row(oracle):
     assert torch.cuda.is_available(), "this test needs the MI355X"
     from paper_2605_19269_amd import coda
-    _run_pair(coda, oracle, 1024, 1024, 4096, seed=4100, first_call_on_this_gpu=True)   # 16 tiles in 4 parts: 16 MiB of partials, 16 counters
+    _run_pair(coda, oracle, 1024, 1024, 4096, seed=4100, first_call_on_this_gpu=True)   # planned as 16 tiles in 4 parts: 16 MiB
     _run_pair(coda, oracle, 504, 264, 4168, seed=4101)     # smaller, ragged in M, N and K: 4 tiles in 3 parts
     torch.cuda.synchronize()
 
