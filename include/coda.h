@@ -186,8 +186,9 @@ typedef struct coda_epi_op {
  * divisibility is required (edge tiles are predicated).
  *
  * Reproducibility: the order of the fp32 additions behind an element of D depends only on the shapes, operand type, layouts,
- * on whether a workspace is given and on the element's position, never on the program or on timing; with CODA_REDUCE_PARTIALS every output of a call is bitwise identical from call
- * to call (CODA_REDUCE_ATOMIC sums may differ in their last bits).
+ * on whether a workspace is given and on the element's position, never on the program or on timing; with
+ * CODA_REDUCE_PARTIALS every output of a call is bitwise identical from call to call (CODA_REDUCE_ATOMIC sums may differ in
+ * their last bits).
  *
  * 8-bit operands: A and B may both be CODA_F8E4M3 (ld in elements = bytes, a multiple of 16), in any of the four
  * trans combinations: forward weights kept [in x out], the backward form A B^T and the weight-gradient form A^T B
@@ -204,8 +205,10 @@ typedef struct coda_epi_op {
  * and the contraction is long enough (K >= 2048, and every workgroup must be spared at least 64 K-steps of 32 elements),
  * coda_gemm_workspace_bytes returns a non-zero size, and a call that brings that much workspace divides the tail in one of
  * two ways, chosen from the sizes, operand type and layouts alone:
- *   - few tiles or few rows: tiles of 32, 64 or 128 rows x 128 columns, each cut along K into equal ranges, one workgroup
- *     each; the fp32 partials go to the workspace and a second kernel adds them up in range order and runs the program;
+ *   - few tiles or few rows: tiles of 32, 64 or 128 rows x 128 columns or 128 x 256, each cut along K into equal ranges, one
+ *     workgroup each; the fp32 partials go to the workspace and a second kernel adds them up in range order and runs the
+ *     program.  Where there is a tile for most of the chip the plan makes one range of it; a program may then run in one
+ *     kernel that leaves the workspace alone, with the same sums (long ranges fold their accumulators either way);
  *   - otherwise the K-steps of the tail, laid end to end, are cut into up to 256 equal contiguous ranges, one or two
  *     workgroups each (a range may end in one tile and begin in the next): partial tiles go to the workspace in fp32, and
  *     the workgroup that reaches a tile last adds its parts up in a fixed order (the result does not depend on arrival
