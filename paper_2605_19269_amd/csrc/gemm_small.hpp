@@ -221,9 +221,10 @@ __device__ __forceinline__ void small_contract(SmallAcc<C> &acc, const SmallPara
             if (i >= q * NB / Q && i < (q + 1) * NB / Q) fa[i] = small_frag<C, AK, C::BM>(ta, wm * C::WTM + i * C::FR, lane, h);
     };
     // One MFMA step on f*, a row of blocks at a time (8-bit: block by block, those take twice as long).  `beside(i, n)` issues part i
-    // of n of the loads and fragment reads of the next step: behind row i where two waves share a SIMD in step, so that the matrix pipe starts at once after a barrier and works while they
-    // are issued in its shadow (128x256: 509 x 16384 x 2048 37.5 -> 34.7 us); ahead of the rows where a wave has its SIMD to
-    // itself or shares it with another workgroup's (1 x 6144 x 2048 at 64x64: 12.8 us against 13.5).
+    // of n of the loads and fragment reads of the next step: behind row i where two waves share a SIMD in step, so that the
+    // matrix pipe starts at once after a barrier and works while they are issued in its shadow (128x256: 509 x 16384 x 2048
+    // 37.5 -> 34.7 us); ahead of the rows where a wave has its SIMD to itself or shares it with another workgroup's (1 x 6144 x
+    // 2048 at 64x64: 12.8 us against 13.5).
     auto mma = [&](const SmallFrag<C>(&fa)[NB], const SmallFrag<C>(&fb)[NU], auto beside) {
         if (C::NW < 8) {
 #pragma unroll
@@ -261,7 +262,8 @@ __device__ __forceinline__ void small_contract(SmallAcc<C> &acc, const SmallPara
     };
     // Chains: the accumulators are added to `sum` and start again from zero every p.chain stages, so that a range that is longer
     // than the ones the shape had on shared 256 x 256 tiles is no less accurate (509 x 2048 x 8192 in four ranges against 64 bits:
-    // 2.7e-7 in one chain each, 1.9e-7 in two, as in eight ranges).  Not in launches that nothing divides (2 to 3 % at 128x256).
+    // 2.7e-7 in one chain each, 1.9e-7 in two, as in eight ranges).  Not in launches that nothing divides (2 to 3 % at
+    // 128x256; 8-bit 1 %).
     Block sum[CHAINS ? NB : 1][CHAINS ? NU : 1];
     int chain = p.chain;
     if constexpr (CHAINS) {

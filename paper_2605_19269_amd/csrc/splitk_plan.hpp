@@ -148,8 +148,8 @@ inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_c
 // row sums: 64x256 41.1, 128x256 46.0, before 67.8; 509 x 6144 x 2048: 128x128 22.6, 128x256 31.7, before 46.1; 509 x 16384 x
 // 2048: 128x256 34.8, 128x128 44.4, before 46.8; 257 x 22312 x 4096: 64x256 105, 128x256 120, 256 x 256 94, which keeps it, as it
 // does 1000 x 16384 x 2048 (128x256 66.8, 256 x 256 55.4).
-// A plan_small() with one range per tile gives way to these (`chains`: all but PAIR and 32x256 keep to its chain) where the model says so: 96 x 28672 x 4096 8-bit SwiGLU: 128x128
-// 29.2, partials and second kernel 34.2.
+// A plan_small() with one range per tile gives way to these where the model says so, see plan_route; `chains`: those that keep to
+// its chain, all but PAIR and 32x256.
 // The gradient program also reads and writes 8 bytes per element, two thirds of it (PAIR: half) beside the contraction of
 // other workgroups: 2048 x 11264 x 1000: PAIR 78, 256 x 256 85; 5976 x 2968 x 720: 52, 67; 5632 x 2048 x 2552: 72, 69 and 11008 x
 // 4096 x 1000: 129, 126, which stay.
@@ -214,8 +214,8 @@ inline DirectPlan plan_direct(int64_t M, int64_t N, int64_t K, bool f8, bool a_k
 //   shared: the ranges of `shared`;
 //   divided: the ranges of `small`, folded every `chain` stages, started at the stage of rot_cols.
 // The program chooses only between tiles of one order: an undivided tile takes the place of a division into one range, with
-// that range's chain and starting stages (96 x 28672 x 4096 8-bit SwiGLU: 29 us against 34 with partials and a second kernel).
-// It does not take the place of more ranges, where it would be 5 to 20 % ahead for a program without row reductions (809 x
+// that range's chain and starting stages (96 x 28672 x 4096 8-bit SwiGLU: 27 us; partials of 11 MB to write, read and run a second
+// kernel on are 5 more).  It does not take the place of more ranges, where it would be 5 to 20 % ahead for a program without row reductions (809 x
 // 4096 x 4096: 37 us against 44, 512 x 6144 x 4096 A^T B SwiGLU 40, 43) and behind for one with.
 enum RouteKind : int { ROUTE_WHOLE = 0, ROUTE_SHARED, ROUTE_DIVIDED, ROUTE_DIRECT };
 struct Route {
