@@ -34,7 +34,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
 # registers, and the compiler then keeps the accumulators in the upper half and copies them around every MFMA.
 FLAGS_SMALL = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
 
-SOURCES = ["coda_api.hip", "aux_kernels.hip", "gemm_small_inst.hip",
+SOURCES = ["coda_api.hip", "aux_kernels.hip", "gemm_small_inst.hip", "gemm_narrow_inst.hip",
            "gemm_direct_inst_nn.hip", "gemm_direct_inst_nt.hip", "gemm_direct_inst_tn.hip", "gemm_direct_inst_tt.hip",
            "gemm_direct_inst_f8_nn.hip", "gemm_direct_inst_f8_nt.hip", "gemm_direct_inst_f8_tn.hip", "gemm_direct_inst_f8_tt.hip",
            "gemm_inst_nn.hip", "gemm_inst_nt.hip", "gemm_inst_tn.hip", "gemm_inst_tt.hip",

@@ -5,6 +5,7 @@
 
 #include "aux_kernels.hpp"
 #include "gemm_launch.hpp"
+#include "narrow_launch.hpp"
 #include "small_launch.hpp"
 #include "splitk_plan.hpp"
 
@@ -324,6 +325,7 @@ coda_status gemm_impl(void *stream, int64_t M, int64_t N, int64_t K, const coda_
         return launch_status(coda::launch_gemm_small(route.small, ps.mode, f8, ak, bkc, p, route.chain, static_cast<float *>(workspace), s));
     if (route.kind == coda::ROUTE_DIRECT)
         return launch_status(coda::launch_gemm_direct(route.tile, ps.mode, f8, ak, bkc, p, route.chain, route.rot_cols, s));
+    if (route.narrow) return launch_status(coda::launch_gemm_narrow(ps.mode, p, s));
     if (route.kind == coda::ROUTE_WHOLE) p.rot_cols = route.rot_cols > 0 ? route.rot_cols : 0;
     if (route.kind == coda::ROUTE_SHARED) {
         const coda::SplitPlan &pl = route.shared;

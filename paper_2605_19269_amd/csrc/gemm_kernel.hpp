@@ -91,10 +91,18 @@ struct GemmParams {
 // The transposing read serves 32 lanes per LDS cycle: four k-rows (k & 3) of two adjacent granules.
 // XOR-ing the granule with 2*(k & 3) sends those eight 32-byte pieces to eight different bank groups.
 __device__ __forceinline__ int mn_swz(int k) { return ((k & 3) << 1) | ((k >> 3) & 1); }
+// ROWS = 192: twelve granules, in which only the lower two bits can be XOR-ed.  Consecutive k-rows lie 384 bytes apart, so k & 1 is
+// half the banks by itself and k & 2 takes the granule bit.
+template <int ROWS>
+__device__ __forceinline__ int mn_swz_of(int k)
+{
+    static_assert(ROWS == 192 || (ROWS & (ROWS - 1)) == 0, "granules of a k-row");
+    return ROWS == 192 ? (k & 2) | ((k >> 3) & 1) : mn_swz(k) & (ROWS / 16 - 1);
+}
 template <int ROWS>
 __device__ __forceinline__ uint32_t lds_mn(int k, int gr)
 {
-    return (uint32_t)(k * (ROWS * 2) + (((gr ^ mn_swz(k)) & (ROWS / 16 - 1)) << 5));
+    return (uint32_t)(k * (ROWS * 2) + ((gr ^ mn_swz_of<ROWS>(k)) << 5));
 }
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b)
@@ -155,7 +163,7 @@ struct TileCfg {
     static constexpr int FM = WTM / 32, FN = WTN / 32;
     static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
     static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
-    static_assert(BM % (WGM * 32) == 0 && BN % (WGN * 32) == 0, "wave tiles are multiples of 32");
+    static_assert(BM % (WGM * 32) == 0 && BN % (WGN * 16) == 0, "wave tiles are whole MFMA blocks");
     static_assert(BM >= 128 && BN >= 128, "granule swizzle needs >= 8 granules per k-row");
 };
 
@@ -398,6 +406,9 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
     constexpr int BM = C::BM, WTM = C::WTM, WTN = C::WTN;
     constexpr int LR = ACC::LR, LQ = ACC::LQ, NB = ACC::NB, NU = ACC::NU, UC = 4 * LQ;   // UC: column step between units
     constexpr int REG = RING / (C::WGM * C::WGN);   // private staging bytes per wave
+    // wave tiles of 48 columns are staged in rows of 64, whose last chunks are neither fetched nor stored
+    constexpr int WTP = WTN == 48 ? 64 : WTN;
+    constexpr bool BOUNDS = EDGE || WTP != WTN;
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave % C::WGM, wn = wave / C::WGM;
     const int lrow = lane % LR, lcol = (lane / LR) * 4;           // the lane's row in a block, first column in a unit step
@@ -618,7 +629,7 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
         }
     } else if constexpr (EPI == EPI_SWIGLU_FWD) {
         // ---- row scale, pairwise SwiGLU (width halves), optional pre-activation side output
-        constexpr int RBH = WTN, RBZ = WTN * 2;
+        constexpr int RBH = WTP, RBZ = WTP * 2;
         constexpr int P = pass_rows(REG, RBZ, WTM), FPP = P / LR;
         static_assert(P % LR == 0 && WTM % P == 0, "staging pass");
         uint16_t *outp = reinterpret_cast<uint16_t *>(p.out);
@@ -643,7 +654,7 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
             stage_fence();
             // ordinary stores: a wave's H rows are 64-byte halves of 128-byte lines, which L2 merges with the neighbouring
             // wave's halves; with the streaming hint the L2 -> fabric write counter reads 10 % above the output bytes
-            stage_store<RBH, P, EDGE, false>(reg, reinterpret_cast<unsigned char *>(outp + (int64_t)(mw + r0) * p.ld_out + (nw >> 1)),
+            stage_store<RBH, P, BOUNDS, false>(reg, reinterpret_cast<unsigned char *>(outp + (int64_t)(mw + r0) * p.ld_out + (nw >> 1)),
                                       p.ld_out * 2, rows_ok - r0, cols_ok, lane);
             if (p.out2) {
                 stage_fence();
@@ -659,7 +670,7 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
                     }
                 }
                 stage_fence();
-                stage_store<RBZ, P, EDGE>(reg, reinterpret_cast<unsigned char *>(p.out2 + (int64_t)(mw + r0) * p.ld_out2 + nw),
+                stage_store<RBZ, P, BOUNDS, WTP == WTN>(reg, reinterpret_cast<unsigned char *>(p.out2 + (int64_t)(mw + r0) * p.ld_out2 + nw),
                                           p.ld_out2 * 2, rows_ok - r0, cols_ok * 2, lane);
             }
             stage_fence();
@@ -667,19 +678,19 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
     } else if constexpr (EPI == EPI_SWIGLU_BWD) {
         // ---- pairwise SwiGLU backward (width doubles): Z in and dZ out staged; row statistic; the optional
         // recomputed activation silu(g)*u is a second sweep over 32-row passes that re-reads Z.
-        constexpr int RB = WTN * 4, RBO = WTN * 2, P = 32, FPP = P / LR, NP = WTM / P;
+        constexpr int RB = WTP * 4, RBO = WTP * 2, P = 32, FPP = P / LR, NP = WTM / P;
         static_assert(P * (RB + RBO) <= REG && WTM % P == 0, "staging pass");
         uint16_t *outp = reinterpret_cast<uint16_t *>(p.out);
         const uint32_t ulane = Stage<RB>::template unit_lane<16, LR>(lane), ulane_o = Stage<RBO>::template unit_lane<8, LR>(lane);
         // 32-row passes; the Z rows of the next pass are fetched into registers while this pass is computed and stored
         u32x4 zt[P / Stage<RB>::RPI];
         auto zrows = [&](int ps) { return reinterpret_cast<const unsigned char *>(p.Z + (int64_t)(mw + ps * P) * p.ldz + 2 * nw); };
-        stage_fetch<RB, P, EDGE, true>(zt, zrows(0), p.ldz * 2, rows_ok, cols_ok * 4, lane);
+        stage_fetch<RB, P, BOUNDS, true>(zt, zrows(0), p.ldz * 2, rows_ok, cols_ok * 4, lane);
 #pragma unroll
         for (int ps = 0; ps < NP; ++ps) {
             stage_put<RB, P>(reg, zt, lane);
             stage_fence();
-            if (ps + 1 < NP) stage_fetch<RB, P, EDGE, true>(zt, zrows(ps + 1), p.ldz * 2, rows_ok - (ps + 1) * P, cols_ok * 4, lane);
+            if (ps + 1 < NP) stage_fetch<RB, P, BOUNDS, true>(zt, zrows(ps + 1), p.ldz * 2, rows_ok - (ps + 1) * P, cols_ok * 4, lane);
             stage_fence();
 #pragma unroll
             for (int fi = 0; fi < FPP; ++fi) {
@@ -707,7 +718,7 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
                 }
             }
             stage_fence();
-            stage_store<RB, P, EDGE, false>(reg, reinterpret_cast<unsigned char *>(outp + (int64_t)(mw + ps * P) * p.ld_out + 2 * nw), p.ld_out * 2,
+            stage_store<RB, P, BOUNDS, false>(reg, reinterpret_cast<unsigned char *>(outp + (int64_t)(mw + ps * P) * p.ld_out + 2 * nw), p.ld_out * 2,
                                      rows_ok - ps * P, cols_ok * 4, lane);
             stage_fence();
         }
@@ -716,7 +727,7 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
 #pragma unroll
             for (int ps = 0; ps < NP; ++ps) {
                 const int r0 = ps * P;
-                stage_load<RB, P, EDGE>(reg, reinterpret_cast<const unsigned char *>(p.Z + (int64_t)(mw + r0) * p.ldz + 2 * nw),
+                stage_load<RB, P, BOUNDS>(reg, reinterpret_cast<const unsigned char *>(p.Z + (int64_t)(mw + r0) * p.ldz + 2 * nw),
                                         p.ldz * 2, rows_ok - r0, cols_ok * 4, lane);
                 stage_fence();
 #pragma unroll
@@ -734,21 +745,22 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
                             u32x2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
                     }
                 stage_fence();
-                stage_store<RBO, P, EDGE, false>(rego, reinterpret_cast<unsigned char *>(p.out2 + (int64_t)(mw + r0) * p.ld_out2 + nw),
+                stage_store<RBO, P, BOUNDS, false>(rego, reinterpret_cast<unsigned char *>(p.out2 + (int64_t)(mw + r0) * p.ld_out2 + nw),
                                           p.ld_out2 * 2, rows_ok - r0, cols_ok * 2, lane);
                 stage_fence();
             }
         }
-    } else if (EPI == EPI_LINEAR && !p.out_f32 && p.rope_cos && WTN == 64 && (p.rope_half & 31) == 0) {
+    } else if (EPI == EPI_LINEAR && !p.out_f32 && p.rope_cos && (WTN == 48 || (WTN == 64 && (p.rope_half & 31) == 0))) {
         // ---- row scale, RoPE, bf16 store with the cos / sin rows staged like tiles: per 32-row pass the wave gathers
         // each token's 32 table entries (128 bytes of cos, 128 of sin; the wave's 64 columns are 32 consecutive pairs
         // inside one head because head_dim/2 is a multiple of 32) with row-contiguous 16-byte loads into its region,
-        // so the per-unit table reads come from LDS instead of 8-byte gathers from 32 different rows.
+        // so the per-unit table reads come from LDS instead of 8-byte gathers from 32 different rows.  48 columns are 24
+        // pairs, which may reach into the next head; head_dim/2 is a multiple of 4, so a load of four entries does not.
         constexpr int RB = 128, P = 32, FPP = P / LR, NP = WTM / P;
         using St = Stage<RB>;
         const uint32_t ulane = St::template unit_lane<8, LR>(lane);
         const uint32_t rlane = St::row_lane(lane);
-        const int f0 = (nw >> 1) % p.rope_half;                        // first frequency index of this wave's columns
+        const int f0 = ((nw >> 1) + (lane & 7) * 4) % p.rope_half;     // first frequency index of this lane's four
         float rsv[NB];
         fetch_row_scales(rsv);
         unsigned char *rcos = reg + P * RB, *rsin = reg + 2 * P * RB;
@@ -756,10 +768,10 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
         u32x4 tc[4], ts[4];
         auto gather = [&](int ps) {                                    // table slices of 32-row pass ps -> registers
             const int m = mw + ps * P + (lane & 31);
-            const int trow = (!EDGE || m < p.M) ? clampi(p.rope_pos[m], 0, p.rope_T - 1) * p.rope_half + f0 : f0;
+            const int trow = (!EDGE || m < p.M) ? clampi(p.rope_pos[m], 0, p.rope_T - 1) * p.rope_half : 0;
 #pragma unroll
             for (int it = 0; it < 4; ++it) {                           // 8 rows x 128 bytes per access
-                const int src = __shfl(trow, it * 8 + (lane >> 3), 64) + (lane & 7) * 4;
+                const int src = __shfl(trow, it * 8 + (lane >> 3), 64) + f0;
                 tc[it] = *reinterpret_cast<const u32x4 *>(p.rope_cos + src);
                 ts[it] = *reinterpret_cast<const u32x4 *>(p.rope_sin + src);
             }
@@ -794,7 +806,7 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
                 }
             }
             stage_fence();
-            stage_store<RB, P, EDGE>(reg, reinterpret_cast<unsigned char *>(outp + (int64_t)(mw + ps * P) * p.ld_out + nw), p.ld_out * 2,
+            stage_store<RB, P, BOUNDS, WTP == WTN>(reg, reinterpret_cast<unsigned char *>(outp + (int64_t)(mw + ps * P) * p.ld_out + nw), p.ld_out * 2,
                                      rows_ok - ps * P, cols_ok * 2, lane);
             stage_fence();
         }
@@ -802,7 +814,7 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
         // ---- row scale, residual add, row sum of squares, bf16 store: all tile I/O staged.  The gamma-scaled side
         // output (when requested) is a second sweep that re-reads the residual and recomputes the value, so that
         // nothing has to stay in registers between the two stores.
-        constexpr int RB = WTN * 2, P = pass_rows(REG, RB, WTM), FPP = P / LR;
+        constexpr int RB = WTP * 2, P = pass_rows(REG, RB, WTM), FPP = P / LR;
         static_assert(P % LR == 0 && WTM % P == 0, "staging pass");
         const uint32_t ulane = Stage<RB>::template unit_lane<8, LR>(lane);
         const int sweeps = p.side ? 2 : 1;
@@ -815,7 +827,7 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
             for (int ps = 0; ps < WTM / P; ++ps) {
                 const int r0 = ps * P;
                 if (p.add) {
-                    stage_load<RB, P, EDGE>(reg, reinterpret_cast<const unsigned char *>(p.add + (int64_t)(mw + r0) * p.ld_add + nw),
+                    stage_load<RB, P, BOUNDS>(reg, reinterpret_cast<const unsigned char *>(p.add + (int64_t)(mw + r0) * p.ld_add + nw),
                                             p.ld_add * 2, rows_ok - r0, cols_ok * 2, lane);
                     stage_fence();
                 }
@@ -862,7 +874,7 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
                     }
                 }
                 stage_fence();
-                stage_store<RB, P, EDGE>(reg, reinterpret_cast<unsigned char *>(dst + (int64_t)(mw + r0) * ldd + nw), ldd * 2,
+                stage_store<RB, P, BOUNDS, WTP == WTN>(reg, reinterpret_cast<unsigned char *>(dst + (int64_t)(mw + r0) * ldd + nw), ldd * 2,
                                          rows_ok - r0, cols_ok * 2, lane);
                 stage_fence();
             }
@@ -989,7 +1001,9 @@ struct DlCfg : TileCfg<BM_, BN_, 32, WGM_, WGN_> {
     static constexpr int WPE = WPE_;   // waves per SIMD the kernel is compiled for (register budget 512 / WPE)
     static constexpr int NW = WGM_ * WGN_;
     static constexpr int LA = Base::A_BYTES / 1024 / NW, LB = Base::B_BYTES / 1024 / NW;  // wave-loads per wave
-    static_assert(Base::A_BYTES % (1024 * NW) == 0 && Base::B_BYTES % (1024 * NW) == 0, "whole wave-loads");
+    // 192 columns: the waves share the wave-loads of a pair of K-steps of B evenly, those of one K-step not
+    static constexpr bool BPAIR = Base::B_BYTES % (1024 * NW) != 0;
+    static_assert(Base::A_BYTES % (1024 * NW) == 0 && 2 * Base::B_BYTES % (1024 * NW) == 0, "whole wave-loads");
     static_assert(STAGES >= 3 && STAGES * Base::STAGE_BYTES <= 160 * 1024, "LDS ring");
 };
 
@@ -1015,7 +1029,7 @@ __device__ __forceinline__ uint32_t dl_goffset(int j, int lane, int64_t ld, int 
         constexpr int CPR = ROWS / 8;  // chunks per k-row
         const int idx = j * 64 + lane;
         const int k = idx / CPR, pc = idx % CPR;
-        const int g = (pc >> 1) ^ mn_swz(k);
+        const int g = (pc >> 1) ^ mn_swz_of<ROWS>(k);
         const int col = (g * 2 + (pc & 1)) * 8;
         const int cg = col < valid ? col : valid - 8;
         return (uint32_t)(((int64_t)k * ld + cg) * 2);
@@ -1281,14 +1295,15 @@ __device__ __forceinline__ bf16x8 dl_frag16(const unsigned char *tile, int row_b
 // bounds-checked epilogue; K is rounded up to whole pairs of K-steps and the tile fill stores zeros at the positions
 // past K.
 // LDS plan of the bf16 kernel.  PAIRED (A K-contiguous): three pair slots of A (two K-steps each) followed by four
-// single-step slots of B -- or, when B is K-contiguous as well (PAIRB), by two pair slots of B -- 160 KB; otherwise four
-// slots of [A | B].  The epilogue stages through the first EPI_RING bytes either way; `red` (row-reduction exchange;
+// single-step slots of B -- or, when B is K-contiguous as well (PAIRB) or 192 columns wide, by two pair slots of B -- 160 KB
+// (144 KB); otherwise four slots of [A | B].  The epilogue stages through the first EPI_RING bytes either way; `red` (row-reduction exchange;
 // second half: sum-exp of the log-sum-exp partials) follows them and, when PAIRED, lies inside the B slots, which are
 // free once the mainloop is over.
 template <class C, bool AK, bool BKC>
 struct DlLds {
-    static constexpr bool PAIRED = AK, PAIRB = AK && BKC;
+    static constexpr bool PAIRED = AK, PAIRB = AK && BKC, BP = PAIRB || C::BPAIR;   // BP: B is fetched in pairs
     static constexpr int S = C::STAGES;
+    static_assert(!C::BPAIR || (AK && !BKC), "narrow tiles: A B");
     static constexpr int EPI_RING = S * C::STAGE_BYTES, RED_BYTES = 2 * C::WGN * C::BM * 4;
     static constexpr int A_REGION = PAIRED ? 3 * 2 * C::A_BYTES : 0;
     static constexpr int LDS_BYTES = PAIRED ? A_REGION + S * C::B_BYTES : EPI_RING + RED_BYTES;
@@ -1306,7 +1321,7 @@ __device__ __forceinline__ void gemm_item_dl(const GemmParams &p, const WorkItem
     constexpr int LA = C::LA, LB = C::LB;
     static_assert(NI % 2 == 0, "two row halves");
     using L = DlLds<C, AK, BKC>;
-    constexpr bool PAIRED = L::PAIRED, PAIRB = L::PAIRB;
+    constexpr bool PAIRED = L::PAIRED, PAIRB = L::PAIRB, BP = L::BP;
     constexpr int EPI_RING = L::EPI_RING, A_REGION = L::A_REGION;
     float *red = reinterpret_cast<float *>(smem + EPI_RING);
 
@@ -1327,8 +1342,8 @@ __device__ __forceinline__ void gemm_item_dl(const GemmParams &p, const WorkItem
     const int valid_n = RAGGED ? (p.N - n0 < BN ? p.N - n0 : BN) : BN;
     // A: LA wave-loads per wave and K-step, or (PAIRED) LAP per wave and pair of K-steps
     constexpr int LAP = 2 * LA;
-    constexpr int LBP = 2 * LB;
-    uint32_t offa[PAIRED ? LAP : LA], offb[PAIRB ? LBP : LB];
+    constexpr int LBP = 2 * C::B_BYTES / 1024 / C::NW;
+    uint32_t offa[PAIRED ? LAP : LA], offb[BP ? LBP : LB];
     if (PAIRED) {
 #pragma unroll
         for (int i = 0; i < LAP; ++i) offa[i] = dl_goffset_pair<C, BM>(wave * LAP + i, lane, p.lda, valid_m);
@@ -1341,7 +1356,7 @@ __device__ __forceinline__ void gemm_item_dl(const GemmParams &p, const WorkItem
         for (int i = 0; i < LBP; ++i) offb[i] = dl_goffset_pair<C, BN>(wave * LBP + i, lane, p.ldb, valid_n);
     } else {
 #pragma unroll
-        for (int i = 0; i < LB; ++i) offb[i] = dl_goffset<C, BN, BKC>(wave * LB + i, lane, p.ldb, valid_n);
+        for (int i = 0; i < (BP ? LBP : LB); ++i) offb[i] = dl_goffset<C, BN, BKC>(wave * (BP ? LBP : LB) + i, lane, p.ldb, valid_n);
     }
     // scalar bases of the tile's first element; advance by one K-step per tile
     const int64_t stepa = AK ? (int64_t)BK * 2 : (int64_t)BK * p.lda * 2;
@@ -1369,9 +1384,11 @@ __device__ __forceinline__ void gemm_item_dl(const GemmParams &p, const WorkItem
     // LDS byte offsets of the slot that holds K-step t of A (PAIRED: the pair that contains t) and of B
     auto a_slot = [&](int t) { return PAIRED ? ((t >> 1) % 3) * (2 * C::A_BYTES) : (t % S) * C::STAGE_BYTES; };
     auto b_slot = [&](int t) {
-        return PAIRB ? A_REGION + ((t >> 1) & 1) * (2 * C::B_BYTES)
-                     : (PAIRED ? A_REGION + (t % S) * C::B_BYTES : (t % S) * C::STAGE_BYTES + C::A_BYTES);
+        return BP ? A_REGION + ((t >> 1) & 1) * (2 * C::B_BYTES)
+                  : (PAIRED ? A_REGION + (t % S) * C::B_BYTES : (t % S) * C::STAGE_BYTES + C::A_BYTES);
     };
+    // K-step t inside its pair slot: the second half of the k-rows, or (PAIRB) of every row
+    auto b_tile = [&](int t) { return b_slot(t) + (BP && !PAIRB ? (t & 1) * C::B_BYTES : 0); };
     // loads of A for K-step t (PAIRED: for K-steps t and t + 1, t even).  A K-step (pair) that reaches past K: a lane whose
     // chunk lies past K stores zeros at its LDS position instead of fetching.
     // PAIRED: `part` 0 / 1 issues the first / second half of the wave's loads of the pair, so that every K-step issues the
@@ -1398,9 +1415,9 @@ __device__ __forceinline__ void gemm_item_dl(const GemmParams &p, const WorkItem
         for (int i = 0; i < L; ++i)
             if (i >= i0 && i < i1) dl_load16(offa[i], sa, lds0 + (uint32_t)(slot + (wave * L + i) * 1024));
     };
-    // B of K-step t (PAIRB: of the pair t, t + 1, t even)
+    // B of K-step t (BP: of the pair t, t + 1, t even)
     auto issue_b = [&](int t, bool inside = false) {
-        constexpr int L = PAIRB ? LBP : LB, SPAN = PAIRB ? 2 : 1;
+        constexpr int L = BP ? LBP : LB, SPAN = BP ? 2 : 1;
         const int slot = b_slot(t);
         const unsigned char *sb = gb + (int64_t)rotated(t) * stepb;
         if (RAGGED && !inside && (kbeg + t + SPAN) * BK > p.K) {
@@ -1476,7 +1493,7 @@ __device__ __forceinline__ void gemm_item_dl(const GemmParams &p, const WorkItem
         }
     };
     auto prep_b = [&](uint32_t(&x)[NAB], int t, int par) {
-        uint32_t so = (uint32_t)b_slot(t);
+        uint32_t so = (uint32_t)b_tile(t);
         asm volatile("" : "+s"(so));
 #pragma unroll
         for (int j = 0; j < NAB; ++j) {
@@ -1508,7 +1525,7 @@ __device__ __forceinline__ void gemm_item_dl(const GemmParams &p, const WorkItem
                               BKC ? x[0] + (uint32_t)(j * 16 * (PAIRB ? 128 : 64)) : x[BKC ? 0 : j]);
     };
     auto read_b = [&](bf16x8(&fb)[NJ], int t) {
-        const unsigned char *sb = smem + b_slot(t);
+        const unsigned char *sb = smem + b_tile(t);
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
             const int col = wn * C::WTN + j * 16;
@@ -1545,7 +1562,7 @@ __device__ __forceinline__ void gemm_item_dl(const GemmParams &p, const WorkItem
     auto step = [&](int kt, const bf16x8(&fbc)[NJ], bf16x8(&fbn)[NJ], bool last, bool steady, bool even) {
         const bool refill = steady || kt + S - 1 < KT;
         bool exact;
-        if (PAIRB) {
+        if (BP) {
             // B's pair kt+3, kt+4 is issued in odd steps only, in memory phase 2: its slot held the pair that ended with
             // K-step kt, read for the last time in memory phase 2 of step kt-1.  Two loads per step before the waits;
             // even steps need no wait at all (both operands of kt+1 are in the pairs already in use)
@@ -1567,7 +1584,7 @@ __device__ __forceinline__ void gemm_item_dl(const GemmParams &p, const WorkItem
         load_a(fah, xah);                                                // memory phase 1 (behind the loads issued above)
         if (!last) {
             // K-step kt+1 must have landed before anybody's memory phase 2, the loads of kt+2 and kt+3 may be in flight
-            if (PAIRB) {
+            if (BP) {
                 if (!even) {
                     if (exact) {
                         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LA) : "memory");   // the two halves of A's newest pair
@@ -1592,7 +1609,7 @@ __device__ __forceinline__ void gemm_item_dl(const GemmParams &p, const WorkItem
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         phase_barrier();
         if (!last) {                                                     // memory phase 2
-            if (PAIRB && !even && (steady || kt + S < KT)) issue_b(kt + S - 1, steady);
+            if (BP && !even && (steady || kt + S < KT)) issue_b(kt + S - 1, steady);
             load_b(fbn, xb);
             load_a(fal, xal);
         }
@@ -1608,12 +1625,12 @@ __device__ __forceinline__ void gemm_item_dl(const GemmParams &p, const WorkItem
     if (KT > 0) {
         // prologue: fill the ring; only K-step 0 has to have landed (loads retire in order)
         bool exact;
-        if (PAIRB) {
+        if (BP) {
             issue_a(0, -1);
             issue_b(0);
             if (2 < KT) issue_a(2, -1);
             if (2 < KT) issue_b(2);
-            exact = KT >= S && (!RAGGED || (kbeg + S) * BK <= p.K);      // A 2-3 and B 2-3 issued in full: (S-2)*(LA+LB) loads
+            exact = KT >= S && (!RAGGED || (kbeg + S) * BK <= p.K);      // A 2-3 and B 2-3 issued in full
         } else if (PAIRED) {
             issue_a(0, -1);
             issue_b(0);
@@ -1631,7 +1648,7 @@ __device__ __forceinline__ void gemm_item_dl(const GemmParams &p, const WorkItem
             exact = KT >= S - 1 && (!RAGGED || (kbeg + S - 1) * BK <= p.K);
         }
         if (exact) {
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 2) * (LA + LB)) : "memory");
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(BP ? LAP + LBP : (S - 2) * (LA + LB)) : "memory");
         } else {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         }
@@ -1684,6 +1701,17 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::WPE, C
         if ((int)blockIdx.x >= p.split_from && wi.kcnt == 0) return;
     }
     gemm_item_dl<C, AK, BKC, EPI, RAGGED>(p, wi, KT_all, smem);
+}
+
+// The same item on 256 x 192 tiles (A B, bf16, nothing shared), for launches that fill their rounds better with three quarters of a
+// tile (plan_narrow): 2048 x 6144 is 192 tiles of 256 x 256 and 256 of these.  A pair of K-steps takes 1.14 us in all compute units
+// against 1.45 (0.75 of it would be 1.09; the column fragments are read for three blocks instead of four), and the bits are the same.
+template <class C, int EPI, bool RAGGED>
+__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::WPE, C::WPE))) void gemm_kernel_narrow(const GemmParams p)
+{
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[DlLds<C, true, false>::LDS_BYTES];
+    const int KT_all = RAGGED ? ((p.K + 63) / 64) * 2 : p.K / 32;
+    gemm_item_dl<C, true, false, EPI, RAGGED>(p, WorkItem{(int)blockIdx.x, 0, 0, 1, 0, KT_all}, KT_all, smem);
 }
 
 // ---------------------------------------------------------------------------------

@@ -207,9 +207,30 @@ inline DirectPlan plan_direct(int64_t M, int64_t N, int64_t K, bool f8, bool a_k
     return best;
 }
 
+// 256 x 192 tiles (gemm_kernel_narrow), for undivided bf16 A B without row reductions: the same bits, in another number of rounds.
+// One round of 129 to 192 large tiles is one round of three quarters the length: 2560 x 3776 x 512 19.3 -> 15.6 us, 1728 x 5184 x
+// 8192 160 -> 136, 2048 x 6144 x 4096 92 -> 82 (the large tiles leave a quarter of the chip idle, so that the rest clocks higher);
+// so are two and a bit (7680 x 4608 x 1024, 2.1 rounds in three: 80.7 -> 70.6).  Where the rounds come out alike the large tiles
+// are ahead by 3 to 7 % (1728 x 23552 x 4096: 295, 303).  `direct`: modelled time of the small tiles that the shape would take.
+// Model in microseconds, per round: fill and epilogue, then a pair of K-steps, which costs less the fewer of the compute units
+// draw power; of 54 shapes on large tiles it takes 28, all of them faster (by 13 % in the mean), and leaves 4 that would gain 2 %.
+constexpr int64_t NARROW_TILE_N = 192;
+inline bool narrow_is_faster(int64_t M, int64_t N, int64_t K, double direct)
+{
+    if (M <= 0 || N <= 0 || K <= 0) return false;
+    const double pairs = (double)((K + 63) / 64);
+    auto us = [&](int64_t bn, double round, double pair, double idle) {
+        const int64_t tiles = ((M + PLAN_TILE_M - 1) / PLAN_TILE_M) * ((N + bn - 1) / bn), rounds = (tiles + SPLITK_CUS - 1) / SPLITK_CUS;
+        const double empty = 1.0 - (double)tiles / (double)(rounds * SPLITK_CUS);
+        return 3.0 + (double)rounds * (round + pairs * (pair - idle * empty));
+    };
+    const double narrow = us(NARROW_TILE_N, 6.0, 1.16, 0.5), large = us(PLAN_TILE_N, 8.0, 1.447, 0.7);
+    return narrow < 0.97 * (direct < large ? direct : large);
+}
+
 // Route of a call.  The order of the additions behind an element must not depend on the program, so what divides the
 // contraction is decided by the sizes, operand type and layouts alone:
-//   whole or undivided small tiles, chain INT32_MAX: the MFMAs of a tile along K from the place that rot_cols says, the same
+//   whole (of 256 or 192 columns) or undivided small tiles, chain INT32_MAX: the MFMAs of a tile along K from the place that rot_cols says, the same
 //     sums on every tile size;
 //   shared: the ranges of `shared`;
 //   divided: the ranges of `small`, folded every `chain` stages, started at the stage of rot_cols.
@@ -225,6 +246,7 @@ struct Route {
     int rot_cols;      // see SmallParams; ROUTE_WHOLE: GemmParams::rot_cols if positive
     SplitPlan shared;  // ROUTE_SHARED; the workspace that any route asks for
     SmallPlan small;   // ROUTE_DIVIDED
+    bool narrow;       // ROUTE_WHOLE: 256 x 192 tiles
 };
 // Where an undivided tile starts along K if B is K-contiguous.  256 x 256 tiles of a whole bf16 A B^T start by XCD, and small tiles
 // with them.  Up to 256 rows (a row of 256 x 256 tiles: no panels to share) the tiles start by column, in steps of 256 (1 x 65536 x 4096
@@ -240,7 +262,7 @@ inline Route plan_route(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_conti
                         bool workspace)
 {
     const SplitPlan big = plan_splitk(M, N, K, f8, workspace);      // once a call
-    Route r = {ROUTE_WHOLE, DIRECT_NONE, INT32_MAX, undivided_rotation(M, N, K, f8, a_k_contiguous, b_k_contiguous, big), big, {0, 0, 0, 0.0}};
+    Route r = {ROUTE_WHOLE, DIRECT_NONE, INT32_MAX, undivided_rotation(M, N, K, f8, a_k_contiguous, b_k_contiguous, big), big, {0, 0, 0, 0.0}, false};
     DirectPlan direct = plan_direct(M, N, K, f8, a_k_contiguous, prog, wide, big);
     // the contraction is divided only when the caller brought the workspace for it; without one the shape runs undivided
     if (workspace && big.chunks > 0) {
@@ -260,6 +282,12 @@ inline Route plan_route(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_conti
     if (direct.tile != DIRECT_NONE) {
         r.kind = ROUTE_DIRECT;
         r.tile = direct.tile;
+    }
+    if (r.chain == INT32_MAX && !f8 && a_k_contiguous && !b_k_contiguous && !wide &&
+        (prog == DIRECT_PROG_LINEAR || prog == DIRECT_PROG_SWIGLU_FWD) &&
+        narrow_is_faster(M, N, K, r.kind == ROUTE_DIRECT ? direct.us : 1e30)) {
+        r.kind = ROUTE_WHOLE;
+        r.narrow = true;
     }
     return r;
 }
