@@ -384,14 +384,16 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2), am
     }
 }
 
-// The whole launch in one kernel: the contraction undivided, then the epilogue program of the large kernels on the tile.
-// The callers' row-reduction partials are per 256 columns, so programs with one take the 256-wide tiles.
+// The contraction of a whole tile, then the epilogue program of the large kernels on it.
+template <class C>
+struct SmallLds {
+    static constexpr int RED = 2 * C::WGN * C::BM * 4, BYTES = C::LDS + RED;
+    static_assert(BYTES <= 160 * 1024, "LDS");
+};
 template <class C, bool AK, bool BKC, int EPI, bool CHAINS>
-__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2), amdgpu_num_vgpr(256))) void gemm_small_direct(const GemmParams g, const SmallParams p)
+__device__ __forceinline__ void small_tile(const GemmParams &g, const SmallParams &p, unsigned char *smem)
 {
-    constexpr int RED = 2 * C::WGN * C::BM * 4;
-    static_assert(C::LDS + RED <= 160 * 1024 && EPI != EPI_RMSNORM_BWD, "LDS; column partials are per 256 rows");
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[C::LDS + RED];
+    static_assert(EPI != EPI_RMSNORM_BWD, "column partials are per 256 rows");
     int tm, tn, split;
     small_coords((int)blockIdx.x, p.tiles_m, p.tiles_n, 1, tm, tn, split);
     const int m0 = tm * C::BM, n0 = tn * C::BN;
@@ -408,6 +410,25 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2), am
         run_epilogue<C, SmallAcc<C>, EPI, true, C::LDS>(acc, g, m0, n0, tn, smem, red, (int)threadIdx.x);
     else
         run_epilogue<C, SmallAcc<C>, EPI, false, C::LDS>(acc, g, m0, n0, tn, smem, red, (int)threadIdx.x);
+}
+
+// The whole launch in one kernel.  The callers' row-reduction partials are per 256 columns, so programs with one take the 256-wide
+// tiles.
+template <class C, bool AK, bool BKC, int EPI, bool CHAINS>
+__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2), amdgpu_num_vgpr(256))) void gemm_small_direct(const GemmParams g, const SmallParams p)
+{
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[SmallLds<C>::BYTES];
+    small_tile<C, AK, BKC, EPI, CHAINS>(g, p, smem);
+}
+
+// A division into one range (up to 64 rows, weights of 129 to 256 tiles of 128 columns) for a program without row reductions: nothing
+// to add up, so no partials and no second kernel.  Bound by HBM: 28672 x 4096 bf16 in 43.8 us with the launch, 5.4 TB/s (partials and
+// a second kernel: 45.0).
+template <class C, bool BKC, int EPI>
+__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2), amdgpu_num_vgpr(256))) void gemm_small_stream(const GemmParams g, const SmallParams p)
+{
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[SmallLds<C>::BYTES];
+    small_tile<C, true, BKC, EPI, true>(g, p, smem);
 }
 
 }  // namespace coda

@@ -111,11 +111,12 @@ struct SmallPlan {
     int bm, bn;    // the tile: 32, 64 or 128 rows, 128 (or, with 128 rows, 256) columns
     int nsplit;    // ranges of the contraction; 0: the shape runs on the large tiles
     double us;     // modelled time
+    bool fused;    // one range, whose epilogue runs in the same kernel
 };
 constexpr int64_t SMALL_MAX_SPLIT = 16, SMALL_MIN_STAGES = 4;   // beyond that the exchange costs what the ranges save
 inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_contiguous, const SplitPlan &big)
 {
-    const SmallPlan none = {0, 0, 0, 0.0};
+    const SmallPlan none = {0, 0, 0, 0.0, false};
     if (big.chunks == 0 || big.first != 0) return none;
     const int64_t esz = f8 ? 1 : 2, stages = (K * esz + 127) / 128;
     const int64_t budget = (int64_t)splitk_bytes(big) / (M * N * 4);              // ranges whose partials fit
@@ -126,7 +127,7 @@ inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_c
         if (ns > stages / SMALL_MIN_STAGES) ns = stages / SMALL_MIN_STAGES;
         if (ns > budget) ns = budget;
         if (ns < 1) return none;
-        return SmallPlan{bm, bn, (int)ns, 6.0 + stage_us * (double)((stages + ns - 1) / ns) + (double)(ns * M * N) * 8.0 / 5e6};
+        return SmallPlan{bm, bn, (int)ns, 6.0 + stage_us * (double)((stages + ns - 1) / ns) + (double)(ns * M * N) * 8.0 / 5e6, false};
     };
     if (M <= 64 && a_k_contiguous) return M <= 32 ? offer(32, 128, 0.62) : offer(64, 128, 0.62);
     const SmallPlan narrow = offer(128, 128, 0.57), wide = offer(128, 256, 0.83);
@@ -238,6 +239,9 @@ inline bool narrow_is_faster(int64_t M, int64_t N, int64_t K, double direct)
 // that range's chain and starting stages (96 x 28672 x 4096 8-bit SwiGLU: 27 us; partials of 11 MB to write, read and run a second
 // kernel on are 5 more).  It does not take the place of more ranges, where it would be 5 to 20 % ahead for a program without row reductions (809 x
 // 4096 x 4096: 37 us against 44, 512 x 6144 x 4096 A^T B SwiGLU 40, 43) and behind for one with.
+// One range of 32- or 64-row tiles needs no partials where the program reduces over no rows (`fused`, gemm_small_stream): 1 x 28672 x
+// 4096 bf16 45.0 -> 43.8 us, 32 rows with SwiGLU 45.6 (128 x 128 tiles) -> 43.8, 64 x 32768 x 4096 56.6 -> 50.1, 57 x 28672 x 4096
+// 8-bit 32.2 -> 28.5; over 129 to 256 tiles and K of 4096 and 8192 the fastest of all tiles, by 1 to 13 % (one in 76 behind, by 3.5 %).
 enum RouteKind : int { ROUTE_WHOLE = 0, ROUTE_SHARED, ROUTE_DIVIDED, ROUTE_DIRECT };
 struct Route {
     RouteKind kind;
@@ -262,7 +266,7 @@ inline Route plan_route(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_conti
                         bool workspace)
 {
     const SplitPlan big = plan_splitk(M, N, K, f8, workspace);      // once a call
-    Route r = {ROUTE_WHOLE, DIRECT_NONE, INT32_MAX, undivided_rotation(M, N, K, f8, a_k_contiguous, b_k_contiguous, big), big, {0, 0, 0, 0.0}, false};
+    Route r = {ROUTE_WHOLE, DIRECT_NONE, INT32_MAX, undivided_rotation(M, N, K, f8, a_k_contiguous, b_k_contiguous, big), big, {0, 0, 0, 0.0, false}, false};
     DirectPlan direct = plan_direct(M, N, K, f8, a_k_contiguous, prog, wide, big);
     // the contraction is divided only when the caller brought the workspace for it; without one the shape runs undivided
     if (workspace && big.chunks > 0) {
@@ -273,8 +277,11 @@ inline Route plan_route(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_conti
         }
         r.chain = splitk_chain(big, K, f8);
         r.rot_cols = (int)PLAN_TILE_N;      // a column of the widest tile
-        if (r.small.nsplit == 1) direct = plan_direct(M, N, K, f8, a_k_contiguous, prog, wide, big, true);
-        if (r.small.nsplit > 1 || direct.tile == DIRECT_NONE || r.small.us <= direct.us) {
+        if (r.small.nsplit == 1) {
+            direct = plan_direct(M, N, K, f8, a_k_contiguous, prog, wide, big, true);
+            r.small.fused = r.small.bm <= 64 && !wide && (prog == DIRECT_PROG_LINEAR || prog == DIRECT_PROG_SWIGLU_FWD);
+        }
+        if (r.small.nsplit > 1 || r.small.fused || direct.tile == DIRECT_NONE || r.small.us <= direct.us) {
             r.kind = ROUTE_DIVIDED;
             return r;
         }
