@@ -6,22 +6,25 @@ Each translation unit is compiled to an object under paper_2605_19269_amd/_build
 (in parallel).  libcoda.so is the product: it exports exactly what include/coda.h declares.
 libcoda_bench.so holds what only the measurement needs (the unfused baseline kernels of
 include/coda_unfused.h and the MFMA-only calibration loops of include/coda_calib.h) and links
-nothing of the product.  The ctypes binding loads both.  hipcc cross-compiles for gfx950
-without a GPU present.
+nothing of the product.  _binding.so is the C half of coda.py (host code, linked to libcoda.so beside it).  hipcc
+cross-compiles for gfx950 without a GPU present.
 """
 import concurrent.futures
 import os
 import re
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libcoda.so")
 LIB_BENCH = os.path.join(HERE, "libcoda_bench.so")
+BINDING = os.path.join(HERE, "_binding.so")
 RESOURCES = os.path.join(HERE, "libcoda.resources.txt")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+CXX = os.environ.get("CXX", "g++")
 
 # -packed-fp32-ops is switched off: the compiler must not form packed fp32 VALU ops.
 # -fvisibility=hidden: only the entry points marked CODA_API in the headers are exported.
@@ -110,6 +113,17 @@ def _link(lib, objs, force):
             raise RuntimeError("link failed:\n" + r.stdout + r.stderr)
 
 
+def _build_binding(force):
+    src = os.path.join(CSRC, "binding.cpp")
+    deps = [src, os.path.join(os.path.dirname(HERE), "include", "coda.h")]
+    if not force and os.path.exists(BINDING) and all(os.path.getmtime(d) <= os.path.getmtime(BINDING) for d in deps):
+        return
+    r = subprocess.run([CXX, "-O2", "-std=c++17", "-Wall", "-fPIC", "-shared", "-fvisibility=hidden", "-I", sysconfig.get_paths()["include"], src,
+                        "-o", BINDING, "-L", HERE, "-l:libcoda.so", "-Wl,-rpath,$ORIGIN"], capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("%s failed on binding.cpp:\n%s" % (CXX, r.stdout + r.stderr))
+
+
 def build(force=False, jobs=None):
     os.makedirs(BUILD, exist_ok=True)
     srcs = SOURCES + SOURCES_BENCH
@@ -122,6 +136,7 @@ def build(force=False, jobs=None):
             print(log)
     _link(LIB, objs[:len(SOURCES)], force)
     _link(LIB_BENCH, objs[len(SOURCES):], force)
+    _build_binding(force)
     # registers, scratch and LDS of every kernel of the two libraries, as the compiler reported them (read by the host tests)
     with open(RESOURCES, "w") as f:
         for o in objs:

@@ -1,7 +1,8 @@
-"""ctypes binding of libcoda.so -- argument marshalling only.
+"""Binding of libcoda.so -- argument marshalling only.
 
 Every function here has the name of the C entry point it forwards to (include/coda.h)
-and does nothing but turn torch tensors into raw device pointers, sizes and pitches.
+and does nothing but turn torch tensors into raw device pointers, sizes and pitches: the
+calls that a program makes for every layer in C (csrc/binding.cpp), the others by ctypes.
 All arithmetic happens in the HIP kernels.  If the library has not been built the
 import of this module fails loudly; there is no fallback path of any kind.
 The measurement-only entry points (include/coda_unfused.h, include/coda_calib.h) live in
@@ -21,6 +22,9 @@ if not os.path.exists(LIB_PATH):
 LIB_BENCH_PATH = os.path.join(_HERE, "libcoda_bench.so")
 if not os.path.exists(LIB_BENCH_PATH):
     raise ImportError("libcoda_bench.so is not built (%s). Build it with `python -m paper_2605_19269_amd.build`." % LIB_BENCH_PATH)
+
+if not os.path.exists(os.path.join(_HERE, "_binding.so")):
+    raise ImportError("_binding.so is not built (%s). Build it with `python -m paper_2605_19269_amd.build`." % _HERE)
 
 _lib = ctypes.CDLL(LIB_PATH)
 _blib = ctypes.CDLL(LIB_BENCH_PATH)
@@ -56,8 +60,7 @@ class coda_epi_op(ctypes.Structure):
 
 _vp, _i64, _i32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32
 _lib.coda_gemm.restype = ctypes.c_int
-_lib.coda_gemm.argtypes = [_vp, _i64, _i64, _i64, ctypes.POINTER(coda_mat), ctypes.POINTER(coda_mat),
-                           ctypes.POINTER(coda_epi_op), _i32, _vp, ctypes.c_size_t]
+_lib.coda_gemm.argtypes = [_vp, _i64, _i64, _i64, _vp, _vp, _vp, _i32, _vp, ctypes.c_size_t]     # structures: a pointer to one, or its bytes
 _lib.coda_gemm_static_ws.restype = ctypes.c_int
 _lib.coda_gemm_static_ws.argtypes = [_vp, _i64, _i64, _i64, ctypes.POINTER(coda_mat), ctypes.POINTER(coda_mat),
                                      ctypes.POINTER(coda_epi_op), _i32]
@@ -74,7 +77,7 @@ _lib.coda_col_finalize.argtypes = [_vp, _vp, _i64, _i64, _vp]
 _lib.coda_lse_finalize.restype = ctypes.c_int
 _lib.coda_lse_finalize.argtypes = [_vp, _vp, _vp, _i64, _i64, _vp, _vp, _vp]
 _lib.coda_row_sumsq.restype = ctypes.c_int
-_lib.coda_row_sumsq.argtypes = [_vp, ctypes.POINTER(coda_mat), _vp]
+_lib.coda_row_sumsq.argtypes = [_vp, _vp, _vp]
 _lib.coda_fold_gamma.restype = ctypes.c_int
 _lib.coda_fold_gamma.argtypes = [_vp, ctypes.POINTER(coda_mat), _vp, _vp, _i64]
 _lib.coda_interleave_pairs.restype = ctypes.c_int
@@ -98,6 +101,14 @@ _blib.coda_calib_mfma_loop.argtypes = [_vp, _vp, _vp, _i64, _i64, _vp]
 _blib.coda_calib_mfma_loop16.restype = ctypes.c_int
 _blib.coda_calib_mfma_loop16.argtypes = [_vp, _vp, _vp, _i64, _i64, _vp]
 
+# The calls of every layer: the C functions take their place, and hand unusual arguments on to them.
+from . import _binding  # noqa: E402  (links libcoda.so)
+
+_NATIVE = ("coda_gemm", "coda_row_finalize", "coda_row_sumsq", "coda_col_finalize", "coda_lse_finalize")
+_binding.ctypes_calls(*(getattr(_lib, _n) for _n in _NATIVE))
+for _n in _NATIVE:
+    setattr(_lib, _n, getattr(_binding, _n))
+
 
 class CodaError(RuntimeError):
     def __init__(self, status):
@@ -113,9 +124,6 @@ def _check(status):
         raise CodaError(status)
 
 
-# A call on a small problem is host work: its kernels take a few microseconds.  The marshalling below therefore asks a tensor
-# for each property once, sets only the fields that an op has, and takes the raw stream handle without building a Stream
-# object (a four-op coda_gemm: 10.6 -> 5.3 us before the launch; a 256 x 512 x 256 linear layer of four calls: 36.3 -> 23.4 us a pass).
 _torch = None
 
 
@@ -149,54 +157,30 @@ def mat(t, trans=False):
     return coda_mat(t.data_ptr(), rows, cols, ld, 1 if trans else 0, _DTYPES.get(t.dtype, CODA_F32))
 
 
-def _op(kind, flags=0, in_=None, out=None, out2=None, in2=None, in3=None, in4=None, out3=None, i0=0, i1=0):
-    op = coda_epi_op(kind, flags)
-    if in_ is not None:
-        op.in_ = in_.data_ptr()
-        pitch = in_.stride()
-        if len(pitch) == 2:
-            op.ld_in = pitch[0]
-    if out is not None:
-        op.out = out.data_ptr()
-        pitch = out.stride()
-        if len(pitch) == 2:
-            op.ld_out = pitch[0]
-    if out2 is not None:
-        op.out2 = out2.data_ptr()
-    if in2 is not None:
-        op.in2 = in2.data_ptr()
-    if in3 is not None:
-        op.in3 = in3.data_ptr()
-    if in4 is not None:
-        op.in4 = in4.data_ptr()
-    if out3 is not None:
-        op.out3 = out3.data_ptr()
-    if i0 or i1:
-        op.i0, op.i1 = i0, i1
-    op._keep = (in_, out, out2, in2, in3, in4, out3)     # the op owns a reference, so a temporary passed inline survives
-    return op
-
-
 # --- epilogue op constructors (each op holds its tensors for as long as the op object lives) ---
+# _op(type, kind, flags, in_, out, out2, in2, in3, in4, out3, i0, i1); the pitches are those of a 2-D in_ and out
+_op = _binding.op
+
+
 def row_scale(r):
-    return _op(CODA_EPI_ROW_SCALE, in_=r)
+    return _op(coda_epi_op, CODA_EPI_ROW_SCALE, 0, r, None, None, None, None, None, None, 0, 0)
 
 
 def col_scale_side(gamma, out):
-    return _op(CODA_EPI_COL_SCALE_SIDE, in_=gamma, out=out)
+    return _op(coda_epi_op, CODA_EPI_COL_SCALE_SIDE, 0, gamma, out, None, None, None, None, None, 0, 0)
 
 
 def rope(cos, sin, pos, head_dim, rope_cols):
     """cos / sin: f32 [T x head_dim/2] dense tables; pos: int32 [M]."""
-    op = _op(CODA_EPI_ROPE, in_=cos, in2=sin, in3=pos, i0=head_dim, i1=rope_cols)
+    op = _op(coda_epi_op, CODA_EPI_ROPE, 0, cos, None, None, sin, pos, None, None, head_dim, rope_cols)
     op.ld_in = cos.shape[0]     # T: rows of the tables
     return op
 
 
 def rmsnorm_bwd(C, r, z, gamma, c_out=None, dgamma_out=None, atomic=False, z_sum_over=0):
     """z: f32 [M] row statistic; with z_sum_over = d > 0 it holds the raw row sums and the kernel divides by d."""
-    return _op(CODA_EPI_RMSNORM_BWD, CODA_REDUCE_ATOMIC if atomic else CODA_REDUCE_PARTIALS, in_=C, in2=r, in3=z,
-               in4=gamma, out=c_out, out2=dgamma_out, i0=z_sum_over)
+    return _op(coda_epi_op, CODA_EPI_RMSNORM_BWD, CODA_REDUCE_ATOMIC if atomic else CODA_REDUCE_PARTIALS, C, c_out, dgamma_out, r, z, gamma, None,
+               z_sum_over, 0)
 
 
 def lse_partial(y, pmax, psum, ztgt):
@@ -207,28 +191,28 @@ def lse_partial(y, pmax, psum, ztgt):
 
 
 def add_tile(C):
-    return _op(CODA_EPI_ADD_TILE, in_=C)
+    return _op(coda_epi_op, CODA_EPI_ADD_TILE, 0, C, None, None, None, None, None, None, 0, 0)
 
 
 def swiglu_fwd(preact_out=None):
-    return _op(CODA_EPI_SWIGLU_FWD, out=preact_out)
+    return _op(coda_epi_op, CODA_EPI_SWIGLU_FWD, 0, None, preact_out, None, None, None, None, None, 0, 0)
 
 
 def swiglu_bwd(Z, act_out=None, stat_out=None, atomic=False):
-    return _op(CODA_EPI_SWIGLU_BWD, CODA_REDUCE_ATOMIC if atomic else CODA_REDUCE_PARTIALS, in_=Z,
-               out=act_out, out2=stat_out)
+    return _op(coda_epi_op, CODA_EPI_SWIGLU_BWD, CODA_REDUCE_ATOMIC if atomic else CODA_REDUCE_PARTIALS, Z, act_out, stat_out, None, None, None, None,
+               0, 0)
 
 
 def row_sumsq(out, atomic=False):
-    return _op(CODA_EPI_ROW_SUMSQ, CODA_REDUCE_ATOMIC if atomic else CODA_REDUCE_PARTIALS, out=out)
+    return _op(coda_epi_op, CODA_EPI_ROW_SUMSQ, CODA_REDUCE_ATOMIC if atomic else CODA_REDUCE_PARTIALS, None, out, None, None, None, None, None, 0, 0)
 
 
 def store(out, f32=False):
-    return _op(CODA_EPI_STORE, CODA_STORE_F32 if f32 else 0, out=out)
+    return _op(coda_epi_op, CODA_EPI_STORE, CODA_STORE_F32 if f32 else 0, None, out, None, None, None, None, None, 0, 0)
 
 
 def accum_f32(G):
-    return _op(CODA_EPI_ACCUM_F32, out=G)
+    return _op(coda_epi_op, CODA_EPI_ACCUM_F32, 0, None, G, None, None, None, None, None, 0, 0)
 
 
 _PROG = [coda_epi_op * max(1, n) for n in range(9)]
@@ -251,12 +235,13 @@ def coda_gemm_raw(stream, M, N, K, A, B, ops, workspace=None, workspace_bytes=0)
 def coda_gemm(A, B, ops, transA=False, transB=False, stream=None, workspace=None):
     """D = op(A) op(B), then the epilogue ops in order.  A, B: 2-D bf16 CUDA tensors as stored.
     workspace: optional device tensor of at least coda_gemm_workspace_bytes(...) bytes (enables split-K)."""
-    a, b = mat(A, transA), mat(B, transB)
-    M, K = (a.cols, a.rows) if transA else (a.rows, a.cols)
-    N = b.rows if transB else b.cols
+    _torch or _import_torch()
+    M, N, K, a, b = _binding.gemm_mats(A, B, transA, transB, _DTYPES)
     ops = list(ops)      # of a generator too: the ops own the tensors, and stay until the call returns
-    arr, n = _prog(ops)
-    _check(_lib.coda_gemm(_stream(stream), M, N, K, ctypes.byref(a), ctypes.byref(b), arr, n,
+    arr = _binding.prog(ops, coda_epi_op)
+    if arr is None:
+        arr = _prog(ops)[0]
+    _check(_lib.coda_gemm(_stream(stream), M, N, K, a, b, arr, len(ops),
                           None if workspace is None else workspace.data_ptr(),
                           0 if workspace is None else workspace.numel() * workspace.element_size()))
 
@@ -307,8 +292,8 @@ def coda_col_finalize(partials, N, nblk, out, stream=None):
 
 
 def coda_row_sumsq(X, sum_out, stream=None):
-    m = mat(X)
-    _check(_lib.coda_row_sumsq(_stream(stream), ctypes.byref(m), _ptr(sum_out)))
+    _torch or _import_torch()
+    _check(_lib.coda_row_sumsq(_stream(stream), _binding.mat(X, False, _DTYPES), _ptr(sum_out)))
 
 
 def coda_fold_gamma(W, gamma, W_out, stream=None):
