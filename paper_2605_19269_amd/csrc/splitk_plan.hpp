@@ -107,29 +107,56 @@ inline int splitk_chain(const SplitPlan &pl, int64_t K, bool f8)
 // / 32.9 / 61.7; 1000 x 2048 x 11264: 64.0 / 58.7 / 90.5; 768 x 4096 x 14336: 137 / 110 / 144; 1024 x 4096 x 14336: 150 / 129 /
 // 124, where the large tiles stay.  The small tiles must win by a tenth.  (Two workgroups of 128 x 128 tiles per CU, four
 // waves and two stages each, lie between: 384 x 6144 x 4096 40.6, 128 x 256 38.0; 768 x 4096 x 14336 113.)
+// From SMALL_MODEL_TILES tiles of 256 x 256 on the figures are others: there the small tiles fill the chip with one range or two, and
+// the exchange of that many tiles is what costs:
+//   launches and epilogue 6; one stage of a 128 x 128 tile 0.57, of a 128 x 256 tile 0.52 and 0.37 more when every CU has one
+//   (they share the L2s), 0.05 for a K-contiguous B; partials as above, but not for one range of 128 x 256 tiles, which all
+//   programs but RMSNORM_BWD run undivided (that one comes with bf16 A B^T);
+//   256 x 256 tiles: a pair of K-steps 1.42; the exchange of parts 4, 0.06 a range, 0.02 a range and slot; where ranges
+//   straddle tiles 30, and 1.3, 1.75 or 2 times the longest range, as the pieces of 8, 16 or more ranges repeat.
+// Of 110 random shapes that the older figures left on shared tiles those that now take small ones gain 2 to 35 %, 16 % in the mean over
+// all: 1232 x 5568 x 15040 329 -> 213 us, 1072 x 3840 x 11072 176 -> 119, 960 x 5376 x 10432 174 -> 127, 1024 x 8192 x 4096 77 -> 62.
+// Shared tiles stay at 2048 x 4096 x 14336 (179, small 189), 1440 x 4096 x 14336 (164, 181), 384 x 16384 x 14336 A B^T (189, 228).
 struct SmallPlan {
     int bm, bn;    // the tile: 32, 64 or 128 rows, 128 (or, with 128 rows, 256) columns
     int nsplit;    // ranges of the contraction; 0: the shape runs on the large tiles
     double us;     // modelled time
     bool fused;    // one range, whose epilogue runs in the same kernel
 };
+constexpr int64_t SMALL_MODEL_TILES = 70;
 constexpr int64_t SMALL_MAX_SPLIT = 16, SMALL_MIN_STAGES = 4;   // beyond that the exchange costs what the ranges save
-inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_contiguous, const SplitPlan &big)
+inline double shared_tiles_us(const SplitPlan &big, int64_t K, bool f8)
+{
+    const double pairs = splitk_longest_stages(big, K, f8);
+    if (big.pieces == 1) return 4.0 + 0.06 * big.chunks + 0.02 * (double)big.chunks * big.stride + 1.42 * pairs;
+    int period = big.chunks;                        // ranges after which the pieces of the tiles repeat
+    for (int tail = big.tail; tail % 2 == 0 && period % 2 == 0; tail /= 2) period /= 2;
+    return 30.0 + 1.42 * pairs * (period <= 8 ? 1.3 : period <= 16 ? 1.75 : 2.0);
+}
+inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_contiguous, const SplitPlan &big, bool b_k_contiguous = false)
 {
     const SmallPlan none = {0, 0, 0, 0.0, false};
     if (big.chunks == 0 || big.first != 0) return none;
     const int64_t esz = f8 ? 1 : 2, stages = (K * esz + 127) / 128;
     const int64_t budget = (int64_t)splitk_bytes(big) / (M * N * 4);              // ranges whose partials fit
-    auto offer = [&](int bm, int bn, double stage_us) {
+    const bool many = big.tail >= SMALL_MODEL_TILES;
+    auto offer = [&](int bm, int bn, double stage_us, double shared_us = 0.0) {
         const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
         int64_t ns = SPLITK_CUS / tiles;
         if (ns > SMALL_MAX_SPLIT) ns = SMALL_MAX_SPLIT;
         if (ns > stages / SMALL_MIN_STAGES) ns = stages / SMALL_MIN_STAGES;
         if (ns > budget) ns = budget;
         if (ns < 1) return none;
-        return SmallPlan{bm, bn, (int)ns, 6.0 + stage_us * (double)((stages + ns - 1) / ns) + (double)(ns * M * N) * 8.0 / 5e6, false};
+        const double stage = stage_us + shared_us * (double)(tiles * ns) / (double)SPLITK_CUS;
+        const bool undivided = many && ns == 1 && bn == 256 && (f8 || !b_k_contiguous);
+        return SmallPlan{bm, bn, (int)ns, 6.0 + stage * (double)((stages + ns - 1) / ns) + (undivided ? 0.0 : (double)(ns * M * N) * 8.0 / 5e6), false};
     };
     if (M <= 64 && a_k_contiguous) return M <= 32 ? offer(32, 128, 0.62) : offer(64, 128, 0.62);
+    if (many) {
+        const SmallPlan narrow = offer(128, 128, 0.57), wide = offer(128, 256, b_k_contiguous ? 0.57 : 0.52, 0.37);
+        const SmallPlan best = wide.nsplit == 0 || (narrow.nsplit != 0 && narrow.us <= wide.us) ? narrow : wide;
+        return best.nsplit != 0 && best.us <= 0.95 * shared_tiles_us(big, K, f8) ? best : none;
+    }
     const SmallPlan narrow = offer(128, 128, 0.57), wide = offer(128, 256, 0.83);
     // one range: most programs run undivided and pay no partials (plan_route), and all take the same plan
     auto cost = [&](const SmallPlan &p) { return p.us - (p.nsplit == 1 ? 0.5 * (double)(M * N) * 8.0 / 5e6 : 0.0); };
@@ -270,7 +297,7 @@ inline Route plan_route(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_conti
     DirectPlan direct = plan_direct(M, N, K, f8, a_k_contiguous, prog, wide, big);
     // the contraction is divided only when the caller brought the workspace for it; without one the shape runs undivided
     if (workspace && big.chunks > 0) {
-        r.small = plan_small(M, N, K, f8, a_k_contiguous, big);
+        r.small = plan_small(M, N, K, f8, a_k_contiguous, big, b_k_contiguous);
         if (r.small.nsplit == 0) {
             r.kind = ROUTE_SHARED;
             return r;
@@ -281,7 +308,9 @@ inline Route plan_route(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_conti
             direct = plan_direct(M, N, K, f8, a_k_contiguous, prog, wide, big, true);
             r.small.fused = r.small.bm <= 64 && !wide && (prog == DIRECT_PROG_LINEAR || prog == DIRECT_PROG_SWIGLU_FWD);
         }
-        if (r.small.nsplit > 1 || r.small.fused || direct.tile == DIRECT_NONE || r.small.us <= direct.us) {
+        // the figures from SMALL_MODEL_TILES on do not compare with plan_direct's: one range of 128 x 256 tiles runs undivided if it can
+        const bool undivided = big.tail >= SMALL_MODEL_TILES && r.small.bn == 256;
+        if (r.small.nsplit > 1 || r.small.fused || direct.tile == DIRECT_NONE || (!undivided && r.small.us <= direct.us)) {
             r.kind = ROUTE_DIVIDED;
             return r;
         }
