@@ -5,7 +5,7 @@
 // without staging, the pairwise maps stay inside a lane, and a block's row reduction -- the 256-column granularity that
 // the callers' partial buffers have -- is one wave reduction in a fixed order.  M / 4 x N / 256 workgroups, so even a
 // few rows spread over the chip.  Bound by reading the partials (from the memory-side cache, where the first kernel left them):
-// 509 x 2048 in four ranges, 21 MB with the residual and the result, 5.5 us; with one row by the latency of a few loads, 3.8 us.
+// 509 x 2048 in four ranges, 21 MB with the residual and the result, 5.2 us; with one row by the latency of a few loads, 3.8 us.
 //
 // RMSNORM_BWD also reduces over the columns of 256-row blocks: there a workgroup owns 256 rows x 32 columns, 8 lanes a row.
 #pragma once
@@ -13,20 +13,31 @@
 
 namespace coda {
 
-// The ranges' partials of four columns, added up in range order, eight loads in flight: with one row there is nothing else to
-// hide a load's latency under (4096 columns of 8 ranges, one row: 4.0 us with the last three loaded one by one).
-__device__ __forceinline__ f32x4 sum_parts(const float *part, int nsplit, int64_t stride)
+// The ranges' partials of four columns of R rows, each row's added up in range order, R * W loads in flight: with few rows there is
+// nothing else to hide a load's latency under (4096 columns of 8 ranges, one row: 4.0 us with the last three loaded one by one).
+template <int W, int R>
+__device__ __forceinline__ void sum_parts_by(f32x4 (&v)[R], const float *const (&part)[R], int nsplit, int64_t stride)
 {
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    for (int s = 0; s < nsplit; s += 8) {
-        f32x4 t[8];
+    for (int s = 0; s < nsplit; s += W) {
+        f32x4 t[R][W];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) t[q] = *reinterpret_cast<const f32x4 *>(part + (s + q < nsplit ? s + q : nsplit - 1) * stride);
+        for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int q = 0; q < 8; ++q)
-            if (s + q < nsplit) v = s + q == 0 ? t[q] : v + t[q];
+            for (int q = 0; q < W; ++q) t[r][q] = *reinterpret_cast<const f32x4 *>(part[r] + (s + q < nsplit ? s + q : nsplit - 1) * stride);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int q = 0; q < W; ++q)
+                if (s + q < nsplit) v[r] = s + q == 0 ? t[r][q] : v[r] + t[r][q];
     }
-    return v;
+}
+// No more loads than ranges, rounded up to 2, 4 or 8 (always eight: 509 x 2048 in four ranges 5.5 us, here 5.2)
+template <int R>
+__device__ __forceinline__ void sum_parts(f32x4 (&v)[R], const float *const (&part)[R], int nsplit, int64_t stride)
+{
+    if (nsplit <= 2) sum_parts_by<2>(v, part, nsplit, stride);
+    else if (nsplit <= 4) sum_parts_by<4>(v, part, nsplit, stride);
+    else sum_parts_by<8>(v, part, nsplit, stride);
 }
 __device__ __forceinline__ f32x4 unpack4(u32x2 c) { return f32x4{bf16_lo(c[0]), bf16_hi(c[0]), bf16_lo(c[1]), bf16_hi(c[1])}; }
 __device__ __forceinline__ u32x2 pack4(f32x4 v) { return u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])}; }
@@ -58,8 +69,9 @@ __global__ __launch_bounds__(256) void epi_rows_kernel(const GemmParams p, const
     if (EPI == EPI_LINEAR && p.rope_cos) pos = clampi(p.rope_pos[m], 0, p.rope_T - 1);
     if (EPI == EPI_LINEAR && p.add && ok) res = *reinterpret_cast<const u32x2 *>(p.add + (int64_t)m * p.ld_add + n);
     if (EPI == EPI_SWIGLU_BWD && ok) z = *reinterpret_cast<const u32x4 *>(p.Z + (int64_t)m * p.ldz + 2 * n);
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    if (ok) v = sum_parts(part + (int64_t)m * p.N + n, nsplit, plane);
+    f32x4 sum[1] = {{0.f, 0.f, 0.f, 0.f}};
+    if (ok) sum_parts(sum, {part + (int64_t)m * p.N + n}, nsplit, plane);
+    f32x4 v = sum[0];
     float red = 0.0f;
 
     if constexpr (EPI == EPI_ACCUM) {
@@ -133,33 +145,46 @@ __global__ __launch_bounds__(256) void epi_rows_kernel(const GemmParams p, const
     }
 }
 
-// RMSNORM_BWD: 256 rows x 32 columns, 16 waves of eight rows a step, 8 lanes x 4 columns a row.
+// RMSNORM_BWD: 256 rows x 32 columns, 16 waves of eight rows a step, 8 lanes x 4 columns a row.  A workgroup a CU, so what both steps
+// read is in flight together: 1000 x 2048 in four ranges, 49 MB, 13.0 -> 10.8 us.
 template <int EPI>
 __global__ __launch_bounds__(1024) void epi_cols_kernel(const GemmParams p, const float *__restrict__ part, const int nsplit)
 {
-    constexpr int ROWS = 256, COLS = EPI_COLS, STEP = 128;
+    constexpr int ROWS = 256, COLS = EPI_COLS, STEP = 128, STEPS = ROWS / STEP;
     __shared__ f32x4 cs[16][COLS / 4];
     const int rl = threadIdx.x >> 3, cl = threadIdx.x & 7, n = blockIdx.x * COLS + cl * 4;
     const bool nok = n < p.N;
     const int64_t plane = (int64_t)p.M * p.N;
-    f32x4 dg = {0.f, 0.f, 0.f, 0.f}, gm = dg;
-    if (nok) gm = *reinterpret_cast<const f32x4 *>(p.rn_gamma + n);
+    f32x4 dg = {0.f, 0.f, 0.f, 0.f};
+    if (nok) {
+        const f32x4 gm = *reinterpret_cast<const f32x4 *>(p.rn_gamma + n);
+        float rr[STEPS], zz[STEPS];
+        u32x2 c[STEPS], res[STEPS];
+        f32x4 d[STEPS];
+        const float *at[STEPS];
 #pragma unroll
-    for (int st = 0; st < ROWS / STEP; ++st) {
-        const int m = blockIdx.y * ROWS + st * STEP + rl;
-        if (m >= p.M || !nok) continue;
-        // the row's own inputs travel with the partials
-        const float rr = p.rn_r[m], zz = p.rn_z[m] * p.rn_zscale;
-        const u32x2 c = *reinterpret_cast<const u32x2 *>(p.rn_c + (int64_t)m * p.ld_rn_c + n);
-        u32x2 res = {0u, 0u};
-        if (p.add) res = *reinterpret_cast<const u32x2 *>(p.add + (int64_t)m * p.ld_add + n);
-        const f32x4 d = sum_parts(part + (int64_t)m * p.N + n, nsplit, plane);
-        const f32x4 cn = unpack4(c) * rr;
-        f32x4 o = (d * gm - cn * zz) * rr;
-        if (p.add) o += unpack4(res);
-        dg += d * cn;
-        *reinterpret_cast<u32x2 *>(reinterpret_cast<uint16_t *>(p.out) + (int64_t)m * p.ld_out + n) = pack4(o);
-        if (p.out2) *reinterpret_cast<u32x2 *>(p.out2 + (int64_t)m * p.ld_out2 + n) = pack4(cn * gm);
+        for (int st = 0; st < STEPS; ++st) {
+            const int m = min((int)blockIdx.y * ROWS + st * STEP + rl, p.M - 1);      // past M: the last row again, dropped below
+            rr[st] = p.rn_r[m];
+            zz[st] = p.rn_z[m] * p.rn_zscale;
+            c[st] = *reinterpret_cast<const u32x2 *>(p.rn_c + (int64_t)m * p.ld_rn_c + n);
+            res[st] = u32x2{0u, 0u};
+            if (p.add) res[st] = *reinterpret_cast<const u32x2 *>(p.add + (int64_t)m * p.ld_add + n);
+            at[st] = part + (int64_t)m * p.N + n;
+            d[st] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        sum_parts(d, at, nsplit, plane);
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) {
+            const int m = blockIdx.y * ROWS + st * STEP + rl;
+            if (m >= p.M) continue;
+            const f32x4 cn = unpack4(c[st]) * rr[st];
+            f32x4 o = (d[st] * gm - cn * zz[st]) * rr[st];
+            if (p.add) o += unpack4(res[st]);
+            dg += d[st] * cn;
+            *reinterpret_cast<u32x2 *>(reinterpret_cast<uint16_t *>(p.out) + (int64_t)m * p.ld_out + n) = pack4(o);
+            if (p.out2) *reinterpret_cast<u32x2 *>(p.out2 + (int64_t)m * p.ld_out2 + n) = pack4(cn * gm);
+        }
     }
     if (p.colred_mode == ROWRED_NONE) return;
     // column sums: the eight rows of a wave, then the sixteen waves in order
