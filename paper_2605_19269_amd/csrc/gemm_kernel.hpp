@@ -1084,6 +1084,15 @@ __device__ __forceinline__ void dl_load16(uint32_t voff, const void *sbase, uint
                  : "memory", "m0");
 }
 
+// The same, past the caches: for bytes that are read once
+__device__ __forceinline__ void dl_load16_once(uint32_t voff, const void *sbase, uint32_t lds_addr)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
+                 :
+                 : "v"(voff), "s"(sbase), "s"(lds_addr)
+                 : "memory", "m0");
+}
+
 // Virtual workgroup -> its work items.  A work item is an output tile, a contiguous range of that tile's K-steps, and --
 // when the tile is shared -- which of its `nsplit` parts this is.
 //  * Workgroups below split_from (all of them when nothing is shared) own one whole tile each.
@@ -1704,7 +1713,7 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::WPE, C
 }
 
 // The same item on 256 x 192 tiles (A B, bf16, nothing shared), for launches that fill their rounds better with three quarters of a
-// tile (plan_narrow): 2048 x 6144 is 192 tiles of 256 x 256 and 256 of these.  A pair of K-steps takes 1.14 us in all compute units
+// tile (narrow_is_faster): 2048 x 6144 is 192 tiles of 256 x 256 and 256 of these.  A pair of K-steps takes 1.14 us in all compute units
 // against 1.45 (0.75 of it would be 1.09; the column fragments are read for three blocks instead of four), and the bits are the same.
 template <class C, int EPI, bool RAGGED>
 __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::WPE, C::WPE))) void gemm_kernel_narrow(const GemmParams p)

@@ -38,7 +38,7 @@ struct SmallParams {
 template <int BM_, int BN_, int WGM_, int WGN_, int S_, bool F8_>
 struct SmallCfg {
     static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, BKB = 128, S = S_, NW = WGM * WGN, NT = NW * 64;
-    static constexpr bool F8 = F8_;
+    static constexpr bool F8 = F8_, ONCE = false;
     static constexpr int ESZ = F8 ? 1 : 2, BK = BKB / ESZ;        // contraction elements per stage
     static constexpr int WTM = BM / WGM, WTN = BN / WGN;
     static constexpr int FR = F8 ? 32 : 16;                       // rows (columns) of an MFMA block
@@ -47,6 +47,23 @@ struct SmallCfg {
     static_assert(A_BYTES % (1024 * NW) == 0 && B_BYTES % (1024 * NW) == 0, "every wave issues the same number of loads");
     static_assert(WTM % FR == 0 && WTN % FR == 0 && S >= 2 && LDS <= 160 * 1024, "LDS");
 };
+
+// The same tile with B fetched past the caches (the non-temporal hint), for a weight matrix that one row of tiles reads once and that
+// will not be there when it is read again.  Weights that take their turn through the 256 MB Infinity Cache leave nothing in it for the
+// next pass, and bringing them in costs a tenth of the rate: 8B block, one row, 87.5 -> 80.3 us, 32 rows 93.1 -> 86.5; 8-bit MLP, 128 rows,
+// 57.3 -> 53.4.  Where they do stay (the same 176 MB of 8-bit weights pass after pass) the hint costs 44.5 -> 55.9, and under 100 MB of
+// weights a layer, layer after layer, it gains 1 % at one row (32.8 -> 32.5).  So matrices from STREAM_BYTES on: no two layers with one of
+// these fit.  Whole lines only: of a line that is fetched in two pieces the second must still find it.
+template <class C>
+struct Once : C {
+    static constexpr bool ONCE = true;
+};
+constexpr int64_t STREAM_BYTES = 96ll << 20;
+template <class C>
+inline bool reads_once(const SmallParams &p)
+{
+    return p.M <= C::BM && (int64_t)p.N * p.K * C::ESZ >= STREAM_BYTES && p.ldb % 128 == 0 && (uintptr_t)p.B % 128 == 0;
+}
 
 // 8-bit k-rows of ROWS bytes: the eight k-rows of a transposing read of two adjacent chunks fall into different bank groups
 template <int ROWS>
@@ -178,6 +195,10 @@ __device__ __forceinline__ void small_contract(SmallAcc<C> &acc, const SmallPara
         if (BKC) next = next == KT ? 0 : next;
         slot_in = slot_in + C::STAGE == C::LDS ? 0u : slot_in + C::STAGE;
     };
+    auto load_b = [&](uint32_t off, const void *from, uint32_t to) {
+        if constexpr (C::ONCE) dl_load16_once(off, from, to);
+        else dl_load16(off, from, to);
+    };
     // part q of Q of the stage's loads; the last part moves on to the next stage
     auto issue_part = [&](int q, int Q) {
         const unsigned char *sa = ga + (int64_t)next * stepa, *sb = gb + (int64_t)next * stepb;
@@ -186,7 +207,7 @@ __device__ __forceinline__ void small_contract(SmallAcc<C> &acc, const SmallPara
         for (int i = 0; i < L; ++i) {
             if (i < q * L / Q || i >= (q + 1) * L / Q) continue;
             if (i < C::LA) dl_load16(offa[i < C::LA ? i : 0], sa, la + (uint32_t)(i * 1024));
-            else dl_load16(offb[i < C::LA ? 0 : i - C::LA], sb, lb + (uint32_t)((i - C::LA) * 1024));
+            else load_b(offb[i < C::LA ? 0 : i - C::LA], sb, lb + (uint32_t)((i - C::LA) * 1024));
         }
         if (q == Q - 1) advance();
     };
@@ -204,7 +225,7 @@ __device__ __forceinline__ void small_contract(SmallAcc<C> &acc, const SmallPara
 #pragma unroll
         for (int i = 0; i < C::LB; ++i) {
             const int at = C::A_BYTES + (wave * C::LB + i) * 1024;
-            if (ckb[i] < have) dl_load16(offb[i], sb, lds0 + slot_in + (uint32_t)at);
+            if (ckb[i] < have) load_b(offb[i], sb, lds0 + slot_in + (uint32_t)at);
             else *reinterpret_cast<u32x4 *>(slot + at) = u32x4{0u, 0u, 0u, 0u};
         }
     };

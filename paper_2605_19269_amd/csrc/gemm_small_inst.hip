@@ -12,6 +12,11 @@ static hipError_t launch_partial(const SmallParams &p, hipStream_t s)
     hipLaunchKernelGGL((gemm_small_partial<C, AK, BKC>), dim3((unsigned)(p.tiles_m * p.tiles_n * p.nsplit)), dim3(C::NT), 0, s, p);
     return hipGetLastError();
 }
+template <class C, bool AK, bool BKC>
+static hipError_t launch_partial_once(const SmallParams &p, hipStream_t s)
+{
+    return reads_once<C>(p) ? launch_partial<Once<C>, AK, BKC>(p, s) : launch_partial<C, AK, BKC>(p, s);
+}
 // Rings (measured at N x K = 28672 x 4096 bf16, 235 MB of weights): 32 rows, stages of 20 KB: two 58 us, three 45, four 48,
 // seven 50 -- past the ~40 KB in flight that the latency of memory asks for, more only queue up; 64 rows, stages of 24 KB:
 // two 62, three 50, six 50.  128 rows: eight waves, one workgroup per CU, four stages of 32 KB (two: 81, four: 58) or, for
@@ -19,14 +24,14 @@ static hipError_t launch_partial(const SmallParams &p, hipStream_t s)
 template <bool BKC, bool F8>
 static hipError_t launch_tile(const SmallPlan &pl, bool ak, const SmallParams &p, hipStream_t s)
 {
-    if (pl.bm == 32) return launch_partial<SmallCfg<32, 128, 1, 4, 3, F8>, true, BKC>(p, s);
-    if (pl.bm == 64) return launch_partial<SmallCfg<64, 128, 1, 4, 3, F8>, true, BKC>(p, s);
+    if (pl.bm == 32) return launch_partial_once<SmallCfg<32, 128, 1, 4, 3, F8>, true, BKC>(p, s);
+    if (pl.bm == 64) return launch_partial_once<SmallCfg<64, 128, 1, 4, 3, F8>, true, BKC>(p, s);
     if (pl.bn == 256) return ak ? launch_partial<SmallCfg<128, 256, 2, 4, 3, F8>, true, BKC>(p, s) : launch_partial<SmallCfg<128, 256, 2, 4, 3, F8>, false, BKC>(p, s);
     return ak ? launch_partial<SmallCfg<128, 128, 2, 4, 4, F8>, true, BKC>(p, s) : launch_partial<SmallCfg<128, 128, 2, 4, 4, F8>, false, BKC>(p, s);
 }
 
 template <class C, bool BKC>
-static hipError_t launch_stream(int mode, const GemmParams &g, const SmallParams &p, hipStream_t s)
+static hipError_t launch_stream_tile(int mode, const GemmParams &g, const SmallParams &p, hipStream_t s)
 {
     const dim3 grid((unsigned)(p.tiles_m * p.tiles_n));
     if (mode == EPI_LINEAR)
@@ -34,6 +39,12 @@ static hipError_t launch_stream(int mode, const GemmParams &g, const SmallParams
     else
         hipLaunchKernelGGL((gemm_small_stream<C, BKC, EPI_SWIGLU_FWD>), grid, dim3(C::NT), 0, s, g, p);
     return hipGetLastError();
+}
+
+template <class C, bool BKC>
+static hipError_t launch_stream(int mode, const GemmParams &g, const SmallParams &p, hipStream_t s)
+{
+    return reads_once<C>(p) ? launch_stream_tile<Once<C>, BKC>(mode, g, p, s) : launch_stream_tile<C, BKC>(mode, g, p, s);
 }
 
 // Three stages (four: 46.2 us at 1 x 28672 x 4096, three 43.1: more in flight only queues up); 64 rows in four waves of 32 x 64 (two of
