@@ -50,10 +50,11 @@ struct SmallCfg {
 
 // The same tile with B fetched past the caches (the non-temporal hint), for a weight matrix that one row of tiles reads once and that
 // will not be there when it is read again.  Weights that take their turn through the 256 MB Infinity Cache leave nothing in it for the
-// next pass, and bringing them in costs a tenth of the rate: 8B block, one row, 87.5 -> 80.3 us, 32 rows 93.1 -> 86.5; 8-bit MLP, 128 rows,
-// 57.3 -> 53.4.  Where they do stay (the same 176 MB of 8-bit weights pass after pass) the hint costs 44.5 -> 55.9, and under 100 MB of
-// weights a layer, layer after layer, it gains 1 % at one row (32.8 -> 32.5).  So matrices from STREAM_BYTES on: no two layers with one of
-// these fit.  Whole lines only: of a line that is fetched in two pieces the second must still find it.
+// next pass, and bringing them in costs a tenth of the rate: 8B block, one row, 87.4 -> 80.3 us, 32 rows 93.1 -> 86.5; 8-bit MLP of 4096 and
+// 14336, 128 rows, layer after layer, 57.3 -> 56.0 (up-projection only; with the hint on all its matrices 53.4).  Where the weights of a lone layer do stay in the
+// cache, pass after pass, the hint costs: the same 8-bit MLP 44.5 -> 50.0, 64 rows bf16 on 3072 and 8192 45.6 -> 49.4 (layer after layer
+// 52.8 -> 50.8).  Under 100 MB of weights a layer it gains 1 % at most.  So matrices from STREAM_BYTES on: no two layers with one of these
+// fit.  Whole lines only: of a line that is fetched in two pieces the second must still find it.
 template <class C>
 struct Once : C {
     static constexpr bool ONCE = true;
