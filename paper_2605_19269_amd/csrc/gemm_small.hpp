@@ -53,7 +53,7 @@ struct SmallCfg {
 // next pass, and bringing them in costs a tenth of the rate: 8B block, one row, 87.4 -> 80.3 us, 32 rows 93.1 -> 86.5; 8-bit MLP of 4096 and
 // 14336, 128 rows, layer after layer, 57.3 -> 56.0 (up-projection only; with the hint on all its matrices 53.4).  Where the weights of a lone layer do stay in the
 // cache, pass after pass, the hint costs: the same 8-bit MLP 44.5 -> 50.0, 64 rows bf16 on 3072 and 8192 45.6 -> 49.4 (layer after layer
-// 52.8 -> 50.8).  Under 100 MB of weights a layer it gains 1 % at most.  So matrices from STREAM_BYTES on: no two layers with one of these
+// 52.8 -> 50.8).  Under 100 MB a layer it gains 1 to 5 % in turn and costs up to 20 % alone.  So matrices from STREAM_BYTES on: no two layers with one of these
 // fit.  Whole lines only: of a line that is fetched in two pieces the second must still find it.
 template <class C>
 struct Once : C {
