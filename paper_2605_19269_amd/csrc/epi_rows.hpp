@@ -145,46 +145,57 @@ __global__ __launch_bounds__(256) void epi_rows_kernel(const GemmParams p, const
     }
 }
 
+// R rows of the RMSNorm backward, EPI_STEP apart from m on, in four columns: what they read is in flight together.  Rows past M read the
+// last row and are dropped.
+constexpr int EPI_STEP = 128;
+template <int R>
+__device__ __forceinline__ void cols_rows(const GemmParams &p, const float *part, int nsplit, int m, int n, f32x4 gm, f32x4 &dg)
+{
+    float rr[R], zz[R];
+    u32x2 c[R], res[R];
+    f32x4 d[R];
+    const float *at[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const int64_t mi = min(m + i * EPI_STEP, p.M - 1);
+        rr[i] = p.rn_r[mi];
+        zz[i] = p.rn_z[mi] * p.rn_zscale;
+        c[i] = *reinterpret_cast<const u32x2 *>(p.rn_c + mi * p.ld_rn_c + n);
+        res[i] = u32x2{0u, 0u};
+        if (p.add) res[i] = *reinterpret_cast<const u32x2 *>(p.add + mi * p.ld_add + n);
+        at[i] = part + mi * p.N + n;
+        d[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    sum_parts(d, at, nsplit, (int64_t)p.M * p.N);
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const int64_t mi = m + i * EPI_STEP;
+        if (mi >= p.M) continue;
+        const f32x4 cn = unpack4(c[i]) * rr[i];
+        f32x4 o = (d[i] * gm - cn * zz[i]) * rr[i];
+        if (p.add) o += unpack4(res[i]);
+        dg += d[i] * cn;
+        *reinterpret_cast<u32x2 *>(reinterpret_cast<uint16_t *>(p.out) + mi * p.ld_out + n) = pack4(o);
+        if (p.out2) *reinterpret_cast<u32x2 *>(p.out2 + mi * p.ld_out2 + n) = pack4(cn * gm);
+    }
+}
+
 // RMSNORM_BWD: 256 rows x 32 columns, 16 waves of eight rows a step, 8 lanes x 4 columns a row.  A workgroup a CU, so what both steps
-// read is in flight together: 1000 x 2048 in four ranges, 49 MB, 13.0 -> 10.8 us.
+// read is in flight together: 1000 x 2048 in four ranges, 49 MB, 13.0 -> 10.8 us.  A wave reads no step that lies past M: with both
+// steps read for every wave a few rows took 11.2 us that take 7.9 (one row, 416 x 3280; 30 rows, 1544 x 5056: 14.9, 12.0).
 template <int EPI>
 __global__ __launch_bounds__(1024) void epi_cols_kernel(const GemmParams p, const float *__restrict__ part, const int nsplit)
 {
-    constexpr int ROWS = 256, COLS = EPI_COLS, STEP = 128, STEPS = ROWS / STEP;
+    constexpr int ROWS = 256, COLS = EPI_COLS;
+    static_assert(ROWS == 2 * EPI_STEP, "two steps");
     __shared__ f32x4 cs[16][COLS / 4];
-    const int rl = threadIdx.x >> 3, cl = threadIdx.x & 7, n = blockIdx.x * COLS + cl * 4;
-    const bool nok = n < p.N;
-    const int64_t plane = (int64_t)p.M * p.N;
+    const int rl = threadIdx.x >> 3, cl = threadIdx.x & 7, n = blockIdx.x * COLS + cl * 4, m = blockIdx.y * ROWS + rl;
     f32x4 dg = {0.f, 0.f, 0.f, 0.f};
-    if (nok) {
+    const int mw = m - (rl & 7);                     // the wave's first row
+    if (n < p.N && mw < p.M) {
         const f32x4 gm = *reinterpret_cast<const f32x4 *>(p.rn_gamma + n);
-        float rr[STEPS], zz[STEPS];
-        u32x2 c[STEPS], res[STEPS];
-        f32x4 d[STEPS];
-        const float *at[STEPS];
-#pragma unroll
-        for (int st = 0; st < STEPS; ++st) {
-            const int m = min((int)blockIdx.y * ROWS + st * STEP + rl, p.M - 1);      // past M: the last row again, dropped below
-            rr[st] = p.rn_r[m];
-            zz[st] = p.rn_z[m] * p.rn_zscale;
-            c[st] = *reinterpret_cast<const u32x2 *>(p.rn_c + (int64_t)m * p.ld_rn_c + n);
-            res[st] = u32x2{0u, 0u};
-            if (p.add) res[st] = *reinterpret_cast<const u32x2 *>(p.add + (int64_t)m * p.ld_add + n);
-            at[st] = part + (int64_t)m * p.N + n;
-            d[st] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-        sum_parts(d, at, nsplit, plane);
-#pragma unroll
-        for (int st = 0; st < STEPS; ++st) {
-            const int m = blockIdx.y * ROWS + st * STEP + rl;
-            if (m >= p.M) continue;
-            const f32x4 cn = unpack4(c[st]) * rr[st];
-            f32x4 o = (d[st] * gm - cn * zz[st]) * rr[st];
-            if (p.add) o += unpack4(res[st]);
-            dg += d[st] * cn;
-            *reinterpret_cast<u32x2 *>(reinterpret_cast<uint16_t *>(p.out) + (int64_t)m * p.ld_out + n) = pack4(o);
-            if (p.out2) *reinterpret_cast<u32x2 *>(p.out2 + (int64_t)m * p.ld_out2 + n) = pack4(cn * gm);
-        }
+        if (mw + EPI_STEP < p.M) cols_rows<2>(p, part, nsplit, m, n, gm, dg);
+        else cols_rows<1>(p, part, nsplit, m, n, gm, dg);
     }
     if (p.colred_mode == ROWRED_NONE) return;
     // column sums: the eight rows of a wave, then the sixteen waves in order
