@@ -107,8 +107,8 @@ inline int splitk_chain(const SplitPlan &pl, int64_t K, bool f8)
 // / 32.9 / 61.7; 1000 x 2048 x 11264: 64.0 / 58.7 / 90.5; 768 x 4096 x 14336: 137 / 110 / 144; 1024 x 4096 x 14336: 150 / 129 /
 // 124, where the large tiles stay.  The small tiles must win by a tenth.  (Two workgroups of 128 x 128 tiles per CU, four
 // waves and two stages each, lie between: 384 x 6144 x 4096 40.6, 128 x 256 38.0; 768 x 4096 x 14336 113.)
-// From SMALL_MODEL_TILES tiles of 256 x 256 on the figures are others: there the small tiles fill the chip with one range or two, and
-// the exchange of that many tiles is what costs:
+// Shapes of SMALL_MODEL_TILES tiles of 256 x 256 and more that these figures leave on shared tiles are priced once more: there the small
+// tiles fill the chip with one range or two, and the exchange of that many tiles is what costs:
 //   launches and epilogue 6; one stage of a 128 x 128 tile 0.57, of a 128 x 256 tile 0.52 and 0.37 more when every CU has one
 //   (they share the L2s), 0.05 for a K-contiguous B; partials as above, but not for one range of 128 x 256 tiles, which all
 //   programs but RMSNORM_BWD run undivided (that one comes with bf16 A B^T);
@@ -116,6 +116,10 @@ inline int splitk_chain(const SplitPlan &pl, int64_t K, bool f8)
 //   straddle tiles 30, and 1.3, 1.75 or 2 times the longest range, as the pieces of 8, 16 or more ranges repeat.
 // Of 110 random shapes that the older figures left on shared tiles those that now take small ones gain 2 to 35 %, 16 % in the mean over
 // all: 1232 x 5568 x 15040 329 -> 213 us, 1072 x 3840 x 11072 176 -> 119, 960 x 5376 x 10432 174 -> 127, 1024 x 8192 x 4096 77 -> 62.
+// A shape that the first figures give small tiles keeps them, and its tile: back on shared tiles its chains would be up to half as long
+// again (fp32 error 12 to 14 % larger) and it would be slower (543 x 8192 x 8192 A B^T 97 us, shared 126; 930 x 6144 x 5632 A B^T 75, 89;
+// faster only at few, 1393 x 4088 x 7608 A B^T 148, 109), and the second figures charge partials for one range of 128 x 128 tiles, which
+// most programs run undivided (99 x 22016 x 4096 8-bit: 24.2, two ranges of 128 x 256 29.4).
 // Shared tiles stay at 2048 x 4096 x 14336 (179, small 189), 1440 x 4096 x 14336 (164, 181), 384 x 16384 x 14336 A B^T (189, 228).
 struct SmallPlan {
     int bm, bn;    // the tile: 32, 64 or 128 rows, 128 (or, with 128 rows, 256) columns
@@ -139,8 +143,7 @@ inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_c
     if (big.chunks == 0 || big.first != 0) return none;
     const int64_t esz = f8 ? 1 : 2, stages = (K * esz + 127) / 128;
     const int64_t budget = (int64_t)splitk_bytes(big) / (M * N * 4);              // ranges whose partials fit
-    const bool many = big.tail >= SMALL_MODEL_TILES;
-    auto offer = [&](int bm, int bn, double stage_us, double shared_us = 0.0) {
+    auto offer = [&](int bm, int bn, double stage_us, double shared_us = 0.0, bool undivided = false) {      // undivided: if in one range
         const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
         int64_t ns = SPLITK_CUS / tiles;
         if (ns > SMALL_MAX_SPLIT) ns = SMALL_MAX_SPLIT;
@@ -148,21 +151,19 @@ inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_c
         if (ns > budget) ns = budget;
         if (ns < 1) return none;
         const double stage = stage_us + shared_us * (double)(tiles * ns) / (double)SPLITK_CUS;
-        const bool undivided = many && ns == 1 && bn == 256 && (f8 || !b_k_contiguous);
-        return SmallPlan{bm, bn, (int)ns, 6.0 + stage * (double)((stages + ns - 1) / ns) + (undivided ? 0.0 : (double)(ns * M * N) * 8.0 / 5e6), false};
+        return SmallPlan{bm, bn, (int)ns, 6.0 + stage * (double)((stages + ns - 1) / ns) + (undivided && ns == 1 ? 0.0 : (double)(ns * M * N) * 8.0 / 5e6), false};
     };
     if (M <= 64 && a_k_contiguous) return M <= 32 ? offer(32, 128, 0.62) : offer(64, 128, 0.62);
-    if (many) {
-        const SmallPlan narrow = offer(128, 128, 0.57), wide = offer(128, 256, b_k_contiguous ? 0.57 : 0.52, 0.37);
-        const SmallPlan best = wide.nsplit == 0 || (narrow.nsplit != 0 && narrow.us <= wide.us) ? narrow : wide;
-        return best.nsplit != 0 && best.us <= 0.95 * shared_tiles_us(big, K, f8) ? best : none;
-    }
     const SmallPlan narrow = offer(128, 128, 0.57), wide = offer(128, 256, 0.83);
     // one range: most programs run undivided and pay no partials (plan_route), and all take the same plan
     auto cost = [&](const SmallPlan &p) { return p.us - (p.nsplit == 1 ? 0.5 * (double)(M * N) * 8.0 / 5e6 : 0.0); };
     const SmallPlan best = wide.nsplit == 0 || (narrow.nsplit != 0 && cost(narrow) <= cost(wide)) ? narrow : wide;
     const double t_big = 0.83 * 2.0 * splitk_longest_stages(big, K, f8) + 12.0 + 0.019 * big.chunks * big.stride + (big.pieces > 1 ? 25.0 : 0.0);
-    return best.nsplit != 0 && best.us <= 0.9 * t_big ? best : none;
+    if (best.nsplit != 0 && best.us <= 0.9 * t_big) return best;
+    if (big.tail < SMALL_MODEL_TILES) return none;
+    const SmallPlan wide2 = offer(128, 256, b_k_contiguous ? 0.57 : 0.52, 0.37, f8 || !b_k_contiguous);
+    const SmallPlan best2 = wide2.nsplit == 0 || (narrow.nsplit != 0 && narrow.us <= wide2.us) ? narrow : wide2;
+    return best2.nsplit != 0 && best2.us <= 0.95 * shared_tiles_us(big, K, f8) ? best2 : none;
 }
 
 // Undivided launches with small tiles, rows x columns of the tile: for what neither plan above divides (a short

@@ -54,6 +54,18 @@ def test_chains_are_as_short_as_the_pieces_of_a_shared_tile(lib):
     assert straddling > 20
 
 
+@pytest.mark.parametrize("M,N,K,f8", [(8144, 720, 6448, False), (12088, 384, 8448, False), (1000, 6016, 7280, False), (4000, 1520, 4528, False), (543, 8192, 8192, False),
+                                      (736, 8016, 16208, True)])
+def test_no_longer_chains_on_shared_tiles(lib, M, N, K, f8):
+    """96 tiles in 256 ranges, B K-contiguous: the longest range is 1.4 to 1.5 times as long as the chains that small tiles fold at."""
+    first, tail, chunks, pieces = small_plan.shared(lib, M, N, K, f8)
+    stages = -(-K * (1 if f8 else 2) // 128)
+    assert (first, tail, chunks, pieces) == (0, 96, 256, 2)
+    for prog, wide in ALL:
+        r = small_plan.Route(lib, M, N, K, f8, True, True, prog, wide, True)
+        assert r.kind in ("direct", "divided") and r.order[1] < 0.72 * -(-tail * stages // chunks), (r.kind, r.order)
+
+
 @pytest.mark.parametrize("tiles_m", [1, 2, 3, 7, 8, 9, 16, 21])
 def test_small_tiles_know_the_xcd_of_their_large_tile(lib, tiles_m):
     for tiles_n in (1, 2, 3, 5, 8, 13, 40):
