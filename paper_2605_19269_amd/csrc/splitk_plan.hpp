@@ -120,6 +120,9 @@ inline int splitk_chain(const SplitPlan &pl, int64_t K, bool f8)
 // again (fp32 error 12 to 14 % larger) and it would be slower (543 x 8192 x 8192 A B^T 97 us, shared 126; 930 x 6144 x 5632 A B^T 75, 89;
 // faster only at few, 1393 x 4088 x 7608 A B^T 148, 109), and the second figures charge partials for one range of 128 x 128 tiles, which
 // most programs run undivided (99 x 22016 x 4096 8-bit: 24.2, two ranges of 128 x 256 29.4).
+// So does A B^T on shared tiles whose K is no whole number of 128-byte lines: a stage's row of B then lies in two lines, and small tiles
+// fetch more rows for what they compute (1128 x 4160 x 12648 with transposed A 195 us, small 233, 768 x 6848 x 7184 8-bit 61, 70; of 150 shapes that
+// would move, storing D, the 22 such gain 1 % in the mean, the others 23 %).
 // Shared tiles stay at 2048 x 4096 x 14336 (179, small 189), 1440 x 4096 x 14336 (164, 181), 384 x 16384 x 14336 A B^T (189, 228).
 struct SmallPlan {
     int bm, bn;    // the tile: 32, 64 or 128 rows, 128 (or, with 128 rows, 256) columns
@@ -160,7 +163,7 @@ inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_c
     const SmallPlan best = wide.nsplit == 0 || (narrow.nsplit != 0 && cost(narrow) <= cost(wide)) ? narrow : wide;
     const double t_big = 0.83 * 2.0 * splitk_longest_stages(big, K, f8) + 12.0 + 0.019 * big.chunks * big.stride + (big.pieces > 1 ? 25.0 : 0.0);
     if (best.nsplit != 0 && best.us <= 0.9 * t_big) return best;
-    if (big.tail < SMALL_MODEL_TILES) return none;
+    if (big.tail < SMALL_MODEL_TILES || (b_k_contiguous && K * esz % 128)) return none;
     const SmallPlan wide2 = offer(128, 256, b_k_contiguous ? 0.57 : 0.52, 0.37, f8 || !b_k_contiguous);
     const SmallPlan best2 = wide2.nsplit == 0 || (narrow.nsplit != 0 && narrow.us <= wide2.us) ? narrow : wide2;
     return best2.nsplit != 0 && best2.us <= 0.95 * shared_tiles_us(big, K, f8) ? best2 : none;

@@ -36,6 +36,17 @@ def test_shared_tiles_where_they_are_faster(plans, M, N, K, f8, tb):
     assert small_plan.Route(plans, M, N, K, f8, True, tb, "linear", True, True).kind == "shared"
 
 
+# A B^T whose K is no whole number of lines: on shared tiles, on small ones (RMSNorm backward), microseconds
+RAGGED = [(1128, 4160, 12648, False, True), (2201, 1808, 15264, False, False), (244, 24768, 5552, True, False), (768, 6848, 7184, True, True)]   # 201 248, 199 234, 74 88, 70 85
+
+
+@pytest.mark.parametrize("M,N,K,f8,ta", RAGGED)
+def test_rows_of_broken_lines_stay_shared(plans, M, N, K, f8, ta):
+    for prog, wide in (("linear", False), ("linear", True), ("swiglu_bwd", True), ("accum", False), ("rmsnorm_bwd", False)):
+        assert small_plan.Route(plans, M, N, K, f8, not ta, True, prog, wide, True).kind == "shared"
+        assert small_plan.Route(plans, M, N, K // 128 * 128, f8, not ta, True, prog, wide, True).kind in ("direct", "divided")
+
+
 # one and two ranges; edges of the 128-row, 128- and 256-column tiles; K past a whole stage; all layouts
 GPU = [(1281, 3720, 4104, False, False, False), (2304, 2304, 4160, False, False, True), (2040, 2312, 6152, False, True, False), (3832, 1288, 6152, False, True, True),
        (1537, 3856, 4112, True, False, False), (2048, 2304, 8208, True, False, True)]
