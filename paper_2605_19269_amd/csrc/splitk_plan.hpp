@@ -243,13 +243,16 @@ inline DirectPlan plan_direct(int64_t M, int64_t N, int64_t K, bool f8, bool a_k
 // One round of 129 to 192 large tiles is one round of three quarters the length: 2560 x 3776 x 512 19.3 -> 15.6 us, 1728 x 5184 x
 // 8192 160 -> 136, 2048 x 6144 x 4096 92 -> 82 (the large tiles leave a quarter of the chip idle, so that the rest clocks higher);
 // so are two and a bit (7680 x 4608 x 1024, 2.1 rounds in three: 80.7 -> 70.6).  Where the rounds come out alike the large tiles
-// are ahead by 3 to 7 % (1728 x 23552 x 4096: 295, 303).  `direct`: modelled time of the small tiles that the shape would take.
+// are ahead by 3 to 7 % (1728 x 23552 x 4096: 295, 303).  Half a round of them or less stands against one round of 128 x 256 tiles, which
+// spread over twice as many compute units: 2996 x 1288 x 7664 108 us, narrow 123, 11518 x 320 x 13128 192, 272; 30 such are 3 to
+// 30 % slower, 14 % in the mean.  `direct`: modelled time of the small tiles that the shape would take.
 // Model in microseconds, per round: fill and epilogue, then a pair of K-steps, which costs less the fewer of the compute units
 // draw power; of 54 shapes on large tiles it takes 28, all of them faster (by 13 % in the mean), and leaves 4 that would gain 2 %.
 constexpr int64_t NARROW_TILE_N = 192;
 inline bool narrow_is_faster(int64_t M, int64_t N, int64_t K, double direct)
 {
     if (M <= 0 || N <= 0 || K <= 0) return false;
+    if (((M + PLAN_TILE_M - 1) / PLAN_TILE_M) * ((N + NARROW_TILE_N - 1) / NARROW_TILE_N) <= SPLITK_CUS / 2) return false;
     const double pairs = (double)((K + 63) / 64);
     auto us = [&](int64_t bn, double round, double pair, double idle) {
         const int64_t tiles = ((M + PLAN_TILE_M - 1) / PLAN_TILE_M) * ((N + bn - 1) / bn), rounds = (tiles + SPLITK_CUS - 1) / SPLITK_CUS;

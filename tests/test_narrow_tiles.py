@@ -42,6 +42,16 @@ def test_not_taken_where_slower(narrow, M, N, K):
     assert not narrow(M, N, K) and not narrow(M, N, K, SWIGLU_FWD)
 
 
+# one round of 128 x 256 tiles that half a round of narrow ones would replace: microseconds on either
+HALF = [(2996, 1288, 7664), (7559, 528, 13216), (11518, 320, 13128), (256, 16576, 8640), (1670, 2320, 12904), (193, 17176, 11464)]   # 108 123, 156 185, 192 272, 116 126, 151 192, 177 202
+
+
+@pytest.mark.parametrize("M,N,K", HALF)
+def test_not_taken_for_half_a_round(narrow, M, N, K):
+    for prog in (LINEAR, SWIGLU_FWD):
+        assert not narrow(M, N, K, prog, ws=False)
+
+
 def test_a_shape_that_a_workspace_divides_stays_divided(narrow):
     assert not narrow(1000, 2048, 11264) and not narrow(2048, 4096, 14336)
 
