@@ -24,8 +24,9 @@
  *  - "row" means a row of the GEMM output (a token): a row scale multiplies
  *    row i by r[i], a row reduction sums over the columns of row i.
  *  - Alignment: every matrix pointer 16-byte aligned, every ld a multiple of 8
- *    elements; vectors 4-byte aligned.  Every ld is at most 4194304 elements
- *    (CODA_ERR_SHAPE beyond that: per-lane offsets are formed in 32 bits).
+ *    elements; vectors 4-byte aligned unless the op says more.  Every ld is at
+ *    most 4194304 elements (CODA_ERR_SHAPE beyond that: per-lane offsets are
+ *    formed in 32 bits).
  *  - Errors are return codes; on any error nothing has been enqueued.
  *  - Outputs must not alias inputs, except the in/out buffer of ACCUM_F32.
  */
@@ -117,7 +118,7 @@ typedef enum coda_epi_kind {
     /* Pairwise, width unchanged (Kernels 1, 7: O = RoPE(D)): rotate adjacent column pairs
        (2p, 2p+1) of the first i1 = rope_cols columns by the angle of (position of row i,
        frequency f = p mod (head_dim/2)):  v'[2p] = x0*cos - x1*sin,  v'[2p+1] = x0*sin + x1*cos.
-       in: f32 cos table [T x head_dim/2] (dense), in2: f32 sin table (same shape),
+       in: f32 cos table [T x head_dim/2] (dense, 8-byte aligned), in2: f32 sin table (likewise),
        in3: int32 pos[M], i0 = head_dim (multiple of 8), i1 = rope_cols (multiple of 8, <= N),
        ld_in = T, the number of table rows (T * head_dim/2 < 2^31).  A position outside [0, T) is
        clamped to the nearest table row (never read out of bounds).  Columns >= rope_cols pass through.

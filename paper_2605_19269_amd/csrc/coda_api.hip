@@ -86,7 +86,7 @@ coda_status parse_program(const coda_epi_op *prog, int32_t n_ops, int64_t N, Par
             if (stage > 1 || pair || rmsbwd) return CODA_ERR_PROGRAM;
             if ((st = check_vec(op.in)) != CODA_OK || (st = check_vec(op.in2)) != CODA_OK || (st = check_vec(op.in3)) != CODA_OK)
                 return st;
-            if ((reinterpret_cast<uintptr_t>(op.in) & 7u) || (reinterpret_cast<uintptr_t>(op.in2) & 7u)) return CODA_ERR_ALIGN;
+            if (reinterpret_cast<uintptr_t>(op.in) % coda::ROPE_TABLE_ALIGN || reinterpret_cast<uintptr_t>(op.in2) % coda::ROPE_TABLE_ALIGN) return CODA_ERR_ALIGN;
             if (op.i0 <= 0 || (op.i0 & 7) || op.i0 > INT32_MAX || op.i1 < 0 || (op.i1 & 7) || op.i1 > N || op.ld_in <= 0 ||
                 op.ld_in > INT32_MAX / (op.i0 / 2))    // T rows of head_dim / 2 entries, indexed in 31 bits
                 return CODA_ERR_SHAPE;

@@ -39,6 +39,8 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+constexpr int ROPE_TABLE_ALIGN = 8;      // what coda_gemm asks of the cos / sin tables
+typedef __attribute__((ext_vector_type(4), aligned(ROPE_TABLE_ALIGN))) uint32_t rope_quad;   // four table entries
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 
 enum EpiMode : int { EPI_LINEAR = 0, EPI_SWIGLU_FWD = 1, EPI_SWIGLU_BWD = 2, EPI_ACCUM = 3, EPI_RMSNORM_BWD = 4 };
@@ -772,8 +774,8 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
 #pragma unroll
             for (int it = 0; it < 4; ++it) {                           // 8 rows x 128 bytes per access
                 const int src = __shfl(trow, it * 8 + (lane >> 3), 64) + f0;
-                tc[it] = *reinterpret_cast<const u32x4 *>(p.rope_cos + src);
-                ts[it] = *reinterpret_cast<const u32x4 *>(p.rope_sin + src);
+                tc[it] = *reinterpret_cast<const rope_quad *>(p.rope_cos + src);
+                ts[it] = *reinterpret_cast<const rope_quad *>(p.rope_sin + src);
             }
         };
         gather(0);

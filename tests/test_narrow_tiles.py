@@ -14,11 +14,16 @@ LINEAR, SWIGLU_FWD, SWIGLU_BWD, ACCUM, RMSNORM_BWD = range(5)
 
 
 @pytest.fixture(scope="module")
-def narrow(tmp_path_factory):
+def host(tmp_path_factory):
     so = str(tmp_path_factory.mktemp("narrow") / "narrow_plan_host.so")
-    subprocess.run([small_plan.HIPCC, "--offload-host-only", "-O1", "-std=c++17", "-fPIC", "-shared", "-o", so,
+    subprocess.run([small_plan.HIPCC, "--offload-host-only", "-O1", "-std=c++17", "-fPIC", "-shared", "-Wno-inline-asm", "-o", so,
                     os.path.join(small_plan.ROOT, "tests", "narrow_plan_host.hip")], check=True, capture_output=True)
-    fn = ctypes.CDLL(so).host_narrow
+    return ctypes.CDLL(so)
+
+
+@pytest.fixture(scope="module")
+def narrow(host):
+    fn = host.host_narrow
     fn.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 6
     return lambda M, N, K, prog=LINEAR, f8=False, ta=False, tb=False, wide=False, ws=True: bool(
         fn(M, N, K, int(f8), int(not ta), int(tb), prog, int(wide), int(ws)))
@@ -109,3 +114,36 @@ def test_programs_on_narrow_tiles(narrow, M, N, K):
         ref = D.clone()
         ref[:, 0:cols:2], ref[:, 1:cols:2] = D[:, 0:cols:2] * c - D[:, 1:cols:2] * s, D[:, 0:cols:2] * s + D[:, 1:cols:2] * c
         check(Y, ref, "RoPE, heads of %d" % hd)
+
+
+def test_rope_tables_are_read_at_the_alignment_that_is_asked_of_them(host):
+    from paper_2605_19269_amd import coda
+    P, X, W = 0x10000, coda.coda_mat(0x10000, 0, 32, 32, 0, coda.CODA_BF16), coda.coda_mat(0x10000, 32, 64, 64, 0, coda.CODA_BF16)      # no rows: nothing is launched
+    st = coda.coda_epi_op(coda.CODA_EPI_STORE, out=P, ld_out=64)
+    for at in range(0, 32, 4):
+        for cos, sin in ((P + at, P), (P, P + at)):
+            rope = coda.coda_epi_op(coda.CODA_EPI_ROPE, in_=cos, in2=sin, in3=P, ld_in=128, i0=16, i1=32)
+            assert coda.coda_gemm_raw(None, 0, 64, 32, X, W, [rope, st]) == (coda.CODA_ERR_ALIGN if at % host.host_rope_align() else coda.CODA_OK)
+
+
+# narrow tiles; 256 x 256 tiles, whose heads of 64 and 128 take the same loads
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(2560, 3840, 512), (1409, 6152, 72), (8192, 4096, 64)])
+@pytest.mark.parametrize("hd", [128, 64, 48, 8])
+def test_rope_tables_off_sixteen_bytes(narrow, M, N, K, hd):
+    from paper_2605_19269_amd import coda
+    assert narrow(M, N, K) == (M != 8192)
+    g = torch.Generator(device="cuda").manual_seed(M + N + hd)
+    A, B = (torch.randn(s, device="cuda", generator=g).bfloat16() for s in ((M, K), (K, N)))
+    pos = torch.randint(0, 70, (M,), device="cuda", dtype=torch.int32, generator=g)
+    tables = [torch.randn(70 * hd // 2 + 4, device="cuda", generator=g) for _ in range(2)]
+    off = [t[2:2 + 70 * hd // 2].view(70, hd // 2) for t in tables]
+    outs = []
+    for (cos, sin), at in ((off, 8), ([t.clone() for t in off], 0)):
+        assert (cos.data_ptr() % 16, sin.data_ptr() % 16) == (at, at)
+        Y = G.Guarded(M, N, torch.bfloat16, pad_cols=8)
+        coda.coda_gemm(A, B, [coda.rope(cos, sin, pos, hd, N // hd * hd), coda.store(Y.t)])
+        torch.cuda.synchronize()
+        Y.check_guards(); Y.written()
+        outs.append(Y.t.clone())
+    assert torch.equal(*outs)
