@@ -48,22 +48,15 @@ struct SmallCfg {
     static_assert(WTM % FR == 0 && WTN % FR == 0 && S >= 2 && LDS <= 160 * 1024, "LDS");
 };
 
-// The same tile with B fetched past the caches (the non-temporal hint), for a weight matrix that one row of tiles reads once and that
-// will not be there when it is read again.  Weights that take their turn through the 256 MB Infinity Cache leave nothing in it for the
-// next pass, and bringing them in costs a tenth of the rate: 8B block, one row, 87.4 -> 80.3 us, 32 rows 93.1 -> 86.5; 8-bit MLP of 4096 and
-// 14336, 128 rows, layer after layer, 57.3 -> 56.0 (up-projection only; with the hint on all its matrices 53.4).  Where the weights of a lone layer do stay in the
-// cache, pass after pass, the hint costs: the same 8-bit MLP 44.5 -> 50.0, 64 rows bf16 on 3072 and 8192 45.6 -> 49.4 (layer after layer
-// 52.8 -> 50.8).  Under 100 MB a layer it gains 1 to 5 % in turn and costs up to 20 % alone.  So matrices from STREAM_BYTES on: no two layers with one of these
-// fit.  Whole lines only: of a line that is fetched in two pieces the second must still find it.
+// The same tile with B fetched past the caches, where reads_once() says so
 template <class C>
 struct Once : C {
     static constexpr bool ONCE = true;
 };
-constexpr int64_t STREAM_BYTES = 96ll << 20;
-template <class C>
-inline bool reads_once(const SmallParams &p)
+template <class C, bool BKC>
+inline bool reads_once(const SmallParams &p, int ranges)
 {
-    return p.M <= C::BM && (int64_t)p.N * p.K * C::ESZ >= STREAM_BYTES && p.ldb % 128 == 0 && (uintptr_t)p.B % 128 == 0;
+    return reads_once(p.M, p.N, p.K, C::F8, BKC, C::BM, ranges, p.ldb, (uint64_t)(uintptr_t)p.B);
 }
 
 // 8-bit k-rows of ROWS bytes: the eight k-rows of a transposing read of two adjacent chunks fall into different bank groups

@@ -15,7 +15,7 @@ static hipError_t launch_partial(const SmallParams &p, hipStream_t s)
 template <class C, bool AK, bool BKC>
 static hipError_t launch_partial_once(const SmallParams &p, hipStream_t s)
 {
-    return reads_once<C>(p) ? launch_partial<Once<C>, AK, BKC>(p, s) : launch_partial<C, AK, BKC>(p, s);
+    return reads_once<C, BKC>(p, p.nsplit) ? launch_partial<Once<C>, AK, BKC>(p, s) : launch_partial<C, AK, BKC>(p, s);
 }
 // Rings (measured at N x K = 28672 x 4096 bf16, 235 MB of weights): 32 rows, stages of 20 KB: two 58 us, three 45, four 48,
 // seven 50 -- past the ~40 KB in flight that the latency of memory asks for, more only queue up; 64 rows, stages of 24 KB:
@@ -44,7 +44,7 @@ static hipError_t launch_stream_tile(int mode, const GemmParams &g, const SmallP
 template <class C, bool BKC>
 static hipError_t launch_stream(int mode, const GemmParams &g, const SmallParams &p, hipStream_t s)
 {
-    return reads_once<C>(p) ? launch_stream_tile<Once<C>, BKC>(mode, g, p, s) : launch_stream_tile<C, BKC>(mode, g, p, s);
+    return reads_once<C, BKC>(p, 1) ? launch_stream_tile<Once<C>, BKC>(mode, g, p, s) : launch_stream_tile<C, BKC>(mode, g, p, s);
 }
 
 // Three stages (four: 46.2 us at 1 x 28672 x 4096, three 43.1: more in flight only queues up); 64 rows in four waves of 32 x 64 (two of

@@ -35,7 +35,8 @@ static hipError_t direct_tile(int tile, const GemmParams &g, const SmallParams &
     if constexpr (EPI == EPI_ACCUM)
         if (tile == DIRECT_128x128_PAIR) return launch_direct<SmallCfg<128, 128, 2, 2, 2, F8>, AK, BKC, EPI, false>(g, p, s);
     if constexpr (F8 && AK && (EPI == EPI_LINEAR || EPI == EPI_SWIGLU_FWD))
-        if (tile == DIRECT_128x128 && reads_once<SmallCfg<128, 128, 4, 2, 4, F8>>(p)) return launch_direct<Once<SmallCfg<128, 128, 4, 2, 4, F8>>, AK, BKC, EPI, true>(g, p, s);
+        if (tile == DIRECT_128x128 && reads_once<SmallCfg<128, 128, 4, 2, 4, F8>, BKC>(p, 1))
+            return launch_direct<Once<SmallCfg<128, 128, 4, 2, 4, F8>>, AK, BKC, EPI, true>(g, p, s);
     if (tile == DIRECT_128x128) return launch_direct<SmallCfg<128, 128, 4, 2, 4, F8>, AK, BKC, EPI, true>(g, p, s);
     if (tile == DIRECT_128x256) return launch_wide<SmallCfg<128, 256, 2, 4, 3, F8>, AK, BKC, EPI>(g, p, s);
     return hipErrorInvalidConfiguration;             // a tile that the plan does not give this program

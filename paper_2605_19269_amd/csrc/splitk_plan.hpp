@@ -263,6 +263,30 @@ inline bool narrow_is_faster(int64_t M, int64_t N, int64_t K, double direct)
     return narrow < 0.97 * (direct < large ? direct : large);
 }
 
+// Whether small tiles fetch B past the caches (the non-temporal hint): a weight matrix that one row of tiles reads once, if it will not be
+// there when it is read again.  Weights that take their turn through the 256 MB Infinity Cache leave nothing in it for the next pass, and
+// bringing them in costs a tenth of the rate.  Whole lines only: of a line that is fetched in two pieces the second must still find it.
+// From NEVER_STAYS_BYTES on both sides bear it out: the same matrix again and again gains up to 20 %, with other weights in between 2 to 16 %.
+// Under that the hint is a bet that other weights come in between, as in a model of several layers.  What it gains then, and what it
+// costs a lone matrix that would have stayed, over some 350 calls on 96 to 258 MiB (microseconds, ordinary -> hint):
+//   a workgroup for at least 7/8 of the compute units, up to 32 rows: 2 to 14 % faster; alone 7 % faster to 11 % slower
+//     (1 x 28672 x 4096 42.2 -> 38.6, alone 36.3 -> 37.4; 32 x 14336 x 4096 A B^T 26.5 -> 23.9, 22.0 -> 22.9)
+//   64 rows in one range: 4 to 14 % faster; 4 % faster to 13 % slower (64 x 28672 x 4096 45.3 -> 43.5, 37.5 -> 42.4)
+//   8-bit 128 x 128 tiles, A B^T: 3 to 15 % faster; up to 27 % slower (96 x 28672 x 4096 28.4 -> 25.8, 21.6 -> 26.3)
+// Ordinary loads where what is lost alone is not made good: fewer workgroups, whose loads wait longer (2 to 7 %, 8-bit up to 11; 4 to 43 %
+// slower alone: 1 x 22016 x 4096 35.6 -> 34.9, 29.7 -> 33.8, 64 x 18432 x 4608 44.5 -> 43.3, 29.9 -> 41.9); 64 rows in several ranges (64 x 14336 x 4096
+// 29.1 -> 29.7, 25.2 -> 29.1); 8-bit A B on 128 x 128 tiles (2 to 10 %; up to 38 % slower: 128 x 28672 x 4096 33.4 -> 31.2, 23.2 -> 28.3).  bf16
+// at 65 to 128 rows gains nothing in turn either.
+constexpr int64_t ONCE_BYTES = 96ll << 20, NEVER_STAYS_BYTES = 280ll << 20;
+inline bool reads_once(int64_t M, int64_t N, int64_t K, bool f8, bool b_k_contiguous, int bm, int ranges, int64_t ldb_bytes, uint64_t b_address)
+{
+    const int64_t bytes = N * K * (f8 ? 1 : 2), workgroups = (N + 127) / 128 * ranges;
+    if (M > bm || ldb_bytes % 128 || b_address % 128 || (bm == 128 && !f8)) return false;
+    if (bytes >= NEVER_STAYS_BYTES) return true;
+    if (bytes < ONCE_BYTES || workgroups < SPLITK_CUS - SPLITK_CUS / 8) return false;
+    return bm == 32 || (bm == 64 ? ranges == 1 : b_k_contiguous);
+}
+
 // Route of a call.  The order of the additions behind an element must not depend on the program, so what divides the
 // contraction is decided by the sizes, operand type and layouts alone:
 //   whole (of 256 or 192 columns) or undivided small tiles, chain INT32_MAX: the MFMAs of a tile along K from the place that rot_cols says, the same

@@ -33,6 +33,12 @@ __attribute__((visibility("default"))) void host_split_plan(int64_t M, int64_t N
     plan[0] = pl.first; plan[1] = pl.tail; plan[2] = pl.chunks; plan[3] = pl.pieces;
 }
 
+// whether tiles of bm rows in `ranges` ranges fetch B past the caches
+__attribute__((visibility("default"))) int host_reads_once(int64_t M, int64_t N, int64_t K, int f8, int bkc, int bm, int ranges, int64_t ldb_bytes, uint64_t at)
+{
+    return coda::reads_once(M, N, K, f8 != 0, bkc != 0, bm, ranges, ldb_bytes, at);
+}
+
 // whether tile_xcd() inverts tile_coords() on a grid of tiles
 __attribute__((visibility("default"))) int host_tile_xcd_ok(int tiles_m, int tiles_n)
 {
