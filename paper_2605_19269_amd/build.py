@@ -6,8 +6,8 @@ Each translation unit is compiled to an object under paper_2605_19269_amd/_build
 (in parallel).  libcoda.so is the product: it exports exactly what include/coda.h declares.
 libcoda_bench.so holds what only the measurement needs (the unfused baseline kernels of
 include/coda_unfused.h and the MFMA-only calibration loops of include/coda_calib.h) and links
-nothing of the product.  _binding.so is the C half of coda.py (host code, linked to libcoda.so beside it).  hipcc
-cross-compiles for gfx950 without a GPU present.
+nothing of the product.  _binding.<interpreter>.so is the C half of coda.py (host code, linked to libcoda.so beside it; it takes the
+interpreter's headers, Python.h).  hipcc cross-compiles for gfx950 without a GPU present.
 """
 import concurrent.futures
 import os
@@ -21,10 +21,9 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libcoda.so")
 LIB_BENCH = os.path.join(HERE, "libcoda_bench.so")
-BINDING = os.path.join(HERE, "_binding.so")
+BINDING = os.path.join(HERE, "_binding" + sysconfig.get_config_var("EXT_SUFFIX"))      # named for the interpreter that it is built for: no other loads it
 RESOURCES = os.path.join(HERE, "libcoda.resources.txt")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-CXX = os.environ.get("CXX", "g++")
 
 # -packed-fp32-ops is switched off: the compiler must not form packed fp32 VALU ops.
 # -fvisibility=hidden: only the entry points marked CODA_API in the headers are exported.
@@ -118,10 +117,10 @@ def _build_binding(force):
     deps = [src, os.path.join(os.path.dirname(HERE), "include", "coda.h")]
     if not force and os.path.exists(BINDING) and all(os.path.getmtime(d) <= os.path.getmtime(BINDING) for d in deps):
         return
-    r = subprocess.run([CXX, "-O2", "-std=c++17", "-Wall", "-fPIC", "-shared", "-fvisibility=hidden", "-I", sysconfig.get_paths()["include"], src,
+    r = subprocess.run([HIPCC, "-x", "c++", "-O2", "-std=c++17", "-Wall", "-fPIC", "-shared", "-fvisibility=hidden", "-I", sysconfig.get_paths()["include"], src,
                         "-o", BINDING, "-L", HERE, "-l:libcoda.so", "-Wl,-rpath,$ORIGIN"], capture_output=True, text=True)
     if r.returncode != 0:
-        raise RuntimeError("%s failed on binding.cpp:\n%s" % (CXX, r.stdout + r.stderr))
+        raise RuntimeError("hipcc failed on binding.cpp:\n" + r.stdout + r.stderr)
 
 
 def build(force=False, jobs=None):

@@ -10,6 +10,7 @@ a second library, libcoda_bench.so, loaded here as well.
 """
 import ctypes
 import os
+import sysconfig
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libcoda.so")
@@ -23,8 +24,9 @@ LIB_BENCH_PATH = os.path.join(_HERE, "libcoda_bench.so")
 if not os.path.exists(LIB_BENCH_PATH):
     raise ImportError("libcoda_bench.so is not built (%s). Build it with `python -m paper_2605_19269_amd.build`." % LIB_BENCH_PATH)
 
-if not os.path.exists(os.path.join(_HERE, "_binding.so")):
-    raise ImportError("_binding.so is not built (%s). Build it with `python -m paper_2605_19269_amd.build`." % _HERE)
+_BINDING_PATH = os.path.join(_HERE, "_binding" + sysconfig.get_config_var("EXT_SUFFIX"))
+if not os.path.exists(_BINDING_PATH):
+    raise ImportError("the C half of the binding is not built for this interpreter (%s). Build it with `python -m paper_2605_19269_amd.build`." % _BINDING_PATH)
 
 _lib = ctypes.CDLL(LIB_PATH)
 _blib = ctypes.CDLL(LIB_BENCH_PATH)

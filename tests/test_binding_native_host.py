@@ -1,6 +1,8 @@
 """The C half of the Python binding against the ctypes structures it stands for, without a GPU: the same bytes, the same refusals, and
 unusual arguments handed on to ctypes."""
 import ctypes
+import importlib.machinery
+import os
 
 import pytest
 import torch
@@ -73,3 +75,10 @@ def test_calls_take_every_form_of_argument():
         coda.coda_row_finalize(out, 1.0, 1, sum_out=out, stream=0)
     with pytest.raises(coda.CodaError):
         coda.coda_row_finalize(out, 4, 1, stream=0)                                      # no output
+
+
+def test_the_extension_is_that_of_this_interpreter():
+    from paper_2605_19269_amd import build
+    suffix = importlib.machinery.EXTENSION_SUFFIXES[0]                                   # .cpython-<version>-<platform>.so
+    assert "cpython" in suffix and coda._binding.__file__.endswith("_binding" + suffix)
+    assert os.path.samefile(coda._binding.__file__, build.BINDING)
