@@ -53,8 +53,8 @@ PyObject *op(PyObject *, PyObject *const *a, Py_ssize_t n)
     if (i0 < 0 || i1 < 0) return nullptr;
     if (i0 || i1) {
         if (!PyLong_Check(a[10]) || !PyLong_Check(a[11])) return PyErr_Format(PyExc_TypeError, "int expected");
-        v.i0 = PyLong_AsLongLong(a[10]);
-        v.i1 = PyLong_AsLongLong(a[11]);
+        v.i0 = (int64_t)PyLong_AsUnsignedLongLongMask(a[10]);        // past 64 bits: as a ctypes field takes it
+        v.i1 = (int64_t)PyLong_AsUnsignedLongLongMask(a[11]);
     }
     if (PyErr_Occurred()) return nullptr;
     const void **const at[7] = {(const void **)&v.in, (const void **)&v.out, (const void **)&v.out2, (const void **)&v.in2, (const void **)&v.in3,

@@ -54,6 +54,15 @@ def test_ops_hold_pointers_pitches_and_tensors():
             bad()
 
 
+@pytest.mark.parametrize("n", [-1, 0, True, 2 ** 63 - 1, 2 ** 63, 2 ** 64 - 8, 2 ** 64 + 128, -2 ** 63, -2 ** 70 - 3])
+def test_whole_numbers_of_any_size(n):
+    m, v = torch.zeros(4, 16), torch.zeros(16)
+    field = coda.coda_epi_op(0, 0, i0=n, i1=n)
+    assert coda.rmsnorm_bwd(m, v, v, v, z_sum_over=n).i0 == field.i0
+    o = coda.rope(m, m, v, n, n)
+    assert (o.i0, o.i1) == (field.i0, field.i1)
+
+
 def test_programs_are_the_structures_one_after_the_other():
     v = torch.zeros(16)
     ops = [coda.row_scale(v), coda.store(v.view(4, 4)), coda.coda_epi_op(9, 8, 7)]
