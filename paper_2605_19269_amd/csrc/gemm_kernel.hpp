@@ -408,9 +408,12 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
     constexpr int BM = C::BM, WTM = C::WTM, WTN = C::WTN;
     constexpr int LR = ACC::LR, LQ = ACC::LQ, NB = ACC::NB, NU = ACC::NU, UC = 4 * LQ;   // UC: column step between units
     constexpr int REG = RING / (C::WGM * C::WGN);   // private staging bytes per wave
-    // wave tiles of 48 columns are staged in rows of 64, whose last chunks are neither fetched nor stored
-    constexpr int WTP = WTN == 48 ? 64 : WTN;
-    constexpr bool BOUNDS = EDGE || WTP != WTN;
+    // wave tiles of 48 columns (the linear program without row reductions and SwiGLU forward) are staged in rows of 64, whose last chunks
+    // are neither fetched nor stored
+    constexpr bool NARROW = WTN == 48;
+    constexpr int WTP = NARROW ? 64 : WTN;
+    constexpr bool BOUNDS = EDGE || NARROW;
+    static_assert(!NARROW || EPI == EPI_LINEAR || EPI == EPI_SWIGLU_FWD, "programs of the 256 x 192 tiles");
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave % C::WGM, wn = wave / C::WGM;
     const int lrow = lane % LR, lcol = (lane / LR) * 4;           // the lane's row in a block, first column in a unit step
@@ -418,7 +421,7 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
     unsigned char *reg = ring + wave * REG;
     const int rows_ok = EDGE ? clampi(p.M - mw, 0, WTM) : WTM;   // valid rows / columns of this wave's tile
     const int cols_ok = EDGE ? clampi(p.N - nw, 0, WTN) : WTN;
-    const bool want_red = (EPI == EPI_LINEAR || EPI == EPI_SWIGLU_BWD) && p.rowred_mode != ROWRED_NONE;
+    const bool want_red = !NARROW && (EPI == EPI_LINEAR || EPI == EPI_SWIGLU_BWD) && p.rowred_mode != ROWRED_NONE;
     float rsum[NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i) rsum[i] = 0.0f;
@@ -437,7 +440,7 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
         }
     };
 
-    if (EPI == EPI_LINEAR && p.lse_max) {
+    if (EPI == EPI_LINEAR && !NARROW && p.lse_max) {
         // ---- log-sum-exp partials of this 256-column tile (Kernels 3 / 8) on the fp32 values v = acc * r, before rounding:
         // per lane and row the maximum and the sum of exp(v - max) over its values, merged over the lanes that share the
         // row and then over the four column waves with the usual rescaling rule.
@@ -672,7 +675,7 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
                     }
                 }
                 stage_fence();
-                stage_store<RBZ, P, BOUNDS, WTP == WTN>(reg, reinterpret_cast<unsigned char *>(p.out2 + (int64_t)(mw + r0) * p.ld_out2 + nw),
+                stage_store<RBZ, P, BOUNDS, !NARROW>(reg, reinterpret_cast<unsigned char *>(p.out2 + (int64_t)(mw + r0) * p.ld_out2 + nw),
                                           p.ld_out2 * 2, rows_ok - r0, cols_ok * 2, lane);
             }
             stage_fence();
@@ -680,19 +683,19 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
     } else if constexpr (EPI == EPI_SWIGLU_BWD) {
         // ---- pairwise SwiGLU backward (width doubles): Z in and dZ out staged; row statistic; the optional
         // recomputed activation silu(g)*u is a second sweep over 32-row passes that re-reads Z.
-        constexpr int RB = WTP * 4, RBO = WTP * 2, P = 32, FPP = P / LR, NP = WTM / P;
+        constexpr int RB = WTN * 4, RBO = WTN * 2, P = 32, FPP = P / LR, NP = WTM / P;
         static_assert(P * (RB + RBO) <= REG && WTM % P == 0, "staging pass");
         uint16_t *outp = reinterpret_cast<uint16_t *>(p.out);
         const uint32_t ulane = Stage<RB>::template unit_lane<16, LR>(lane), ulane_o = Stage<RBO>::template unit_lane<8, LR>(lane);
         // 32-row passes; the Z rows of the next pass are fetched into registers while this pass is computed and stored
         u32x4 zt[P / Stage<RB>::RPI];
         auto zrows = [&](int ps) { return reinterpret_cast<const unsigned char *>(p.Z + (int64_t)(mw + ps * P) * p.ldz + 2 * nw); };
-        stage_fetch<RB, P, BOUNDS, true>(zt, zrows(0), p.ldz * 2, rows_ok, cols_ok * 4, lane);
+        stage_fetch<RB, P, EDGE, true>(zt, zrows(0), p.ldz * 2, rows_ok, cols_ok * 4, lane);
 #pragma unroll
         for (int ps = 0; ps < NP; ++ps) {
             stage_put<RB, P>(reg, zt, lane);
             stage_fence();
-            if (ps + 1 < NP) stage_fetch<RB, P, BOUNDS, true>(zt, zrows(ps + 1), p.ldz * 2, rows_ok - (ps + 1) * P, cols_ok * 4, lane);
+            if (ps + 1 < NP) stage_fetch<RB, P, EDGE, true>(zt, zrows(ps + 1), p.ldz * 2, rows_ok - (ps + 1) * P, cols_ok * 4, lane);
             stage_fence();
 #pragma unroll
             for (int fi = 0; fi < FPP; ++fi) {
@@ -720,7 +723,7 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
                 }
             }
             stage_fence();
-            stage_store<RB, P, BOUNDS, false>(reg, reinterpret_cast<unsigned char *>(outp + (int64_t)(mw + ps * P) * p.ld_out + 2 * nw), p.ld_out * 2,
+            stage_store<RB, P, EDGE, false>(reg, reinterpret_cast<unsigned char *>(outp + (int64_t)(mw + ps * P) * p.ld_out + 2 * nw), p.ld_out * 2,
                                      rows_ok - ps * P, cols_ok * 4, lane);
             stage_fence();
         }
@@ -729,7 +732,7 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
 #pragma unroll
             for (int ps = 0; ps < NP; ++ps) {
                 const int r0 = ps * P;
-                stage_load<RB, P, BOUNDS>(reg, reinterpret_cast<const unsigned char *>(p.Z + (int64_t)(mw + r0) * p.ldz + 2 * nw),
+                stage_load<RB, P, EDGE>(reg, reinterpret_cast<const unsigned char *>(p.Z + (int64_t)(mw + r0) * p.ldz + 2 * nw),
                                         p.ldz * 2, rows_ok - r0, cols_ok * 4, lane);
                 stage_fence();
 #pragma unroll
@@ -747,12 +750,12 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
                             u32x2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
                     }
                 stage_fence();
-                stage_store<RBO, P, BOUNDS, false>(rego, reinterpret_cast<unsigned char *>(p.out2 + (int64_t)(mw + r0) * p.ld_out2 + nw),
+                stage_store<RBO, P, EDGE, false>(rego, reinterpret_cast<unsigned char *>(p.out2 + (int64_t)(mw + r0) * p.ld_out2 + nw),
                                           p.ld_out2 * 2, rows_ok - r0, cols_ok * 2, lane);
                 stage_fence();
             }
         }
-    } else if (EPI == EPI_LINEAR && !p.out_f32 && p.rope_cos && (WTN == 48 || (WTN == 64 && (p.rope_half & 31) == 0))) {
+    } else if (EPI == EPI_LINEAR && !p.out_f32 && p.rope_cos && (NARROW || (WTN == 64 && (p.rope_half & 31) == 0))) {
         // ---- row scale, RoPE, bf16 store with the cos / sin rows staged like tiles: per 32-row pass the wave gathers
         // each token's 32 table entries (128 bytes of cos, 128 of sin; the wave's 64 columns are 32 consecutive pairs
         // inside one head because head_dim/2 is a multiple of 32) with row-contiguous 16-byte loads into its region,
@@ -808,7 +811,7 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
                 }
             }
             stage_fence();
-            stage_store<RB, P, BOUNDS, WTP == WTN>(reg, reinterpret_cast<unsigned char *>(outp + (int64_t)(mw + ps * P) * p.ld_out + nw), p.ld_out * 2,
+            stage_store<RB, P, BOUNDS, !NARROW>(reg, reinterpret_cast<unsigned char *>(outp + (int64_t)(mw + ps * P) * p.ld_out + nw), p.ld_out * 2,
                                      rows_ok - ps * P, cols_ok * 2, lane);
             stage_fence();
         }
@@ -876,7 +879,7 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
                     }
                 }
                 stage_fence();
-                stage_store<RB, P, BOUNDS, WTP == WTN>(reg, reinterpret_cast<unsigned char *>(dst + (int64_t)(mw + r0) * ldd + nw), ldd * 2,
+                stage_store<RB, P, BOUNDS, !NARROW>(reg, reinterpret_cast<unsigned char *>(dst + (int64_t)(mw + r0) * ldd + nw), ldd * 2,
                                          rows_ok - r0, cols_ok * 2, lane);
                 stage_fence();
             }
