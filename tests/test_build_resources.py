@@ -68,3 +68,11 @@ def test_spills_of_the_other_instances_stay_small(kernels):
         assert r["spill"] <= limit, (key, r)
     for key, r in _gemm_f8(kernels).items():
         assert r["spill"] == 0 and r["scratch"] == 0, (key, r)
+
+
+def test_narrow_tiles_do_not_spill(kernels):
+    """256 x 192 tiles: the linear program and SwiGLU forward, whole and ragged shapes."""
+    narrow = {m.groups(): r for name, r in kernels.items() for m in [re.search(r"gemm_kernel_narrowINS_5DlCfg\w+?EEELi(\d)ELb([01])EEEv", name)] if m}
+    assert sorted(narrow) == [("0", "0"), ("0", "1"), ("1", "0"), ("1", "1")]
+    for key, r in narrow.items():
+        assert r["vgpr"] <= 256 and r["agpr"] == 0 and r["scratch"] == 0 and r["spill"] == 0 and r["lds"] <= 160 * 1024, (key, r)
