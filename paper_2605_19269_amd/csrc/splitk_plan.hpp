@@ -123,6 +123,10 @@ inline int splitk_chain(const SplitPlan &pl, int64_t K, bool f8)
 // So does A B^T on shared tiles whose K is no whole number of 128-byte lines: a stage's row of B then lies in two lines, and small tiles
 // fetch more rows for what they compute (1128 x 4160 x 12648 with transposed A 195 us, small 233, 768 x 6848 x 7184 8-bit 61, 70; of 150 shapes that
 // would move, storing D, the 22 such gain 1 % in the mean, the others 23 %).
+// Why from 70 tiles on: of 150 shapes of 70 to 128 that move the plain store gains 23 % in the mean and the RMSNorm backward, which pays for
+// its partials in one range as well, 11 % (11 of 128 lose 2 to 8 %, 8-bit and A B, while the other programs of the shape gain 2 to 20 %; the
+// plan cannot depend on the program).  At 60 to 69 tiles, below which none would move, 12 of 80 would lose up to 21 % in the plain store and 31
+// of 80 in the RMSNorm backward (12 and 2 % faster in the mean): the figures do not hold there.
 // Shared tiles stay at 2048 x 4096 x 14336 (179, small 189), 1440 x 4096 x 14336 (164, 181), 384 x 16384 x 14336 A B^T (189, 228).
 struct SmallPlan {
     int bm, bn;    // the tile: 32, 64 or 128 rows, 128 (or, with 128 rows, 256) columns
@@ -140,7 +144,7 @@ inline double shared_tiles_us(const SplitPlan &big, int64_t K, bool f8)
     for (int tail = big.tail; tail % 2 == 0 && period % 2 == 0; tail /= 2) period /= 2;
     return 30.0 + 1.42 * pairs * (period <= 8 ? 1.3 : period <= 16 ? 1.75 : 2.0);
 }
-inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_contiguous, const SplitPlan &big, bool b_k_contiguous = false)
+inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_contiguous, bool b_k_contiguous, const SplitPlan &big)
 {
     const SmallPlan none = {0, 0, 0, 0.0, false};
     if (big.chunks == 0 || big.first != 0) return none;
@@ -328,7 +332,7 @@ inline Route plan_route(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_conti
     DirectPlan direct = plan_direct(M, N, K, f8, a_k_contiguous, prog, wide, big);
     // the contraction is divided only when the caller brought the workspace for it; without one the shape runs undivided
     if (workspace && big.chunks > 0) {
-        r.small = plan_small(M, N, K, f8, a_k_contiguous, big, b_k_contiguous);
+        r.small = plan_small(M, N, K, f8, a_k_contiguous, b_k_contiguous, big);
         if (r.small.nsplit == 0) {
             r.kind = ROUTE_SHARED;
             return r;

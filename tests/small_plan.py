@@ -12,7 +12,7 @@ def load(folder):
     subprocess.run([HIPCC, "--offload-host-only", "-O1", "-std=c++17", "-fPIC", "-shared", "-Wno-inline-asm", "-o", so,
                     os.path.join(ROOT, "tests", "small_plan_host.hip")], check=True, capture_output=True)
     lib = ctypes.CDLL(so)
-    lib.host_small_plan.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 2 + [ctypes.POINTER(ctypes.c_int)]
+    lib.host_small_plan.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 3 + [ctypes.POINTER(ctypes.c_int)]
     lib.host_direct_tile.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 4
     lib.host_route.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 6 + [ctypes.POINTER(ctypes.c_int)]
     lib.host_reads_once.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 4 + [ctypes.c_int64, ctypes.c_uint64]
@@ -21,10 +21,10 @@ def load(folder):
     return lib
 
 
-def plan(lib, M, N, K, f8=False, ak=True):
+def plan(lib, M, N, K, f8=False, ak=True, bkc=False):
     """(tile rows, tile columns, ranges); ranges = 0: the shape runs on the large tiles."""
     out = (ctypes.c_int * 3)()
-    lib.host_small_plan(M, N, K, int(f8), int(ak), out)
+    lib.host_small_plan(M, N, K, int(f8), int(ak), int(bkc), out)
     return tuple(out)
 
 

@@ -6,9 +6,9 @@
 extern "C" {
 
 // plan[0..2] = tile rows, tile columns, ranges (0: large tiles)
-__attribute__((visibility("default"))) void host_small_plan(int64_t M, int64_t N, int64_t K, int f8, int ak, int *plan)
+__attribute__((visibility("default"))) void host_small_plan(int64_t M, int64_t N, int64_t K, int f8, int ak, int bkc, int *plan)
 {
-    const coda::SmallPlan pl = coda::plan_small(M, N, K, f8 != 0, ak != 0, coda::plan_splitk(M, N, K, f8 != 0));
+    const coda::SmallPlan pl = coda::plan_small(M, N, K, f8 != 0, ak != 0, bkc != 0, coda::plan_splitk(M, N, K, f8 != 0));
     plan[0] = pl.bm; plan[1] = pl.bn; plan[2] = pl.nsplit;
 }
 

@@ -53,7 +53,7 @@ CASES = [(1, 264, 4104, False, False, False, (32, 128)), (32, 1000, 6144, False,
 
 @pytest.mark.parametrize("M,N,K,f8,ta,tb,expect", CASES)
 def test_linear_program(oracle, plans, M, N, K, f8, ta, tb, expect):
-    bm, bn, ns = small_plan.plan(plans, M, N, K, f8, not ta)
+    bm, bn, ns = small_plan.plan(plans, M, N, K, f8, not ta, tb)
     assert ns > 0 and (bm, bn) == expect
     g = np.random.Generator(np.random.PCG64(4000 + M + N + K + 2 * ta + tb))
     dA, dB, A, B = operands(oracle, g, M, N, K, ta, tb, f8)

@@ -36,6 +36,12 @@ def test_shared_tiles_where_they_are_faster(plans, M, N, K, f8, tb):
     assert small_plan.Route(plans, M, N, K, f8, True, tb, "linear", True, True).kind == "shared"
 
 
+def test_the_line_lies_at_seventy_tiles(plans):
+    for N, kinds in ((17664, {"shared"}), (17920, {"direct", "divided"})):          # 69 and 70
+        assert -(-N // 256) == (69 if kinds == {"shared"} else 70)
+        assert {small_plan.Route(plans, 256, N, 8192, False, True, False, p, w, True).kind for p, w in (("linear", False), ("linear", True), ("rmsnorm_bwd", False))} <= kinds
+
+
 # A B^T whose K is no whole number of lines: on shared tiles, on small ones (RMSNorm backward), microseconds
 RAGGED = [(1128, 4160, 12648, False, True), (2201, 1808, 15264, False, False), (244, 24768, 5552, True, False), (768, 6848, 7184, True, True)]   # 201 248, 199 234, 74 88, 70 85
 

@@ -21,8 +21,8 @@ def test_plans_fit_the_workspace_of_the_shape(lib):
     for _ in range(4000):
         M, N, K = (int(2 ** rng.uniform(0, 14)), 8 * int(2 ** rng.uniform(0, 12.5)), 16 * int(2 ** rng.uniform(3, 10.5)))
         for f8 in (False, True):
-            for ak in (True, False):
-                bm, bn, ns = small_plan.plan(lib, M, N, K, f8, ak)
+            for ak, bkc in ((True, False), (True, True), (False, False), (False, True)):
+                bm, bn, ns = small_plan.plan(lib, M, N, K, f8, ak, bkc)
                 if ns == 0:
                     continue
                 taken += 1
