@@ -146,11 +146,12 @@ __global__ __launch_bounds__(256) void epi_rows_kernel(const GemmParams p, const
 }
 
 // R rows of the RMSNorm backward, EPI_STEP apart from m on, in four columns: what they read is in flight together.  Rows past M read the
-// last row and are dropped.
+// last row and are dropped.  What is fused is written out: one row at a time and two give the same bits.
 constexpr int EPI_STEP = 128;
 template <int R>
 __device__ __forceinline__ void cols_rows(const GemmParams &p, const float *part, int nsplit, int m, int n, f32x4 gm, f32x4 &dg)
 {
+#pragma clang fp contract(off)
     float rr[R], zz[R];
     u32x2 c[R], res[R];
     f32x4 d[R];
@@ -172,9 +173,9 @@ __device__ __forceinline__ void cols_rows(const GemmParams &p, const float *part
         const int64_t mi = m + i * EPI_STEP;
         if (mi >= p.M) continue;
         const f32x4 cn = unpack4(c[i]) * rr[i];
-        f32x4 o = (d[i] * gm - cn * zz[i]) * rr[i];
+        f32x4 o = __builtin_elementwise_fma(d[i], gm, -(cn * zz[i])) * rr[i];
         if (p.add) o += unpack4(res[i]);
-        dg += d[i] * cn;
+        dg = __builtin_elementwise_fma(d[i], cn, dg);
         *reinterpret_cast<u32x2 *>(reinterpret_cast<uint16_t *>(p.out) + mi * p.ld_out + n) = pack4(o);
         if (p.out2) *reinterpret_cast<u32x2 *>(p.out2 + mi * p.ld_out2 + n) = pack4(cn * gm);
     }

@@ -55,3 +55,22 @@ def test_ranges(plans, M, N, K, ranges):
     ref = D * r.double()[:, None]
     check(F.t, ref, "fp32", 1e-5)
     assert ((S.double().sum(0) - ref.square().sum(1)).abs() <= 1e-5 * ref.square().sum(1)).all(), "row sum of squares"
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 416, 3280), (127, 2056, 4104), (129, 2056, 4104), (257, 2056, 4104), (864, 6016, 3304)])
+def test_rmsnorm_backward_rounds_the_same_in_one_step_and_in_two(M, N, K):
+    """Rows whose wave has a row 128 further on and rows whose wave has none: D * gamma fused with the product that is subtracted, everything
+    else rounded by itself.  The 64-bit product of two fp32 is exact, and its sum with a third rounds to fp32 as the fused operation does but for one case in 2^29."""
+    from paper_2605_19269_amd import coda
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    A, B, C, R = rnd(M, K).bfloat16(), rnd(K, N).mul_(K ** -0.5).bfloat16(), rnd(M, N).bfloat16(), rnd(M, N).bfloat16()
+    r, z, gamma = (rnd(M).abs() + 0.5)[:, None], rnd(M)[:, None], rnd(N)
+    ws = torch.empty(coda.coda_gemm_workspace_bytes(M, N, K, []), dtype=torch.uint8, device="cuda")
+    D, O = torch.empty(M, N, device="cuda"), torch.empty(M, N, device="cuda", dtype=torch.bfloat16)
+    coda.coda_gemm(A, B, [coda.store(D, f32=True)], workspace=ws)
+    coda.coda_gemm(A, B, [coda.rmsnorm_bwd(C, r.view(M), z.view(M), gamma), coda.add_tile(R), coda.store(O)], workspace=ws)
+    torch.cuda.synchronize()
+    sub = (C.float() * r) * z
+    fused = (D.double() * gamma.double() - sub.double()).float()
+    assert torch.equal(O, (fused * r + R.float()).bfloat16())
