@@ -1,7 +1,7 @@
 // binding.cpp -- the marshalling of coda.py in C: tensors to coda_mat / coda_epi_op, and the calls of the entry points that a
 // program makes for every layer.  A call on a small problem is host work (its kernels take a few microseconds), and most of
 // that was the interpreter and ctypes: a coda_gemm with four ops 10 us before the launch, here 4.2; a 256 x 512 x 256 linear layer of
-// four calls 23.2 -> 17.0 us a pass.  Tensors are asked through their Python methods, so whatever answers to them is accepted as
+// four calls 22.2 -> 18.9 us a pass.  Tensors are asked through their Python methods, so whatever answers to them is accepted as
 // before; arguments of other types than the usual ones go to the ctypes function of the same name.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>

@@ -15,9 +15,10 @@
 // K-contiguous operand, or the same number of k-rows of an MN-contiguous one.  One barrier per stage, and the fragments of
 // the next MFMA step are read while the current ones are multiplied.  The MFMA instructions and their order along K are those
 // of the 256 x 256 tiles, so that an undivided launch gives the same sums, bit for bit, on any tile (8-bit: 16x16x128, which rounds
-// otherwise, is within some 10 % of 32x32x64 either way).  Up to 64 rows the kernel is bound by HBM (28672 x 4096 bf16 weights
-// against one row: 45 us with the epilogue, 5.2 TB/s, the rate of a large copy), at 128 rows by LDS: 64 KB or more of fragments
-// and 32 KB of fill per stage against 512 cycles of MFMA.
+// otherwise, is within some 10 % of 32x32x64 either way).  Up to 64 rows the kernel is bound by HBM (28672 x 8192 bf16 weights
+// against one row: 70.6 us, 6.7 TB/s; a large copy 5.2).  At 128 rows no unit is full: of the cycles in which a CU has a
+// workgroup the matrix pipe is busy in 58 % (509 x 16384 x 2048 on 128 x 256) and LDS in 30 %, and 4 % of the wave-cycles wait on LDS.  What
+// is left is that the waves of a workgroup read, wait at the stage's barrier and multiply in step.
 #pragma once
 #include "gemm_kernel.hpp"
 #include "splitk_plan.hpp"
@@ -437,8 +438,8 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2), am
 }
 
 // A division into one range (up to 64 rows, weights of 129 to 256 tiles of 128 columns) for a program without row reductions: nothing
-// to add up, so no partials and no second kernel.  Bound by HBM: 28672 x 4096 bf16 in 43.8 us with the launch, 5.4 TB/s (partials and
-// a second kernel: 45.0).
+// to add up, so no partials and no second kernel.  Bound by HBM: one row of 28672 x 4096 bf16 in 43.8 us with the launch (partials and a
+// second kernel: 45.0), past the caches in 38.6, 6.1 TB/s.
 template <class C, bool BKC, int EPI>
 __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2), amdgpu_num_vgpr(256))) void gemm_small_stream(const GemmParams g, const SmallParams p)
 {

@@ -94,7 +94,7 @@ inline int splitk_chain(const SplitPlan &pl, int64_t K, bool f8)
 // see do not depend on which of the two runs.
 //
 // Up to 64 rows (one tile row) the operands stream from memory once and the small tiles always win: 1 / 32 / 64 rows,
-// N x K = 6144 x 4096: 14 / 15 / 17 us against 47; 28672 x 4096: 45 / 46 / 50 against 104; 4096 x 14336: 26 / 28 / 30
+// N x K = 6144 x 4096: 14 / 15 / 17 us against 47; 28672 x 4096: 39 / 41 / 44 against 104; 4096 x 14336: 23 / 25 / 29
 // against 75.  One workgroup per CU is the best count there (at 6144 x 4096: 96, 240, 480, 768 workgroups: 18.9, 14.1,
 // 15.2, 16.3 us): twice as many pay more exchange and fill for bytes in flight that memory does not need.
 //
@@ -301,9 +301,9 @@ inline bool reads_once(int64_t M, int64_t N, int64_t K, bool f8, bool b_k_contig
 // that range's chain and starting stages (96 x 28672 x 4096 8-bit SwiGLU: 27 us; partials of 11 MB to write, read and run a second
 // kernel on are 5 more).  It does not take the place of more ranges, where it would be 5 to 20 % ahead for a program without row reductions (809 x
 // 4096 x 4096: 37 us against 44, 512 x 6144 x 4096 A^T B SwiGLU 40, 43) and behind for one with.
-// One range of 32- or 64-row tiles needs no partials where the program reduces over no rows (`fused`, gemm_small_stream): 1 x 28672 x
-// 4096 bf16 45.0 -> 43.8 us, 32 rows with SwiGLU 45.6 (128 x 128 tiles) -> 43.8, 64 x 32768 x 4096 56.6 -> 50.1, 57 x 28672 x 4096
-// 8-bit 32.2 -> 28.5; over 129 to 256 tiles and K of 4096 and 8192 the fastest of all tiles, by 1 to 13 % (one in 76 behind, by 3.5 %).
+// One range of 32- or 64-row tiles needs no partials where the program reduces over no rows (`fused`, gemm_small_stream), all with ordinary
+// loads: 1 x 28672 x 4096 bf16 45.0 -> 43.8 us, 32 rows with SwiGLU 45.6 (128 x 128 tiles) -> 43.8, 64 x 32768 x 4096 56.6 -> 50.1, 57 x
+// 28672 x 4096 8-bit 32.2 -> 28.5; over 129 to 256 tiles and K of 4096 and 8192 the fastest of all tiles, by 1 to 13 % (one in 76 behind, by 3.5 %).
 enum RouteKind : int { ROUTE_WHOLE = 0, ROUTE_SHARED, ROUTE_DIVIDED, ROUTE_DIRECT };
 struct Route {
     RouteKind kind;
