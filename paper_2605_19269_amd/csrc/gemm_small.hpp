@@ -373,28 +373,29 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2), am
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int mw = m0 + wave % C::WGM * C::WTM, nw = n0 + wave / C::WGM * C::WTN;
     float *out = p.part + (int64_t)split * p.M * p.N;
-    if constexpr (C::F8) {
-        // a lane's four columns and its partner's are 32 bytes of a row: rows of the wave's tile by way of LDS (eight ranges of 256 x
-        // 1984 x 4336: 17.2 us, stored from registers 18.9)
-        constexpr int RB = C::WTN * 4, UB = 16 * SmallAcc<C>::LQ;
-        unsigned char *reg = smem + wave * 32 * RB;
-        const uint32_t ulane = Stage<RB>::template unit_lane<16, 32>(lane);
+    using ACC = SmallAcc<C>;
+    constexpr int RB = C::WTN * 4, UB = 16 * ACC::LQ, LR = ACC::LR;
+    if constexpr (C::F8 || C::BM == 128) {
+        // straight from registers a lane and its partners would store 32 (8-bit) or 64 bytes of a row: rows of the wave's tile by way of
+        // LDS (eight ranges of 256 x 1984 x 4336 8-bit: 17.2 us, from registers 18.9; a 509-row MLP of bf16 73.5 -> 72.5)
+        unsigned char *reg = smem + wave * LR * RB;
+        const uint32_t ulane = Stage<RB>::template unit_lane<16, LR>(lane);
 #pragma unroll
-        for (int i = 0; i < SmallAcc<C>::NB; ++i) {
+        for (int i = 0; i < ACC::NB; ++i) {
 #pragma unroll
-            for (int u = 0; u < SmallAcc<C>::NU; ++u)
-                *reinterpret_cast<f32x4 *>(reg + Stage<RB>::template unit_addr<32>(ulane, 0, u * UB)) = acc.get(i, u);
+            for (int u = 0; u < ACC::NU; ++u)
+                *reinterpret_cast<f32x4 *>(reg + Stage<RB>::template unit_addr<LR>(ulane, 0, u * UB)) = acc.get(i, u);
             stage_fence();
-            stage_store<RB, 32, true, false>(reg, reinterpret_cast<unsigned char *>(out + (int64_t)(mw + i * 32) * p.N + nw), (int64_t)p.N * 4,
-                                             p.M - mw - i * 32, (p.N - nw) * 4, lane);
+            stage_store<RB, LR, true, false>(reg, reinterpret_cast<unsigned char *>(out + (int64_t)(mw + i * LR) * p.N + nw), (int64_t)p.N * 4,
+                                             p.M - mw - i * LR, (p.N - nw) * 4, lane);
             stage_fence();
         }
-    } else {
+    } else {                                         // up to 64 rows, often few: one row 80.3 us a block, by way of LDS 80.5
         const int m = mw + (lane & 15), n = nw + (lane >> 4) * 4;
 #pragma unroll
-        for (int i = 0; i < SmallAcc<C>::NB; ++i)
+        for (int i = 0; i < ACC::NB; ++i)
 #pragma unroll
-            for (int u = 0; u < SmallAcc<C>::NU; ++u)
+            for (int u = 0; u < ACC::NU; ++u)
                 if (m + i * 16 < p.M && n + u * 16 < p.N)
                     *reinterpret_cast<f32x4 *>(out + (int64_t)(m + i * 16) * p.N + n + u * 16) = acc.get(i, u);
     }
