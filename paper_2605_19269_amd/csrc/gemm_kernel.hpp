@@ -895,27 +895,25 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
         static_assert(WTM % P == 0 && P * RB <= REG, "passes");
         const int lr = lane / St::NCH, lc = (lane % St::NCH) * 4;
         const uint32_t ulane = St::template unit_lane<16, LR>(lane), rlane = St::row_lane(lane);
-        // a row of the wave's tile is a scalar base and the lane's 32-bit offset, so that accesses follow one another; where rows are so long
-        // that the offset would not hold it (WIDE), 64-bit addresses that are formed where they are used
+        // a row of the wave's tile is a scalar base and the lane's 32-bit offset (pitches are at most 16 MB)
         const int64_t pitch = p.ld_out * 4;
         unsigned char *tile = reinterpret_cast<unsigned char *>(p.out) + (int64_t)__builtin_amdgcn_readfirstlane(mw) * pitch + (int64_t)__builtin_amdgcn_readfirstlane(nw) * 4;
         const uint32_t lane_at = (uint32_t)lr * (uint32_t)pitch + (uint32_t)lc * 4;
         auto there = [&](int row) { return !EDGE || (mw + lr + row < p.M && nw + lc < p.N); };
-        auto passes = [&](auto once, auto wide) {
-            constexpr bool ONCE = decltype(once)::value, WIDE = decltype(wide)::value;
+        auto passes = [&](auto once) {
+            constexpr bool ONCE = decltype(once)::value;
             // the lane's part of the addresses of a batch, pinned on the large tile: a batch's addresses are not kept over other batches
             // (50 to 100 spilled registers).  Smaller tiles have the registers, and their stores follow the loads' addresses at once
             // (2048 x 11264 x 304 44.3 us pinned, 39.3)
-            typedef typename std::conditional<WIDE, int64_t, uint32_t>::type Lane;
             auto lane_part = [&]() {
-                Lane at = WIDE ? (Lane)(lr * pitch + lc * 4) : (Lane)lane_at;
+                uint32_t at = lane_at;
                 if (NPASS > 2) asm volatile("" : "+v"(at));
                 return at;
             };
-            auto spot = [&](int row, Lane at) { return reinterpret_cast<f32x4 *>(tile + row * pitch + at); };
+            auto spot = [&](int row, uint32_t at) { return reinterpret_cast<f32x4 *>(tile + row * pitch + at); };
             f32x4 buf[2][NI];
             auto fetch = [&](f32x4(&b)[NI], int pass) {
-                const Lane part = lane_part();
+                const uint32_t part = lane_part();
 #pragma unroll
                 for (int k = 0; k < NI; ++k) {
                     const f32x4 *at = spot(pass * P + k * St::RPI, part);
@@ -933,7 +931,7 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
                         *reinterpret_cast<f32x4 *>(reg + St::template unit_addr<LR>(ulane, fi, u * UC * 4)) = acc.get(b * FPP + fi, u);
                 stage_fence();
                 if (b + 1 < NPASS) fetch(buf[(b + 1) & 1], b + 1);
-                const Lane part = lane_part();
+                const uint32_t part = lane_part();
 #pragma unroll
                 for (int k = 0; k < NI; ++k) {
                     const int row = b * P + k * St::RPI;
@@ -950,9 +948,8 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
         // half of it; 2048 x 11264 x 304 44 -> 40, 4096 x 4096 x 256 in turn with others 37.7 -> 32.2, the same D again and again, which
         // would have stayed, 30.7 -> 31.3), where its rows are whole lines: of a line in two pieces the caches save the second
         // (2000 x 5208 x 2000 63 us with the hint, without 55)
-        if (pitch >= int64_t(1) << 29) passes(std::false_type{}, std::true_type{});
-        else if (pitch % 128 == 0 && reinterpret_cast<uintptr_t>(p.out) % 128 == 0) passes(std::true_type{}, std::false_type{});
-        else passes(std::false_type{}, std::false_type{});
+        if (pitch % 128 == 0 && reinterpret_cast<uintptr_t>(p.out) % 128 == 0) passes(std::true_type{});
+        else passes(std::false_type{});
     } else {
         // ---- fp32 store of the linear program: 16 bytes per lane, direct
         float rsv[NB];
