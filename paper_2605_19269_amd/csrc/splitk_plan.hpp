@@ -186,9 +186,9 @@ inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_c
 // does 1000 x 16384 x 2048 (128x256 66.8, 256 x 256 55.4).
 // A plan_small() with one range per tile gives way to these where the model says so, see plan_route; `chains`: those that keep to
 // its chain, all but PAIR and 32x256.
-// The gradient program also reads and writes 8 bytes per element, two thirds of it (PAIR: half) beside the contraction of
-// other workgroups: 2048 x 11264 x 1000: PAIR 78, 256 x 256 85; 5976 x 2968 x 720: 52, 67; 5632 x 2048 x 2552: 72, 69 and 11008 x
-// 4096 x 1000: 129, 126, which stay.
+// The gradient program also reads and writes 8 bytes per element, part of it beside the contraction of other workgroups.  D cold, PAIR and
+// 256 x 256: 11008 x 4096 x 504 81, 97; 14336 x 4096 x 512 111, 123; 2048 x 11264 x 2000 113, 123; and 2048 x 16384 x 2000 158, 147;
+// 5632 x 2048 x 1000 41, 40 and 4096 x 28672 x 1000 379, 298, which stay on 256 x 256.
 enum DirectTile : int { DIRECT_NONE = 0, DIRECT_64x64, DIRECT_32x256, DIRECT_64x256, DIRECT_128x128, DIRECT_128x128_PAIR, DIRECT_128x256 };
 enum DirectProgram : int { DIRECT_PROG_LINEAR, DIRECT_PROG_SWIGLU_FWD, DIRECT_PROG_SWIGLU_BWD, DIRECT_PROG_ACCUM, DIRECT_PROG_RMSNORM_BWD };
 struct DirectPlan {
@@ -209,6 +209,9 @@ inline DirectPlan plan_direct(int64_t M, int64_t N, int64_t K, bool f8, bool a_k
     const int64_t big = tiles(PLAN_TILE_M, PLAN_TILE_N);
     const double fill = big < SPLITK_CUS ? (double)big / (double)SPLITK_CUS : 1.0;
     best.us = (prog == DIRECT_PROG_ACCUM ? 0.99 : 0.92) * (6.0 + stages * (1.15 + 0.4 * fill) * rounds(big) + 0.64 * rmw);    // what a small tile has to beat
+    // bf16 gradients, since D moves in whole rows; up to 48 stages, what was measured
+    const bool rows = prog == DIRECT_PROG_ACCUM && !f8 && stages <= 48.0;
+    if (rows) best.us = 0.96 * (6.0 + stages * (1.1 + 0.22 * fill) * rounds(big) + 0.82 * rmw);
     auto offer = [&](int tile, double us) {
         if (us < best.us) best = DirectPlan{tile, us};
     };
@@ -230,14 +233,14 @@ inline DirectPlan plan_direct(int64_t M, int64_t N, int64_t K, bool f8, bool a_k
     // every further round pays its fill and epilogue: 897 x 19712 x 200 SwiGLU, five rounds: 28.3, 256 x 256 26.6; 3426 x 2832 x 160
     // 8-bit, three: 17.0, 14.8
     if (!wide) offer(DIRECT_128x128, 2.5 + 2.0 * rounds(tiles(128, 128)) + stream(stages * 0.57 * rounds(tiles(128, 128)), 5.6e6) + rmw);
-    // bf16 contractions of a few stages that 256 x 256 tiles nearly fill one round with have nothing to run the updates under: 4096 x
-    // 4096 x 32 PAIR 29.2, 256 x 256 27.0; 2248 x 5912 x 96 26.8, 25.4
-    const bool bare = !f8 && big <= SPLITK_CUS && fill > 0.8 && stages < 4.0;
+    // bf16 contractions that 256 x 256 tiles nearly fill one round with have no second round to run the updates under: 4096 x 4096 x 32
+    // PAIR 29.2, 256 x 256 27.0; x 256 35.1, 32.7; 8192 x 2048 x 1000 53.3, 47.7
+    const bool bare = !f8 && big <= SPLITK_CUS && fill > 0.8 && (rows || stages < 4.0);
     if (prog == DIRECT_PROG_ACCUM && !chains && !bare) {
         // rounds of two per CU; what is left over runs two or one per CU (1424 x 6304 x 12920: 600 tiles lose 30 % to 256 x 256)
         const int64_t t = tiles(128, 128), whole = t / (2 * SPLITK_CUS), left = t % (2 * SPLITK_CUS);
-        const double rest = left == 0 ? 0.0 : (left <= SPLITK_CUS ? 0.66 : 1.08);
-        offer(DIRECT_128x128_PAIR, 6.0 + stages * (1.08 * (double)whole + rest) + 0.55 * rmw);
+        const double round = rows ? 0.86 : 1.08, rest = left == 0 ? 0.0 : (left <= SPLITK_CUS ? 0.66 : round);
+        offer(DIRECT_128x128_PAIR, 6.0 + stages * (round * (double)whole + rest) + (rows ? 0.62 : 0.55) * rmw);
     }
     if (!crowded(128)) offer(DIRECT_128x256, (6.0 + stages * 0.88 * rounds(tiles(128, 256)) + rmw) * (prog == DIRECT_PROG_ACCUM ? 1.07 : 1.0));
     return best;

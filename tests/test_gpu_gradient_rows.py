@@ -41,3 +41,18 @@ def test_gradient_rows(oracle, M, N, K, f8, rows):
     torch.cuda.synchronize()
     G.assert_f32_signed_close(G.host_f64(D), oracle.gemm_accumulate(A, B, old, transA=True), "accumulate")
     assert bool((beside == G.SENTINEL_F32).all())
+
+
+@pytest.mark.parametrize("M,N,K", [(11008, 4096, 504), (2048, 11264, 1544), (4096, 4096, 256)])
+def test_rounds_of_tiles(oracle, M, N, K):
+    """Shapes of several rounds, on either side of where the plan goes from 256 x 256 tiles to 128 x 128, two a CU: rows of the first, an
+    inner and the last tile."""
+    from paper_2605_19269_amd import coda
+    g = np.random.Generator(np.random.PCG64(950 + K))
+    A, B = synth.normal_bf16(g, (K, M), 1.0), synth.normal_bf16(g, (K, N), 0.05)
+    rows = np.array([0, 127, 128, M // 2 + 5, M - 129, M - 1])
+    D = torch.full((M, N), 0.125, device="cuda")
+    coda.coda_gemm(G.dev_bf16(A), G.dev_bf16(B), [coda.accum_f32(D)], transA=True)
+    torch.cuda.synchronize()
+    ref = oracle.gemm_accumulate(A, B, np.full((M, N), 0.125, np.float32), rows=rows, transA=True)
+    G.assert_f32_signed_close(G.host_f64(D)[rows], ref, "accumulate")
