@@ -209,8 +209,8 @@ inline DirectPlan plan_direct(int64_t M, int64_t N, int64_t K, bool f8, bool a_k
     const int64_t big = tiles(PLAN_TILE_M, PLAN_TILE_N);
     const double fill = big < SPLITK_CUS ? (double)big / (double)SPLITK_CUS : 1.0;
     best.us = (prog == DIRECT_PROG_ACCUM ? 0.99 : 0.92) * (6.0 + stages * (1.15 + 0.4 * fill) * rounds(big) + 0.64 * rmw);    // what a small tile has to beat
-    // bf16 gradients, since D moves in whole rows; up to 48 stages, what was measured
-    const bool rows = prog == DIRECT_PROG_ACCUM && !f8 && stages <= 48.0;
+    // bf16 weight gradients (A^T), since D moves in whole rows; up to 48 stages, what was measured
+    const bool rows = prog == DIRECT_PROG_ACCUM && !f8 && !a_k_contiguous && stages <= 48.0;
     if (rows) best.us = 0.96 * (6.0 + stages * (1.1 + 0.22 * fill) * rounds(big) + 0.82 * rmw);
     auto offer = [&](int tile, double us) {
         if (us < best.us) best = DirectPlan{tile, us};
