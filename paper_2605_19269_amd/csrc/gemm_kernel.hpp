@@ -224,7 +224,7 @@ struct Stage {
 
 // 16-byte global load, optionally with the non-temporal hint: for epilogue inputs that are read exactly once, so that they
 // do not displace operand panels in L2.  Measured: +2 % on the SwiGLU backward (Z), +6 % on the RMSNorm backward (C, O_in);
-// the residual of the down-projection (-0.5 %) and the fp32 gradient buffer (-0.6 %) keep ordinary loads.
+// the residual of the down-projection (-0.5 %) keeps ordinary loads.
 template <bool STREAM>
 __device__ __forceinline__ u32x4 load16(const unsigned char *g)
 {

@@ -18,7 +18,8 @@
 // otherwise, is within some 10 % of 32x32x64 either way).  Up to 64 rows the kernel is bound by HBM (28672 x 8192 bf16 weights
 // against one row: 70.6 us, 6.7 TB/s; a large copy 5.2).  At 128 rows no unit is full: of the cycles in which a CU has a
 // workgroup the matrix pipe is busy in 58 % (509 x 16384 x 2048 on 128 x 256) and LDS in 30 %, and 4 % of the wave-cycles wait on LDS.  What
-// is left is that the waves of a workgroup read, wait at the stage's barrier and multiply in step.
+// is left is that the waves of a workgroup read, wait at the stage's barrier and multiply in step.  Two groups of waves a phase apart, as on
+// the large tiles, were slower (1426 -> 1666 cycles a stage: the eight fragment reads of a phase take longer than its 256 cycles of MFMA).
 #pragma once
 #include "gemm_kernel.hpp"
 #include "splitk_plan.hpp"

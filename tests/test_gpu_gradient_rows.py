@@ -14,13 +14,10 @@ SHAPES = [(256, 512, 64, False), (264, 520, 72, False), (1280, 1024, 128, False)
 ROWS = ["lines", "inside a line", "base inside a line", "long"]
 
 
-@pytest.mark.parametrize("M,N,K,f8", SHAPES)
-@pytest.mark.parametrize("rows", ROWS)
+@pytest.mark.parametrize("M,N,K,f8,rows", [s + (r,) for s in SHAPES for r in ROWS if r != "long" or s[0] == 8])
 def test_gradient_rows(oracle, M, N, K, f8, rows):
     from paper_2605_19269_amd import coda
     assert torch.cuda.is_available(), "these tests need the MI355X"
-    if rows == "long" and M > 8:
-        pytest.skip("eight rows of 16 MB are enough")
     g = np.random.Generator(np.random.PCG64(900 + M + N + K))
     if f8:
         A, B = synth.normal_f8e4m3(g, (K, M), 1.0), synth.normal_f8e4m3(g, (K, N), 1.0)
