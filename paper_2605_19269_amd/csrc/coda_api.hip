@@ -315,6 +315,7 @@ coda_status gemm_impl(void *stream, int64_t M, int64_t N, int64_t K, const coda_
                                         : ps.mode == coda::EPI_SWIGLU_BWD ? coda::DIRECT_PROG_SWIGLU_BWD
                                         : ps.mode == coda::EPI_ACCUM      ? coda::DIRECT_PROG_ACCUM
                                                                           : coda::DIRECT_PROG_RMSNORM_BWD;
+    if (ps.mode == coda::EPI_ACCUM) p.out_once = coda::gradient_once(M, N, p.ld_out * 4, reinterpret_cast<uintptr_t>(p.out));
     const bool wide = p.rowred_mode != coda::ROWRED_NONE || p.lse_max;
     const coda::Route route = coda::plan_route(M, N, K, f8, ak, bkc, program, wide, workspace != nullptr);
     if (workspace) {

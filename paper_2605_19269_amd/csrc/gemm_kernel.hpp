@@ -59,6 +59,7 @@ struct GemmParams {
     uint16_t *side; int64_t ld_side;     // bf16 [M x N]
     float *rowred; int rowred_mode;      // see RowRedMode; partials are [tiles_n x M]
     void *out; int64_t ld_out; int out_f32;
+    int out_once;                        // ACCUM: D past the caches, see gradient_once()
     const uint16_t *Z; int64_t ldz;      // SWIGLU_BWD saved pre-activation [M x 2N]
     uint16_t *out2; int64_t ld_out2;     // SWIGLU_FWD: pre-activation; SWIGLU_BWD: silu(g)*u
     const float *rope_cos, *rope_sin;    // f32 [T x rope_half] tables (linear mode; null = no rotation)
@@ -944,11 +945,7 @@ __device__ __forceinline__ void run_epilogue(ACC &acc, const GemmParams &p, int 
                 stage_fence();
             }
         };
-        // D past the caches, which then keep the operands (1000-token backward of a 2048 x 5632 layer 226 -> 218 us; loads or stores alone
-        // half of it; 2048 x 11264 x 304 44 -> 40, 4096 x 4096 x 256 in turn with others 37.7 -> 32.2, the same D again and again, which
-        // would have stayed, 30.7 -> 31.3), where its rows are whole lines: of a line in two pieces the caches save the second
-        // (2000 x 5208 x 2000 63 us with the hint, without 55)
-        if (pitch % 128 == 0 && reinterpret_cast<uintptr_t>(p.out) % 128 == 0) passes(std::true_type{});
+        if (p.out_once) passes(std::true_type{});
         else passes(std::false_type{});
     } else {
         // ---- fp32 store of the linear program: 16 bytes per lane, direct

@@ -294,6 +294,19 @@ inline bool reads_once(int64_t M, int64_t N, int64_t K, bool f8, bool b_k_contig
     return bm == 32 || (bm == 64 ? ranges == 1 : b_k_contiguous);
 }
 
+// Whether the gradient program reads and writes D past the caches: where it is too large to stay in them for the next call, from
+// NEVER_STAYS_BYTES on.  Whole lines only: of a line in two pieces the caches save the second (2000 x 5208 x 2000 63 us with the hint, without 55).
+// Microseconds, ordinary -> hint, one D again and again and two in turn: 4096 x 18432 x 1000 222 -> 216, 231 -> 216; 4096 x 20480 x 512 214 -> 169, 211 -> 202;
+// 8192 x 16384 x 1000 416 -> 349, 415 -> 351, x 4096 879 -> 858, 870 -> 885; 8-bit 4096 x 18432 x 1008 171 -> 165, 187 -> 166.
+// Below, D may have stayed from the call before, which is worth more than the operands that the hint leaves in the caches.  76 shapes of 33 to 230 MB,
+// K of 256 to 3900, one D again and again and as many in turn as 700 MB hold: 256 x 256 tiles 12 % slower in the mean (1 to 28) and 4 % faster (2 % slower to 14
+// faster); 128 x 128 two a CU 2 % slower (5 % faster to 8 slower) and 3 % faster (2 % slower to 7 faster).  4096 x 4096 x 256 28 -> 33, 37 -> 33; 2048 x 11264 x
+// 1000 65 -> 68, 81 -> 80; 4096 x 11008 x 1000 117 -> 151, 150 -> 151.  On the loads alone the hint costs half of that and gains half.
+inline bool gradient_once(int64_t M, int64_t N, int64_t ld_bytes, uint64_t address)
+{
+    return M * N * 4 >= NEVER_STAYS_BYTES && ld_bytes % 128 == 0 && address % 128 == 0;
+}
+
 // Route of a call.  The order of the additions behind an element must not depend on the program, so what divides the
 // contraction is decided by the sizes, operand type and layouts alone:
 //   whole (of 256 or 192 columns) or undivided small tiles, chain INT32_MAX: the MFMAs of a tile along K from the place that rot_cols says, the same

@@ -16,6 +16,7 @@ def load(folder):
     lib.host_direct_tile.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 4
     lib.host_route.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 6 + [ctypes.POINTER(ctypes.c_int)]
     lib.host_reads_once.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 4 + [ctypes.c_int64, ctypes.c_uint64]
+    lib.host_gradient_once.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_uint64]
     lib.host_split_plan.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int, ctypes.POINTER(ctypes.c_int)]
     lib.host_small_map.argtypes = [ctypes.c_int] * 3 + [ctypes.POINTER(ctypes.c_int)]
     return lib

@@ -39,6 +39,12 @@ __attribute__((visibility("default"))) int host_reads_once(int64_t M, int64_t N,
     return coda::reads_once(M, N, K, f8 != 0, bkc != 0, bm, ranges, ldb_bytes, at);
 }
 
+// whether the gradient program reads and writes D past the caches
+__attribute__((visibility("default"))) int host_gradient_once(int64_t M, int64_t N, int64_t ld_bytes, uint64_t at)
+{
+    return coda::gradient_once(M, N, ld_bytes, at);
+}
+
 // whether tile_xcd() inverts tile_coords() on a grid of tiles
 __attribute__((visibility("default"))) int host_tile_xcd_ok(int tiles_m, int tiles_n)
 {

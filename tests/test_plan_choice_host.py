@@ -35,3 +35,15 @@ def test_large_tiles_where_they_are_faster(lib, M, N, K, f8, ta, tb, prog, red):
 def test_small_tiles_where_they_are_faster(lib, M, N, K, f8, ta, tb, prog, red, tile):
     r = small_plan.Route(lib, M, N, K, f8, not ta, tb, prog, red)
     assert (r.kind, r.tile) == ("direct", tile)
+
+
+# M, N and microseconds of one D again and again: ordinary, past the caches
+@pytest.mark.parametrize("M,N", [(2048, 5632), (4096, 4096), (2048, 11264), (4096, 8192), (4096, 11008)])     # 36 40, 28 33, 65 68, 65 69, 117 151
+def test_gradients_that_may_stay_go_through_the_caches(lib, M, N):
+    assert not lib.host_gradient_once(M, N, N * 4, 0)
+
+
+@pytest.mark.parametrize("M,N", [(4096, 18432), (4096, 20480), (8192, 16384)])                                # 222 216, 214 169, 416 349
+def test_gradients_that_never_stay_go_past_the_caches(lib, M, N):
+    assert lib.host_gradient_once(M, N, N * 4, 0) and lib.host_gradient_once(M, N, (N + 32) * 4, 128)
+    assert not lib.host_gradient_once(M, N, (N + 4) * 4, 0) and not lib.host_gradient_once(M, N, N * 4, 16)
