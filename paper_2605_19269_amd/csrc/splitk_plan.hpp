@@ -186,9 +186,8 @@ inline SmallPlan plan_small(int64_t M, int64_t N, int64_t K, bool f8, bool a_k_c
 // does 1000 x 16384 x 2048 (128x256 66.8, 256 x 256 55.4).
 // A plan_small() with one range per tile gives way to these where the model says so, see plan_route; `chains`: those that keep to
 // its chain, all but PAIR and 32x256.
-// The gradient program also reads and writes 8 bytes per element, part of it beside the contraction of other workgroups.  D cold, PAIR and
-// 256 x 256: 11008 x 4096 x 504 81, 97; 14336 x 4096 x 512 111, 123; 2048 x 11264 x 2000 113, 123; and 2048 x 16384 x 2000 158, 147;
-// 5632 x 2048 x 1000 41, 40 and 4096 x 28672 x 1000 379, 298, which stay on 256 x 256.
+// The gradient program also reads and writes 8 bytes per element, of which two workgroups of a CU (PAIR) run a part under each other's contraction.
+constexpr int64_t NEVER_STAYS_BYTES = 280ll << 20;    // more than that leaves nothing in the 256 MB Infinity Cache for the next call
 enum DirectTile : int { DIRECT_NONE = 0, DIRECT_64x64, DIRECT_32x256, DIRECT_64x256, DIRECT_128x128, DIRECT_128x128_PAIR, DIRECT_128x256 };
 enum DirectProgram : int { DIRECT_PROG_LINEAR, DIRECT_PROG_SWIGLU_FWD, DIRECT_PROG_SWIGLU_BWD, DIRECT_PROG_ACCUM, DIRECT_PROG_RMSNORM_BWD };
 struct DirectPlan {
@@ -209,9 +208,7 @@ inline DirectPlan plan_direct(int64_t M, int64_t N, int64_t K, bool f8, bool a_k
     const int64_t big = tiles(PLAN_TILE_M, PLAN_TILE_N);
     const double fill = big < SPLITK_CUS ? (double)big / (double)SPLITK_CUS : 1.0;
     best.us = (prog == DIRECT_PROG_ACCUM ? 0.99 : 0.92) * (6.0 + stages * (1.15 + 0.4 * fill) * rounds(big) + 0.64 * rmw);    // what a small tile has to beat
-    // bf16 weight gradients (A^T), since D moves in whole rows; up to 48 stages, what was measured
-    const bool rows = prog == DIRECT_PROG_ACCUM && !f8 && !a_k_contiguous && stages <= 48.0;
-    if (rows) best.us = 0.96 * (6.0 + stages * (1.1 + 0.22 * fill) * rounds(big) + 0.82 * rmw);
+    const bool gradient = prog == DIRECT_PROG_ACCUM && !f8 && !a_k_contiguous;       // bf16 weight gradients (A^T)
     auto offer = [&](int tile, double us) {
         if (us < best.us) best = DirectPlan{tile, us};
     };
@@ -233,16 +230,26 @@ inline DirectPlan plan_direct(int64_t M, int64_t N, int64_t K, bool f8, bool a_k
     // every further round pays its fill and epilogue: 897 x 19712 x 200 SwiGLU, five rounds: 28.3, 256 x 256 26.6; 3426 x 2832 x 160
     // 8-bit, three: 17.0, 14.8
     if (!wide) offer(DIRECT_128x128, 2.5 + 2.0 * rounds(tiles(128, 128)) + stream(stages * 0.57 * rounds(tiles(128, 128)), 5.6e6) + rmw);
-    // bf16 contractions that 256 x 256 tiles nearly fill one round with have no second round to run the updates under: 4096 x 4096 x 32
-    // PAIR 29.2, 256 x 256 27.0; x 256 35.1, 32.7; 8192 x 2048 x 1000 53.3, 47.7
-    const bool bare = !f8 && big <= SPLITK_CUS && fill > 0.8 && (rows || stages < 4.0);
-    if (prog == DIRECT_PROG_ACCUM && !chains && !bare) {
-        // rounds of two per CU; what is left over runs two or one per CU (1424 x 6304 x 12920: 600 tiles lose 30 % to 256 x 256)
-        const int64_t t = tiles(128, 128), whole = t / (2 * SPLITK_CUS), left = t % (2 * SPLITK_CUS);
-        const double round = rows ? 0.86 : 1.08, rest = left == 0 ? 0.0 : (left <= SPLITK_CUS ? 0.66 : round);
-        offer(DIRECT_128x128_PAIR, 6.0 + stages * (round * (double)whole + rest) + (rows ? 0.62 : 0.55) * rmw);
-    }
+    // bf16 contractions that 256 x 256 tiles nearly fill one round with: 4096 x 4096 x 32 PAIR 29.2, 256 x 256 27.0; of ten shapes of 200 to 256 tiles,
+    // K of 64 to 4000, A^T, PAIR is at most 6 % ahead below 256 and 5 to 40 % behind from 512 on (3584 x 4096 x 64 28.3, 29.0; x 1000 52.3, 49.0)
+    const bool bare = !f8 && big <= SPLITK_CUS && fill > 0.8 && (gradient || stages < 4.0);
+    // rounds of two per CU; what is left over runs two or one per CU (1424 x 6304 x 12920: 600 tiles lose 30 % to 256 x 256)
+    const int64_t pairs = tiles(128, 128), whole = pairs / (2 * SPLITK_CUS), left = pairs % (2 * SPLITK_CUS);
+    const double one = left > 0 && left <= SPLITK_CUS ? 1.0 : 0.0, two = (double)whole + (left > SPLITK_CUS ? 1.0 : 0.0);
+    const bool paired = prog == DIRECT_PROG_ACCUM && !chains && !bare;
+    // up to 256 tiles leave a workgroup without its second: bf16 gradients then take one a CU, in the mean of 102 shapes, K up to 9768, 4 % faster with D
+    // cold (9 slower to 29 faster) and 11 % on a D that stays (1000 x 4048 x 504 18.7 -> 17.4, x 816 23.5 -> 20.6; from 257 tiles on 10 to 20 % slower)
+    if (paired) offer(gradient && pairs <= SPLITK_CUS ? DIRECT_128x128 : DIRECT_128x128_PAIR, 6.0 + stages * (1.08 * two + 0.66 * one) + 0.55 * rmw);
     if (!crowded(128)) offer(DIRECT_128x256, (6.0 + stages * 0.88 * rounds(tiles(128, 256)) + rmw) * (prog == DIRECT_PROG_ACCUM ? 1.07 : 1.0));
+    // bf16 gradients for which that leaves 256 x 256 tiles: both in figures of D moved in rows, cold and by way of the caches, fitted to 555 shapes, K of 16 to
+    // 8192 (within 7 %).  They move 147 of the shapes timed, 7 % faster in the mean with D cold (5 slower to 16 faster) and 5 % on a D that stays (14336 x 4096 x
+    // 504 140 -> 125, 2048 x 11264 x 2000 126 -> 120), and not 2048 x 16384 x 504 (85.6, PAIR 92.8), 5632 x 2048 x 1000 (42.9, 46.0), 10240 x 5120 x 4096 (398, 438).  D past
+    // the caches, which N decides here, stays: 4096 x 28672 x 424 222, PAIR 252.
+    if (gradient && paired && best.tile == DIRECT_NONE && (M * N * 4 < NEVER_STAYS_BYTES || N % 32)) {
+        const double large = 3.4 + 9.9 * rounds(big) + stages * (1.14 * rounds(big) + 0.25 * (double)big / (double)SPLITK_CUS) + 0.66 * rmw;
+        const double pair = 7.6 + stages * (0.91 * two + 0.75 * one) + 0.85 * rmw;
+        if (pair < 0.97 * large) best = DirectPlan{DIRECT_128x128_PAIR, pair};
+    }
     return best;
 }
 
@@ -284,7 +291,7 @@ inline bool narrow_is_faster(int64_t M, int64_t N, int64_t K, double direct)
 // slower alone: 1 x 22016 x 4096 35.6 -> 34.9, 29.7 -> 33.8, 64 x 18432 x 4608 44.5 -> 43.3, 29.9 -> 41.9); 64 rows in several ranges (64 x 14336 x 4096
 // 29.1 -> 29.7, 25.2 -> 29.1); 8-bit A B on 128 x 128 tiles (2 to 10 %; up to 38 % slower: 128 x 28672 x 4096 33.4 -> 31.2, 23.2 -> 28.3).  bf16
 // at 65 to 128 rows gains nothing in turn either.
-constexpr int64_t ONCE_BYTES = 96ll << 20, NEVER_STAYS_BYTES = 280ll << 20;
+constexpr int64_t ONCE_BYTES = 96ll << 20;
 inline bool reads_once(int64_t M, int64_t N, int64_t K, bool f8, bool b_k_contiguous, int bm, int ranges, int64_t ldb_bytes, uint64_t b_address)
 {
     const int64_t bytes = N * K * (f8 ? 1 : 2), workgroups = (N + 127) / 128 * ranges;

@@ -17,13 +17,27 @@ LARGE = [(4096, 4096, 32, False, True, False, "accum", False),              # 27
          (3426, 2832, 160, True, False, False, "linear", False),            # 14.7, 17.7 three rounds of 128x128
          (292, 46864, 3920, True, False, True, "linear", True),             # 118.7, 137.7 three rounds of 128x256
          (1915, 12816, 4752, True, False, False, "swiglu_fwd", False),      # 115.0, 133.5
-         (384, 58320, 15968, True, False, False, "swiglu_fwd", False)]      # 402, 480
+         (384, 58320, 15968, True, False, False, "swiglu_fwd", False),      # 402, 480
+         (4096, 4096, 1000, False, True, False, "accum", False),            # 54.9, 59.7 two 128x128 a CU
+         (8192, 2048, 1000, False, True, False, "accum", False),            # 52.8, 60.7
+         (5632, 2048, 504, False, True, False, "accum", False),             # 34.0, 35.2
+         (2048, 16384, 504, False, True, False, "accum", False),            # 85.6, 92.8
+         (4096, 6144, 3072, False, True, False, "accum", False),            # 160, 175
+         (4096, 6144, 3080, False, True, False, "accum", False),            # 171, 177
+         (4096, 28672, 424, False, True, False, "accum", False),            # 222, 252: D past the caches
+         (4096, 22016, 704, False, True, True, "accum", False)]             # 229, 266
 SMALL = [(897, 19712, 200, False, False, False, "swiglu_fwd", False, "128x256"),     # 26.6, 23.6 (128x128 28.2)
          (32, 55056, 176, True, True, False, "accum", False, "128x128_PAIR"),        # 10.0, 8.3 (128x128 11.9)
          (768, 8784, 96, False, False, True, "swiglu_fwd", False, "128x256"),        # 10.6, 7.7 (128x128 9.7)
          (3598, 5456, 352, True, False, True, "linear", True, "128x256"),            # 44.8, 36.9
          (6144, 4096, 96, False, True, False, "accum", False, "128x128_PAIR"),       # 46.4, 41.2
-         (2048, 8192, 128, True, True, False, "accum", False, "128x128_PAIR")]       # 33.5, 30.5
+         (2048, 8192, 128, True, True, False, "accum", False, "128x128_PAIR"),       # 33.5, 30.5
+         (2048, 11264, 1000, False, True, False, "accum", False, "128x128_PAIR"),    # 87.7, 81.4
+         (2048, 11264, 2000, False, True, False, "accum", False, "128x128_PAIR"),    # 126, 120
+         (14336, 4096, 504, False, True, False, "accum", False, "128x128_PAIR"),     # 140, 125
+         (10240, 5120, 1000, False, True, False, "accum", False, "128x128_PAIR"),    # 172, 157
+         (1000, 4048, 504, False, True, False, "accum", False, "128x128"),           # 28.0, 17.4 (two a CU 18.7)
+         (3056, 1032, 272, False, True, False, "accum", False, "128x128")]           # one a CU, see plan_direct
 
 
 @pytest.mark.parametrize("M,N,K,f8,ta,tb,prog,red", LARGE)
