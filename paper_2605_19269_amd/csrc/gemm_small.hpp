@@ -377,8 +377,9 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2), am
     using ACC = SmallAcc<C>;
     constexpr int RB = C::WTN * 4, UB = 16 * ACC::LQ, LR = ACC::LR;
     if constexpr (C::F8 || C::BM == 128) {
-        // straight from registers a lane and its partners would store 32 (8-bit) or 64 bytes of a row: rows of the wave's tile by way of
-        // LDS (eight ranges of 256 x 1984 x 4336 8-bit: 17.2 us, from registers 18.9; a 509-row MLP of bf16 73.5 -> 72.5)
+        // straight from registers a lane and its partners would store 32 (8-bit) or 64 bytes of a row: rows of the wave's tile, 256 bytes of 128x256 and 128
+        // of 128x128, by way of LDS (eight ranges of 256 x 1984 x 4336 8-bit: 17.2 us, from registers 18.9; bf16, contraction and epilogue, 128x128: 159 x 640 x
+        // 10928 18.4 -> 17.4, 509 x 2048 x 8192 34.7 -> 34.3, of 28 shapes one 0.6 % slower; 128x256: 144 x 10144 x 3848 39.8 -> 37.5, 1000 x 2048 x 5632 39.8 -> 39.4)
         unsigned char *reg = smem + wave * LR * RB;
         const uint32_t ulane = Stage<RB>::template unit_lane<16, LR>(lane);
 #pragma unroll
